@@ -70,7 +70,7 @@ struct BwdWs {
     tok.H_res = c.take<float>(T * n * n);
     tok.H_pre = c.take<float>(T * n);
     tok.H_post = c.take<float>(T * n);
-    tok.vr = c.take<float>(T * M);
+    tok.vr = c.take<float>(T * ((M + 15) / 16 * 16));
     tok.coefx = c.take<float>(T);
     tok.gz = c.take<float>(T * (M + 3));
     gH_res = gH_pre = gH_post = nullptr;
@@ -79,7 +79,7 @@ struct BwdWs {
       gH_pre = c.take<float>(T * n);
       gH_post = c.take<float>(T * n);
     }
-    const int chunks = gw_chunks_generic(d);
+    const int chunks = gw_chunks_fullprec(d);
     partials = chunks > 1 ? c.take<float>(static_cast<size_t>(chunks) * n * d.C * M) : nullptr;
     Wp = fast_path_ok(d) ? c.take<char>(packed_w_b_bytes(d, M)) : nullptr;
     psum = c.take<float>(static_cast<size_t>(param_sum_blocks(d)) * (M + 3));
@@ -445,7 +445,7 @@ int mhcl_coeffs_bwd(const mhcl_desc *desc, const void *x, const float *W, const 
   MHCL_HIP(run_coeffs_bwd_epilogue(*desc, w.u_raw, w.sumsq, b, alpha, g_H_res, g_H_pre, g_H_post,
                                    w.tok, s));
   MHCL_HIP(launch_gx_generic(*desc, M, false, x, W, nullptr, nullptr, w.tok, g_x, nullptr, s));
-  MHCL_HIP(launch_gw_generic(*desc, M, x, w.tok.vr, w.partials, g_W, s));
+  MHCL_HIP(launch_gw_fullprec(*desc, M, x, w.tok.vr, w.partials, g_W, s));
   MHCL_HIP(launch_param_sums(*desc, M, w.tok.gz, g_b, g_alpha, w.psum, s));
   return MHCL_OK;
 }
@@ -516,7 +516,7 @@ int mhcl_bwd_fused(const mhcl_desc *desc, const void *x, const void *y, const fl
     StageBracket br(MHCL_STAGE_BWD_OUT, s);
     MHCL_HIP(launch_gx_generic(*desc, M, true, x, W, g_xout, g_h, w.tok, g_x, g_y, s));
   }
-  MHCL_HIP(launch_gw_generic(*desc, M, x, w.tok.vr, w.partials, g_W, s));
+  MHCL_HIP(launch_gw_fullprec(*desc, M, x, w.tok.vr, w.partials, g_W, s));
   MHCL_HIP(launch_param_sums(*desc, M, w.tok.gz, g_b, g_alpha, w.psum, s));
   return MHCL_OK;
 }

@@ -252,6 +252,7 @@ __global__ __launch_bounds__(128) void coeffs_bwd_epilogue_kernel(
   for (int j = 0; j < N; ++j) { o.H_pre[t * N + j] = Hp[j]; o.H_post[t * N + j] = Hq[j]; }
   token_coeffs_bwd<N, MODE>(gr, gp, gq, a, Hr, Hp, Hq, sums, sk_iters, gz);
   // z_m = alpha_g (r u_raw_m) + b_m
+  constexpr int MP = (M + 15) / 16 * 16;   // row of vr, zero past the last logit
   float ga[3] = {0.f, 0.f, 0.f}, dot = 0.f;
 #pragma unroll
   for (int m = 0; m < M; ++m) {
@@ -259,10 +260,12 @@ __global__ __launch_bounds__(128) void coeffs_bwd_epilogue_kernel(
     const float al = g == 0 ? p.alpha_res : (g == 1 ? p.alpha_pre : p.alpha_post);
     const float vr = r * al * gz[m];
     o.gz[t * (M + 3) + m] = gz[m];
-    o.vr[t * M + m] = vr;
+    o.vr[t * MP + m] = vr;
     ga[g] += gz[m] * (r * u[m]);
     dot += vr * u[m];
   }
+#pragma unroll
+  for (int m = M; m < MP; ++m) o.vr[t * MP + m] = 0.f;
 #pragma unroll
   for (int g = 0; g < 3; ++g) o.gz[t * (M + 3) + M + g] = ga[g];
   o.coefx[t] = (r * r / static_cast<float>(nC)) * dot;
@@ -479,7 +482,8 @@ __global__ __launch_bounds__(kBlock) void gx_generic_kernel(
   constexpr int V = IO::kVec;
   __shared__ float sv[160];
   const int64_t t = blockIdx.y;
-  for (int m = threadIdx.x; m < M; m += kBlock) sv[m] = o.vr[t * M + m];
+  const int MP = (M + 15) / 16 * 16;
+  for (int m = threadIdx.x; m < M; m += kBlock) sv[m] = o.vr[t * MP + m];
   __syncthreads();
   const int c = (blockIdx.x * kBlock + threadIdx.x) * V;
   if (c >= C) return;
@@ -530,29 +534,6 @@ __global__ __launch_bounds__(kBlock) void gx_generic_kernel(
       for (int e = 0; e < V; ++e) acc[e] += old[e];
     }
     IO::store(g_x, (t * N + j) * C + c, acc);
-  }
-}
-
-// g_W[k][m] = sum_t x_hat[t][k] vr[t][m]: the one reduction over tokens.
-// Block (k block of 8, token chunk); thread (m lane, k); partial sums per
-// chunk, then added over chunks in order.
-template <typename IO>
-__global__ __launch_bounds__(kBlock) void gw_generic_kernel(const void *__restrict__ x,
-                                                            const float *__restrict__ vr, int nC,
-                                                            int M, int64_t T, int64_t chunk,
-                                                            float *__restrict__ out) {
-  const int ml = threadIdx.x & 31, kk = threadIdx.x >> 5;
-  const int k = blockIdx.x * 8 + kk;
-  const int64_t tb = static_cast<int64_t>(blockIdx.y) * chunk;
-  const int64_t te = tb + chunk < T ? tb + chunk : T;
-  float *dst = out + static_cast<size_t>(blockIdx.y) * nC * M;
-  if (k >= nC) return;
-  for (int m0 = 0; m0 < M; m0 += 32) {
-    const int m = m0 + ml;
-    if (m >= M) break;
-    float acc = 0.f;
-    for (int64_t t = tb; t < te; ++t) acc += IO::load1(x, t * nC + k) * vr[t * M + m];
-    dst[static_cast<size_t>(k) * M + m] = acc;
   }
 }
 
@@ -816,7 +797,7 @@ hipError_t launch_gx_generic(const mhcl_desc &d, int M, bool fused, const void *
         const unsigned gy = static_cast<unsigned>(d.T - t0 < 65535 ? d.T - t0 : 65535);
         BwdTokenBufs oo = o;
         oo.H_res += t0 * N * N; oo.H_pre += t0 * N; oo.H_post += t0 * N;
-        oo.vr += t0 * M; oo.coefx += t0;
+        oo.vr += t0 * ((M + 15) / 16 * 16); oo.coefx += t0;
         const size_t so = static_cast<size_t>(t0) * N * d.C * IO::kBytes;
         const size_t ro = static_cast<size_t>(t0) * d.C * IO::kBytes;
         const char *xo = static_cast<const char *>(x) + so;
@@ -840,30 +821,11 @@ hipError_t launch_gx_generic(const mhcl_desc &d, int M, bool fused, const void *
   });
 }
 
-int gw_chunks_generic(const mhcl_desc &d) {
-  int64_t c = (d.T + 1023) / 1024;
-  if (c < 1) c = 1;
-  if (c > 32) c = 32;
-  return static_cast<int>(c);
-}
-
-hipError_t launch_gw_generic(const mhcl_desc &d, int M, const void *x, const float *vr,
-                             float *partials, float *g_W, hipStream_t s) {
-  const int chunks = gw_chunks_generic(d);
-  const int nC = d.n * d.C;
-  const int64_t chunk = (d.T + chunks - 1) / chunks;
-  return dispatch_io(d.io_dtype, [&](auto io) {
-    using IO = decltype(io);
-    float *dst = chunks == 1 ? g_W : partials;
-    hipLaunchKernelGGL(gw_generic_kernel<IO>, dim3(blocks_for(nC, 8), chunks), dim3(kBlock), 0, s,
-                       x, vr, nC, M, d.T, chunk, dst);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || chunks == 1) return e;
-    const size_t size = static_cast<size_t>(nC) * M;
-    hipLaunchKernelGGL(sum_partials_kernel, dim3(blocks_for(size, 64)), dim3(kBlock), 0, s,
-                       (const float *)partials, size, chunks, g_W);
-    return hipGetLastError();
-  });
+hipError_t launch_sum_partials(const float *partials, size_t size, int chunks, float *out,
+                               hipStream_t s) {
+  hipLaunchKernelGGL(sum_partials_kernel, dim3(blocks_for(size, 64)), dim3(kBlock), 0, s, partials,
+                     size, chunks, out);
+  return hipGetLastError();
 }
 
 hipError_t launch_bwd_finish(const float *partials, size_t size, int chunks, float *g_W,

@@ -34,7 +34,7 @@ struct BwdTokenBufs {
   float *H_res;   // [T, n*n]
   float *H_pre;   // [T, n]
   float *H_post;  // [T, n]
-  float *vr;      // [T, M]   r * alpha_g * g_z   (the vector multiplied with W and x)
+  float *vr;      // [T, 16 ceil(M / 16)] r * alpha_g * g_z (the vector multiplied with W and x), zero-padded
   float *coefx;   // [T]      (r^2 / nC) <vr, u_raw>
   float *gz;      // [T, M+3] g_z, then the three per-group sums of g_z * u
 };
@@ -67,9 +67,9 @@ hipError_t launch_coeffs_bwd_epilogue(const mhcl_desc &d, int parts, const float
 hipError_t launch_gx_generic(const mhcl_desc &d, int M, bool fused, const void *x, const float *W,
                              const void *g_xout, const void *g_h, const BwdTokenBufs &o, void *g_x,
                              void *g_y, hipStream_t s);
-int gw_chunks_generic(const mhcl_desc &d);
-hipError_t launch_gw_generic(const mhcl_desc &d, int M, const void *x, const float *vr,
-                             float *partials, float *g_W, hipStream_t s);
+// out = sum over the chunks' partial results [chunks][size], in a fixed order
+hipError_t launch_sum_partials(const float *partials, size_t size, int chunks, float *out,
+                               hipStream_t s);
 hipError_t launch_copy(void *dst, const void *src, size_t bytes, hipStream_t s);
 // a fill kernel (safe under graph capture, unlike a memset node)
 hipError_t launch_fill_zero(float *p, size_t count, hipStream_t s);
@@ -81,6 +81,13 @@ hipError_t launch_param_sums(const mhcl_desc &d, int M, const float *gz, float *
 // the same over `rows` rows of [M+3] (rows <= T: `part` as above is large enough)
 hipError_t launch_param_sums_rows(int64_t rows, int M, const float *src, float *g_b,
                                   float *g_alpha, float *part, hipStream_t s);
+
+// ---- full-precision products on the matrix cores: any C, bf16 or f32 streams -----
+// g_W from x and vr (rows as in BwdTokenBufs); `partials` holds gw_chunks_fullprec(d) results
+// of [nC, M] when that is more than one
+int gw_chunks_fullprec(const mhcl_desc &d);
+hipError_t launch_gw_fullprec(const mhcl_desc &d, int M, const void *x, const float *vr,
+                              float *partials, float *g_W, hipStream_t s);
 
 // ---- permutation-subset form (run-time table d.perm, n up to 8) --------------
 // eight lanes per token: permutation subsets and the full form at n = 5

@@ -24,6 +24,12 @@ __device__ __forceinline__ f32x4 mfma16(const u32x4 &a, const u32x4 &b, f32x4 c)
                                                  __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
+// fp32 operands: v_mfma_f32_16x16x4_f32, D[16x16] += A[16x4] * B[4x16] in fp32; lane (r, q)
+// holds A[r][q] and B[q][r]; D as above
+__device__ __forceinline__ f32x4 mfma_f32(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
 // the same tile shape and lane layout with fp16 operands
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));

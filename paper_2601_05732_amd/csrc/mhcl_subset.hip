@@ -117,7 +117,8 @@ __global__ __launch_bounds__(kThreads) void coeffs_bwd_subset_kernel(
   for (int k = 0; k < K; ++k) mean += a_s[k][threadIdx.x] * g_a(k);
   float ga[3] = {0.f, 0.f, 0.f}, dot = 0.f;
   float *gz = o.gz + t * (M + 3);
-  float *vr = o.vr + t * M;
+  const int MP = (M + 15) / 16 * 16;
+  float *vr = o.vr + t * MP;   // (rows padded with zeros)
   for (int k = 0; k < K; ++k) {
     const float g = a_s[k][threadIdx.x] * (g_a(k) - mean);
     const float u = raw_logit(u_raw, parts, T, t, M, k);
@@ -146,6 +147,7 @@ __global__ __launch_bounds__(kThreads) void coeffs_bwd_subset_kernel(
     ga[2] += gq * (r * uq);
     dot += vp * up + vq * uq;
   }
+  for (int m = M; m < MP; ++m) vr[m] = 0.f;
 #pragma unroll
   for (int g = 0; g < 3; ++g) gz[M + g] = ga[g];
   o.coefx[t] = (r * r / static_cast<float>(nC)) * dot;
