@@ -67,11 +67,8 @@ struct BwdWs {
     const size_t parts = static_cast<size_t>(proj_ksplit(d));
     u_raw = c.take<float>(parts * T * M);
     sumsq = c.take<float>(parts * T);
-    tok.H_res = c.take<float>(T * n * n);
-    tok.H_pre = c.take<float>(T * n);
-    tok.H_post = c.take<float>(T * n);
+    tok.rec = c.take<float>(T * token_rec_floats(n));
     tok.vr = c.take<float>(T * ((M + 15) / 16 * 16));
-    tok.coefx = c.take<float>(T);
     tok.gz = c.take<float>(T * (M + 3));
     gH_res = gH_pre = gH_post = nullptr;
     if (need_dots) {
@@ -444,7 +441,7 @@ int mhcl_coeffs_bwd(const mhcl_desc *desc, const void *x, const float *W, const 
   MHCL_HIP(run_projection(*desc, x, W, w.u_raw, w.sumsq, w.Wp, MHCL_STAGE_BWD_REDUCE, s));
   MHCL_HIP(run_coeffs_bwd_epilogue(*desc, w.u_raw, w.sumsq, b, alpha, g_H_res, g_H_pre, g_H_post,
                                    w.tok, s));
-  MHCL_HIP(launch_gx_generic(*desc, M, false, x, W, nullptr, nullptr, w.tok, g_x, nullptr, s));
+  MHCL_HIP(launch_gx_fullprec(*desc, M, false, x, W, nullptr, nullptr, w.tok, g_x, nullptr, s));
   MHCL_HIP(launch_gw_fullprec(*desc, M, x, w.tok.vr, w.partials, g_W, s));
   MHCL_HIP(launch_param_sums(*desc, M, w.tok.gz, g_b, g_alpha, w.psum, s));
   return MHCL_OK;
@@ -514,7 +511,7 @@ int mhcl_bwd_fused(const mhcl_desc *desc, const void *x, const void *y, const fl
                                    w.gH_post, w.tok, s));
   {
     StageBracket br(MHCL_STAGE_BWD_OUT, s);
-    MHCL_HIP(launch_gx_generic(*desc, M, true, x, W, g_xout, g_h, w.tok, g_x, g_y, s));
+    MHCL_HIP(launch_gx_fullprec(*desc, M, true, x, W, g_xout, g_h, w.tok, g_x, g_y, s));
   }
   MHCL_HIP(launch_gw_fullprec(*desc, M, x, w.tok.vr, w.partials, g_W, s));
   MHCL_HIP(launch_param_sums(*desc, M, w.tok.gz, g_b, g_alpha, w.psum, s));

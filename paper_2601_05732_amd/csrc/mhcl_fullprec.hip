@@ -11,6 +11,20 @@ namespace mhcl {
 namespace {
 
 template <typename F>
+hipError_t dispatch_n(int n, F &&f) {
+  switch (n) {
+    case 1: return f(std::integral_constant<int, 1>{});
+    case 2: return f(std::integral_constant<int, 2>{});
+    case 3: return f(std::integral_constant<int, 3>{});
+    case 4: return f(std::integral_constant<int, 4>{});
+    case 5: return f(std::integral_constant<int, 5>{});
+    case 6: return f(std::integral_constant<int, 6>{});
+    case 7: return f(std::integral_constant<int, 7>{});
+    case 8: return f(std::integral_constant<int, 8>{});
+  }
+  return hipErrorInvalidValue;
+}
+template <typename F>
 hipError_t dispatch_io(int io, F &&f) {
   if (io == MHCL_BF16) return f(BF16{});
   return f(F32{});
@@ -163,6 +177,132 @@ __global__ __launch_bounds__(64 * kGwWaves, 1) void gw_fullprec_kernel(
   }
 }
 
+// ---------------------------------------------------------------------------
+// Gradient on x.  With vr = r alpha g_z and coefx = (r^2/nC) <vr, u_raw>, the RMSNorm +
+// projection part is  W vr - x_hat coefx.
+//   FUSED: g_x = H_res^T g_xout + H_pre g_h + (that part), rounded once;
+//          g_y = sum_i H_post[i] g_xout[i]
+//   else : g_x += (that part)
+// W vr is a product of W (left operand) and the vr of 16 tokens: a wave owns a window of 4 V
+// columns of every stream, the rows of tile h are arranged so that lane (token, q) receives the V
+// columns 4 q ... it reads and writes of the streams (row 4 q + i of tile h = column V q + 4 h + i).
+// Four steps of the contraction are taken from one 16-byte read of W (LDS) and of vr: step i of
+// group s covers the logits 16 s + 4 q + i.  The block's slice of W sits in LDS for its whole
+// walk down the tokens; `win` of the eight waves take adjacent windows (so that a row visit covers
+// win x 64 contiguous bytes), the others the next tokens.
+// Bound by HBM (bf16, n = 4, C = 1024, 5003 tokens: 123 MB in 40 us; f32, C = 768, 4096 tokens,
+// FUSED: 176 MB in 45 us).  A block per token, every thread re-reading its rows of W from L2
+// for each token, took 340 and 218 us.
+constexpr int kGxWaves = 8;
+
+template <typename IO, int N, bool FUSED>
+__global__ __launch_bounds__(64 * kGxWaves, 1) void gx_fullprec_kernel(
+    const void *__restrict__ x, const float *__restrict__ W, const void *__restrict__ g_xout,
+    const void *__restrict__ g_h, const float *__restrict__ rec, const float *__restrict__ vr, int M,
+    int S, int C, int64_t T, int win, int tokens_per_block, void *__restrict__ g_x,
+    void *__restrict__ g_y) {
+  constexpr int V = IO::kVec, TL = V / 4, CP = token_rec<N>();
+  extern __shared__ f32x4 wl_all[];   // [window][stream][tile][group of 16 logits][lane]
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r = lane & 15, q = lane >> 4;
+  const int per_win = N * TL * S * 64;
+  for (int e = threadIdx.x; e < win * per_win; e += 64 * kGxWaves) {
+    const int ln = e & 63, lr = ln & 15, lq = ln >> 4;
+    int idx = e >> 6;
+    const int s = idx % S; idx /= S;
+    const int h = idx % TL; idx /= TL;
+    const int j = idx % N, w = idx / N;
+    const int col = (blockIdx.x * win + w) * (4 * V) + V * (lr >> 2) + 4 * h + (lr & 3);
+    const int m = 16 * s + 4 * lq;
+    f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (col < C) {
+      const float *row = W + (static_cast<size_t>(j) * C + col) * M;
+      if (M % 4 == 0) {
+        if (m < M) v = *reinterpret_cast<const f32x4 *>(row + m);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (m + i < M) v[i] = row[m + i];
+      }
+    }
+    wl_all[e] = v;
+  }
+  __syncthreads();
+  const int wi = wave % win, sub = wave / win, subs = kGxWaves / win;
+  const f32x4 *wl = wl_all + wi * per_win + lane;
+  const int c0 = (blockIdx.x * win + wi) * (4 * V) + V * q;
+  const bool col_ok = c0 < C;
+  const int cl = col_ok ? c0 : C - V;
+  const int64_t tb = static_cast<int64_t>(blockIdx.y) * tokens_per_block;
+  const int64_t te = tb + tokens_per_block < T ? tb + tokens_per_block : T;
+  for (int64_t t0 = tb + 16 * sub; t0 < te; t0 += 16 * subs) {
+    const int64_t t = t0 + r;
+    const bool live = t < te && col_ok;
+    const int64_t tl = t < te ? t : te - 1;
+    // g: g_xout (FUSED) or the g_x so far
+    Piece<IO, V> xp[N], gp[N], hp;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      xp[j].load(x, (static_cast<size_t>(tl) * N + j) * C + cl);
+      gp[j].load(FUSED ? g_xout : g_x, (static_cast<size_t>(tl) * N + j) * C + cl);
+    }
+    if constexpr (FUSED) hp.load(g_h, static_cast<size_t>(tl) * C + cl);
+    f32x4 rc[CP / 4];
+#pragma unroll
+    for (int e = 0; e < CP / 4; ++e)
+      if (FUSED || e == (N * N + 2 * N) / 4)
+        rc[e] = *reinterpret_cast<const f32x4 *>(rec + tl * CP + 4 * e);
+    auto cf = [&](int e) { return rc[e >> 2][e & 3]; };
+    const float cx = cf(N * N + 2 * N);
+
+    f32x4 acc[N][TL];
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+#pragma unroll
+      for (int h = 0; h < TL; ++h) acc[j][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const float *vrow = vr + tl * (16 * S) + 4 * q;
+    for (int s = 0; s < S; ++s) {
+      const f32x4 b = *reinterpret_cast<const f32x4 *>(vrow + 16 * s);
+#pragma unroll
+      for (int j = 0; j < N; ++j)
+#pragma unroll
+        for (int h = 0; h < TL; ++h) {
+          const f32x4 a = wl[((j * TL + h) * S + s) * 64];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc[j][h] = mfma_f32(a[i], b[i], acc[j][h]);
+        }
+    }
+    if constexpr (FUSED) {
+      if (g_y != nullptr && live) {   // (optional output)
+        float gy[V];
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+          gy[e] = 0.f;
+#pragma unroll
+          for (int i = 0; i < N; ++i) gy[e] += cf(N * N + N + i) * gp[i].at(e);
+        }
+        IO::store(g_y, t * C + c0, gy);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      float o[V];
+#pragma unroll
+      for (int e = 0; e < V; ++e) {
+        o[e] = acc[j][e >> 2][e & 3] - xp[j].at(e) * cx;
+        if constexpr (FUSED) {
+#pragma unroll
+          for (int i = 0; i < N; ++i) o[e] += cf(i * N + j) * gp[i].at(e);
+          o[e] += cf(N * N + j) * hp.at(e);
+        } else {
+          o[e] += gp[j].at(e);
+        }
+      }
+      if (live) IO::store(g_x, (t * N + j) * C + c0, o);
+    }
+  }
+}
+
 // columns per wave: 16-byte pieces, 8-byte ones where the accumulators of a 16-byte bf16
 // piece (8 NT x 4 registers) no longer fit
 int gw_columns(const mhcl_desc &d, int M) {
@@ -205,6 +345,37 @@ hipError_t launch_gw_fullprec(const mhcl_desc &d, int M, const void *x, const fl
   });
   if (e != hipSuccess || chunks == 1) return e;
   return launch_sum_partials(partials, static_cast<size_t>(nC) * M, chunks, g_W, s);
+}
+
+hipError_t launch_gx_fullprec(const mhcl_desc &d, int M, bool fused, const void *x, const float *W,
+                              const void *g_xout, const void *g_h, const BwdTokenBufs &o, void *g_x,
+                              void *g_y, hipStream_t s) {
+  const int V = d.io_dtype == MHCL_BF16 ? BF16::kVec : F32::kVec, S = logit_tiles(M);
+  const int per_win = d.n * (V / 4) * S * 1024;   // bytes of W in LDS per window (147 KiB at most)
+  const int windows = (d.C + 4 * V - 1) / (4 * V);
+  int win = kGxWaves;   // adjacent windows per block: two blocks per compute unit where possible
+  while (win > 1 && (win * per_win > 64 * 1024 || win > windows)) win /= 2;
+  const int lds = win * per_win, xb = (windows + win - 1) / win;
+  const int64_t step = 16 * (kGxWaves / win);     // tokens of one round of the block's waves
+  int64_t chunks = (lds <= 80 * 1024 ? 512 : 256) / xb;   // one round of resident blocks
+  if (chunks < 1) chunks = 1;
+  int64_t tpb = ((d.T + chunks - 1) / chunks + step - 1) / step * step;
+  const dim3 grid(xb, static_cast<unsigned>((d.T + tpb - 1) / tpb));
+  return dispatch_io(d.io_dtype, [&](auto io) {
+    return dispatch_n(d.n, [&](auto nn) {
+      using IO = decltype(io);
+      constexpr int N = decltype(nn)::value;
+      auto kern = fused ? gx_fullprec_kernel<IO, N, true> : gx_fullprec_kernel<IO, N, false>;
+      if (lds > 64 * 1024) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e != hipSuccess) return e;
+      }
+      hipLaunchKernelGGL(kern, grid, dim3(64 * kGxWaves), lds, s, x, W, g_xout, g_h, o.rec, o.vr, M, S,
+                         d.C, d.T, win, static_cast<int>(tpb), g_x, g_y);
+      return hipGetLastError();
+    });
+  });
 }
 
 }  // namespace mhcl

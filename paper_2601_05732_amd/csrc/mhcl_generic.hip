@@ -246,10 +246,11 @@ __global__ __launch_bounds__(128) void coeffs_bwd_epilogue_kernel(
   const TokenParams p{alpha[0], alpha[1], alpha[2], eps, sk_iters};
   const float r = token_coeffs<N, MODE>(u, ssq, nC, bb, p, Hr, Hp, Hq, a,
                                         (MODE == MHCL_RES_SK) ? sums : nullptr);
+  float *rec = o.rec + t * token_rec<N>();
 #pragma unroll
-  for (int e = 0; e < N * N; ++e) o.H_res[t * N * N + e] = Hr[e];
+  for (int e = 0; e < N * N; ++e) rec[e] = Hr[e];
 #pragma unroll
-  for (int j = 0; j < N; ++j) { o.H_pre[t * N + j] = Hp[j]; o.H_post[t * N + j] = Hq[j]; }
+  for (int j = 0; j < N; ++j) { rec[N * N + j] = Hp[j]; rec[N * N + N + j] = Hq[j]; }
   token_coeffs_bwd<N, MODE>(gr, gp, gq, a, Hr, Hp, Hq, sums, sk_iters, gz);
   // z_m = alpha_g (r u_raw_m) + b_m
   constexpr int MP = (M + 15) / 16 * 16;   // row of vr, zero past the last logit
@@ -268,7 +269,7 @@ __global__ __launch_bounds__(128) void coeffs_bwd_epilogue_kernel(
   for (int m = M; m < MP; ++m) o.vr[t * MP + m] = 0.f;
 #pragma unroll
   for (int g = 0; g < 3; ++g) o.gz[t * (M + 3) + M + g] = ga[g];
-  o.coefx[t] = (r * r / static_cast<float>(nC)) * dot;
+  rec[N * N + 2 * N] = (r * r / static_cast<float>(nC)) * dot;
 }
 
 // ------------------------------------------------------------ stream mixing
@@ -465,75 +466,6 @@ __global__ __launch_bounds__(kBlock) void bwd_dots_kernel(
   if (threadIdx.x < N) {
     g_H_post[t * N + threadIdx.x] = red[N * N + threadIdx.x];
     g_H_pre[t * N + threadIdx.x] = red[N * N + N + threadIdx.x];
-  }
-}
-
-// Gradient on x.  With vr = r alpha g_z and coefx = (r^2/nC) <vr, u_raw>, the
-// RMSNorm + projection part is  W vr - x_hat coefx.
-//   FUSED: g_x = H_res^T g_xout + H_pre g_h + (that part), rounded once;
-//          g_y = sum_i H_post[i] g_xout[i]
-//   else : g_x += (that part)
-// One block per (token, 256 chunks of C); vr of the token sits in LDS.
-template <typename IO, int N, bool FUSED>
-__global__ __launch_bounds__(kBlock) void gx_generic_kernel(
-    const void *__restrict__ x, const float *__restrict__ W, const void *__restrict__ g_xout,
-    const void *__restrict__ g_h, BwdTokenBufs o, int M, int C, void *__restrict__ g_x,
-    void *__restrict__ g_y) {
-  constexpr int V = IO::kVec;
-  __shared__ float sv[160];
-  const int64_t t = blockIdx.y;
-  const int MP = (M + 15) / 16 * 16;
-  for (int m = threadIdx.x; m < M; m += kBlock) sv[m] = o.vr[t * MP + m];
-  __syncthreads();
-  const int c = (blockIdx.x * kBlock + threadIdx.x) * V;
-  if (c >= C) return;
-  const float cx = o.coefx[t];
-  float gv[N][V], gh[V];
-  if constexpr (FUSED) {
-#pragma unroll
-    for (int i = 0; i < N; ++i) IO::load(g_xout, (t * N + i) * C + c, gv[i]);
-    IO::load(g_h, t * C + c, gh);
-    if (g_y != nullptr) {   // (optional output)
-      float gy[V];
-#pragma unroll
-      for (int e = 0; e < V; ++e) gy[e] = 0.f;
-#pragma unroll
-      for (int i = 0; i < N; ++i) {
-        const float w = o.H_post[t * N + i];
-#pragma unroll
-        for (int e = 0; e < V; ++e) gy[e] += w * gv[i][e];
-      }
-      IO::store(g_y, t * C + c, gy);
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < N; ++j) {
-    float xv[V], acc[V];
-    IO::load(x, (t * N + j) * C + c, xv);
-#pragma unroll
-    for (int e = 0; e < V; ++e) {
-      const float *wr = W + static_cast<size_t>(j * C + c + e) * M;
-      float s = 0.f;
-      for (int m = 0; m < M; ++m) s += wr[m] * sv[m];
-      acc[e] = s - xv[e] * cx;
-    }
-    if constexpr (FUSED) {
-#pragma unroll
-      for (int i = 0; i < N; ++i) {
-        const float w = o.H_res[(t * N + i) * N + j];
-#pragma unroll
-        for (int e = 0; e < V; ++e) acc[e] += w * gv[i][e];
-      }
-      const float wp = o.H_pre[t * N + j];
-#pragma unroll
-      for (int e = 0; e < V; ++e) acc[e] += wp * gh[e];
-    } else {
-      float old[V];
-      IO::load(g_x, (t * N + j) * C + c, old);
-#pragma unroll
-      for (int e = 0; e < V; ++e) acc[e] += old[e];
-    }
-    IO::store(g_x, (t * N + j) * C + c, acc);
   }
 }
 
@@ -780,43 +712,6 @@ hipError_t launch_bwd_dots(const mhcl_desc &d, const void *x, const void *y, con
       hipLaunchKernelGGL((bwd_dots_kernel<IO, N>), dim3(static_cast<unsigned>(d.T)), dim3(kBlock),
                          0, s, x, y, g_xout, g_h, g_H_res, g_H_post, g_H_pre, d.C);
       return hipGetLastError();
-    });
-  });
-}
-
-hipError_t launch_gx_generic(const mhcl_desc &d, int M, bool fused, const void *x, const float *W,
-                             const void *g_xout, const void *g_h, const BwdTokenBufs &o, void *g_x,
-                             void *g_y, hipStream_t s) {
-  return dispatch_io(d.io_dtype, [&](auto io) {
-    return dispatch_n(d.n, [&](auto nn) {
-      using IO = decltype(io);
-      constexpr int N = decltype(nn)::value;
-      // grid.y carries the token index: at most 65535 per launch
-      const unsigned gx = blocks_for(d.C / IO::kVec, kBlock);
-      for (int64_t t0 = 0; t0 < d.T; t0 += 65535) {
-        const unsigned gy = static_cast<unsigned>(d.T - t0 < 65535 ? d.T - t0 : 65535);
-        BwdTokenBufs oo = o;
-        oo.H_res += t0 * N * N; oo.H_pre += t0 * N; oo.H_post += t0 * N;
-        oo.vr += t0 * ((M + 15) / 16 * 16); oo.coefx += t0;
-        const size_t so = static_cast<size_t>(t0) * N * d.C * IO::kBytes;
-        const size_t ro = static_cast<size_t>(t0) * d.C * IO::kBytes;
-        const char *xo = static_cast<const char *>(x) + so;
-        const char *go = g_xout ? static_cast<const char *>(g_xout) + so : nullptr;
-        const char *gh = g_h ? static_cast<const char *>(g_h) + ro : nullptr;
-        char *gxo = static_cast<char *>(g_x) + so;
-        char *gyo = g_y ? static_cast<char *>(g_y) + ro : nullptr;
-        if (fused)
-          hipLaunchKernelGGL((gx_generic_kernel<IO, N, true>), dim3(gx, gy), dim3(kBlock), 0, s,
-                             (const void *)xo, W, (const void *)go, (const void *)gh, oo, M, d.C,
-                             (void *)gxo, (void *)gyo);
-        else
-          hipLaunchKernelGGL((gx_generic_kernel<IO, N, false>), dim3(gx, gy), dim3(kBlock), 0, s,
-                             (const void *)xo, W, (const void *)go, (const void *)gh, oo, M, d.C,
-                             (void *)gxo, (void *)gyo);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-      }
-      return hipSuccess;
     });
   });
 }

@@ -29,13 +29,15 @@ struct WsCursor {
   }
 };
 
+// floats of a token's coefficient record, whole 16-byte pieces
+constexpr int token_rec_floats(int n) { return (n * n + 2 * n + 1 + 3) / 4 * 4; }
+template <int N>
+constexpr int token_rec() { return token_rec_floats(N); }
+
 // Per-token results of the backward's coefficient stage, all [T, ...] fp32.
 struct BwdTokenBufs {
-  float *H_res;   // [T, n*n]
-  float *H_pre;   // [T, n]
-  float *H_post;  // [T, n]
+  float *rec;     // [T, token_rec<n>()] H_res | H_pre | H_post | coefx = (r^2 / nC) <vr, u_raw>
   float *vr;      // [T, 16 ceil(M / 16)] r * alpha_g * g_z (the vector multiplied with W and x), zero-padded
-  float *coefx;   // [T]      (r^2 / nC) <vr, u_raw>
   float *gz;      // [T, M+3] g_z, then the three per-group sums of g_z * u
 };
 
@@ -62,11 +64,6 @@ hipError_t launch_coeffs_bwd_epilogue(const mhcl_desc &d, int parts, const float
                                       const float *b, const float *alpha, const float *g_H_res,
                                       const float *g_H_pre, const float *g_H_post,
                                       const BwdTokenBufs &o, hipStream_t s);
-// fused == true : g_x = H_res^T g_xout + H_pre g_h + W vr - x coefx ; g_y = H_post g_xout
-// fused == false: g_x += W vr - x coefx
-hipError_t launch_gx_generic(const mhcl_desc &d, int M, bool fused, const void *x, const float *W,
-                             const void *g_xout, const void *g_h, const BwdTokenBufs &o, void *g_x,
-                             void *g_y, hipStream_t s);
 // out = sum over the chunks' partial results [chunks][size], in a fixed order
 hipError_t launch_sum_partials(const float *partials, size_t size, int chunks, float *out,
                                hipStream_t s);
@@ -88,6 +85,11 @@ hipError_t launch_param_sums_rows(int64_t rows, int M, const float *src, float *
 int gw_chunks_fullprec(const mhcl_desc &d);
 hipError_t launch_gw_fullprec(const mhcl_desc &d, int M, const void *x, const float *vr,
                               float *partials, float *g_W, hipStream_t s);
+// fused == true : g_x = H_res^T g_xout + H_pre g_h + W vr - x coefx ; g_y = H_post g_xout
+// fused == false: g_x += W vr - x coefx
+hipError_t launch_gx_fullprec(const mhcl_desc &d, int M, bool fused, const void *x, const float *W,
+                             const void *g_xout, const void *g_h, const BwdTokenBufs &o, void *g_x,
+                             void *g_y, hipStream_t s);
 
 // ---- permutation-subset form (run-time table d.perm, n up to 8) --------------
 // eight lanes per token: permutation subsets and the full form at n = 5

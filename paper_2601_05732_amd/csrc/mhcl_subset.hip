@@ -102,9 +102,10 @@ __global__ __launch_bounds__(kThreads) void coeffs_bwd_subset_kernel(
   const float r = subset_weights<N>(u_raw, sumsq, parts, b, a0, nC, eps, T, t, K, M, a_s);
   float H[N * N];
   subset_mix<N>(a_s, sig, K, H);
+  float *rec = o.rec + t * token_rec<N>();
 #pragma unroll
   for (int e = 0; e < N * N; ++e) {
-    o.H_res[t * N * N + e] = H[e];
+    rec[e] = H[e];
     g_s[e][threadIdx.x] = gH_res[t * N * N + e];
   }
   auto g_a = [&](int k) {
@@ -134,8 +135,8 @@ __global__ __launch_bounds__(kThreads) void coeffs_bwd_subset_kernel(
     const float uq = raw_logit(u_raw, parts, T, t, M, K + N + j);
     const float hp = sigmoidf(a1 * (r * up) + b[K + j]);
     const float hq = 2.f * sigmoidf(a2 * (r * uq) + b[K + N + j]);
-    o.H_pre[t * N + j] = hp;
-    o.H_post[t * N + j] = hq;
+    rec[N * N + j] = hp;
+    rec[N * N + N + j] = hq;
     const float gp = gH_pre[t * N + j] * hp * (1.f - hp);
     const float gq = gH_post[t * N + j] * hq * (1.f - 0.5f * hq);
     gz[K + j] = gp;
@@ -150,7 +151,7 @@ __global__ __launch_bounds__(kThreads) void coeffs_bwd_subset_kernel(
   for (int m = M; m < MP; ++m) vr[m] = 0.f;
 #pragma unroll
   for (int g = 0; g < 3; ++g) gz[M + g] = ga[g];
-  o.coefx[t] = (r * r / static_cast<float>(nC)) * dot;
+  rec[N * N + 2 * N] = (r * r / static_cast<float>(nC)) * dot;
 }
 
 // ---------------------------------------------------------------------------
