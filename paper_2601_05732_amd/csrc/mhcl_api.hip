@@ -107,18 +107,18 @@ struct Disarm {
     if ((expr) != hipSuccess) return MHCL_ERR_HIP;  \
   } while (0)
 
-// u_raw, sumsq of every token: MFMA kernel when the shape allows, else plain ALU
+// u_raw, sumsq of every token: bf16 MFMAs on packed W, or fp64 ones on W as it is
 hipError_t run_projection(const mhcl_desc &d, const void *x, const float *W, float *u_raw,
                           float *sumsq, char *Wp, int stage, hipStream_t s) {
   const int M = logits(d);
-  if (fast_path_ok(d)) {
+  if (!proj_fullprec_used(d)) {
     hipError_t e = launch_pack_w_b(d, M, W, Wp, s);
     if (e != hipSuccess) return e;
     StageBracket br(stage, s);
     return launch_proj_mfma(d, M, x, Wp, u_raw, sumsq, s);
   }
   StageBracket br(stage, s);
-  return launch_proj_generic(d, M, x, W, u_raw, sumsq, s);
+  return launch_proj_fullprec(d, M, x, W, u_raw, sumsq, s);
 }
 
 // per-token coefficients from the projection: compile-time tables for the full
@@ -478,7 +478,10 @@ int mhcl_bwd_fused(const mhcl_desc *desc, const void *x, const void *y, const fl
     {
       StageBracket br(MHCL_STAGE_BWD_REDUCE, s);
       if (wide) {
-        MHCL_HIP(launch_proj_mfma(*desc, M, x, f.Wp, f.u_raw, f.sumsq, s));
+        if (proj_fullprec_used(*desc))
+          MHCL_HIP(launch_proj_fullprec(*desc, M, x, W, f.u_raw, f.sumsq, s));
+        else
+          MHCL_HIP(launch_proj_mfma(*desc, M, x, f.Wp, f.u_raw, f.sumsq, s));
         MHCL_HIP(launch_bwd_dots_fast(*desc, x, y, g_xout, g_h, f, s));
       } else {
         MHCL_HIP(launch_bwd_reduce(*desc, M, x, y, g_xout, g_h, f, s));

@@ -1700,7 +1700,7 @@ hipError_t launch_pack_w_b(const mhcl_desc &d, int M, const float *W, void *Wp, 
 }
 
 int proj_ksplit(const mhcl_desc &d) {
-  if (!fast_path_ok(d)) return 1;
+  if (proj_fullprec_used(d)) return proj_fullprec_parts(d);
   const int M = res_logits(d) + 2 * d.n;
   int kc = 4, tok = 128;
   const int want = 256;   // one block per CU
@@ -1833,7 +1833,9 @@ FastBwdWs::FastBwdWs(const mhcl_desc &d, void *ws) {
 hipError_t launch_pack_w_ab(const mhcl_desc &d, int M, const float *W, const FastBwdWs &w,
                             hipStream_t s) {
   const int K = d.n * d.C, NT = logit_tiles(M), MS = logit_steps(M);
-  const int nb_b = ((K / 32) * NT * 64 + 255) / 256;
+  // (the B layout has no reader where the wide path recomputes with the fp64 projection)
+  const bool no_b = fast_bwd_wide(d) && proj_fullprec_used(d);
+  const int nb_b = no_b ? 0 : ((K / 32) * NT * 64 + 255) / 256;
   const int nb_a = ((K / 64) * 4 * MS * 64 + 255) / 256;
   // one fp16 part where the only reader is bwd_out_w16_kernel; its scale needs max |W| first
   const bool a16 = fast_bwd_whi(d);

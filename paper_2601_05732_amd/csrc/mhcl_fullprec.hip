@@ -78,6 +78,119 @@ struct Piece<F32, 4> {
 };
 
 // ---------------------------------------------------------------------------
+// u_raw[t][m] = sum_k x_hat[t][k] W[k][m] and sumsq[t] = sum_k x_hat[t][k]^2 (the two reductions
+// over nC behind RMSNorm and the linear maps of Sec. 3.2), with exact products and fp64 sums
+// (v_mfma_f64_16x16x4_f64): f32 streams keep their logits to fp32 rounding at any width.
+// A block takes 16 tokens, its eight waves every eighth step of 4 V columns of the block's part of
+// the row (gridDim.y parts; the consumer adds the parts' slices in order).  Lane (r, q) reads V
+// consecutive columns of token r; element e is the left operand of the MFMAs whose contraction
+// index q stands for column k0 + V q + e, the right operand comes straight from W (fp32, as
+// it is; all blocks read the same rows, so these are L2 hits).
+// Bound by the fp64 matrix rate (67 TFLOP/s: 12 us for f32 n = 4, C = 768, 4096 tokens; it takes
+// 23; one thread per logit and eighth of the row, fp64 on the vector units, took 145).
+constexpr int kProjWaves = 8;
+
+template <typename IO, int NT>
+__global__ __launch_bounds__(64 * kProjWaves, 1) void proj_fullprec_kernel(
+    const void *__restrict__ x, const float *__restrict__ W, int nC, int M, int64_t T,
+    int steps_per_part, float *__restrict__ u_raw, float *__restrict__ sumsq) {
+  constexpr int V = IO::kVec;
+  __shared__ double red[2][kProjWaves][4][64];
+  __shared__ double red_ss[kProjWaves][16];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r = lane & 15, q = lane >> 4;
+  const int64_t t0 = static_cast<int64_t>(blockIdx.x) * 16;
+  const int64_t tl = t0 + r < T ? t0 + r : T - 1;
+  const size_t row = static_cast<size_t>(tl) * nC;
+  const int nsteps = (nC + 4 * V - 1) / (4 * V);
+  const int s0 = blockIdx.y * steps_per_part;
+  const int s1 = s0 + steps_per_part < nsteps ? s0 + steps_per_part : nsteps;
+  int mj[NT];   // this lane's logit of tile j (past the last one: the last again, not stored)
+#pragma unroll
+  for (int j = 0; j < NT; ++j) mj[j] = 16 * j + r < M ? 16 * j + r : M - 1;
+
+  f64x4 acc[NT];
+  double ss = 0.0;
+#pragma unroll
+  for (int j = 0; j < NT; ++j) acc[j] = f64x4{0.0, 0.0, 0.0, 0.0};
+  struct In {
+    Piece<IO, V> x;
+    float w[V][NT];
+  };
+  auto load = [&](In &in, int s) {
+    const int k = s * 4 * V + V * q;
+    const int kc = k < nC ? k : nC - V;   // (only the row's last step can reach past it)
+    in.x.load(x, row + kc);
+#pragma unroll
+    for (int e = 0; e < V; ++e)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) in.w[e][j] = W[static_cast<size_t>(kc + e) * M + mj[j]];
+  };
+  auto compute = [&](In &in, int s) {
+    if (s * 4 * V + V * q >= nC) {
+      in.x.clear();
+#pragma unroll
+      for (int e = 0; e < V; ++e)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) in.w[e][j] = 0.f;
+    }
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      const double xv = in.x.at(e);
+      ss += xv * xv;
+#pragma unroll
+      for (int j = 0; j < NT; ++j) acc[j] = mfma_f64(xv, static_cast<double>(in.w[e][j]), acc[j]);
+    }
+  };
+  {
+    In a, b;
+    int s = s0 + wave;
+    load(a, s < s1 ? s : s1 - 1);
+    for (; s + kProjWaves < s1; s += 2 * kProjWaves) {
+      load(b, s + kProjWaves);
+      __builtin_amdgcn_sched_barrier(0);
+      compute(a, s);
+      load(a, s + 2 * kProjWaves < s1 ? s + 2 * kProjWaves : s1 - 1);
+      __builtin_amdgcn_sched_barrier(0);
+      compute(b, s + kProjWaves);
+    }
+    if (s < s1) compute(a, s);
+  }
+
+  ss += __shfl_xor(ss, 16, 64);   // the four lanes of a token
+  ss += __shfl_xor(ss, 32, 64);
+  if (q == 0) red_ss[wave][r] = ss;
+  // the waves' sums, two logit tiles at a time, in wave order
+#pragma unroll
+  for (int base = 0; base < NT; base += 2) {
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      if (base + j < NT) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) red[j][wave][i][lane] = acc[base + j][i];
+      }
+    __syncthreads();
+    const int j = threadIdx.x >> 8, i = (threadIdx.x >> 6) & 3;
+    if (base + j < NT) {
+      double sum = red[j][0][i][lane];
+#pragma unroll
+      for (int w = 1; w < kProjWaves; ++w) sum += red[j][w][i][lane];
+      // fp64 tiles hold rows 4 i + q: token 4 i + q, logit 16 (base + j) + r
+      const int64_t t = t0 + 4 * i + q;
+      const int m = 16 * (base + j) + r;
+      if (t < T && m < M) u_raw[(blockIdx.y * T + t) * M + m] = static_cast<float>(sum);
+    }
+  }
+  if (threadIdx.x < 16 && t0 + threadIdx.x < T) {   // (red_ss was complete at the barriers above)
+    double sum = red_ss[0][threadIdx.x];
+#pragma unroll
+    for (int w = 1; w < kProjWaves; ++w) sum += red_ss[w][threadIdx.x];
+    sumsq[blockIdx.y * T + t0 + threadIdx.x] = static_cast<float>(sum);
+  }
+}
+
+// ---------------------------------------------------------------------------
 // g_W[k][m] = sum_t x_hat[t][k] vr[t][m], the one reduction over tokens.
 // A wave owns 16 V columns and takes four tokens per step: lane (r, q) reads V consecutive
 // columns of token q, which are the left operands of V MFMAs (tile v: rows are columns
@@ -310,6 +423,48 @@ int gw_columns(const mhcl_desc &d, int M) {
 }
 
 }  // namespace
+
+// Where the bf16 MFMA projection applies too, this one is used for few tokens: it needs no packed W
+// and spreads over the chip by splitting rows, but runs at the fp64 rate.  Its time is about
+// 0.65 us per million of T tiles nC; the other one's, while its blocks do not fill the chip, 5.5 us
+// for packing W and 1.66 us per 1000 columns of a row.  Both sides measured (the mhcl_coeffs call,
+// n = 4): C = 4096 at 16 tokens 15 against 36 us, at 1024 31 / 46, at 2048 54 / 46; C = 1024 at
+// 1024 tokens 15 / 22, at 2048 21 / 22, at 4096 31 / 22; C = 256 at 4096 tokens 14.6 / 16.0.
+bool proj_fullprec_used(const mhcl_desc &d) {
+  if (!fast_path_ok(d)) return true;
+  const int64_t nC = static_cast<int64_t>(d.n) * d.C;
+  const int tiles = logit_tiles(res_logits(d) + 2 * d.n);
+  return d.T * tiles <= 8000000 / nC + 2500;
+}
+
+// Parts of a row: enough blocks for two per compute unit, each wave with at least one step.
+// The coefficient stages add the parts' slices one after the other, so they are few.
+int proj_fullprec_parts(const mhcl_desc &d) {
+  const int M = res_logits(d) + 2 * d.n;
+  const int V = d.io_dtype == MHCL_BF16 ? BF16::kVec : F32::kVec;
+  const int nsteps = (d.n * d.C + 4 * V - 1) / (4 * V);
+  const int64_t groups = (d.T + 15) / 16;
+  const bool sliced = M % 4 == 0 && M <= 32 && d.res_mode != MHCL_RES_SUBSET;
+  const int most = sliced ? 16 : 4;
+  int parts = 1;
+  while (parts < most && groups * parts < 512 && nsteps >= 2 * parts * kProjWaves) parts *= 2;
+  return parts;
+}
+
+hipError_t launch_proj_fullprec(const mhcl_desc &d, int M, const void *x, const float *W,
+                                float *u_raw, float *sumsq, hipStream_t s) {
+  const int V = d.io_dtype == MHCL_BF16 ? BF16::kVec : F32::kVec;
+  const int nC = d.n * d.C, parts = proj_fullprec_parts(d);
+  const int nsteps = (nC + 4 * V - 1) / (4 * V), spp = (nsteps + parts - 1) / parts;
+  const dim3 grid(static_cast<unsigned>((d.T + 15) / 16), parts);
+  return dispatch_io(d.io_dtype, [&](auto io) {
+    return dispatch_tiles(logit_tiles(M), [&](auto nt) {
+      hipLaunchKernelGGL((proj_fullprec_kernel<decltype(io), decltype(nt)::value>), grid,
+                         dim3(64 * kProjWaves), 0, s, x, W, nC, M, d.T, spp, u_raw, sumsq);
+      return hipGetLastError();
+    });
+  });
+}
 
 // Token chunks: one round of blocks on the 256 compute units, each with at least two steps
 // of its loop (128 tokens each) to run ahead in.

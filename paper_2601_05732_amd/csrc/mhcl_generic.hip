@@ -62,67 +62,6 @@ __device__ __forceinline__ void block_sum(float (&v)[CNT], float *red /* [4*CNT]
   __syncthreads();
 }
 
-// ------------------------------------------------------------ projection
-// u_raw[t][m] = sum_k x_hat[t][k] W[k][m] and sumsq[t] = sum_k x_hat[t][k]^2
-// (the two reductions over nC behind RMSNorm and the linear maps of Sec. 3.2).
-// One block per kTok tokens; thread (m lane 0..31, k slice 0..7).
-constexpr int kTok = 4;
-
-template <typename IO>
-__global__ __launch_bounds__(kBlock) void proj_generic_kernel(const void *__restrict__ x,
-                                                              const float *__restrict__ W, int nC,
-                                                              int M, int64_t T,
-                                                              float *__restrict__ u_raw,
-                                                              float *__restrict__ sumsq) {
-  __shared__ float red[8][kTok][32];
-  __shared__ float red2[4 * kTok];
-  const int64_t t0 = static_cast<int64_t>(blockIdx.x) * kTok;
-  const int ml = threadIdx.x & 31, ks = threadIdx.x >> 5;
-  int64_t row[kTok];
-#pragma unroll
-  for (int i = 0; i < kTok; ++i) row[i] = (t0 + i < T ? t0 + i : T - 1) * nC;
-
-  float ss[kTok];
-#pragma unroll
-  for (int i = 0; i < kTok; ++i) ss[i] = 0.f;
-  for (int k = threadIdx.x; k < nC; k += kBlock) {
-#pragma unroll
-    for (int i = 0; i < kTok; ++i) {
-      const float v = IO::load1(x, row[i] + k);
-      ss[i] += v * v;
-    }
-  }
-  block_sum<kTok>(ss, red2);
-  if (threadIdx.x < kTok && t0 + threadIdx.x < T) sumsq[t0 + threadIdx.x] = red2[threadIdx.x];
-
-  for (int m0 = 0; m0 < M; m0 += 32) {
-    const int m = m0 + ml;
-    // nC / 8 terms per thread (2048 at n C = 16384): carried in fp64 so that this path,
-    // the one f32 streams take, keeps its logits to fp32 rounding at any width
-    double acc[kTok];
-#pragma unroll
-    for (int i = 0; i < kTok; ++i) acc[i] = 0.0;
-    if (m < M) {
-      for (int k = ks; k < nC; k += 8) {
-        const double w = W[static_cast<size_t>(k) * M + m];
-#pragma unroll
-        for (int i = 0; i < kTok; ++i) acc[i] += static_cast<double>(IO::load1(x, row[i] + k)) * w;
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kTok; ++i) red[ks][i][ml] = static_cast<float>(acc[i]);
-    __syncthreads();
-    if (threadIdx.x < kTok * 32) {
-      const int i = threadIdx.x >> 5;
-      float s = 0.f;
-#pragma unroll
-      for (int q = 0; q < 8; ++q) s += red[q][i][ml];
-      if (m < M && t0 + i < T) u_raw[(t0 + i) * M + m] = s;
-    }
-  }
-}
-
 // ------------------------------------------------------------ coefficients
 template <int N, int MODE>
 __global__ __launch_bounds__(128) void coeffs_epilogue_kernel(
@@ -601,16 +540,6 @@ inline unsigned blocks_for(int64_t items, int per) {
 }  // namespace
 
 // ================================================================ launchers
-hipError_t launch_proj_generic(const mhcl_desc &d, int M, const void *x, const float *W,
-                               float *u_raw, float *sumsq, hipStream_t s) {
-  return dispatch_io(d.io_dtype, [&](auto io) {
-    using IO = decltype(io);
-    hipLaunchKernelGGL(proj_generic_kernel<IO>, dim3(blocks_for(d.T, kTok)), dim3(kBlock), 0, s, x,
-                       W, d.n * d.C, M, d.T, u_raw, sumsq);
-    return hipGetLastError();
-  });
-}
-
 hipError_t launch_coeffs_epilogue(const mhcl_desc &d, int parts, const float *u_raw,
                                   const float *sumsq, const float *b, const float *alpha, float *H_res, float *H_pre,
                                   float *H_post, hipStream_t s) {

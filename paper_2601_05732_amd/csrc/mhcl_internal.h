@@ -42,8 +42,6 @@ struct BwdTokenBufs {
 };
 
 // ---- generic (plain ALU) kernels: any n in 1..5, bf16 or f32 streams -----
-hipError_t launch_proj_generic(const mhcl_desc &d, int M, const void *x, const float *W,
-                               float *u_raw, float *sumsq, hipStream_t s);
 hipError_t launch_coeffs_epilogue(const mhcl_desc &d, int parts, const float *u_raw,
                                   const float *sumsq, const float *b, const float *alpha, float *H_res, float *H_pre,
                                   float *H_post, hipStream_t s);
@@ -80,6 +78,11 @@ hipError_t launch_param_sums_rows(int64_t rows, int M, const float *src, float *
                                   float *g_alpha, float *part, hipStream_t s);
 
 // ---- full-precision products on the matrix cores: any C, bf16 or f32 streams -----
+// whether u_raw, sumsq come from the fp64 projection below (else from launch_proj_mfma)
+bool proj_fullprec_used(const mhcl_desc &d);
+int proj_fullprec_parts(const mhcl_desc &d);   // slices it writes
+hipError_t launch_proj_fullprec(const mhcl_desc &d, int M, const void *x, const float *W,
+                                float *u_raw, float *sumsq, hipStream_t s);
 // g_W from x and vr (rows as in BwdTokenBufs); `partials` holds gw_chunks_fullprec(d) results
 // of [nC, M] when that is more than one
 int gw_chunks_fullprec(const mhcl_desc &d);
@@ -112,8 +115,8 @@ hipError_t launch_ds_chain(int n, int L, int64_t T, const float *H, float *colsu
 
 // ---- bf16 fast path (MFMA projections); needs fast_path_ok(desc) ---------
 bool fast_path_ok(const mhcl_desc &d);
-// The MFMA projection may split K over up to kMaxKSplit blocks per token tile;
-// u_raw and sumsq then hold that many slices ([parts][T][M], [parts][T]).
+// Either projection may split K over several blocks per token tile (the MFMA one over up to
+// kMaxKSplit); u_raw and sumsq then hold that many slices ([parts][T][M], [parts][T]).
 constexpr int kMaxKSplit = 4;
 int proj_ksplit(const mhcl_desc &d);
 size_t packed_w_b_bytes(const mhcl_desc &d, int M);
