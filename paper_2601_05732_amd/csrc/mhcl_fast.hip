@@ -1769,7 +1769,9 @@ int out_gw_tokens_per_block(const mhcl_desc &d) {
   // Token chunks: as many as make the grid one round of resident blocks (all blocks
   // then start together and the blocks of a chunk walk down the same rows side by
   // side), never more than 64 MiB of partial g_W copies, and blocks of a whole
-  // number of 64-token iterations (at least 256 tokens, to amortise staging W).
+  // number of 64-token iterations.  With few tokens a block is down to one of them: filling the
+  // chip is worth more than sharing a block's copy of W among tokens (the fused backward at n = 4,
+  // C = 1024, 2048 tokens: 126 us with at least 256 tokens per block, 109 with 128, 102 with 64).
   const int64_t M = res_logits(d) + 2 * d.n;
   const int64_t copy_bytes = static_cast<int64_t>(d.n) * d.C * M * 4;
   const bool pair = (d.C / 64) % 2 == 0;            // two 64-column steps per block
@@ -1780,7 +1782,6 @@ int out_gw_tokens_per_block(const mhcl_desc &d) {
   const int64_t cap = (64ll << 20) / copy_bytes;
   if (chunks > cap) chunks = cap < 1 ? 1 : cap;
   int64_t tpb = ((d.T + chunks - 1) / chunks + 63) / 64 * 64;
-  if (tpb < 256) tpb = 256;
   return static_cast<int>(tpb);
 }
 
