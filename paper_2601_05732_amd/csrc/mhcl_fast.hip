@@ -1781,8 +1781,8 @@ int out_gw_tokens_per_block(const mhcl_desc &d) {
   if (chunks < 1) chunks = 1;
   const int64_t cap = (64ll << 20) / copy_bytes;
   if (chunks > cap) chunks = cap < 1 ? 1 : cap;
-  int64_t tpb = ((d.T + chunks - 1) / chunks + 63) / 64 * 64;
-  return static_cast<int>(tpb);
+  const int64_t tpb = ((d.T + chunks - 1) / chunks + 63) / 64 * 64;
+  return tpb > 0 ? static_cast<int>(tpb) : 64;   // (no tokens: workspace queries still divide by it)
 }
 
 int gw_chunks_fast(const mhcl_desc &d) {
