@@ -56,7 +56,7 @@ struct CoeffsWs {
 };
 
 struct BwdWs {
-  float *u_raw, *sumsq, *gH_res, *gH_pre, *gH_post, *partials, *psum;
+  float *u_raw, *sumsq, *gH_res, *gH_pre, *gH_post, *partials;
   char *Wp;
   BwdTokenBufs tok;
   size_t bytes;
@@ -69,7 +69,7 @@ struct BwdWs {
     sumsq = c.take<float>(parts * T);
     tok.rec = c.take<float>(T * token_rec_floats(n));
     tok.vr = c.take<float>(T * ((M + 15) / 16 * 16));
-    tok.gz = c.take<float>(T * (M + 3));
+    tok.gz = c.take<float>(static_cast<size_t>(gz_rows(d)) * (M + 3));
     gH_res = gH_pre = gH_post = nullptr;
     if (need_dots) {
       gH_res = c.take<float>(T * n * n);
@@ -79,7 +79,6 @@ struct BwdWs {
     const int chunks = gw_chunks_fullprec(d);
     partials = chunks > 1 ? c.take<float>(static_cast<size_t>(chunks) * n * d.C * M) : nullptr;
     Wp = fast_path_ok(d) ? c.take<char>(packed_w_b_bytes(d, M)) : nullptr;
-    psum = c.take<float>(static_cast<size_t>(param_sum_blocks(d)) * (M + 3));
     bytes = c.off;
   }
 };
@@ -128,17 +127,17 @@ hipError_t run_coeffs_epilogue(const mhcl_desc &d, int parts, const float *u_raw
                                float *H_res, float *H_pre, float *H_post, hipStream_t s) {
   if (coeffs_group_ok(d))
     return launch_coeffs_group(d, parts, u_raw, sumsq, b, alpha, H_res, H_pre, H_post, s);
-  return launch_coeffs_epilogue(d, parts, u_raw, sumsq, b, alpha, H_res, H_pre, H_post, s);
+  return launch_token_coeffs(d, parts, u_raw, sumsq, b, alpha, H_res, H_pre, H_post, s);
 }
 hipError_t run_coeffs_bwd_epilogue(const mhcl_desc &d, const float *u_raw, const float *sumsq,
                                    const float *b, const float *alpha, const float *g_H_res,
                                    const float *g_H_pre, const float *g_H_post,
                                    const BwdTokenBufs &o, hipStream_t s) {
-  if (d.res_mode == MHCL_RES_SUBSET)
-    return launch_coeffs_bwd_subset(d, proj_ksplit(d), u_raw, sumsq, b, alpha, g_H_res, g_H_pre,
-                                    g_H_post, o, s);
-  return launch_coeffs_bwd_epilogue(d, proj_ksplit(d), u_raw, sumsq, b, alpha, g_H_res, g_H_pre,
-                                    g_H_post, o, s);
+  if (coeffs_group_ok(d))
+    return launch_coeffs_bwd_group(d, proj_ksplit(d), u_raw, sumsq, b, alpha, g_H_res, g_H_pre,
+                                   g_H_post, o, s);
+  return launch_token_bwd_full(d, proj_ksplit(d), u_raw, sumsq, b, alpha, g_H_res, g_H_pre, g_H_post,
+                               o, s);
 }
 
 // argument checks of mhcl_fwd_coeffs_pre and its allocation-free variant
@@ -443,7 +442,9 @@ int mhcl_coeffs_bwd(const mhcl_desc *desc, const void *x, const float *W, const 
                                    w.tok, s));
   MHCL_HIP(launch_gx_fullprec(*desc, M, false, x, W, nullptr, nullptr, w.tok, g_x, nullptr, s));
   MHCL_HIP(launch_gw_fullprec(*desc, M, x, w.tok.vr, w.partials, g_W, s));
-  MHCL_HIP(launch_param_sums(*desc, M, w.tok.gz, g_b, g_alpha, w.psum, s));
+  MHCL_HIP(launch_bwd_finish(w.partials, static_cast<size_t>(desc->n) * desc->C * M,
+                             gw_chunks_fullprec(*desc), g_W, w.tok.gz, gz_rows(*desc), M, g_b, g_alpha,
+                             s));
   return MHCL_OK;
 }
 
@@ -490,7 +491,7 @@ int mhcl_bwd_fused(const mhcl_desc *desc, const void *x, const void *y, const fl
     if (coeffs_group_ok(*desc))
       MHCL_HIP(launch_bwd_epilogue_group(*desc, b, alpha, f, s));
     else
-      MHCL_HIP(launch_bwd_epilogue_fast(*desc, b, alpha, f, s));
+      MHCL_HIP(launch_token_bwd_fast(*desc, b, alpha, f, s));
     if (wide) {
       {
         StageBracket br(MHCL_STAGE_BWD_OUT, s);
@@ -503,7 +504,7 @@ int mhcl_bwd_fused(const mhcl_desc *desc, const void *x, const void *y, const fl
       MHCL_HIP(launch_bwd_out_gw(*desc, M, x, g_xout, g_h, f, g_x, g_y, g_W, s));
     }
     MHCL_HIP(launch_bwd_finish(f.partials, static_cast<size_t>(desc->n) * desc->C * M,
-                               fast_gw_chunks(*desc), g_W, f.gz, (desc->T + 63) / 64, M, g_b, g_alpha,
+                               fast_gw_chunks(*desc), g_W, f.gz, gz_rows(*desc), M, g_b, g_alpha,
                                s));
     return MHCL_OK;
   }
@@ -517,7 +518,9 @@ int mhcl_bwd_fused(const mhcl_desc *desc, const void *x, const void *y, const fl
     MHCL_HIP(launch_gx_fullprec(*desc, M, true, x, W, g_xout, g_h, w.tok, g_x, g_y, s));
   }
   MHCL_HIP(launch_gw_fullprec(*desc, M, x, w.tok.vr, w.partials, g_W, s));
-  MHCL_HIP(launch_param_sums(*desc, M, w.tok.gz, g_b, g_alpha, w.psum, s));
+  MHCL_HIP(launch_bwd_finish(w.partials, static_cast<size_t>(desc->n) * desc->C * M,
+                             gw_chunks_fullprec(*desc), g_W, w.tok.gz, gz_rows(*desc), M, g_b, g_alpha,
+                             s));
   return MHCL_OK;
 }
 

@@ -12,11 +12,6 @@ namespace mhcl {
 
 namespace {
 
-__device__ __forceinline__ void split_bf16(float w, uint16_t &hi, uint16_t &lo) {
-  hi = f32_to_bf16(w);
-  lo = f32_to_bf16(w - bf16_to_f32(hi));
-}
-
 // W [K, M] fp32 -> B layout (see mhcl_mfma.h).  One thread per (block pair, lane).
 __device__ __forceinline__ void pack_w_b_thread(int idx, const float *__restrict__ W, int K, int M,
                                                 int NT, uint4 *__restrict__ Wp) {
@@ -626,126 +621,6 @@ __global__ __launch_bounds__(256) void bwd_dots_fast_kernel(
       gH_post[t * N + i] = dots[N * N + i];
       gH_pre[t * N + i] = dots[N * N + N + i];
     }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Per-token stage between the two backward passes: coefficients (recomputed),
-// g_z, and the operands pass 2 needs, in the layouts its MFMAs read:
-//   cpk  [T][CP] f32 : H_res (N*N) | H_pre (N) | H_post (N) | coefx
-//   vr   [Tpad][MP32] bf16 hi, lo : vr = r alpha g_z, row per token
-//   vrT  [Tpad/32][MP16][32] bf16 hi, lo : the same, tokens innermost
-//   gzs  [Tpad/64][M+3] f32 : per 64 tokens, the sums of g_z and of the per-group
-//        g_z u (what g_b and g_alpha are summed from), in a fixed butterfly order
-// Tokens T..Tpad-1 get zero vr so that padded tiles add nothing to g_W.
-// One wave per block, one token per lane.
-// F16ROWS (the single-kernel wide pass 2): the vr ROWS hold fp16 hi, lo parts of
-// vr / s with s = max_m |vr_m| of the token (1 if that is 0), so that any gradient
-// scale fits fp16; s goes to cpk[N*N + 2N + 1].  vrT stays bf16 in either case.
-template <int N, int MODE, bool F16ROWS>
-__global__ __launch_bounds__(64) void bwd_epilogue_fast_kernel(
-    const float *__restrict__ u_raw, const float *__restrict__ sumsq, int parts,
-    const float *__restrict__ b, const float *__restrict__ alpha, const float *__restrict__ gH_res,
-    const float *__restrict__ gH_pre, const float *__restrict__ gH_post, int nC, float eps,
-    int sk_iters, int64_t T, int CP, float *__restrict__ cpk, uint16_t *__restrict__ vr_hi,
-    uint16_t *__restrict__ vr_lo, uint16_t *__restrict__ vrT_hi, uint16_t *__restrict__ vrT_lo,
-    float *__restrict__ gz_sums) {
-  constexpr int R = Dims<N, MODE>::R, M = Dims<N, MODE>::M;
-  constexpr int MP32 = (M + 31) / 32 * 32, MP16 = (M + 15) / 16 * 16;
-  const int64_t t = static_cast<int64_t>(blockIdx.x) * 64 + threadIdx.x;   // < Tpad
-  const int64_t blk = t >> 5;
-  const int tin = static_cast<int>(t & 31);
-  const bool live = t < T;
-  const int64_t tl = live ? t : T - 1;   // padded lanes recompute the last token and discard it
-  float u[M], a[R], Hr[N * N], Hp[N], Hq[N], gz[M + 3];
-  float gr[N * N], gp[N], gq[N];
-  float sums[(MODE == MHCL_RES_SK) ? 2 * kMaxSkIters * N : 1];
-  float ssq = sumsq[tl];
-#pragma unroll
-  for (int m = 0; m < M; ++m) u[m] = u_raw[tl * M + m];
-  for (int pt = 1; pt < parts; ++pt) {   // K-split slices of the projection, added in order
-    ssq += sumsq[pt * T + tl];
-#pragma unroll
-    for (int m = 0; m < M; ++m) u[m] += u_raw[(pt * T + tl) * M + m];
-  }
-#pragma unroll
-  for (int e = 0; e < N * N; ++e) gr[e] = gH_res[tl * N * N + e];
-#pragma unroll
-  for (int j = 0; j < N; ++j) { gp[j] = gH_pre[tl * N + j]; gq[j] = gH_post[tl * N + j]; }
-  const TokenParams p{alpha[0], alpha[1], alpha[2], eps, sk_iters};
-  const float r = token_coeffs<N, MODE>(u, ssq, nC, b, p, Hr, Hp, Hq, a,
-                                        (MODE == MHCL_RES_SK) ? sums : nullptr);
-  if (live) {
-    float *cp = cpk + t * CP;
-#pragma unroll
-    for (int e = 0; e < N * N; ++e) cp[e] = Hr[e];
-#pragma unroll
-    for (int j = 0; j < N; ++j) { cp[N * N + j] = Hp[j]; cp[N * N + N + j] = Hq[j]; }
-  }
-  token_coeffs_bwd<N, MODE>(gr, gp, gq, a, Hr, Hp, Hq, sums, sk_iters, gz);
-  float ga[3] = {0.f, 0.f, 0.f}, dot = 0.f;
-  uint32_t ph[MP32 / 2], pl[MP32 / 2];   // the token's vr row, two 16-bit parts per word
-#pragma unroll
-  for (int i = 0; i < MP32 / 2; ++i) { ph[i] = 0; pl[i] = 0; }
-  float inv_s = 1.f;
-  if constexpr (F16ROWS) {
-    float vmax = 0.f;
-#pragma unroll
-    for (int m = 0; m < M; ++m) {
-      const int g = m < R ? 0 : (m < R + N ? 1 : 2);
-      const float al = g == 0 ? p.alpha_res : (g == 1 ? p.alpha_pre : p.alpha_post);
-      vmax = fmaxf(vmax, fabsf(r * al * (live ? gz[m] : 0.f)));
-    }
-    const float sc = vmax > 0.f ? vmax : 1.f;
-    inv_s = 1.f / sc;
-    if (live) cpk[t * CP + N * N + 2 * N + 1] = sc;
-  }
-#pragma unroll
-  for (int m = 0; m < M; ++m) {
-    const int g = m < R ? 0 : (m < R + N ? 1 : 2);
-    const float al = g == 0 ? p.alpha_res : (g == 1 ? p.alpha_pre : p.alpha_post);
-    if (!live) gz[m] = 0.f;
-    const float vr = r * al * gz[m];
-    ga[g] += gz[m] * (r * u[m]);
-    dot += vr * u[m];
-    uint16_t hi, lo;
-    split_bf16(vr, hi, lo);
-    vrT_hi[(blk * MP16 + m) * 32 + tin] = hi;
-    vrT_lo[(blk * MP16 + m) * 32 + tin] = lo;
-    if constexpr (F16ROWS) {
-      const float vs = vr * inv_s;
-      const _Float16 h16 = static_cast<_Float16>(vs);
-      const _Float16 l16 = static_cast<_Float16>(vs - static_cast<float>(h16));
-      hi = __builtin_bit_cast(uint16_t, h16);
-      lo = __builtin_bit_cast(uint16_t, l16);
-    }
-    ph[m / 2] |= static_cast<uint32_t>(hi) << (16 * (m & 1));
-    pl[m / 2] |= static_cast<uint32_t>(lo) << (16 * (m & 1));
-  }
-#pragma unroll
-  for (int m = M; m < MP16; ++m) {
-    vrT_hi[(blk * MP16 + m) * 32 + tin] = 0;
-    vrT_lo[(blk * MP16 + m) * 32 + tin] = 0;
-  }
-  u32x4 *rh = reinterpret_cast<u32x4 *>(vr_hi + t * MP32);
-  u32x4 *rl = reinterpret_cast<u32x4 *>(vr_lo + t * MP32);
-#pragma unroll
-  for (int i = 0; i < MP32 / 8; ++i) {
-    rh[i] = u32x4{ph[4 * i], ph[4 * i + 1], ph[4 * i + 2], ph[4 * i + 3]};
-    rl[i] = u32x4{pl[4 * i], pl[4 * i + 1], pl[4 * i + 2], pl[4 * i + 3]};
-  }
-  if (live) cpk[t * CP + N * N + 2 * N] = (r * r / static_cast<float>(nC)) * dot;
-#pragma unroll
-  for (int g = 0; g < 3; ++g) gz[M + g] = ga[g];   // zero for padded lanes
-  // sum over the 64 tokens of the wave: butterfly, the same order in every run
-#pragma unroll
-  for (int m = 0; m < M + 3; ++m) {
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) gz[m] += __shfl_xor(gz[m], off, 64);
-  }
-  if (threadIdx.x == 0) {
-#pragma unroll
-    for (int m = 0; m < M + 3; ++m) gz_sums[static_cast<int64_t>(blockIdx.x) * (M + 3) + m] = gz[m];
   }
 }
 
@@ -1811,7 +1686,7 @@ FastBwdWs::FastBwdWs(const mhcl_desc &d, void *ws) {
   gH_pre = c.take<float>(T * n);
   gH_post = c.take<float>(T * n);
   cpk = c.take<float>(T * CP);
-  gz = c.take<float>((Tpad / 64) * (M + 3));
+  gz = c.take<float>(static_cast<size_t>(gz_rows(d)) * (M + 3));
   vr_hi = c.take<uint16_t>(Tpad * MP32);
   vr_lo = c.take<uint16_t>(Tpad * MP32);
   vrT_hi = c.take<uint16_t>(Tpad * MP16);
@@ -1826,7 +1701,6 @@ FastBwdWs::FastBwdWs(const mhcl_desc &d, void *ws) {
     const size_t chunks = fused_chunks > static_cast<size_t>(gw_chunks_fast(d)) ? fused_chunks : gw_chunks_fast(d);
     partials = c.take<float>(chunks * K * M);
   }
-  psum = c.take<float>(static_cast<size_t>(param_sum_blocks(d)) * (M + 3));
   D = fast_bwd_wide(d) ? c.take<float>(T * K) : nullptr;
   bytes = c.off;
 }
@@ -1908,35 +1782,6 @@ hipError_t launch_bwd_dots_fast(const mhcl_desc &d, const void *x, const void *y
     case 6: return go(std::integral_constant<int, 6>{});
     case 7: return go(std::integral_constant<int, 7>{});
     case 8: return go(std::integral_constant<int, 8>{});
-  }
-  return hipErrorInvalidValue;
-}
-
-hipError_t launch_bwd_epilogue_fast(const mhcl_desc &d, const float *b, const float *alpha,
-                                    const FastBwdWs &w, hipStream_t s) {
-  const int64_t Tpad = (d.T + 63) / 64 * 64;
-  auto go = [&](auto nn, auto mm) {
-    constexpr int N = decltype(nn)::value, MODE = decltype(mm)::value;
-    if (w.MP32 != (Dims<N, MODE>::M + 31) / 32 * 32 || w.MP16 != (Dims<N, MODE>::M + 15) / 16 * 16)
-      return hipErrorInvalidValue;
-    constexpr bool kF16 = N == 5;   // the widths of fast_bwd_whi(): rows for bwd_out_w16_kernel
-    if (kF16 != fast_bwd_whi(d) || (kF16 && w.CP < N * N + 2 * N + 2)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((bwd_epilogue_fast_kernel<N, MODE, kF16>),
-                       dim3(static_cast<unsigned>(Tpad / 64)), dim3(64), 0, s, w.u_raw, w.sumsq,
-                       w.parts, b, alpha, w.gH_res, w.gH_pre, w.gH_post, d.n * d.C, d.eps,
-                       d.sk_iters, d.T, w.CP, w.cpk, w.vr_hi, w.vr_lo, w.vrT_hi, w.vrT_lo, w.gz);
-    return hipGetLastError();
-  };
-  using L = std::integral_constant<int, MHCL_RES_LITE>;
-  using S = std::integral_constant<int, MHCL_RES_SK>;
-  const bool lite = d.res_mode == MHCL_RES_LITE;
-  switch (d.n) {
-    case 1: return lite ? go(std::integral_constant<int, 1>{}, L{}) : go(std::integral_constant<int, 1>{}, S{});
-    case 2: return lite ? go(std::integral_constant<int, 2>{}, L{}) : go(std::integral_constant<int, 2>{}, S{});
-    case 3: return lite ? go(std::integral_constant<int, 3>{}, L{}) : go(std::integral_constant<int, 3>{}, S{});
-    case 4: return lite ? go(std::integral_constant<int, 4>{}, L{}) : go(std::integral_constant<int, 4>{}, S{});
-    // the full permutation form at n = 5 (120 permutations) takes the eight-lanes-per-token kernel
-    case 5: return lite ? hipErrorInvalidValue : go(std::integral_constant<int, 5>{}, S{});
   }
   return hipErrorInvalidValue;
 }

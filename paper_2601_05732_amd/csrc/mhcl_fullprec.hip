@@ -489,7 +489,7 @@ hipError_t launch_gw_fullprec(const mhcl_desc &d, int M, const void *x, const fl
                        M, d.T, chunk, dst);
     return hipGetLastError();
   };
-  hipError_t e = dispatch_io(d.io_dtype, [&](auto io) {
+  return dispatch_io(d.io_dtype, [&](auto io) {   // (the chunks are added by launch_bwd_finish)
     return dispatch_tiles(logit_tiles(M), [&](auto nt) {
       using IO = decltype(io);
       if constexpr (IO::kVec == 8 && decltype(nt)::value <= 3)
@@ -498,8 +498,6 @@ hipError_t launch_gw_fullprec(const mhcl_desc &d, int M, const void *x, const fl
         return go(io, nt, std::integral_constant<int, 4>{});
     });
   });
-  if (e != hipSuccess || chunks == 1) return e;
-  return launch_sum_partials(partials, static_cast<size_t>(nC) * M, chunks, g_W, s);
 }
 
 hipError_t launch_gx_fullprec(const mhcl_desc &d, int M, bool fused, const void *x, const float *W,

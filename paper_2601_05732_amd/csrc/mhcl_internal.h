@@ -38,13 +38,10 @@ constexpr int token_rec() { return token_rec_floats(N); }
 struct BwdTokenBufs {
   float *rec;     // [T, token_rec<n>()] H_res | H_pre | H_post | coefx = (r^2 / nC) <vr, u_raw>
   float *vr;      // [T, 16 ceil(M / 16)] r * alpha_g * g_z (the vector multiplied with W and x), zero-padded
-  float *gz;      // [T, M+3] g_z, then the three per-group sums of g_z * u
+  float *gz;      // [gz_rows(d), M+3] sums over a block's tokens of g_z and of the per-group g_z u
 };
 
 // ---- generic (plain ALU) kernels: any n in 1..5, bf16 or f32 streams -----
-hipError_t launch_coeffs_epilogue(const mhcl_desc &d, int parts, const float *u_raw,
-                                  const float *sumsq, const float *b, const float *alpha, float *H_res, float *H_pre,
-                                  float *H_post, hipStream_t s);
 hipError_t launch_pre(const mhcl_desc &d, const void *x, const float *H_pre, void *h, hipStream_t s);
 hipError_t launch_post(const mhcl_desc &d, const void *x, const void *y, const float *H_res,
                        const float *H_post, void *x_out, hipStream_t s);
@@ -57,25 +54,9 @@ hipError_t launch_pre_bwd(const mhcl_desc &d, const void *x, const float *H_pre,
 hipError_t launch_bwd_dots(const mhcl_desc &d, const void *x, const void *y, const void *g_xout,
                            const void *g_h, float *g_H_res, float *g_H_post, float *g_H_pre,
                            hipStream_t s);
-hipError_t launch_coeffs_bwd_epilogue(const mhcl_desc &d, int parts, const float *u_raw,
-                                      const float *sumsq,
-                                      const float *b, const float *alpha, const float *g_H_res,
-                                      const float *g_H_pre, const float *g_H_post,
-                                      const BwdTokenBufs &o, hipStream_t s);
-// out = sum over the chunks' partial results [chunks][size], in a fixed order
-hipError_t launch_sum_partials(const float *partials, size_t size, int chunks, float *out,
-                               hipStream_t s);
 hipError_t launch_copy(void *dst, const void *src, size_t bytes, hipStream_t s);
 // a fill kernel (safe under graph capture, unlike a memset node)
 hipError_t launch_fill_zero(float *p, size_t count, hipStream_t s);
-// g_b [M] and g_alpha [3] from gz [T, M+3]; part is scratch of
-// param_sum_blocks(d) * (M+3) floats
-int param_sum_blocks(const mhcl_desc &d);
-hipError_t launch_param_sums(const mhcl_desc &d, int M, const float *gz, float *g_b, float *g_alpha,
-                             float *part, hipStream_t s);
-// the same over `rows` rows of [M+3] (rows <= T: `part` as above is large enough)
-hipError_t launch_param_sums_rows(int64_t rows, int M, const float *src, float *g_b,
-                                  float *g_alpha, float *part, hipStream_t s);
 
 // ---- full-precision products on the matrix cores: any C, bf16 or f32 streams -----
 // whether u_raw, sumsq come from the fp64 projection below (else from launch_proj_mfma)
@@ -94,16 +75,28 @@ hipError_t launch_gx_fullprec(const mhcl_desc &d, int M, bool fused, const void 
                              const void *g_xout, const void *g_h, const BwdTokenBufs &o, void *g_x,
                              void *g_y, hipStream_t s);
 
+// ---- per-token stage of the other forms (n <= 4, Sinkhorn-Knopp) --------------
+bool token_stage_many(const mhcl_desc &d, bool backward);   // the variant for many tokens
+hipError_t launch_token_coeffs(const mhcl_desc &d, int parts, const float *u_raw, const float *sumsq,
+                               const float *b, const float *alpha, float *H_res, float *H_pre,
+                               float *H_post, hipStream_t s);
+hipError_t launch_token_bwd_full(const mhcl_desc &d, int parts, const float *u_raw,
+                                 const float *sumsq, const float *b, const float *alpha,
+                                 const float *g_H_res, const float *g_H_pre, const float *g_H_post,
+                                 const BwdTokenBufs &o, hipStream_t s);
+
 // ---- permutation-subset form (run-time table d.perm, n up to 8) --------------
 // eight lanes per token: permutation subsets and the full form at n = 5
 bool coeffs_group_ok(const mhcl_desc &d);
+// rows of the g_z sums that the backward's per-token stage leaves for launch_bwd_finish
+int64_t gz_rows(const mhcl_desc &d);
 hipError_t launch_coeffs_group(const mhcl_desc &d, int parts, const float *u_raw,
                                const float *sumsq, const float *b, const float *alpha,
                                float *H_res, float *H_pre, float *H_post, hipStream_t s);
-hipError_t launch_coeffs_bwd_subset(const mhcl_desc &d, int parts, const float *u_raw,
-                                    const float *sumsq, const float *b, const float *alpha,
-                                    const float *g_H_res, const float *g_H_pre,
-                                    const float *g_H_post, const BwdTokenBufs &o, hipStream_t s);
+hipError_t launch_coeffs_bwd_group(const mhcl_desc &d, int parts, const float *u_raw,
+                                   const float *sumsq, const float *b, const float *alpha,
+                                   const float *g_H_res, const float *g_H_pre, const float *g_H_post,
+                                   const BwdTokenBufs &o, hipStream_t s);
 
 // ---- diagnostics ----------------------------------------------------------
 // z [T,M] and spread [T] (max - min of the residual logits); either may be null
@@ -151,9 +144,9 @@ bool fast_bwd_whi(const mhcl_desc &d);    // wide case, n >= 5, where W fits LDS
 bool fast_bwd_wide(const mhcl_desc &d);   // n >= 5 or a subset: pass 2 split into W vr and the mixing
 int gw_chunks_fast(const mhcl_desc &d);
 struct FastBwdWs {
-  // gz: [ceil(T/64)][M+3] sums of g_z and g_z u over each 64 tokens
+  // gz: [gz_rows(d)][M+3] sums of g_z and g_z u over each block's tokens
   // wmax_part: partial maxima of |W|; wscale: {scale, 1 / scale} of the fp16 copy of W
-  float *u_raw, *sumsq, *gH_res, *gH_pre, *gH_post, *cpk, *gz, *partials, *psum, *D, *wmax_part, *wscale;
+  float *u_raw, *sumsq, *gH_res, *gH_pre, *gH_post, *cpk, *gz, *partials, *D, *wmax_part, *wscale;
   uint16_t *vr_hi, *vr_lo, *vrT_hi, *vrT_lo;
   char *Wp, *Wa;
   int CP, MP32, MP16, parts;
@@ -167,8 +160,9 @@ hipError_t launch_bwd_reduce(const mhcl_desc &d, int M, const void *x, const voi
                              hipStream_t s);
 hipError_t launch_bwd_dots_fast(const mhcl_desc &d, const void *x, const void *y, const void *g_xout,
                                 const void *g_h, const FastBwdWs &w, hipStream_t s);
-hipError_t launch_bwd_epilogue_fast(const mhcl_desc &d, const float *b, const float *alpha,
-                                    const FastBwdWs &w, hipStream_t s);
+// per-token stage between the two passes: coefficients again, g_z and what pass 2 reads
+hipError_t launch_token_bwd_fast(const mhcl_desc &d, const float *b, const float *alpha,
+                                 const FastBwdWs &w, hipStream_t s);
 // the same stage for the permutation-subset form (run-time table)
 hipError_t launch_bwd_epilogue_group(const mhcl_desc &d, const float *b, const float *alpha,
                                      const FastBwdWs &w, hipStream_t s);
@@ -181,7 +175,7 @@ hipError_t launch_bwd_out_gw(const mhcl_desc &d, int M, const void *x, const voi
 hipError_t launch_bwd_gw(const mhcl_desc &d, int M, const void *x, const FastBwdWs &w, float *g_W,
                          hipStream_t s);
 // g_W from the chunks' partial sums (none if chunks == 1) and g_b, g_alpha from the
-// [rows, M+3] per-64-token sums of g_z, in one launch
+// [rows, M+3] sums of g_z, in one launch
 hipError_t launch_bwd_finish(const float *partials, size_t size, int chunks, float *g_W,
                              const float *gz_rows, int64_t rows, int M, float *g_b, float *g_alpha,
                              hipStream_t s);

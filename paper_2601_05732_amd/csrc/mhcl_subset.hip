@@ -3,11 +3,8 @@
 // paragraph on larger n: a run-time subset, n up to 8, K up to 128; also the
 // full form at n = 5, whose 120 permutations make the unrolled compile-time
 // sums too large for the registers); gates as in Sec. 3.2.
-//   coeffs_group_kernel     : eight lanes per token; forward coefficients and
-//                             the stage between the two passes of the fused backward
-//   coeffs_bwd_subset_kernel: one token per thread, for the separable
-//                             mhcl_coeffs_bwd (weights in LDS: a register array
-//                             indexed by a run-time k would go to scratch memory)
+// Eight lanes per token: forward coefficients and the stage of the backward between the
+// reductions over C and the stream outputs.
 #include "mhcl_common.h"
 #include "mhcl_internal.h"
 
@@ -15,162 +12,29 @@ namespace mhcl {
 
 namespace {
 
-constexpr int kThreads = 64;
-
-// Entries are clamped to 0..n-1 so that a malformed table cannot index outside
-// the n x n arrays (the result is then simply not doubly stochastic).
-__device__ __forceinline__ void stage_table(const int8_t *__restrict__ sigma, int count, int n,
-                                            int8_t *dst) {
-  for (int i = threadIdx.x; i < count; i += kThreads) {
-    int v = sigma[i];
-    v = v < 0 ? 0 : (v > n - 1 ? n - 1 : v);
-    dst[i] = static_cast<int8_t>(v);
-  }
-  __syncthreads();
-}
-
-// logits of token t summed over the K-split slices, in slice order
-__device__ __forceinline__ float raw_logit(const float *__restrict__ u_raw, int parts, int64_t T,
-                                           int64_t t, int M, int m) {
-  float u = u_raw[t * M + m];
-  for (int pt = 1; pt < parts; ++pt) u += u_raw[(pt * T + t) * M + m];
-  return u;
-}
-
-// softmax weights of the residual logits into a_s[k][thread]; returns r
-template <int N>
-__device__ __forceinline__ float subset_weights(const float *__restrict__ u_raw,
-                                                const float *__restrict__ sumsq, int parts,
-                                                const float *__restrict__ b, float alpha_res,
-                                                int nC, float eps, int64_t T, int64_t t, int K,
-                                                int M, float (*a_s)[kThreads]) {
-  float ssq = sumsq[t];
-  for (int pt = 1; pt < parts; ++pt) ssq += sumsq[pt * T + t];
-  const float r = 1.f / sqrtf(ssq / static_cast<float>(nC) + eps);
-  float zmax = -INFINITY;
-  for (int k = 0; k < K; ++k) {
-    const float z = alpha_res * (r * raw_logit(u_raw, parts, T, t, M, k)) + b[k];
-    a_s[k][threadIdx.x] = z;
-    zmax = fmaxf(zmax, z);
-  }
-  float sum = 0.f;
-  for (int k = 0; k < K; ++k) {
-    const float e = expf(a_s[k][threadIdx.x] - zmax);
-    a_s[k][threadIdx.x] = e;
-    sum += e;
-  }
-  for (int k = 0; k < K; ++k) a_s[k][threadIdx.x] = a_s[k][threadIdx.x] / sum;
-  return r;
-}
-
-// H[i][j] = sum over the given permutations with sigma_k(i) = j of a_k
-template <int N>
-__device__ __forceinline__ void subset_mix(const float (*a_s)[kThreads], const int8_t *sig, int K,
-                                           float (&H)[N * N]) {
-#pragma unroll
-  for (int e = 0; e < N * N; ++e) H[e] = 0.f;
-  for (int k = 0; k < K; ++k) {
-    const float w = a_s[k][threadIdx.x];
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const int sj = sig[k * N + i];
-#pragma unroll
-      for (int j = 0; j < N; ++j) H[i * N + j] += (j == sj) ? w : 0.f;
-    }
-  }
-}
-
-// Backward: g_a[k] = sum_i g_H_res[i][sigma_k(i)], g_z_res = a (g_a - <a, g_a>),
-// gates through the logistic function; then the operands of the projection's
-// backward as in the other forms: vr = r alpha_g g_z, coefx, and gz | sums of
-// g_z u per group.
-template <int N>
-__global__ __launch_bounds__(kThreads) void coeffs_bwd_subset_kernel(
-    const float *__restrict__ u_raw, const float *__restrict__ sumsq, int parts,
-    const float *__restrict__ b, const float *__restrict__ alpha,
-    const float *__restrict__ gH_res, const float *__restrict__ gH_pre,
-    const float *__restrict__ gH_post, int nC, float eps, int64_t T, int K,
-    const int8_t *__restrict__ sigma, BwdTokenBufs o) {
-  __shared__ float a_s[kMaxPerm][kThreads];
-  __shared__ float g_s[N * N][kThreads];
-  __shared__ int8_t sig[kMaxPerm * N];
-  stage_table(sigma, K * N, N, sig);
-  const int64_t t = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
-  if (t >= T) return;
-  const int M = K + 2 * N;
-  const float a0 = alpha[0], a1 = alpha[1], a2 = alpha[2];
-  const float r = subset_weights<N>(u_raw, sumsq, parts, b, a0, nC, eps, T, t, K, M, a_s);
-  float H[N * N];
-  subset_mix<N>(a_s, sig, K, H);
-  float *rec = o.rec + t * token_rec<N>();
-#pragma unroll
-  for (int e = 0; e < N * N; ++e) {
-    rec[e] = H[e];
-    g_s[e][threadIdx.x] = gH_res[t * N * N + e];
-  }
-  auto g_a = [&](int k) {
-    float s = 0.f;
-#pragma unroll
-    for (int i = 0; i < N; ++i) s += g_s[i * N + sig[k * N + i]][threadIdx.x];
-    return s;
-  };
-  float mean = 0.f;
-  for (int k = 0; k < K; ++k) mean += a_s[k][threadIdx.x] * g_a(k);
-  float ga[3] = {0.f, 0.f, 0.f}, dot = 0.f;
-  float *gz = o.gz + t * (M + 3);
-  const int MP = (M + 15) / 16 * 16;
-  float *vr = o.vr + t * MP;   // (rows padded with zeros)
-  for (int k = 0; k < K; ++k) {
-    const float g = a_s[k][threadIdx.x] * (g_a(k) - mean);
-    const float u = raw_logit(u_raw, parts, T, t, M, k);
-    const float v = r * a0 * g;
-    gz[k] = g;
-    vr[k] = v;
-    ga[0] += g * (r * u);
-    dot += v * u;
-  }
-#pragma unroll
-  for (int j = 0; j < N; ++j) {
-    const float up = raw_logit(u_raw, parts, T, t, M, K + j);
-    const float uq = raw_logit(u_raw, parts, T, t, M, K + N + j);
-    const float hp = sigmoidf(a1 * (r * up) + b[K + j]);
-    const float hq = 2.f * sigmoidf(a2 * (r * uq) + b[K + N + j]);
-    rec[N * N + j] = hp;
-    rec[N * N + N + j] = hq;
-    const float gp = gH_pre[t * N + j] * hp * (1.f - hp);
-    const float gq = gH_post[t * N + j] * hq * (1.f - 0.5f * hq);
-    gz[K + j] = gp;
-    gz[K + N + j] = gq;
-    const float vp = r * a1 * gp, vq = r * a2 * gq;
-    vr[K + j] = vp;
-    vr[K + N + j] = vq;
-    ga[1] += gp * (r * up);
-    ga[2] += gq * (r * uq);
-    dot += vp * up + vq * uq;
-  }
-  for (int m = M; m < MP; ++m) vr[m] = 0.f;
-#pragma unroll
-  for (int g = 0; g < 3; ++g) gz[M + g] = ga[g];
-  rec[N * N + 2 * N] = (r * r / static_cast<float>(nC)) * dot;
-}
-
 // ---------------------------------------------------------------------------
-// The same per-token work with eight lanes per token (block = 64 tokens, 512
-// threads), for the table forms with many logits (a permutation subset, or
-// the full form at n = 5 with its 120 permutations): one token per lane left
-// a single wave per CU walking K-long dependent loops over strided global
-// loads.  Here the block first stages its tokens' logits, summed over the
+// Block = 64 tokens, 512 threads (one token per lane leaves a single wave per CU walking K-long
+// dependent loops over strided global loads).  The block first stages its tokens' logits, summed over the
 // K-split slices, with contiguous loads into LDS; lane l of a token then owns
 // the logits k = l, l + 8, ... (softmax, g_a, g_z) and row l of H_res.
-//   BWD = false: H_res, H_pre, H_post                       (forward)
-//   BWD = true : the stage between the two backward passes, outputs as
-//                bwd_epilogue_fast_kernel writes them (cpk, vr, vrT, gz sums);
-//                F16ROWS as there.
+//   kGroupForward: H_res, H_pre, H_post
+//   kGroupFast   : for the bf16 backward, in the layouts its MFMAs read:
+//     cpk  [T][CP] f32 : H_res (N*N) | H_pre (N) | H_post (N) | coefx
+//     vr   [Tpad][MP32] bf16 hi, lo : vr = r alpha g_z, row per token
+//     vrT  [Tpad/32][MP16][32] bf16 hi, lo : the same, tokens innermost
+//     gzs  [Tpad/64][M+3] f32 : per 64 tokens, the sums of g_z and of the per-group g_z u
+//          (what g_b and g_alpha are summed from), in token order
+//     Tokens T..Tpad-1 get zero vr so that padded tiles add nothing to g_W.
+//     F16ROWS (the single-kernel wide pass 2): the vr ROWS hold fp16 hi, lo parts of vr / s with
+//     s = max_m |vr_m| of the token (1 if that is 0), so that any gradient scale fits fp16; s
+//     goes to cpk[N*N + 2N + 1].  vrT stays bf16 in either case.
+//   kGroupFull   : for the full-precision backward: cpk, gzs and vr as fp32 rows [T][MP16]
 // The table comes from device memory (`sigma`) or, if `use_tab`, by value.
 struct TableArg {
   int8_t s[kMaxPerm * kMaxNSubset];
 };
 constexpr int kGTok = 64, kGThreads = 512, kOwn = kMaxPerm / 8;
+enum { kGroupForward, kGroupFast, kGroupFull };
 
 __device__ __forceinline__ float group_sum(float v) {
   v += __shfl_xor(v, 1, 64);
@@ -193,7 +57,7 @@ inline size_t group_lds_bytes(int N, int K, bool bwd) {
   return fl * sizeof(float) + static_cast<size_t>(K) * N;
 }
 
-template <int N, bool BWD, bool F16ROWS>
+template <int N, int OUT, bool F16ROWS>
 __global__ __launch_bounds__(kGThreads) void coeffs_group_kernel(
     const float *__restrict__ u_raw, const float *__restrict__ sumsq, int parts,
     const float *__restrict__ b, const float *__restrict__ alpha,
@@ -203,7 +67,8 @@ __global__ __launch_bounds__(kGThreads) void coeffs_group_kernel(
     float *__restrict__ H_res, float *__restrict__ H_pre, float *__restrict__ H_post, int CP,
     int MP32, int MP16, float *__restrict__ cpk, uint16_t *__restrict__ vr_hi,
     uint16_t *__restrict__ vr_lo, uint16_t *__restrict__ vrT_hi, uint16_t *__restrict__ vrT_lo,
-    float *__restrict__ gz_sums) {
+    float *__restrict__ vr32, float *__restrict__ gz_sums) {
+  constexpr bool BWD = OUT != kGroupForward;
   extern __shared__ float smem[];
   const int M = K + 2 * N, ld = M | 1;
   constexpr int NN = N * N, gld = NN + 1;
@@ -405,6 +270,12 @@ __global__ __launch_bounds__(kGThreads) void coeffs_group_kernel(
       const float al = m < K ? a0 : (m < K + N ? a1 : a2);
       return r_s[tk] * al * a_s[tk * ld + m];
     };
+    if constexpr (OUT == kGroupFull) {
+      for (int e = tid; e < kGTok * MP16; e += kGThreads) {
+        const int tk = e / MP16, m = e - tk * MP16;
+        if (t0 + tk < T) vr32[(t0 + tk) * MP16 + m] = vr_of(tk, m);
+      }
+    } else {
     auto split = [](float v, bool f16, uint16_t &hi, uint16_t &lo) {
       if (f16) {
         const _Float16 h16 = static_cast<_Float16>(v);
@@ -446,6 +317,7 @@ __global__ __launch_bounds__(kGThreads) void coeffs_group_kernel(
       *reinterpret_cast<uint4 *>(vrT_hi + off) = pack8(hi);
       *reinterpret_cast<uint4 *>(vrT_lo + off) = pack8(lo);
     }
+    }
     // sums over the block's 64 tokens, token order
     if (tid < M + 3) {
       float sacc = 0.f;
@@ -473,9 +345,6 @@ hipError_t dispatch_n8(int n, F &&f) {
   }
   return hipErrorInvalidValue;
 }
-
-inline unsigned blocks_of(int64_t T) { return static_cast<unsigned>((T + kThreads - 1) / kThreads); }
-
 
 // table of the launch: the caller's subset, or all 120 permutations of n = 5 in
 // lexicographic order (full form), passed by value
@@ -521,28 +390,36 @@ hipError_t launch_coeffs_group(const mhcl_desc &d, int parts, const float *u_raw
   if (!group_table(d, g)) return hipErrorInvalidValue;
   return dispatch_n8(d.n, [&](auto nn) {
     constexpr int N = decltype(nn)::value;
-    auto kern = coeffs_group_kernel<N, false, false>;
+    auto kern = coeffs_group_kernel<N, kGroupForward, false>;
     const size_t lds = group_lds_bytes(N, g.K, false);
     hipError_t e = allow_lds(kern, lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>((d.T + kGTok - 1) / kGTok)),
                        dim3(kGThreads), lds, s, u_raw, sumsq, parts, b, alpha, nullptr, nullptr,
                        nullptr, d.n * d.C, d.eps, d.T, g.K, g.sigma, g.tab, g.use_tab, H_res, H_pre,
-                       H_post, 0, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
+                       H_post, 0, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
     return hipGetLastError();
   });
 }
 
-hipError_t launch_coeffs_bwd_subset(const mhcl_desc &d, int parts, const float *u_raw,
-                                    const float *sumsq, const float *b, const float *alpha,
-                                    const float *g_H_res, const float *g_H_pre,
-                                    const float *g_H_post, const BwdTokenBufs &o, hipStream_t s) {
-  if (d.n_perm < 1 || d.n_perm > kMaxPerm || !d.perm) return hipErrorInvalidValue;
+hipError_t launch_coeffs_bwd_group(const mhcl_desc &d, int parts, const float *u_raw,
+                                   const float *sumsq, const float *b, const float *alpha,
+                                   const float *g_H_res, const float *g_H_pre, const float *g_H_post,
+                                   const BwdTokenBufs &o, hipStream_t s) {
+  GroupTable g;
+  if (!group_table(d, g)) return hipErrorInvalidValue;
+  const int M = g.K + 2 * d.n;
   return dispatch_n8(d.n, [&](auto nn) {
     constexpr int N = decltype(nn)::value;
-    hipLaunchKernelGGL(coeffs_bwd_subset_kernel<N>, dim3(blocks_of(d.T)), dim3(kThreads), 0, s,
-                       u_raw, sumsq, parts, b, alpha, g_H_res, g_H_pre, g_H_post, d.n * d.C, d.eps,
-                       d.T, d.n_perm, d.perm, o);
+    auto kern = coeffs_group_kernel<N, kGroupFull, false>;
+    const size_t lds = group_lds_bytes(N, g.K, true);
+    hipError_t e = allow_lds(kern, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>((d.T + kGTok - 1) / kGTok)),
+                       dim3(kGThreads), lds, s, u_raw, sumsq, parts, b, alpha, g_H_res, g_H_pre,
+                       g_H_post, d.n * d.C, d.eps, d.T, g.K, g.sigma, g.tab, g.use_tab, nullptr, nullptr,
+                       nullptr, token_rec<N>(), 0, (M + 15) / 16 * 16, o.rec, nullptr, nullptr, nullptr,
+                       nullptr, o.vr, o.gz);
     return hipGetLastError();
   });
 }
@@ -566,13 +443,13 @@ hipError_t launch_bwd_epilogue_group(const mhcl_desc &d, const float *b, const f
                          w.u_raw, w.sumsq, w.parts, b, alpha, w.gH_res, w.gH_pre, w.gH_post,
                          d.n * d.C, d.eps, d.T, g.K, g.sigma, g.tab, g.use_tab, nullptr, nullptr,
                          nullptr, w.CP, w.MP32, w.MP16, w.cpk, w.vr_hi, w.vr_lo, w.vrT_hi, w.vrT_lo,
-                         w.gz);
+                         nullptr, w.gz);
       return hipGetLastError();
     };
     if constexpr (N >= 5) {
-      if (f16) return launch(coeffs_group_kernel<N, true, true>);
+      if (f16) return launch(coeffs_group_kernel<N, kGroupFast, true>);
     }
-    return launch(coeffs_group_kernel<N, true, false>);
+    return launch(coeffs_group_kernel<N, kGroupFast, false>);
   });
 }
 

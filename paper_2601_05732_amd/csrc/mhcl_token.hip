@@ -1,0 +1,597 @@
+// Per-token stage of the compile-time forms (all n! permutations for n <= 4, Sinkhorn-Knopp):
+// from the raw projection to the coefficients, and in the backward on to g_z and the operands of
+// what follows.  The work of one token is a few hundred dependent instructions, so it is spread
+// over a group of lanes: 16 for n <= 4 (lane 4 i + j owns entry (i, j) of H_res, and the
+// residual logits l, l + 16), 64 for n = 5 (8 i + j).  Sums over the group are DPP steps.
+#include "mhcl_common.h"
+#include "mhcl_internal.h"
+#include "mhcl_mfma.h"
+
+namespace mhcl {
+
+namespace {
+
+// tokens and threads per block
+template <int L>
+constexpr int kTokBlock = L == 4 ? 64 : 32;
+template <int L>
+constexpr int kTokThreads = L == 4 ? 4 * kTokBlock<4> : 512;
+
+// kinds of output
+enum { kOutForward, kOutFast, kOutFull };
+
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+constexpr int kRor1 = 0x121, kRor2 = 0x122, kRor4 = 0x124, kRor8 = 0x128;   // rotate in rows of 16 lanes
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E;                                   // exchange in quads
+constexpr int kHalfMirror = 0x141;                                          // reverse eight lanes
+
+// over all lanes of a token's group (every lane gets the same bits: each step adds a pair)
+template <int L, typename OP>
+__device__ __forceinline__ float group_reduce(float v, OP op) {
+  if constexpr (L == 4) {
+    v = op(v, dpp<kXor2>(v));
+    v = op(v, dpp<kXor1>(v));
+  } else {
+    v = op(v, dpp<kRor8>(v));
+    v = op(v, dpp<kRor4>(v));
+    v = op(v, dpp<kRor2>(v));
+    v = op(v, dpp<kRor1>(v));
+  }
+  if constexpr (L == 64) {
+    v = op(v, __shfl_xor(v, 16, 64));
+    v = op(v, __shfl_xor(v, 32, 64));
+  }
+  return v;
+}
+struct Add {
+  __device__ __forceinline__ float operator()(float a, float b) const { return a + b; }
+};
+struct Max {
+  __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); }
+};
+// Sums over the rows i (one per column that the lane has entries of) and over the columns j (one:
+// a lane's entries are of one row) of a matrix spread over the group.
+template <int L, int CC>
+__device__ __forceinline__ void column_sums(const float (&v)[CC], float (&s)[CC]) {
+#pragma unroll
+  for (int c = 0; c < CC; ++c) {
+    s[c] = v[c];
+    if constexpr (L == 4) {
+      s[c] += dpp<kXor2>(s[c]);
+      s[c] += dpp<kXor1>(s[c]);
+    } else if constexpr (L == 16) {
+      s[c] += dpp<kRor8>(s[c]);
+      s[c] += dpp<kRor4>(s[c]);
+    } else {
+      s[c] += dpp<kRor8>(s[c]);
+      s[c] += __shfl_xor(s[c], 16, 64);
+      s[c] += __shfl_xor(s[c], 32, 64);
+    }
+  }
+}
+template <int L, int CC>
+__device__ __forceinline__ float row_sum(const float (&v)[CC]) {
+  float s = v[0];
+#pragma unroll
+  for (int c = 1; c < CC; ++c) s += v[c];
+  if constexpr (L != 4) {
+    s += dpp<kXor1>(s);
+    s += dpp<kXor2>(s);
+  }
+  if constexpr (L == 64) s += dpp<kHalfMirror>(s);
+  return s;
+}
+
+// bit k set: permutation k has its 1 of row i in column j
+template <int N>
+constexpr uint32_t cell_mask(int i, int j) {
+  uint32_t m = 0;
+  for (int k = 0; k < factorial(N); ++k)
+    if (Perm<N>::tab.s[k][i] == j) m |= 1u << k;
+  return m;
+}
+// the columns of permutation k, two bits each
+template <int N>
+constexpr uint32_t perm_bits(int k) {
+  uint32_t b = 0;
+  for (int i = 0; i < N; ++i) b |= static_cast<uint32_t>(Perm<N>::tab.s[k][i]) << (2 * i);
+  return b;
+}
+template <int N, int... C>
+__device__ __forceinline__ uint32_t select_mask(int cell, std::integer_sequence<int, C...>) {
+  uint32_t m = 0;
+  ((m = cell == C ? std::integral_constant<uint32_t, cell_mask<N>(C / N, C % N)>::value : m), ...);
+  return m;
+}
+template <int N, int... K>
+__device__ __forceinline__ uint32_t select_perm(int k, std::integer_sequence<int, K...>) {
+  uint32_t b = 0;
+  ((b = k == K ? std::integral_constant<uint32_t, perm_bits<N>(K)>::value : b), ...);
+  return b;
+}
+
+struct TokenIn {
+  const float *u_raw, *sumsq;              // [parts][T][M], [parts][T]
+  int parts;
+  const float *gH_res, *gH_pre, *gH_post;  // backward: [gparts][T][n*n], [gparts][T][n]
+  int gparts;
+  const float *b, *alpha;
+  int nC;
+  float eps;
+  int sk_iters;
+  int64_t T;
+};
+struct TokenOut {
+  float *H_res, *H_pre, *H_post;                     // forward
+  float *rec;                                        // backward: records of `rec_ld` floats
+  int rec_ld;
+  uint16_t *vr_hi, *vr_lo, *vrT_hi, *vrT_lo;         // fast
+  float *vr;                                         // full
+  float *gz_sums;                                    // [blocks][M + 3]
+};
+
+// dst[tok][0..W) = the sums over the slices of src [slices][T][W], tokens t0 ... of the block
+// (past the last token: some valid element again).  begin() requests the first slice, so that
+// several arrays can be on their way together; finish() requests eight more slices at a time
+// and adds them in order.
+template <int W, int L>
+struct StageSums {
+  static constexpr int THREADS = kTokThreads<L>, BT = kTokBlock<L>;
+  static constexpr int IT = (BT * W + THREADS - 1) / THREADS;
+  const float *src;
+  size_t stride, e[IT];
+  float s[IT];
+  __device__ __forceinline__ void begin(const float *p, int64_t T, int64_t t0) {
+    src = p;
+    stride = static_cast<size_t>(T) * W;
+#pragma unroll
+    for (int i = 0; i < IT; ++i) {
+      const size_t at = static_cast<size_t>(t0) * W + threadIdx.x + i * THREADS;
+      e[i] = at < stride ? at : stride - 1;
+      s[i] = src[e[i]];
+    }
+  }
+  __device__ __forceinline__ void finish(int slices, float *dst, int ld) {
+    for (int p0 = 1; p0 < slices; p0 += 8) {
+      float v[IT][8];
+#pragma unroll
+      for (int i = 0; i < IT; ++i)
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[i][k] = src[(p0 + k < slices ? p0 + k : slices - 1) * stride + e[i]];
+#pragma unroll
+      for (int i = 0; i < IT; ++i)
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+          if (p0 + k < slices) s[i] += v[i][k];
+    }
+#pragma unroll
+    for (int i = 0; i < IT; ++i) {
+      const int idx = threadIdx.x + i * THREADS;
+      if (idx < BT * W) dst[(idx / W) * ld + idx % W] = s[i];
+    }
+  }
+};
+
+// floats of dynamic LDS per Sinkhorn-Knopp iteration: the divisors of its two half steps and their
+// reciprocals, one pair per line and token of a pass (backward only)
+template <int N, int MODE, int OUT, int L>
+constexpr int kSkPerIter = (MODE == MHCL_RES_SK && OUT != kOutForward)
+                               ? 2 * 2 * (N <= 4 ? kTokBlock<L> * 4 : 8 * 8) : 0;
+
+template <int N, int MODE, int OUT, int L>
+__global__ __launch_bounds__(kTokThreads<L>) void token_stage_kernel(TokenIn in, TokenOut out) {
+  constexpr int R = Dims<N, MODE>::R, M = Dims<N, MODE>::M, NN = N * N;
+  constexpr int THREADS = kTokThreads<L>, BT = kTokBlock<L>, NP = L == 64 ? 8 : 4;   // NP: lines per token, padded
+  constexpr int TP = THREADS / L;                              // tokens per pass
+  constexpr int CC = L == 4 ? N : 1;                           // entries of H_res per lane
+  constexpr int KK = MODE == MHCL_RES_LITE ? (R + L - 1) / L : CC;   // residual logits per lane
+  constexpr int GG = (2 * N + L - 1) / L;                      // gates per lane
+  constexpr int MP32 = (M + 31) / 32 * 32, MP16 = (M + 15) / 16 * 16;
+  constexpr bool BWD = OUT != kOutForward, F16ROWS = OUT == kOutFast && N == 5;
+  static_assert(MODE == MHCL_RES_SK || N <= 4, "the table of n = 5 does not fit these lanes");
+  static_assert((N <= 4) == (L != 64), "lanes per token");
+  constexpr int UL = (M + 2) | 1;                              // odd row lengths keep banks apart
+  constexpr int AL = (R + 3) / 4 * 4 + 4;
+  __shared__ float u_s[BT][UL];
+  __shared__ __align__(16) float a_s[MODE == MHCL_RES_LITE ? BT : 1][AL];
+  __shared__ float g_s[BWD ? BT : 1][(NN + 2 * N) | 1];
+  __shared__ float v_s[BWD ? BT : 1][MP32 + 1];         // vr, zero past the last logit
+  __shared__ float z_s[BWD ? BT : 1][(M + 3) | 1];      // g_z and the per-group sums of g_z u
+  __shared__ float sc_s[BT];                            // scale of the token's fp16 row
+  extern __shared__ float2 sk_s[];                             // {s, 1 / s} of every half step
+  const int tid = threadIdx.x;
+  const int64_t T = in.T, t0 = static_cast<int64_t>(blockIdx.x) * BT;
+
+  StageSums<M, L> su;
+  StageSums<1, L> ss;
+  StageSums<NN, L> sr;
+  StageSums<N, L> sp, sq;
+  su.begin(in.u_raw, T, t0);
+  ss.begin(in.sumsq, T, t0);
+  if constexpr (BWD) {
+    sr.begin(in.gH_res, T, t0);
+    sp.begin(in.gH_pre, T, t0);
+    sq.begin(in.gH_post, T, t0);
+  }
+  const int l = tid % L;
+  const int li = L == 4 ? l : l / NP, lj0 = L == 4 ? 0 : l % NP;   // row, column of the first entry
+  const bool row_ok = li < N, cell_ok = row_ok && lj0 < N;         // (all CC entries or none)
+  const int cell0 = cell_ok ? li * N + lj0 : 0;
+  // residual logit kk of this lane
+  auto logit = [&](int kk) { return MODE == MHCL_RES_LITE ? l + L * kk : cell0 + kk; };
+  auto owns = [&](int kk) { return MODE == MHCL_RES_LITE ? l + L * kk < R : cell_ok; };
+  const float a_res = in.alpha[0], a_pre = in.alpha[1], a_post = in.alpha[2];
+  float bk[KK], bg[GG], a_gate[GG];
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) bk[kk] = in.b[owns(kk) ? logit(kk) : 0];
+#pragma unroll
+  for (int gi = 0; gi < GG; ++gi) {   // gate l + L gi of pre | post
+    const int gt = l + L * gi < 2 * N ? l + L * gi : 0;
+    bg[gi] = in.b[R + gt];
+    a_gate[gi] = gt < N ? a_pre : a_post;
+  }
+  uint32_t mask[CC], pbits[KK];
+  if constexpr (MODE == MHCL_RES_LITE) {
+#pragma unroll
+    for (int c = 0; c < CC; ++c)
+      mask[c] = cell_ok ? select_mask<N>(cell0 + c, std::make_integer_sequence<int, NN>{}) : 0u;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk)
+      pbits[kk] = BWD ? select_perm<N>(l + L * kk, std::make_integer_sequence<int, R>{}) : 0u;
+  }
+  su.finish(in.parts, &u_s[0][0], UL);
+  ss.finish(in.parts, &u_s[0][M], UL);
+  if constexpr (BWD) {
+    constexpr int GL = (NN + 2 * N) | 1, PAD = MP32 - M > 0 ? MP32 - M : 1;
+    sr.finish(in.gparts, &g_s[0][0], GL);
+    sp.finish(in.gparts, &g_s[0][NN], GL);
+    sq.finish(in.gparts, &g_s[0][NN + N], GL);
+    for (int e = tid; e < BT * (MP32 - M); e += THREADS) v_s[e / PAD][M + e % PAD] = 0.f;
+  }
+  __syncthreads();
+
+  for (int pass = 0; pass < BT / TP; ++pass) {
+    const int tok = pass * TP + tid / L;
+    const int64_t t = t0 + tok;
+    const bool live = t < T;
+    const float *u = u_s[tok];
+    const float r = 1.f / sqrtf(u[M] / static_cast<float>(in.nC) + in.eps);
+
+    // residual logits of this lane, softmax weights / Sinkhorn-Knopp input a, entries H of H_res
+    float a[KK], uk[KK], H[CC];
+    float zmax = -INFINITY;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+      uk[kk] = u[owns(kk) ? logit(kk) : 0];
+      a[kk] = owns(kk) ? a_res * (r * uk[kk]) + bk[kk] : -INFINITY;
+      zmax = fmaxf(zmax, a[kk]);
+    }
+    zmax = group_reduce<L>(zmax, Max{});
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) a[kk] = owns(kk) ? expf(a[kk] - zmax) : 0.f;
+    // Sinkhorn-Knopp: one pair of floats per line, columns in the even half steps, rows in the odd
+    // ones; kHalf pairs per half step
+    constexpr int kHalf = TP * NP;
+    float2 *sk = MODE == MHCL_RES_SK ? sk_s + (tid / L) * NP : nullptr;
+    if constexpr (MODE == MHCL_RES_LITE) {
+      float s = 0.f;
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) s += a[kk];
+      s = group_reduce<L>(s, Add{});
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) {
+        a[kk] = a[kk] / s;
+        if (owns(kk)) a_s[tok][l + L * kk] = a[kk];
+      }
+      __builtin_amdgcn_wave_barrier();   // (a token's lanes are one wave's: LDS serves it in order)
+      const float *at = a_s[tok];
+#pragma unroll
+      for (int c = 0; c < CC; ++c) H[c] = 0.f;
+#pragma unroll
+      for (int k = 0; k < R; ++k) {   // k ascending
+        const float w = at[k];
+#pragma unroll
+        for (int c = 0; c < CC; ++c) H[c] += (mask[c] >> k) & 1u ? w : 0.f;
+      }
+    } else {
+#pragma unroll
+      for (int c = 0; c < CC; ++c) H[c] = a[c];
+      for (int it = 0; it < in.sk_iters; ++it) {
+        float s[CC], inv[CC];
+        column_sums<L>(H, s);
+#pragma unroll
+        for (int c = 0; c < CC; ++c) {
+          inv[c] = 1.f / s[c];
+          if (BWD && li == 0) sk[(2 * it) * kHalf + lj0 + c] = make_float2(s[c], inv[c]);
+          H[c] = cell_ok ? H[c] * inv[c] : 0.f;
+        }
+        const float rs = row_sum<L>(H), rinv = 1.f / rs;
+        if (BWD && lj0 == 0) sk[(2 * it + 1) * kHalf + li] = make_float2(rs, rinv);
+#pragma unroll
+        for (int c = 0; c < CC; ++c) H[c] = cell_ok ? H[c] * rinv : 0.f;
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+    float ug[GG], gate[GG];
+#pragma unroll
+    for (int gi = 0; gi < GG; ++gi) {
+      const int gt = l + L * gi < 2 * N ? l + L * gi : 0;
+      ug[gi] = u[R + gt];
+      const float sg = sigmoidf(a_gate[gi] * (r * ug[gi]) + bg[gi]);
+      gate[gi] = gt < N ? sg : 2.f * sg;
+    }
+
+    if constexpr (!BWD) {
+      if (live) {
+        if (cell_ok) {
+#pragma unroll
+          for (int c = 0; c < CC; ++c) out.H_res[t * NN + cell0 + c] = H[c];
+        }
+#pragma unroll
+        for (int gi = 0; gi < GG; ++gi) {
+          const int gt = l + L * gi;
+          if (gt < N) out.H_pre[t * N + gt] = gate[gi];
+          else if (gt < 2 * N) out.H_post[t * N + gt - N] = gate[gi];
+        }
+      }
+    } else {
+      float *rec = out.rec + t * out.rec_ld;
+      if (live) {
+        if (cell_ok) {
+#pragma unroll
+          for (int c = 0; c < CC; ++c) rec[cell0 + c] = H[c];
+        }
+#pragma unroll
+        for (int gi = 0; gi < GG; ++gi)
+          if (l + L * gi < 2 * N) rec[NN + l + L * gi] = gate[gi];
+      }
+      // gradient on this lane's residual logits
+      const float *g = g_s[tok];
+      float gz[KK];
+      if constexpr (MODE == MHCL_RES_LITE) {
+        float mean = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) {   // g_a[k] = sum_i g_H[i][sigma_k(i)]
+          gz[kk] = 0.f;
+#pragma unroll
+          for (int i = 0; i < N; ++i) gz[kk] += g[i * N + ((pbits[kk] >> (2 * i)) & 3u)];
+          mean += a[kk] * gz[kk];
+        }
+        mean = group_reduce<L>(mean, Add{});
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) gz[kk] = a[kk] * (gz[kk] - mean);
+      } else {
+        // back through the half steps: for Y = X / s, g_X = (g_Y - sum(g_Y Y)) / s and X = Y s
+        float gh[CC], p[CC], d[CC];
+#pragma unroll
+        for (int c = 0; c < CC; ++c) gh[c] = cell_ok ? g[cell0 + c] : 0.f;
+        for (int it = in.sk_iters - 1; it >= 0; --it) {
+          const float2 rs = sk[(2 * it + 1) * kHalf + li];
+          float2 cs[CC];
+#pragma unroll
+          for (int c = 0; c < CC; ++c) cs[c] = sk[(2 * it) * kHalf + lj0 + c];
+#pragma unroll
+          for (int c = 0; c < CC; ++c) p[c] = gh[c] * H[c];
+          const float dr = row_sum<L>(p);
+#pragma unroll
+          for (int c = 0; c < CC; ++c) {
+            gh[c] = cell_ok ? (gh[c] - dr) * rs.y : 0.f;
+            H[c] = cell_ok ? H[c] * rs.x : 0.f;
+            p[c] = gh[c] * H[c];
+          }
+          column_sums<L>(p, d);
+#pragma unroll
+          for (int c = 0; c < CC; ++c) {
+            gh[c] = cell_ok ? (gh[c] - d[c]) * cs[c].y : 0.f;
+            H[c] = cell_ok ? H[c] * cs[c].x : 0.f;
+          }
+        }
+#pragma unroll
+        for (int c = 0; c < CC; ++c) gz[c] = gh[c] * a[c];
+      }
+      // gradient on this lane's gates, vr = r alpha g_z and the sums
+      float dot = 0.f, ga0 = 0.f, ga1 = 0.f, ga2 = 0.f, vmax = 0.f;
+#pragma unroll
+      for (int gi = 0; gi < GG; ++gi) {
+        const int gt = l + L * gi;
+        const bool ok = live && gt < 2 * N;
+        const float gg = g[NN + (gt < 2 * N ? gt : 0)];
+        const float gzg = !ok ? 0.f : (gt < N ? gg * gate[gi] * (1.f - gate[gi])
+                                              : gg * gate[gi] * (1.f - 0.5f * gate[gi]));
+        const float v = ok ? r * a_gate[gi] * gzg : 0.f;
+        dot += v * ug[gi];
+        vmax = fmaxf(vmax, fabsf(v));
+        const float gag = gzg * (r * ug[gi]);
+        if (gt < N) ga1 += gag;
+        else ga2 += gag;
+        if (gt < 2 * N) { z_s[tok][R + gt] = gzg; v_s[tok][R + gt] = v; }
+      }
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) {
+        const bool ok = live && owns(kk);
+        if (!ok) gz[kk] = 0.f;
+        const float v = ok ? r * a_res * gz[kk] : 0.f;
+        ga0 += gz[kk] * (r * uk[kk]);
+        dot += v * uk[kk];
+        vmax = fmaxf(vmax, fabsf(v));
+        if (owns(kk)) { z_s[tok][logit(kk)] = gz[kk]; v_s[tok][logit(kk)] = v; }
+      }
+      dot = group_reduce<L>(dot, Add{});
+      ga0 = group_reduce<L>(ga0, Add{});
+      ga1 = group_reduce<L>(ga1, Add{});
+      ga2 = group_reduce<L>(ga2, Add{});
+      if constexpr (F16ROWS) vmax = group_reduce<L>(vmax, Max{});
+      if (l == 0) {
+        z_s[tok][M] = ga0;
+        z_s[tok][M + 1] = ga1;
+        z_s[tok][M + 2] = ga2;
+        if (live) rec[NN + 2 * N] = (r * r / static_cast<float>(in.nC)) * dot;
+        if constexpr (F16ROWS) {
+          const float sc = vmax > 0.f ? vmax : 1.f;
+          sc_s[tok] = 1.f / sc;
+          if (live) rec[NN + 2 * N + 1] = sc;
+        }
+      }
+      if constexpr (MODE == MHCL_RES_SK) __builtin_amdgcn_wave_barrier();   // the next pass rewrites sk
+    }
+  }
+  if constexpr (BWD) {
+    __syncthreads();
+    if constexpr (OUT == kOutFull) {
+      for (int e = tid; e < BT * MP16; e += THREADS) {
+        const int tk = e / MP16, m = e % MP16;
+        if (t0 + tk < T) out.vr[(t0 + tk) * MP16 + m] = v_s[tk][m];
+      }
+    } else {
+      // (tokens up to the next multiple of 64 exist in these arrays; past T they are zeros)
+      // eight values as hi and lo parts, packed two to a word (value = hi + lo up to 2^-17)
+      auto split8 = [](const float (&v)[8], auto f16, u32x4 &hi, u32x4 &lo) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float v0 = v[2 * i], v1 = v[2 * i + 1];
+          if constexpr (decltype(f16)::value) {
+            hi[i] = cvt_pk_f16(v0, v1);
+            const f16x2 h = __builtin_bit_cast(f16x2, static_cast<uint32_t>(hi[i]));
+            lo[i] = cvt_pk_f16(v0 - static_cast<float>(h[0]), v1 - static_cast<float>(h[1]));
+          } else {
+            hi[i] = cvt_pk_bf16(v0, v1);
+            lo[i] = cvt_pk_bf16(v0 - bf16lo(hi[i]), v1 - bf16hi(hi[i]));
+          }
+        }
+      };
+      // rows [Tpad][MP32]: eight logits of a token per thread; then, by the next threads, tokens
+      // innermost [Tpad/32][MP16][32]: eight tokens of a logit
+      constexpr int kRows = BT * MP32 / 8, kCols = MP16 * BT / 8;
+      for (int e = tid; e < kRows + kCols; e += THREADS) {
+        u32x4 hi, lo;
+        float v[8];
+        if (e < kRows) {
+          const int tk = e / (MP32 / 8), v8 = e % (MP32 / 8);
+          const float inv = F16ROWS ? sc_s[tk] : 1.f;
+#pragma unroll
+          for (int i = 0; i < 8; ++i) v[i] = v_s[tk][8 * v8 + i] * inv;
+          split8(v, std::bool_constant<F16ROWS>{}, hi, lo);
+          const size_t off = static_cast<size_t>(t0 + tk) * MP32 + 8 * v8;
+          *reinterpret_cast<u32x4 *>(out.vr_hi + off) = hi;
+          *reinterpret_cast<u32x4 *>(out.vr_lo + off) = lo;
+        } else {
+          const int half = (e - kRows) / (4 * MP16), m = ((e - kRows) / 4) % MP16, tg = (e - kRows) & 3;
+#pragma unroll
+          for (int i = 0; i < 8; ++i) v[i] = v_s[32 * half + tg * 8 + i][m];
+          split8(v, std::false_type{}, hi, lo);
+          const size_t off = ((static_cast<size_t>(blockIdx.x) * (BT / 32) + half) * MP16 + m) * 32 + tg * 8;
+          *reinterpret_cast<u32x4 *>(out.vrT_hi + off) = hi;
+          *reinterpret_cast<u32x4 *>(out.vrT_lo + off) = lo;
+        }
+      }
+    }
+    // sums over the block's tokens (zeros past T), in token order, by the last threads
+    for (int m = THREADS - 1 - tid; m < M + 3; m += THREADS) {
+      float s = 0.f;
+#pragma unroll
+      for (int tk = 0; tk < BT; ++tk) s += z_s[tk][m];
+      out.gz_sums[static_cast<int64_t>(blockIdx.x) * (M + 3) + m] = s;
+    }
+  }
+}
+
+template <int OUT>
+hipError_t launch_token_stage(const mhcl_desc &d, const TokenIn &in,
+                              const TokenOut &out, hipStream_t s) {
+  const bool many = token_stage_many(d, OUT != kOutForward);
+  const int64_t blocks64 = (d.T + 63) / 64;
+  const unsigned blocks = static_cast<unsigned>(many ? blocks64 : 2 * blocks64);
+  auto go = [&](auto nn, auto mm) {
+    constexpr int N = decltype(nn)::value, MODE = decltype(mm)::value;
+    constexpr int LF = N <= 4 ? 16 : 64;   // lanes per token with few tokens
+    auto kern = token_stage_kernel<N, MODE, OUT, LF>;
+    int threads = kTokThreads<LF>, per_iter = kSkPerIter<N, MODE, OUT, LF>;
+    if constexpr (N <= 4) {
+      if (many) {
+        kern = token_stage_kernel<N, MODE, OUT, 4>;
+        threads = kTokThreads<4>;
+        per_iter = kSkPerIter<N, MODE, OUT, 4>;
+      }
+    }
+    const size_t lds = static_cast<size_t>(per_iter) * d.sk_iters * sizeof(float);
+    if (MODE == MHCL_RES_SK && lds > 16 * 1024) {   // (with the static arrays it may pass 64 KiB)
+      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                         hipFuncAttributeMaxDynamicSharedMemorySize,
+                                         static_cast<int>(lds));
+      if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(threads), MODE == MHCL_RES_SK ? lds : 0, s, in, out);
+    return hipGetLastError();
+  };
+  using L = std::integral_constant<int, MHCL_RES_LITE>;
+  using S = std::integral_constant<int, MHCL_RES_SK>;
+  const bool lite = d.res_mode == MHCL_RES_LITE;
+  switch (d.n) {
+    case 1: return lite ? go(std::integral_constant<int, 1>{}, L{}) : go(std::integral_constant<int, 1>{}, S{});
+    case 2: return lite ? go(std::integral_constant<int, 2>{}, L{}) : go(std::integral_constant<int, 2>{}, S{});
+    case 3: return lite ? go(std::integral_constant<int, 3>{}, L{}) : go(std::integral_constant<int, 3>{}, S{});
+    case 4: return lite ? go(std::integral_constant<int, 4>{}, L{}) : go(std::integral_constant<int, 4>{}, S{});
+    case 5: return lite ? hipErrorInvalidValue : go(std::integral_constant<int, 5>{}, S{});
+  }
+  return hipErrorInvalidValue;
+}
+
+TokenIn token_in(const mhcl_desc &d, int parts, const float *u_raw, const float *sumsq,
+                 const float *b, const float *alpha) {
+  TokenIn in{};
+  in.u_raw = u_raw; in.sumsq = sumsq; in.parts = parts;
+  in.b = b; in.alpha = alpha;
+  in.nC = d.n * d.C; in.eps = d.eps; in.sk_iters = d.sk_iters; in.T = d.T;
+  return in;
+}
+
+}  // namespace
+
+// Four lanes per token against sixteen, measured (n = 4, the calls at C = 64 where this stage
+// dominates): forward 25.4 / 23.2 us at 512 tokens, 23.5 / 25.5 at 16384, 46 / 48 at 65536; backward
+// 32.0 / 29.7, 38.3 / 38.8, 91.5 / 95.2.  The Sinkhorn-Knopp backward is a chain of 4 sk_iters sums
+// per token, which sixteen lanes walk faster at every count (65.8 against 69.3 us at 32768 tokens).
+bool token_stage_many(const mhcl_desc &d, bool backward) {
+  return d.n <= 4 && d.T >= 16384 && !(backward && d.res_mode == MHCL_RES_SK);
+}
+
+// one per block: the blocks cover tokens up to the next multiple of 64, as the readers of vr do
+int64_t gz_rows(const mhcl_desc &d) {
+  const int64_t blocks64 = (d.T + 63) / 64;
+  return coeffs_group_ok(d) || token_stage_many(d, true) ? blocks64 : 2 * blocks64;
+}
+
+hipError_t launch_token_coeffs(const mhcl_desc &d, int parts, const float *u_raw, const float *sumsq,
+                               const float *b, const float *alpha, float *H_res, float *H_pre,
+                               float *H_post, hipStream_t s) {
+  TokenOut out{};
+  out.H_res = H_res; out.H_pre = H_pre; out.H_post = H_post;
+  return launch_token_stage<kOutForward>(d, token_in(d, parts, u_raw, sumsq, b, alpha), out, s);
+}
+
+hipError_t launch_token_bwd_fast(const mhcl_desc &d, const float *b, const float *alpha,
+                                 const FastBwdWs &w, hipStream_t s) {
+  TokenIn in = token_in(d, w.parts, w.u_raw, w.sumsq, b, alpha);
+  in.gH_res = w.gH_res; in.gH_pre = w.gH_pre; in.gH_post = w.gH_post; in.gparts = 1;
+  TokenOut out{};
+  out.rec = w.cpk; out.rec_ld = w.CP;
+  out.vr_hi = w.vr_hi; out.vr_lo = w.vr_lo; out.vrT_hi = w.vrT_hi; out.vrT_lo = w.vrT_lo;
+  out.gz_sums = w.gz;
+  return launch_token_stage<kOutFast>(d, in, out, s);
+}
+
+hipError_t launch_token_bwd_full(const mhcl_desc &d, int parts, const float *u_raw,
+                                 const float *sumsq, const float *b, const float *alpha,
+                                 const float *g_H_res, const float *g_H_pre, const float *g_H_post,
+                                 const BwdTokenBufs &o, hipStream_t s) {
+  TokenIn in = token_in(d, parts, u_raw, sumsq, b, alpha);
+  in.gH_res = g_H_res; in.gH_pre = g_H_pre; in.gH_post = g_H_post; in.gparts = 1;
+  TokenOut out{};
+  out.rec = o.rec; out.rec_ld = token_rec_floats(d.n); out.vr = o.vr; out.gz_sums = o.gz;
+  return launch_token_stage<kOutFull>(d, in, out, s);
+}
+
+}  // namespace mhcl
