@@ -386,9 +386,12 @@ template <int N, int NT, int WAVES>
 __global__ __launch_bounds__(64 * WAVES, (WAVES == 4 || N <= 3) ? 2 : 1) void bwd_reduce_kernel(
     const uint16_t *__restrict__ x, const uint16_t *__restrict__ y,
     const uint16_t *__restrict__ g, const uint16_t *__restrict__ gh,
-    const u32x4 *__restrict__ Wp, int C, int M, int64_t T, float *__restrict__ u_raw,
-    float *__restrict__ sumsq, float *__restrict__ gH_res, float *__restrict__ gH_post,
-    float *__restrict__ gH_pre) {
+    const u32x4 *__restrict__ Wp, int C, int M, int64_t T, int steps_per_part,
+    float *__restrict__ u_raw, float *__restrict__ sumsq, float *__restrict__ gH_res,
+    float *__restrict__ gH_post, float *__restrict__ gH_pre) {
+  // gridDim.y blocks share the columns of the same tokens: block (bx, part) walks the 64-column
+  // steps [part * steps_per_part, ...) of every stream and writes slice `part` of the outputs;
+  // the per-token stage adds the slices in order.
   using Cfg = ReduceCfg<N, NT, WAVES>;
   constexpr int D = N * N + 2 * N;
   extern __shared__ u32x4 lds[];
@@ -480,8 +483,10 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 4 || N <= 3) ? 2 : 1) void bw
   // taken in a rotated order): with every block at the same columns at the same time, all
   // requests differ only in address bits above the row length and crowd a few memory
   // channels (0.62 -> 0.52 ms at n = 4, C = 4096; W, 2 MiB, stays in L2 either way).
-  const int rot = static_cast<int>((blockIdx.x * 13u) % static_cast<unsigned>(ncs));
-  auto turn = [&](int c) { const int v = c + rot; return v >= ncs ? v - ncs : v; };
+  const int cs0 = blockIdx.y * steps_per_part;
+  const int nst = cs0 + steps_per_part < ncs ? steps_per_part : ncs - cs0;   // steps of this block
+  const int rot = static_cast<int>((blockIdx.x * 13u) % static_cast<unsigned>(nst));
+  auto turn = [&](int c) { const int v = c + rot; return cs0 + (v >= nst ? v - nst : v); };
   load_w(turn(0));
   store_w(0);
   __syncthreads();
@@ -493,7 +498,7 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 4 || N <= 3) ? 2 : 1) void bw
     Tile ta, tb2;
     load_tile(ta, turn(0));
     auto step = [&](const Tile &cur, Tile &nxt, int cs) {
-      const int nx = cs + 1 < ncs ? cs + 1 : cs;   // the last step re-requests itself (unused)
+      const int nx = cs + 1 < nst ? cs + 1 : cs;   // the last step re-requests itself (unused)
       load_w(turn(nx));
       load_tile(nxt, turn(nx));
       __builtin_amdgcn_sched_barrier(0);
@@ -503,15 +508,15 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 4 || N <= 3) ? 2 : 1) void bw
       __syncthreads();
     };
     int cs = 0;
-    for (; cs + 1 < ncs; cs += 2) {
+    for (; cs + 1 < nst; cs += 2) {
       step(ta, tb2, cs);
       step(tb2, ta, cs + 1);
     }
-    if (cs < ncs) step(ta, tb2, cs);
+    if (cs < nst) step(ta, tb2, cs);
   } else {
     Tile tile;
-    for (int cs = 0; cs < ncs; ++cs) {
-      const int nx = cs + 1 < ncs ? cs + 1 : cs;   // last step re-stages itself (unused)
+    for (int cs = 0; cs < nst; ++cs) {
+      const int nx = cs + 1 < nst ? cs + 1 : cs;   // last step re-stages itself (unused)
       load_w(turn(nx));
       load_tile(tile, turn(cs));
       __builtin_amdgcn_sched_barrier(0);
@@ -522,6 +527,11 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 4 || N <= 3) ? 2 : 1) void bw
     }
   }
 
+  u_raw += blockIdx.y * T * M;
+  sumsq += blockIdx.y * T;
+  gH_res += blockIdx.y * T * (N * N);
+  gH_post += blockIdx.y * T * N;
+  gH_pre += blockIdx.y * T * N;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int64_t t = tw + 4 * q + i;
@@ -1640,6 +1650,29 @@ int gw_xblocks(const mhcl_desc &d) {
 }
 }  // namespace
 
+// eight-wave blocks of 128 tokens in pass 1 (they halve the W traffic from L2: 0.52 -> 0.48 ms at
+// n = 4, C = 4096, T = 32768) once there are enough of them to put one on every CU
+static bool reduce_wide_blocks(const mhcl_desc &d) { return (d.T + 127) / 128 >= 256; }
+
+// 64-column steps of a block of pass 1: all of them, or so many that the blocks of 64 tokens put
+// one on every CU.  The fused backward at n = 4, whole rows against this: C = 4096, 1024 tokens 307
+// / 84 us, 4096 tokens 384 / 218, 8192 tokens 491 / 395; C = 1024, 2048 tokens 98 / 53; equal from
+// 256 blocks on.  (Aiming at two blocks per CU instead: 3 % slower at 8192 tokens, else equal.)
+static int reduce_steps(const mhcl_desc &d) {
+  const int ncs = d.C / 64;
+  if (reduce_wide_blocks(d) || d.T == 0) return ncs;
+  const int64_t blocks = (d.T + 63) / 64;
+  int64_t parts = 256 / blocks;
+  if (parts > 16) parts = 16;
+  if (parts > ncs) parts = ncs;
+  if (parts < 1) parts = 1;
+  return static_cast<int>((ncs + parts - 1) / parts);
+}
+int reduce_parts(const mhcl_desc &d) {
+  const int spp = reduce_steps(d);
+  return (d.C / 64 + spp - 1) / spp;
+}
+
 int out_gw_tokens_per_block(const mhcl_desc &d) {
   // Token chunks: as many as make the grid one round of resident blocks (all blocks
   // then start together and the blocks of a chunk walk down the same rows side by
@@ -1679,12 +1712,15 @@ FastBwdWs::FastBwdWs(const mhcl_desc &d, void *ws) {
   CP = (n * n + 2 * n + 2 + 7) / 8 * 8;   // H_res | H_pre | H_post | coefx | scale of the vr row, padded
   MP32 = logit_steps(M) * 32;
   MP16 = logit_tiles(M) * 16;
-  parts = fast_bwd_wide(d) ? proj_ksplit(d) : 1;   // the wide path recomputes with proj_mfma_kernel
+  // slices of the projection and of the dot products: pass 1 may split the columns; the wide path
+  // runs the forward's projection and a kernel of its own for the dot products
+  parts = fast_bwd_wide(d) ? proj_ksplit(d) : reduce_parts(d);
+  gparts = fast_bwd_wide(d) ? 1 : parts;
   u_raw = c.take<float>(static_cast<size_t>(parts) * T * M);
   sumsq = c.take<float>(static_cast<size_t>(parts) * T);
-  gH_res = c.take<float>(T * n * n);
-  gH_pre = c.take<float>(T * n);
-  gH_post = c.take<float>(T * n);
+  gH_res = c.take<float>(gparts * T * n * n);
+  gH_pre = c.take<float>(gparts * T * n);
+  gH_post = c.take<float>(gparts * T * n);
   cpk = c.take<float>(T * CP);
   gz = c.take<float>(static_cast<size_t>(gz_rows(d)) * (M + 3));
   vr_hi = c.take<uint16_t>(Tpad * MP32);
@@ -1735,18 +1771,17 @@ hipError_t launch_bwd_reduce(const mhcl_desc &d, int M, const void *x, const voi
     auto launch = [&](auto wv) {
       constexpr int WAVES = decltype(wv)::value;
       auto kern = bwd_reduce_kernel<N, NT, WAVES>;
-      hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>((d.T + 16 * WAVES - 1) / (16 * WAVES))),
+      hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>((d.T + 16 * WAVES - 1) / (16 * WAVES)),
+                                    reduce_parts(d)),
                          dim3(64 * WAVES), (ReduceCfg<N, NT, WAVES>::kLdsBytes), s,
                          static_cast<const uint16_t *>(x), static_cast<const uint16_t *>(y),
                          static_cast<const uint16_t *>(g_xout), static_cast<const uint16_t *>(g_h),
-                         reinterpret_cast<const u32x4 *>(w.Wp), d.C, M, d.T, w.u_raw, w.sumsq,
-                         w.gH_res, w.gH_post, w.gH_pre);
+                         reinterpret_cast<const u32x4 *>(w.Wp), d.C, M, d.T, reduce_steps(d),
+                         w.u_raw, w.sumsq, w.gH_res, w.gH_post, w.gH_pre);
       return hipGetLastError();
     };
-    // 128-token blocks halve the W traffic from L2 (0.52 -> 0.48 ms at n = 4, C = 4096,
-    // T = 32768) but need enough tokens to put a block on every CU
-    return (d.T + 127) / 128 >= 256 ? launch(std::integral_constant<int, 8>{})
-                                    : launch(std::integral_constant<int, 4>{});
+    return reduce_wide_blocks(d) ? launch(std::integral_constant<int, 8>{})
+                                 : launch(std::integral_constant<int, 4>{});
   };
   const int NT = logit_tiles(M);
   using I1 = std::integral_constant<int, 1>;

@@ -143,13 +143,14 @@ bool fast_bwd_ok(const mhcl_desc &d);
 bool fast_bwd_whi(const mhcl_desc &d);    // wide case, n >= 5, where W fits LDS as one fp16 part: that pass 2 as one kernel
 bool fast_bwd_wide(const mhcl_desc &d);   // n >= 5 or a subset: pass 2 split into W vr and the mixing
 int gw_chunks_fast(const mhcl_desc &d);
+int reduce_parts(const mhcl_desc &d);     // slices that launch_bwd_reduce writes
 struct FastBwdWs {
   // gz: [gz_rows(d)][M+3] sums of g_z and g_z u over each block's tokens
   // wmax_part: partial maxima of |W|; wscale: {scale, 1 / scale} of the fp16 copy of W
   float *u_raw, *sumsq, *gH_res, *gH_pre, *gH_post, *cpk, *gz, *partials, *D, *wmax_part, *wscale;
   uint16_t *vr_hi, *vr_lo, *vrT_hi, *vrT_lo;
   char *Wp, *Wa;
-  int CP, MP32, MP16, parts;
+  int CP, MP32, MP16, parts, gparts;   // slices of u_raw, sumsq and of gH_*
   size_t bytes;
   FastBwdWs(const mhcl_desc &d, void *ws);
 };

@@ -575,7 +575,7 @@ hipError_t launch_token_coeffs(const mhcl_desc &d, int parts, const float *u_raw
 hipError_t launch_token_bwd_fast(const mhcl_desc &d, const float *b, const float *alpha,
                                  const FastBwdWs &w, hipStream_t s) {
   TokenIn in = token_in(d, w.parts, w.u_raw, w.sumsq, b, alpha);
-  in.gH_res = w.gH_res; in.gH_pre = w.gH_pre; in.gH_post = w.gH_post; in.gparts = 1;
+  in.gH_res = w.gH_res; in.gH_pre = w.gH_pre; in.gH_post = w.gH_post; in.gparts = w.gparts;
   TokenOut out{};
   out.rec = w.cpk; out.rec_ld = w.CP;
   out.vr_hi = w.vr_hi; out.vr_lo = w.vr_lo; out.vrT_hi = w.vrT_hi; out.vrT_lo = w.vrT_lo;
