@@ -15,7 +15,7 @@ namespace {
 template <int L>
 constexpr int kTokBlock = L == 4 ? 64 : 32;
 template <int L>
-constexpr int kTokThreads = L == 4 ? 4 * kTokBlock<4> : 512;
+constexpr int kTokThreads = L * kTokBlock<L>;
 
 // kinds of output
 enum { kOutForward, kOutFast, kOutFull };
@@ -31,18 +31,15 @@ constexpr int kHalfMirror = 0x141;                                          // r
 // over all lanes of a token's group (every lane gets the same bits: each step adds a pair)
 template <int L, typename OP>
 __device__ __forceinline__ float group_reduce(float v, OP op) {
-  if constexpr (L == 4) {
-    v = op(v, dpp<kXor2>(v));
-    v = op(v, dpp<kXor1>(v));
-  } else {
+  if constexpr (L == 16) {
     v = op(v, dpp<kRor8>(v));
     v = op(v, dpp<kRor4>(v));
     v = op(v, dpp<kRor2>(v));
     v = op(v, dpp<kRor1>(v));
-  }
-  if constexpr (L == 64) {
-    v = op(v, __shfl_xor(v, 16, 64));
-    v = op(v, __shfl_xor(v, 32, 64));
+  } else {
+    v = op(v, dpp<kXor2>(v));
+    v = op(v, dpp<kXor1>(v));
+    if constexpr (L == 8) v = op(v, dpp<kHalfMirror>(v));
   }
   return v;
 }
@@ -59,16 +56,13 @@ __device__ __forceinline__ void column_sums(const float (&v)[CC], float (&s)[CC]
 #pragma unroll
   for (int c = 0; c < CC; ++c) {
     s[c] = v[c];
-    if constexpr (L == 4) {
-      s[c] += dpp<kXor2>(s[c]);
-      s[c] += dpp<kXor1>(s[c]);
-    } else if constexpr (L == 16) {
+    if constexpr (L == 16) {
       s[c] += dpp<kRor8>(s[c]);
       s[c] += dpp<kRor4>(s[c]);
     } else {
-      s[c] += dpp<kRor8>(s[c]);
-      s[c] += __shfl_xor(s[c], 16, 64);
-      s[c] += __shfl_xor(s[c], 32, 64);
+      s[c] += dpp<kXor2>(s[c]);
+      s[c] += dpp<kXor1>(s[c]);
+      if constexpr (L == 8) s[c] += dpp<kHalfMirror>(s[c]);
     }
   }
 }
@@ -77,11 +71,10 @@ __device__ __forceinline__ float row_sum(const float (&v)[CC]) {
   float s = v[0];
 #pragma unroll
   for (int c = 1; c < CC; ++c) s += v[c];
-  if constexpr (L != 4) {
+  if constexpr (L == 16) {
     s += dpp<kXor1>(s);
     s += dpp<kXor2>(s);
   }
-  if constexpr (L == 64) s += dpp<kHalfMirror>(s);
   return s;
 }
 
@@ -177,22 +170,23 @@ struct StageSums {
 
 // floats of dynamic LDS per Sinkhorn-Knopp iteration: the divisors of its two half steps and their
 // reciprocals, one pair per line and token of a pass (backward only)
+template <int N, int L>
+constexpr int kLines = L == 16 ? 4 : N;   // lines per token, as they are spaced
 template <int N, int MODE, int OUT, int L>
 constexpr int kSkPerIter = (MODE == MHCL_RES_SK && OUT != kOutForward)
-                               ? 2 * 2 * (N <= 4 ? kTokBlock<L> * 4 : 8 * 8) : 0;
+                               ? 2 * 2 * kTokBlock<L> * kLines<N, L> : 0;
 
 template <int N, int MODE, int OUT, int L>
 __global__ __launch_bounds__(kTokThreads<L>) void token_stage_kernel(TokenIn in, TokenOut out) {
   constexpr int R = Dims<N, MODE>::R, M = Dims<N, MODE>::M, NN = N * N;
-  constexpr int THREADS = kTokThreads<L>, BT = kTokBlock<L>, NP = L == 64 ? 8 : 4;   // NP: lines per token, padded
-  constexpr int TP = THREADS / L;                              // tokens per pass
-  constexpr int CC = L == 4 ? N : 1;                           // entries of H_res per lane
+  constexpr int THREADS = kTokThreads<L>, BT = kTokBlock<L>, NP = kLines<N, L>;
+  constexpr int CC = L == 16 ? 1 : N;                          // entries of H_res per lane
   constexpr int KK = MODE == MHCL_RES_LITE ? (R + L - 1) / L : CC;   // residual logits per lane
   constexpr int GG = (2 * N + L - 1) / L;                      // gates per lane
   constexpr int MP32 = (M + 31) / 32 * 32, MP16 = (M + 15) / 16 * 16;
   constexpr bool BWD = OUT != kOutForward, F16ROWS = OUT == kOutFast && N == 5;
   static_assert(MODE == MHCL_RES_SK || N <= 4, "the table of n = 5 does not fit these lanes");
-  static_assert((N <= 4) == (L != 64), "lanes per token");
+  static_assert(N <= 4 ? L == 4 || L == 16 : L == 8, "lanes per token");
   constexpr int UL = (M + 2) | 1;                              // odd row lengths keep banks apart
   constexpr int AL = (R + 3) / 4 * 4 + 4;
   __shared__ float u_s[BT][UL];
@@ -217,7 +211,7 @@ __global__ __launch_bounds__(kTokThreads<L>) void token_stage_kernel(TokenIn in,
     sq.begin(in.gH_post, T, t0);
   }
   const int l = tid % L;
-  const int li = L == 4 ? l : l / NP, lj0 = L == 4 ? 0 : l % NP;   // row, column of the first entry
+  const int li = L == 16 ? l / 4 : l, lj0 = L == 16 ? l % 4 : 0;   // row, column of the first entry
   const bool row_ok = li < N, cell_ok = row_ok && lj0 < N;         // (all CC entries or none)
   const int cell0 = cell_ok ? li * N + lj0 : 0;
   // residual logit kk of this lane
@@ -253,8 +247,8 @@ __global__ __launch_bounds__(kTokThreads<L>) void token_stage_kernel(TokenIn in,
   }
   __syncthreads();
 
-  for (int pass = 0; pass < BT / TP; ++pass) {
-    const int tok = pass * TP + tid / L;
+  {
+    const int tok = tid / L;
     const int64_t t = t0 + tok;
     const bool live = t < T;
     const float *u = u_s[tok];
@@ -274,7 +268,7 @@ __global__ __launch_bounds__(kTokThreads<L>) void token_stage_kernel(TokenIn in,
     for (int kk = 0; kk < KK; ++kk) a[kk] = owns(kk) ? expf(a[kk] - zmax) : 0.f;
     // Sinkhorn-Knopp: one pair of floats per line, columns in the even half steps, rows in the odd
     // ones; kHalf pairs per half step
-    constexpr int kHalf = TP * NP;
+    constexpr int kHalf = BT * NP;
     float2 *sk = MODE == MHCL_RES_SK ? sk_s + (tid / L) * NP : nullptr;
     if constexpr (MODE == MHCL_RES_LITE) {
       float s = 0.f;
@@ -304,14 +298,14 @@ __global__ __launch_bounds__(kTokThreads<L>) void token_stage_kernel(TokenIn in,
         column_sums<L>(H, s);
 #pragma unroll
         for (int c = 0; c < CC; ++c) {
-          inv[c] = 1.f / s[c];
+          inv[c] = L == 16 && !cell_ok ? 0.f : 1.f / s[c];   // (entries that are none stay 0)
           if (BWD && li == 0) sk[(2 * it) * kHalf + lj0 + c] = make_float2(s[c], inv[c]);
-          H[c] = cell_ok ? H[c] * inv[c] : 0.f;
+          H[c] *= inv[c];
         }
-        const float rs = row_sum<L>(H), rinv = 1.f / rs;
-        if (BWD && lj0 == 0) sk[(2 * it + 1) * kHalf + li] = make_float2(rs, rinv);
+        const float rs = row_sum<L>(H), rinv = cell_ok ? 1.f / rs : 0.f;
+        if (BWD && lj0 == 0 && row_ok) sk[(2 * it + 1) * kHalf + li] = make_float2(rs, rinv);
 #pragma unroll
-        for (int c = 0; c < CC; ++c) H[c] = cell_ok ? H[c] * rinv : 0.f;
+        for (int c = 0; c < CC; ++c) H[c] *= rinv;
       }
       __builtin_amdgcn_wave_barrier();
     }
@@ -369,7 +363,7 @@ __global__ __launch_bounds__(kTokThreads<L>) void token_stage_kernel(TokenIn in,
 #pragma unroll
         for (int c = 0; c < CC; ++c) gh[c] = cell_ok ? g[cell0 + c] : 0.f;
         for (int it = in.sk_iters - 1; it >= 0; --it) {
-          const float2 rs = sk[(2 * it + 1) * kHalf + li];
+          const float2 rs = sk[(2 * it + 1) * kHalf + (row_ok ? li : 0)];
           float2 cs[CC];
 #pragma unroll
           for (int c = 0; c < CC; ++c) cs[c] = sk[(2 * it) * kHalf + lj0 + c];
@@ -435,7 +429,6 @@ __global__ __launch_bounds__(kTokThreads<L>) void token_stage_kernel(TokenIn in,
           if (live) rec[NN + 2 * N + 1] = sc;
         }
       }
-      if constexpr (MODE == MHCL_RES_SK) __builtin_amdgcn_wave_barrier();   // the next pass rewrites sk
     }
   }
   if constexpr (BWD) {
@@ -506,7 +499,7 @@ hipError_t launch_token_stage(const mhcl_desc &d, const TokenIn &in,
   const unsigned blocks = static_cast<unsigned>(many ? blocks64 : 2 * blocks64);
   auto go = [&](auto nn, auto mm) {
     constexpr int N = decltype(nn)::value, MODE = decltype(mm)::value;
-    constexpr int LF = N <= 4 ? 16 : 64;   // lanes per token with few tokens
+    constexpr int LF = N <= 4 ? 16 : 8;   // lanes per token with few tokens
     auto kern = token_stage_kernel<N, MODE, OUT, LF>;
     int threads = kTokThreads<LF>, per_iter = kSkPerIter<N, MODE, OUT, LF>;
     if constexpr (N <= 4) {
