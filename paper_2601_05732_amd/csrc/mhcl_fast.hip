@@ -146,31 +146,46 @@ __global__ __launch_bounds__(ProjCfg<NT>::kThreads, 1) void proj_mfma_kernel(con
       lds[buf * Cfg::kChunkVec + o] = wst[i];
     }
   };
-  // `tail`: the chunk may run past the last K step; such steps get a zero A tile
+  // `tail`: the chunk may run past the last K step; such steps get a zero A tile.
+  // The W operands of a logit tile are requested kAhead tiles before their MFMAs and the order is
+  // pinned: left to itself the compiler requests each pair right before its use, and with two waves
+  // per SIMD in step the matrix cores then wait for LDS at every tile (mhcl_coeffs at n = 5,
+  // C = 2560: 137 -> 123 us at 4096 tokens, 279 -> 262 at 32768; n = 4, C = 4096, 32768 tokens
+  // 200 -> 191; three or four tiles ahead: the same).
+  constexpr int kTiles = KC * NT, kAhead = 2;
   auto compute = [&](const u32x4 (&av)[TG][KC], int buf, int c, auto tail) {
-    const u32x4 *wb = lds + buf * Cfg::kChunkVec;
+    const u32x4 *wb = lds + buf * Cfg::kChunkVec + lane;
+    u32x4 w[kAhead + 1][2];
 #pragma unroll
-    for (int s = 0; s < KC; ++s) {
-      u32x4 at[TG];
+    for (int i = 0; i < (kAhead < kTiles ? kAhead : kTiles); ++i) {
+      w[i][0] = wb[(i * 2 + 0) * 64];
+      w[i][1] = wb[(i * 2 + 1) * 64];
+    }
+    u32x4 at[TG];
 #pragma unroll
-      for (int g = 0; g < TG; ++g) {
-        if constexpr (decltype(tail)::value)
-          at[g] = c * KC + s < nsteps ? av[g][s] : u32x4{0, 0, 0, 0};
-        else
-          at[g] = av[g][s];
+    for (int i = 0; i < kTiles; ++i) {   // tile j of step s
+      const int s = i / NT, j = i % NT;
+      if (i + kAhead < kTiles) {
+        w[(i + kAhead) % (kAhead + 1)][0] = wb[((i + kAhead) * 2 + 0) * 64];
+        w[(i + kAhead) % (kAhead + 1)][1] = wb[((i + kAhead) * 2 + 1) * 64];
       }
-#pragma unroll
-      for (int j = 0; j < NT; ++j) {
-        const u32x4 bh = wb[((s * NT + j) * 2 + 0) * 64 + lane];
-        const u32x4 bl = wb[((s * NT + j) * 2 + 1) * 64 + lane];
+      __builtin_amdgcn_sched_barrier(0);
+      if (j == 0) {
 #pragma unroll
         for (int g = 0; g < TG; ++g) {
-          acc[g][j] = mfma16(at[g], bh, acc[g][j]);
-          acc[g][j] = mfma16(at[g], bl, acc[g][j]);
+          if constexpr (decltype(tail)::value)
+            at[g] = c * KC + s < nsteps ? av[g][s] : u32x4{0, 0, 0, 0};
+          else
+            at[g] = av[g][s];
         }
-      }
 #pragma unroll
-      for (int g = 0; g < TG; ++g) ss[g] = mfma16(at[g], at[g], ss[g]);
+        for (int g = 0; g < TG; ++g) ss[g] = mfma16(at[g], at[g], ss[g]);
+      }
+      const u32x4 bh = w[i % (kAhead + 1)][0], bl = w[i % (kAhead + 1)][1];
+#pragma unroll
+      for (int g = 0; g < TG; ++g) acc[g][j] = mfma16(at[g], bh, acc[g][j]);
+#pragma unroll
+      for (int g = 0; g < TG; ++g) acc[g][j] = mfma16(at[g], bl, acc[g][j]);
     }
   };
   constexpr std::false_type kFull{};
