@@ -39,10 +39,10 @@ from .layer import PHASE_G_X, PHASE_G_XOUT, PHASE_X, empty_stream
 
 class _Link:
     """What the post node leaves for the coefficient node of the same layer."""
-    __slots__ = ("y", "g_xout", "H_pre", "ws", "g_x_phase", "perm")
+    __slots__ = ("y", "g_xout", "H_pre", "g_x_phase", "perm")
 
     def __init__(self, g_x_phase=PHASE_G_X, perm=None):
-        self.y = self.g_xout = self.H_pre = self.ws = None
+        self.y = self.g_xout = self.H_pre = None
         self.g_x_phase = g_x_phase
         self.perm = perm      # int8 [K, n] table of the permutation-subset form, else None
 
@@ -69,6 +69,7 @@ class _CoeffsPre(torch.autograd.Function):
         ctx.link, ctx.d = link, d
         link.H_pre = H_pre
         ctx.mark_non_differentiable(H_pre)
+        ctx.set_materialize_grads(False)     # the gradients on H_* are not read: no zeros for them
         return h, H_res, H_post, H_pre
 
     @staticmethod
@@ -111,9 +112,9 @@ class _Post(torch.autograd.Function):
         link.g_xout = g_xout
         g_y = torch.empty(d.T, d.C, device=g_xout.device, dtype=g_xout.dtype)
         mhcl.mhcl_pre(d, g_xout, H_post, g_y)            # g_y = sum_i H_post[i] g_xout[i]
-        # x and the coefficients get their gradients from the coefficient node
-        # (fused kernel); zeros here only keep that node in the graph.
-        return None, g_y, torch.zeros_like(H_res), torch.zeros_like(H_post), None, None, None, None
+        # x and the coefficients get their gradients from the coefficient node (fused kernel), which
+        # autograd runs once this node is done, also where no gradient reaches it through f
+        return None, g_y, None, None, None, None, None, None
 
 
 def init_params(n: int, C: int, res_mode: int = mhcl.RES_LITE, one_index: int = 0, device="cuda",

@@ -150,6 +150,8 @@ def perm_table(n: int):
 def _ptr(t, dtype, shape, name):
     if t is None:
         return None
+    if t.is_cuda and t.dtype is dtype and t.shape == shape and t.is_contiguous():
+        return t.data_ptr() or None     # an empty tensor has no storage: pass NULL
     if not t.is_cuda:
         raise ValueError(f"{name} must be a GPU tensor")
     if t.dtype != dtype:
@@ -158,10 +160,13 @@ def _ptr(t, dtype, shape, name):
         raise ValueError(f"{name}: shape {tuple(t.shape)}, expected {tuple(shape)}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    return t.data_ptr() or None     # an empty tensor has no storage: pass NULL
+    return t.data_ptr() or None
 
 
 def _stream():
+    """Handle of the current stream of the current device."""
+    if torch.cuda.is_initialized():     # (without building a Stream object: 4 us a call)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return torch.cuda.current_stream().cuda_stream
 
 

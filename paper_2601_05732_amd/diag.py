@@ -37,21 +37,20 @@ def layer_stack(wl, L: int, inputs, device: str = "cuda"):
     H = torch.empty(L, wl.T, wl.n, wl.n, device=device, dtype=f)
     z = torch.empty(L, wl.T, wl.M, device=device, dtype=f)
     spread = torch.empty(L, wl.T, device=device, dtype=f)
-    # the library wants 16-byte aligned pointers, which a slice H[l] need not be:
-    # each call writes its own buffers, copied into the stack afterwards
-    Hl = torch.empty(wl.T, wl.n, wl.n, device=device, dtype=f)
-    zl = torch.empty(wl.T, wl.M, device=device, dtype=f)
-    sl = torch.empty(wl.T, device=device, dtype=f)
+    # the library wants 16-byte aligned pointers: a layer's slice where that holds for all of
+    # them, else a buffer of its own, copied into the stack afterwards
+    own = [None if t[0].numel() % 4 == 0 else torch.empty_like(t[0]) for t in (H, z, spread)]
     Hp = torch.empty(wl.T, wl.n, device=device, dtype=f)
     Hq = torch.empty(wl.T, wl.n, device=device, dtype=f)
     ws = mhcl.new_workspace(d, mhcl.OP_COEFFS, device)
     for l in range(L):
         inp = inputs(l) if callable(inputs) else inputs[l]
-        mhcl.mhcl_coeffs(d, inp["x"], inp["W"], inp["b"], inp["alpha"], Hl, Hp, Hq, ws)
-        mhcl.mhcl_logits(d, inp["x"], inp["W"], inp["b"], inp["alpha"], zl, sl, ws)
-        H[l].copy_(Hl)
-        z[l].copy_(zl)
-        spread[l].copy_(sl)
+        into = [t[l] if o is None else o for t, o in zip((H, z, spread), own)]
+        mhcl.mhcl_coeffs(d, inp["x"], inp["W"], inp["b"], inp["alpha"], into[0], Hp, Hq, ws)
+        mhcl.mhcl_logits(d, inp["x"], inp["W"], inp["b"], inp["alpha"], into[1], into[2], ws)
+        for t, o in zip((H, z, spread), own):
+            if o is not None:
+                t[l].copy_(o)
     return H, z, spread
 
 

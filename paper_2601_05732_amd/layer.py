@@ -32,13 +32,13 @@ def empty_stream(shape, dtype, device, phase: int = 0) -> torch.Tensor:
     16, below 1024) past a 1 KiB boundary: a view into a buffer 1 KiB larger than needed."""
     if phase % 16 or not 0 <= phase < 1024:
         raise ValueError("phase must be a multiple of 16 in [0, 1024)")
-    numel = 1
-    for v in shape:
-        numel *= int(v)
-    esize = torch.empty((), dtype=dtype).element_size()
-    buf = torch.empty(numel * esize + 1024, dtype=torch.uint8, device=device)
-    off = (phase - buf.data_ptr()) % 1024
-    return buf[off:off + numel * esize].view(dtype).view(*shape)
+    numel, strides = 1, []
+    for v in reversed([int(v) for v in shape]):
+        strides.insert(0, numel)
+        numel *= v
+    esize = dtype.itemsize
+    buf = torch.empty(numel + 1024 // esize, dtype=dtype, device=device)
+    return buf.as_strided(tuple(shape), strides, (phase - buf.data_ptr()) % 1024 // esize)
 
 
 def place_stream(t: torch.Tensor, phase: int) -> torch.Tensor:
