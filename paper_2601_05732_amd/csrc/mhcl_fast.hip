@@ -589,7 +589,7 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 4 || N <= 3) ? 2 : 1) void bw
 template <int N>
 __global__ __launch_bounds__(256) void bwd_dots_fast_kernel(
     const uint16_t *__restrict__ x, const uint16_t *__restrict__ y,
-    const uint16_t *__restrict__ g, const uint16_t *__restrict__ gh, int C, int64_t T,
+    const uint16_t *__restrict__ g, const uint16_t *__restrict__ gh, int C, int64_t T, int steps_per_part,
     float *__restrict__ gH_res, float *__restrict__ gH_post, float *__restrict__ gH_pre) {
   constexpr int D = N * N + 2 * N;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -605,9 +605,12 @@ __global__ __launch_bounds__(256) void bwd_dots_fast_kernel(
   float dots[D];
 #pragma unroll
   for (int e = 0; e < D; ++e) dots[e] = 0.f;
-  const int rot = static_cast<int>((blockIdx.x * 13u) % static_cast<unsigned>(ncs));   // as in bwd_reduce_kernel
-  for (int cl = 0; cl < ncs; ++cl) {
-    const int cs = cl + rot >= ncs ? cl + rot - ncs : cl + rot;
+  // column parts and the order of a block's steps as in bwd_reduce_kernel
+  const int cs0 = blockIdx.y * steps_per_part;
+  const int nst = cs0 + steps_per_part < ncs ? steps_per_part : ncs - cs0;
+  const int rot = static_cast<int>((blockIdx.x * 13u) % static_cast<unsigned>(nst));
+  for (int cl = 0; cl < nst; ++cl) {
+    const int cs = cs0 + (cl + rot >= nst ? cl + rot - nst : cl + rot);
     u32x4 X[N][2], G[N][2], Y[2], H[2];
 #pragma unroll
     for (int j = 0; j < N; ++j)
@@ -637,6 +640,9 @@ __global__ __launch_bounds__(256) void bwd_dots_fast_kernel(
     dots[e] += __shfl_xor(dots[e], 16, 64);
     dots[e] += __shfl_xor(dots[e], 32, 64);
   }
+  gH_res += blockIdx.y * T * (N * N);
+  gH_post += blockIdx.y * T * N;
+  gH_pre += blockIdx.y * T * N;
   const int64_t t = tw + r;
   if (q == 0 && t < T) {
 #pragma unroll
@@ -1667,7 +1673,9 @@ int gw_xblocks(const mhcl_desc &d) {
 
 // eight-wave blocks of 128 tokens in pass 1 (they halve the W traffic from L2: 0.52 -> 0.48 ms at
 // n = 4, C = 4096, T = 32768) once there are enough of them to put one on every CU
-static bool reduce_wide_blocks(const mhcl_desc &d) { return (d.T + 127) / 128 >= 256; }
+static bool reduce_wide_blocks(const mhcl_desc &d) {
+  return !fast_bwd_wide(d) && (d.T + 127) / 128 >= 256;
+}
 
 // 64-column steps of a block of pass 1: all of them, or so many that the blocks of 64 tokens put
 // one on every CU.  The fused backward at n = 4, whole rows against this: C = 4096, 1024 tokens 307
@@ -1728,9 +1736,9 @@ FastBwdWs::FastBwdWs(const mhcl_desc &d, void *ws) {
   MP32 = logit_steps(M) * 32;
   MP16 = logit_tiles(M) * 16;
   // slices of the projection and of the dot products: pass 1 may split the columns; the wide path
-  // runs the forward's projection and a kernel of its own for the dot products
+  // takes the projection from the forward's kernels
   parts = fast_bwd_wide(d) ? proj_ksplit(d) : reduce_parts(d);
-  gparts = fast_bwd_wide(d) ? 1 : parts;
+  gparts = reduce_parts(d);
   u_raw = c.take<float>(static_cast<size_t>(parts) * T * M);
   sumsq = c.take<float>(static_cast<size_t>(parts) * T);
   gH_res = c.take<float>(gparts * T * n * n);
@@ -1817,10 +1825,11 @@ hipError_t launch_bwd_dots_fast(const mhcl_desc &d, const void *x, const void *y
                                 const void *g_h, const FastBwdWs &w, hipStream_t s) {
   auto go = [&](auto nn) {
     constexpr int N = decltype(nn)::value;
-    hipLaunchKernelGGL(bwd_dots_fast_kernel<N>, dim3(static_cast<unsigned>((d.T + 63) / 64)),
-                       dim3(256), 0, s, static_cast<const uint16_t *>(x),
+    hipLaunchKernelGGL(bwd_dots_fast_kernel<N>,
+                       dim3(static_cast<unsigned>((d.T + 63) / 64), reduce_parts(d)), dim3(256), 0, s, static_cast<const uint16_t *>(x),
                        static_cast<const uint16_t *>(y), static_cast<const uint16_t *>(g_xout),
-                       static_cast<const uint16_t *>(g_h), d.C, d.T, w.gH_res, w.gH_post, w.gH_pre);
+                       static_cast<const uint16_t *>(g_h), d.C, d.T, reduce_steps(d), w.gH_res,
+                       w.gH_post, w.gH_pre);
     return hipGetLastError();
   };
   switch (d.n) {

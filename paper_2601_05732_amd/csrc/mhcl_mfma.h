@@ -8,6 +8,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 namespace mhcl {
 
@@ -58,6 +59,26 @@ __device__ __forceinline__ uint32_t cvt_pk_bf16(float lo, float hi) {
   r[0] = static_cast<__bf16>(lo);
   r[1] = static_cast<__bf16>(hi);
   return __builtin_bit_cast(uint32_t, r);
+}
+
+// eight values as hi and lo parts, packed two to a word (value = hi + lo up to 2^-17 of its size
+// as bf16, 2^-22 as fp16)
+template <bool F16>
+__device__ __forceinline__ void split8(const float (&v)[8], std::bool_constant<F16>, u32x4 &hi, u32x4 &lo) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float v0 = v[2 * i], v1 = v[2 * i + 1];
+    if constexpr (F16) {
+      const uint32_t h = cvt_pk_f16(v0, v1);
+      const f16x2 hf = __builtin_bit_cast(f16x2, h);
+      hi[i] = h;
+      lo[i] = cvt_pk_f16(v0 - static_cast<float>(hf[0]), v1 - static_cast<float>(hf[1]));
+    } else {
+      const uint32_t h = cvt_pk_bf16(v0, v1);
+      hi[i] = h;
+      lo[i] = cvt_pk_bf16(v0 - __uint_as_float(h << 16), v1 - __uint_as_float(h & 0xffff0000u));
+    }
+  }
 }
 
 // Packed layouts of the projection matrix W [K, M] (fp32) as bf16 pairs

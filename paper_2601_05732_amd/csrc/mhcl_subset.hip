@@ -7,6 +7,7 @@
 // reductions over C and the stream outputs.
 #include "mhcl_common.h"
 #include "mhcl_internal.h"
+#include "mhcl_mfma.h"
 
 namespace mhcl {
 
@@ -33,7 +34,7 @@ namespace {
 struct TableArg {
   int8_t s[kMaxPerm * kMaxNSubset];
 };
-constexpr int kGTok = 64, kGThreads = 512, kOwn = kMaxPerm / 8;
+constexpr int kGTok = 64, kGThreads = 512;
 enum { kGroupForward, kGroupFast, kGroupFull };
 
 __device__ __forceinline__ float group_sum(float v) {
@@ -57,12 +58,53 @@ inline size_t group_lds_bytes(int N, int K, bool bwd) {
   return fl * sizeof(float) + static_cast<size_t>(K) * N;
 }
 
-template <int N, int OUT, bool F16ROWS>
+// dst[tok][0..W) = the sums over the slices of src [slices][T][W] for the block's 64 tokens (past the
+// last one: some valid element again), slices in order.  Eight elements per thread and three more
+// slices of each are on their way together: with one slice of four elements at a time the
+// block, alone on its CU, spent 20 us in round trips at n = 5.
+__device__ __forceinline__ void stage_run(const float *__restrict__ src, int slices, int64_t T,
+                                          int64_t t0, int W, float *dst, int ld) {
+  constexpr int E = 8, S = 3;
+  const int64_t stride = T * W, base = t0 * W;
+  for (int e0 = threadIdx.x; e0 < kGTok * W; e0 += E * kGThreads) {
+    float s[E];
+    int64_t at[E];
+#pragma unroll
+    for (int v = 0; v < E; ++v) {
+      const int e = e0 + v * kGThreads;
+      at[v] = base + (e < kGTok * W ? e : kGTok * W - 1);
+      if (at[v] > stride - 1) at[v] = stride - 1;
+      s[v] = src[at[v]];
+    }
+    for (int p0 = 1; p0 < slices; p0 += S) {
+      float w[S][E];
+#pragma unroll
+      for (int k = 0; k < S; ++k) {
+        const float *slice = src + (p0 + k < slices ? p0 + k : slices - 1) * stride;
+#pragma unroll
+        for (int v = 0; v < E; ++v) w[k][v] = slice[at[v]];
+      }
+#pragma unroll
+      for (int k = 0; k < S; ++k)
+#pragma unroll
+        for (int v = 0; v < E; ++v)
+          if (p0 + k < slices) s[v] += w[k][v];
+    }
+#pragma unroll
+    for (int v = 0; v < E; ++v) {
+      const int e = e0 + v * kGThreads;
+      if (e < kGTok * W) dst[(e / W) * ld + e % W] = s[v];
+    }
+  }
+}
+
+// OWN: residual logits per lane, 8 OWN >= K
+template <int N, int OUT, bool F16ROWS, int OWN>
 __global__ __launch_bounds__(kGThreads) void coeffs_group_kernel(
     const float *__restrict__ u_raw, const float *__restrict__ sumsq, int parts,
     const float *__restrict__ b, const float *__restrict__ alpha,
     const float *__restrict__ gH_res, const float *__restrict__ gH_pre,
-    const float *__restrict__ gH_post, int nC, float eps, int64_t T, int K,
+    const float *__restrict__ gH_post, int gparts, int nC, float eps, int64_t T, int K,
     const int8_t *__restrict__ sigma, const TableArg tab, int use_tab,
     float *__restrict__ H_res, float *__restrict__ H_pre, float *__restrict__ H_post, int CP,
     int MP32, int MP16, float *__restrict__ cpk, uint16_t *__restrict__ vr_hi,
@@ -87,33 +129,15 @@ __global__ __launch_bounds__(kGThreads) void coeffs_group_kernel(
     v = v < 0 ? 0 : (v > N - 1 ? N - 1 : v);
     sig[i] = static_cast<int8_t>(v);
   }
-  // (four elements per thread at a time: their loads, one per K-split slice, are all
-  // requested before the first sum; the block is alone on its CU when T is small)
-  for (int e0 = tid; e0 < kGTok * M; e0 += 4 * kGThreads) {
-    float u[4];
-    int64_t src[4];
-    int dst[4];
+  const int tok = tid >> 3, l = tid & 7;
+  // Every lane takes OWN logits; past the last one it repeats that (same loads on every path, all
+  // requested together: under a condition each was a round trip of its own) and drops the result.
+  auto kc = [&](int kk) { return l + 8 * kk < K ? l + 8 * kk : K - 1; };
+  auto owns = [&](int kk) { return l + 8 * kk < K; };
+  float bk[OWN];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      int e = e0 + v * kGThreads;
-      if (e > kGTok * M - 1) e = kGTok * M - 1;   // surplus threads repeat the last element
-      const int tk = e / M, m = e - tk * M;
-      int64_t tt = t0 + tk;
-      if (tt > T - 1) tt = T - 1;
-      src[v] = tt * M + m;
-      dst[v] = tk * ld + m;
-      u[v] = u_raw[src[v]];
-    }
-    for (int pt = 1; pt < parts; ++pt) {
-      float w[4];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) w[v] = u_raw[static_cast<int64_t>(pt) * T * M + src[v]];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) u[v] += w[v];
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) u_s[dst[v]] = u[v];
-  }
+  for (int kk = 0; kk < OWN; ++kk) bk[kk] = b[kc(kk)];
+  stage_run(u_raw, parts, T, t0, M, u_s, ld);
   if (tid < kGTok) {
     int64_t tt = t0 + tid;
     if (tt > T - 1) tt = T - 1;
@@ -121,17 +145,9 @@ __global__ __launch_bounds__(kGThreads) void coeffs_group_kernel(
     for (int pt = 1; pt < parts; ++pt) ssq += sumsq[pt * T + tt];
     r_s[tid] = 1.f / sqrtf(ssq / static_cast<float>(nC) + eps);
   }
-  if constexpr (BWD) {
-    for (int e = tid; e < kGTok * NN; e += kGThreads) {
-      const int tk = e / NN, c = e - tk * NN;
-      int64_t tt = t0 + tk;
-      if (tt > T - 1) tt = T - 1;
-      g_s[tk * gld + c] = gH_res[tt * NN + c];
-    }
-  }
+  if constexpr (BWD) stage_run(gH_res, gparts, T, t0, NN, g_s, gld);
   __syncthreads();
 
-  const int tok = tid >> 3, l = tid & 7;
   const int64_t t = t0 + tok;
   const bool live = t < T;
   const int64_t tl = live ? t : T - 1;
@@ -141,31 +157,26 @@ __global__ __launch_bounds__(kGThreads) void coeffs_group_kernel(
   float *at = a_s + tok * ld;
 
   // softmax over the K residual logits; own[] = this lane's weights
-  float own[kOwn];
+  float own[OWN];
   float zmax = -INFINITY;
 #pragma unroll
-  for (int kk = 0; kk < kOwn; ++kk) {
-    const int k = l + 8 * kk;
-    own[kk] = -INFINITY;
-    if (k < K) {
-      own[kk] = a0 * (r * ut[k]) + b[k];
-      zmax = fmaxf(zmax, own[kk]);
-    }
+  for (int kk = 0; kk < OWN; ++kk) {
+    const float z = a0 * (r * ut[kc(kk)]) + bk[kk];
+    own[kk] = owns(kk) ? z : -INFINITY;
+    zmax = fmaxf(zmax, own[kk]);
   }
   zmax = group_max(zmax);
   float sum = 0.f;
 #pragma unroll
-  for (int kk = 0; kk < kOwn; ++kk) {
-    const int k = l + 8 * kk;
-    own[kk] = k < K ? expf(own[kk] - zmax) : 0.f;
+  for (int kk = 0; kk < OWN; ++kk) {
+    own[kk] = owns(kk) ? expf(own[kk] - zmax) : 0.f;
     sum += own[kk];
   }
   sum = group_sum(sum);
 #pragma unroll
-  for (int kk = 0; kk < kOwn; ++kk) {
-    const int k = l + 8 * kk;
+  for (int kk = 0; kk < OWN; ++kk) {
     own[kk] = own[kk] / sum;
-    if (k < K) at[k] = own[kk];
+    if (owns(kk)) at[l + 8 * kk] = own[kk];
   }
   __syncthreads();
 
@@ -174,6 +185,7 @@ __global__ __launch_bounds__(kGThreads) void coeffs_group_kernel(
     float row[N];
 #pragma unroll
     for (int j = 0; j < N; ++j) row[j] = 0.f;
+#pragma unroll 8
     for (int k = 0; k < K; ++k) {
       const float w = at[k];
       const int sj = sig[k * N + l];
@@ -196,42 +208,42 @@ __global__ __launch_bounds__(kGThreads) void coeffs_group_kernel(
   } else {
     // g_a[k] = sum_i g_H_res[i][sigma_k(i)], g_z = a (g_a - <a, g_a>)
     const float *gt = g_s + tok * gld;
-    float gown[kOwn];
+    float gown[OWN];
     float meanp = 0.f;
 #pragma unroll
-    for (int kk = 0; kk < kOwn; ++kk) {
-      const int k = l + 8 * kk;
-      gown[kk] = 0.f;
-      if (k < K) {
-        float sg = 0.f;
+    for (int kk = 0; kk < OWN; ++kk) {
+      float sg = 0.f;
 #pragma unroll
-        for (int i = 0; i < N; ++i) sg += gt[i * N + sig[k * N + i]];
-        gown[kk] = sg;
-        meanp += own[kk] * sg;
-      }
+      for (int i = 0; i < N; ++i) sg += gt[i * N + sig[kc(kk) * N + i]];
+      gown[kk] = sg;
+      meanp += owns(kk) ? own[kk] * sg : 0.f;
     }
     const float mean = group_sum(meanp);
     __syncthreads();   // the weights in a_s are no longer needed: it now takes g_z
     float dotp = 0.f, gap[3] = {0.f, 0.f, 0.f}, vmaxp = 0.f;
 #pragma unroll
-    for (int kk = 0; kk < kOwn; ++kk) {
-      const int k = l + 8 * kk;
-      if (k < K) {
-        const float g = live ? own[kk] * (gown[kk] - mean) : 0.f;
-        const float u = ut[k];
-        const float v = r * a0 * g;
-        at[k] = g;
-        gap[0] += g * (r * u);
-        dotp += v * u;
-        vmaxp = fmaxf(vmaxp, fabsf(v));
-      }
+    for (int kk = 0; kk < OWN; ++kk) {
+      const bool ok = live && owns(kk);
+      const float g = ok ? own[kk] * (gown[kk] - mean) : 0.f;
+      const float uk = ut[kc(kk)];
+      const float v = ok ? r * a0 * g : 0.f;
+      if (owns(kk)) at[l + 8 * kk] = g;
+      gap[0] += g * (r * uk);
+      dotp += v * uk;
+      vmaxp = fmaxf(vmaxp, fabsf(v));
     }
     if (l < N) {
       const float up = ut[K + l], uq = ut[K + N + l];
       const float hp = sigmoidf(a1 * (r * up) + b[K + l]);
       const float hq = 2.f * sigmoidf(a2 * (r * uq) + b[K + N + l]);
-      float gp = gH_pre[tl * N + l] * hp * (1.f - hp);
-      float gq = gH_post[tl * N + l] * hq * (1.f - 0.5f * hq);
+      float dp = gH_pre[tl * N + l], dq = gH_post[tl * N + l];
+#pragma unroll 4
+      for (int pt = 1; pt < gparts; ++pt) {
+        dp += gH_pre[(pt * T + tl) * N + l];
+        dq += gH_post[(pt * T + tl) * N + l];
+      }
+      float gp = dp * hp * (1.f - hp);
+      float gq = dq * hq * (1.f - 0.5f * hq);
       if (live) {
         cpk[t * CP + NN + l] = hp;
         cpk[t * CP + NN + N + l] = hq;
@@ -276,54 +288,43 @@ __global__ __launch_bounds__(kGThreads) void coeffs_group_kernel(
         if (t0 + tk < T) vr32[(t0 + tk) * MP16 + m] = vr_of(tk, m);
       }
     } else {
-    auto split = [](float v, bool f16, uint16_t &hi, uint16_t &lo) {
-      if (f16) {
-        const _Float16 h16 = static_cast<_Float16>(v);
-        const _Float16 l16 = static_cast<_Float16>(v - static_cast<float>(h16));
-        hi = __builtin_bit_cast(uint16_t, h16);
-        lo = __builtin_bit_cast(uint16_t, l16);
-      } else {
-        hi = f32_to_bf16(v);
-        lo = f32_to_bf16(v - bf16_to_f32(hi));
-      }
-    };
-    auto pack8 = [](const uint16_t (&h)[8]) {
-      uint4 v;
-      v.x = h[0] | (uint32_t(h[1]) << 16); v.y = h[2] | (uint32_t(h[3]) << 16);
-      v.z = h[4] | (uint32_t(h[5]) << 16); v.w = h[6] | (uint32_t(h[7]) << 16);
-      return v;
-    };
     // rows [Tpad][MP32]: eight consecutive logits of one token per thread
     const int nvec = MP32 / 8;
     for (int e = tid; e < kGTok * nvec; e += kGThreads) {
       const int tk = e / nvec, v8 = e - tk * nvec;
       const float inv = F16ROWS ? t_s[tk * 4 + 3] : 1.f;
-      uint16_t hi[8], lo[8];
+      float v[8];
+      u32x4 hi, lo;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) split(vr_of(tk, 8 * v8 + i) * inv, F16ROWS, hi[i], lo[i]);
+      for (int i = 0; i < 8; ++i) v[i] = vr_of(tk, 8 * v8 + i) * inv;
+      split8(v, std::bool_constant<F16ROWS>{}, hi, lo);
       const size_t off = static_cast<size_t>(t0 + tk) * MP32 + 8 * v8;
-      *reinterpret_cast<uint4 *>(vr_hi + off) = pack8(hi);
-      *reinterpret_cast<uint4 *>(vr_lo + off) = pack8(lo);
+      *reinterpret_cast<u32x4 *>(vr_hi + off) = hi;
+      *reinterpret_cast<u32x4 *>(vr_lo + off) = lo;
     }
     // tokens innermost [Tpad/32][MP16][32]: eight consecutive tokens of one logit per thread
     const int64_t blk0 = t0 >> 5;
     for (int e = tid; e < 2 * MP16 * 4; e += kGThreads) {
       const int half = e / (MP16 * 4), rem = e - half * (MP16 * 4);
       const int m = rem >> 2, tg = rem & 3;
-      uint16_t hi[8], lo[8];
+      float v[8];
+      u32x4 hi, lo;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) split(vr_of(half * 32 + tg * 8 + i, m), false, hi[i], lo[i]);
+      for (int i = 0; i < 8; ++i) v[i] = vr_of(half * 32 + tg * 8 + i, m);
+      split8(v, std::false_type{}, hi, lo);
       const size_t off = (static_cast<size_t>(blk0 + half) * MP16 + m) * 32 + tg * 8;
-      *reinterpret_cast<uint4 *>(vrT_hi + off) = pack8(hi);
-      *reinterpret_cast<uint4 *>(vrT_lo + off) = pack8(lo);
+      *reinterpret_cast<u32x4 *>(vrT_hi + off) = hi;
+      *reinterpret_cast<u32x4 *>(vrT_lo + off) = lo;
     }
     }
     // sums over the block's 64 tokens, token order
     if (tid < M + 3) {
       float sacc = 0.f;
       if (tid < M) {
+#pragma unroll 16
         for (int tk = 0; tk < kGTok; ++tk) sacc += a_s[tk * ld + tid];
       } else {
+#pragma unroll 16
         for (int tk = 0; tk < kGTok; ++tk) sacc += t_s[tk * 4 + (tid - M)];
       }
       gz_sums[static_cast<int64_t>(blockIdx.x) * (M + 3) + tid] = sacc;
@@ -390,13 +391,14 @@ hipError_t launch_coeffs_group(const mhcl_desc &d, int parts, const float *u_raw
   if (!group_table(d, g)) return hipErrorInvalidValue;
   return dispatch_n8(d.n, [&](auto nn) {
     constexpr int N = decltype(nn)::value;
-    auto kern = coeffs_group_kernel<N, kGroupForward, false>;
+    auto kern = g.K <= 64 ? coeffs_group_kernel<N, kGroupForward, false, 8>
+                          : coeffs_group_kernel<N, kGroupForward, false, 16>;
     const size_t lds = group_lds_bytes(N, g.K, false);
     hipError_t e = allow_lds(kern, lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>((d.T + kGTok - 1) / kGTok)),
                        dim3(kGThreads), lds, s, u_raw, sumsq, parts, b, alpha, nullptr, nullptr,
-                       nullptr, d.n * d.C, d.eps, d.T, g.K, g.sigma, g.tab, g.use_tab, H_res, H_pre,
+                       nullptr, 1, d.n * d.C, d.eps, d.T, g.K, g.sigma, g.tab, g.use_tab, H_res, H_pre,
                        H_post, 0, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
     return hipGetLastError();
   });
@@ -411,13 +413,14 @@ hipError_t launch_coeffs_bwd_group(const mhcl_desc &d, int parts, const float *u
   const int M = g.K + 2 * d.n;
   return dispatch_n8(d.n, [&](auto nn) {
     constexpr int N = decltype(nn)::value;
-    auto kern = coeffs_group_kernel<N, kGroupFull, false>;
+    auto kern = g.K <= 64 ? coeffs_group_kernel<N, kGroupFull, false, 8>
+                          : coeffs_group_kernel<N, kGroupFull, false, 16>;
     const size_t lds = group_lds_bytes(N, g.K, true);
     hipError_t e = allow_lds(kern, lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>((d.T + kGTok - 1) / kGTok)),
                        dim3(kGThreads), lds, s, u_raw, sumsq, parts, b, alpha, g_H_res, g_H_pre,
-                       g_H_post, d.n * d.C, d.eps, d.T, g.K, g.sigma, g.tab, g.use_tab, nullptr, nullptr,
+                       g_H_post, 1, d.n * d.C, d.eps, d.T, g.K, g.sigma, g.tab, g.use_tab, nullptr, nullptr,
                        nullptr, token_rec<N>(), 0, (M + 15) / 16 * 16, o.rec, nullptr, nullptr, nullptr,
                        nullptr, o.vr, o.gz);
     return hipGetLastError();
@@ -441,15 +444,18 @@ hipError_t launch_bwd_epilogue_group(const mhcl_desc &d, const float *b, const f
       if (e != hipSuccess) return e;
       hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(Tpad / kGTok)), dim3(kGThreads), lds, s,
                          w.u_raw, w.sumsq, w.parts, b, alpha, w.gH_res, w.gH_pre, w.gH_post,
-                         d.n * d.C, d.eps, d.T, g.K, g.sigma, g.tab, g.use_tab, nullptr, nullptr,
+                         w.gparts, d.n * d.C, d.eps, d.T, g.K, g.sigma, g.tab, g.use_tab, nullptr, nullptr,
                          nullptr, w.CP, w.MP32, w.MP16, w.cpk, w.vr_hi, w.vr_lo, w.vrT_hi, w.vrT_lo,
                          nullptr, w.gz);
       return hipGetLastError();
     };
     if constexpr (N >= 5) {
-      if (f16) return launch(coeffs_group_kernel<N, kGroupFast, true>);
+      if (f16)
+        return launch(g.K <= 64 ? coeffs_group_kernel<N, kGroupFast, true, 8>
+                                : coeffs_group_kernel<N, kGroupFast, true, 16>);
     }
-    return launch(coeffs_group_kernel<N, kGroupFast, false>);
+    return launch(g.K <= 64 ? coeffs_group_kernel<N, kGroupFast, false, 8>
+                            : coeffs_group_kernel<N, kGroupFast, false, 16>);
   });
 }
 

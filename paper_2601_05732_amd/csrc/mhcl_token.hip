@@ -440,21 +440,6 @@ __global__ __launch_bounds__(kTokThreads<L>) void token_stage_kernel(TokenIn in,
       }
     } else {
       // (tokens up to the next multiple of 64 exist in these arrays; past T they are zeros)
-      // eight values as hi and lo parts, packed two to a word (value = hi + lo up to 2^-17)
-      auto split8 = [](const float (&v)[8], auto f16, u32x4 &hi, u32x4 &lo) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float v0 = v[2 * i], v1 = v[2 * i + 1];
-          if constexpr (decltype(f16)::value) {
-            hi[i] = cvt_pk_f16(v0, v1);
-            const f16x2 h = __builtin_bit_cast(f16x2, static_cast<uint32_t>(hi[i]));
-            lo[i] = cvt_pk_f16(v0 - static_cast<float>(h[0]), v1 - static_cast<float>(h[1]));
-          } else {
-            hi[i] = cvt_pk_bf16(v0, v1);
-            lo[i] = cvt_pk_bf16(v0 - bf16lo(hi[i]), v1 - bf16hi(hi[i]));
-          }
-        }
-      };
       // rows [Tpad][MP32]: eight logits of a token per thread; then, by the next threads, tokens
       // innermost [Tpad/32][MP16][32]: eight tokens of a logit
       constexpr int kRows = BT * MP32 / 8, kCols = MP16 * BT / 8;
