@@ -50,8 +50,18 @@ struct CoeffsWs {
     const size_t parts = static_cast<size_t>(proj_ksplit(d));
     u_raw = c.take<float>(parts * T * logits(d));
     sumsq = c.take<float>(parts * T);
-    Wp = fast_path_ok(d) ? c.take<char>(packed_w_b_bytes(d, logits(d))) : nullptr;
+    Wp = proj_fullprec_used(d) ? nullptr : c.take<char>(packed_w_b_bytes(d, logits(d)));
     bytes = c.off;
+    if (fast_path_ok(d) && proj_fullprec_used(d)) {
+      // never less than the bf16 projection asks for at this shape: the shapes that the static
+      // array takes do not depend on which one runs (its slices alone are at most 10 MB)
+      WsCursor m(nullptr);
+      const size_t mparts = static_cast<size_t>(mfma_ksplit(d));
+      m.take<float>(mparts * T * logits(d));
+      m.take<float>(mparts * T);
+      m.take<char>(packed_w_b_bytes(d, logits(d)));
+      if (m.off > bytes) bytes = m.off;
+    }
   }
 };
 

@@ -1606,7 +1606,10 @@ hipError_t launch_pack_w_b(const mhcl_desc &d, int M, const float *W, void *Wp, 
 }
 
 int proj_ksplit(const mhcl_desc &d) {
-  if (proj_fullprec_used(d)) return proj_fullprec_parts(d);
+  return proj_fullprec_used(d) ? proj_fullprec_parts(d) : mfma_ksplit(d);
+}
+
+int mfma_ksplit(const mhcl_desc &d) {
   const int M = res_logits(d) + 2 * d.n;
   int kc = 4, tok = 128;
   const int want = 256;   // one block per CU

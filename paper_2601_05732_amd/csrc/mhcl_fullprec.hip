@@ -437,17 +437,15 @@ bool proj_fullprec_used(const mhcl_desc &d) {
   return d.T * tiles <= 8000000 / nC + 2500;
 }
 
-// Parts of a row: enough blocks for two per compute unit, each wave with at least one step.
-// The coefficient stages add the parts' slices one after the other, so they are few.
+// Parts of a row: enough blocks for two per compute unit, each wave with at least one step, at most
+// 16 (the coefficient stages add the slices; 32 gained 1 us for 16 tokens and lost 2 for 256 at
+// C = 4096; 4 instead of 16 for n = 5, C = 2560, 256 tokens: 105 us for mhcl_coeffs against 57).
 int proj_fullprec_parts(const mhcl_desc &d) {
-  const int M = res_logits(d) + 2 * d.n;
   const int V = d.io_dtype == MHCL_BF16 ? BF16::kVec : F32::kVec;
   const int nsteps = (d.n * d.C + 4 * V - 1) / (4 * V);
   const int64_t groups = (d.T + 15) / 16;
-  const bool sliced = M % 4 == 0 && M <= 32 && d.res_mode != MHCL_RES_SUBSET;
-  const int most = sliced ? 16 : 4;
   int parts = 1;
-  while (parts < most && groups * parts < 512 && nsteps >= 2 * parts * kProjWaves) parts *= 2;
+  while (parts < 16 && groups * parts < 512 && nsteps >= 2 * parts * kProjWaves) parts *= 2;
   return parts;
 }
 

@@ -112,6 +112,7 @@ bool fast_path_ok(const mhcl_desc &d);
 // kMaxKSplit); u_raw and sumsq then hold that many slices ([parts][T][M], [parts][T]).
 constexpr int kMaxKSplit = 4;
 int proj_ksplit(const mhcl_desc &d);
+int mfma_ksplit(const mhcl_desc &d);   // slices of launch_proj_mfma
 size_t packed_w_b_bytes(const mhcl_desc &d, int M);
 // packs W (B layout) and, in the same launch, clears `nzero` floats at `zero`
 hipError_t launch_pack_w_b(const mhcl_desc &d, int M, const float *W, void *Wp, hipStream_t s,
