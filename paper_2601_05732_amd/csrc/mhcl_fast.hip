@@ -669,7 +669,9 @@ __global__ __launch_bounds__(256) void bwd_dots_fast_kernel(
 // Per block iteration the four waves load the tiles of 4 x 16 tokens, publish
 // their x tiles in LDS, and wave w (one wave per stream) then accumulates the
 // g_W rows of stream w for all 64 tokens:
-//   D[m][k] += vrT[m][token] * x^T[token][k]
+//   D[k][m] += x[k][token] * vrT[token][m]
+// (the logits along the lanes: a store then covers 64 contiguous bytes of four rows of g_W; with the
+// columns along them it scattered into 64 rows and a block's 32 stores took longer than an iteration)
 // with x^T obtained by an MFMA against a 0/1 selection matrix (exact) as in
 // bwd_gw_kernel.  Accumulators stay in registers over the block's token chunk;
 // partial sums per chunk go to `gw_part` and are added in chunk order.
@@ -870,8 +872,8 @@ __global__ __launch_bounds__(256 * SLABS, SLABS == 1 ? 2 : 1) void bwd_out_gw_ke
           bt.z = cvt_pk_bf16(tb2[0], tb2[1]); bt.w = cvt_pk_bf16(tb2[2], tb2[3]);
 #pragma unroll
           for (int mt = 0; mt < NT; ++mt) {
-            acc[u][h][mt] = mfma16(va[pr][mt][0], bt, acc[u][h][mt]);
-            acc[u][h][mt] = mfma16(va[pr][mt][1], bt, acc[u][h][mt]);
+            acc[u][h][mt] = mfma16(bt, va[pr][mt][0], acc[u][h][mt]);
+            acc[u][h][mt] = mfma16(bt, va[pr][mt][1], acc[u][h][mt]);
           }
         }
       }
@@ -909,14 +911,15 @@ __global__ __launch_bounds__(256 * SLABS, SLABS == 1 ? 2 : 1) void bwd_out_gw_ke
     for (int u = 0; u < 2; ++u)
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const int k = wave * C + S * 64 + u * 32 + 16 * h + r;
+        const int k = wave * C + S * 64 + u * 32 + 16 * h + 4 * q;
 #pragma unroll
-        for (int mt = 0; mt < NT; ++mt)
+        for (int mt = 0; mt < NT; ++mt) {
+          const int m = mt * 16 + r;
+          if (m < M) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int m = mt * 16 + 4 * q + i;
-            if (m < M) dst[static_cast<size_t>(k) * M + m] = acc[u][h][mt][i];
+            for (int i = 0; i < 4; ++i) dst[static_cast<size_t>(k + i) * M + m] = acc[u][h][mt][i];
           }
+        }
       }
   }
 }
@@ -1276,8 +1279,8 @@ __global__ __launch_bounds__(256) void mix_wide_kernel(
 // of tokens 32 at a time.  x arrives with tokens across lanes, but the
 // contraction runs over tokens, so each x tile is first transposed by an MFMA
 // against a 0/1 selection matrix (exact: the values are bf16), which leaves
-// lane (k, q) holding 4 + 4 tokens of column k: the B operand of
-//   D[m][k] += vrT[m][token] * x^T[token][k].
+// lane (k, q) holding 4 + 4 tokens of column k: the left operand of
+//   D[k][m] += x[k][token] * vrT[token][m]  (logits along the lanes, as in bwd_out_gw_kernel).
 // Partial sums per token chunk go to `out`; they are added in chunk order.
 template <int NT, int CSW>
 __global__ __launch_bounds__(256, 2) void bwd_gw_kernel(
@@ -1354,8 +1357,8 @@ __global__ __launch_bounds__(256, 2) void bwd_gw_kernel(
         for (int mt = 0; mt < NT; ++mt) {
           const u32x4 vh = u32x4{in.v[mt][0].x, in.v[mt][0].y, in.v[mt][1].x, in.v[mt][1].y};
           const u32x4 vl = u32x4{in.v[mt][2].x, in.v[mt][2].y, in.v[mt][3].x, in.v[mt][3].y};
-          acc[c][h][mt] = mfma16(vh, bt, acc[c][h][mt]);
-          acc[c][h][mt] = mfma16(vl, bt, acc[c][h][mt]);
+          acc[c][h][mt] = mfma16(bt, vh, acc[c][h][mt]);
+          acc[c][h][mt] = mfma16(bt, vl, acc[c][h][mt]);
         }
       }
     }
@@ -1379,14 +1382,15 @@ __global__ __launch_bounds__(256, 2) void bwd_gw_kernel(
     if (s0 + c < nsteps) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const int k = (s0 + c) * 32 + 16 * h + r;
+        const int k = (s0 + c) * 32 + 16 * h + 4 * q;
 #pragma unroll
-        for (int mt = 0; mt < NT; ++mt)
+        for (int mt = 0; mt < NT; ++mt) {
+          const int m = mt * 16 + r;
+          if (m < M) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int m = mt * 16 + 4 * q + i;
-            if (m < M) dst[static_cast<size_t>(k) * M + m] = acc[c][h][mt][i];
+            for (int i = 0; i < 4; ++i) dst[static_cast<size_t>(k + i) * M + m] = acc[c][h][mt][i];
           }
+        }
       }
     }
   }
@@ -1533,8 +1537,8 @@ __global__ __launch_bounds__(512, 1) void bwd_gw_lds_kernel(
         for (int c = 0; c < CSW; ++c)
 #pragma unroll
           for (int h = 0; h < 2; ++h) {
-            acc[c][h][mt] = mfma16(ah, bt[c][h], acc[c][h][mt]);
-            acc[c][h][mt] = mfma16(al, bt[c][h], acc[c][h][mt]);
+            acc[c][h][mt] = mfma16(bt[c][h], ah, acc[c][h][mt]);
+            acc[c][h][mt] = mfma16(bt[c][h], al, acc[c][h][mt]);
           }
       }
     }
@@ -1548,14 +1552,15 @@ __global__ __launch_bounds__(512, 1) void bwd_gw_lds_kernel(
     if (s0 + c < nsteps) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const int k = (s0 + c) * 32 + 16 * h + r;
+        const int k = (s0 + c) * 32 + 16 * h + 4 * q;
 #pragma unroll
-        for (int mt = 0; mt < NT; ++mt)
+        for (int mt = 0; mt < NT; ++mt) {
+          const int m = mt * 16 + r;
+          if (m < M) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int m = mt * 16 + 4 * q + i;
-            if (m < M) dst[static_cast<size_t>(k) * M + m] = acc[c][h][mt][i];
+            for (int i = 0; i < 4; ++i) dst[static_cast<size_t>(k + i) * M + m] = acc[c][h][mt][i];
           }
+        }
       }
     }
   }
