@@ -121,10 +121,12 @@ hipError_t run_projection(const mhcl_desc &d, const void *x, const float *W, flo
                           float *sumsq, char *Wp, int stage, hipStream_t s) {
   const int M = logits(d);
   if (!proj_fullprec_used(d)) {
-    hipError_t e = launch_pack_w_b(d, M, W, Wp, s);
-    if (e != hipSuccess) return e;
+    if (!proj_mfma_direct(d)) {
+      hipError_t e = launch_pack_w_b(d, M, W, Wp, s);
+      if (e != hipSuccess) return e;
+    }
     StageBracket br(stage, s);
-    return launch_proj_mfma(d, M, x, Wp, u_raw, sumsq, s);
+    return launch_proj_mfma(d, M, x, Wp, W, u_raw, sumsq, s);
   }
   StageBracket br(stage, s);
   return launch_proj_fullprec(d, M, x, W, u_raw, sumsq, s);
@@ -492,7 +494,7 @@ int mhcl_bwd_fused(const mhcl_desc *desc, const void *x, const void *y, const fl
         if (proj_fullprec_used(*desc))
           MHCL_HIP(launch_proj_fullprec(*desc, M, x, W, f.u_raw, f.sumsq, s));
         else
-          MHCL_HIP(launch_proj_mfma(*desc, M, x, f.Wp, f.u_raw, f.sumsq, s));
+          MHCL_HIP(launch_proj_mfma(*desc, M, x, f.Wp, W, f.u_raw, f.sumsq, s));
         MHCL_HIP(launch_bwd_dots_fast(*desc, x, y, g_xout, g_h, f, s));
       } else {
         MHCL_HIP(launch_bwd_reduce(*desc, M, x, y, g_xout, g_h, f, s));

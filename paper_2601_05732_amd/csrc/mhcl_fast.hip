@@ -68,9 +68,10 @@ struct ProjCfg {
   static constexpr int kLdsBytes = 2 * kChunkVec * 16;
 };
 
-template <int NT>
+template <int NT, bool DIRECT>
 __global__ __launch_bounds__(ProjCfg<NT>::kThreads, 1) void proj_mfma_kernel(const uint16_t *__restrict__ x,
-                                                           const u32x4 *__restrict__ Wp, int K,
+                                                           const u32x4 *__restrict__ Wp,
+                                                           const float *__restrict__ W, int K,
                                                            int M, int64_t T,
                                                            float *__restrict__ u_raw,
                                                            float *__restrict__ sumsq) {
@@ -94,7 +95,8 @@ __global__ __launch_bounds__(ProjCfg<NT>::kThreads, 1) void proj_mfma_kernel(con
   const int step0 = blockIdx.y * nsteps;
 #pragma unroll
   for (int g = 0; g < TG; ++g) row[g] += static_cast<size_t>(step0) * 32;
-  Wp += static_cast<size_t>(step0) * NT * 2 * 64;
+  if constexpr (DIRECT) W += static_cast<size_t>(step0) * 32 * M;
+  else Wp += static_cast<size_t>(step0) * NT * 2 * 64;
   u_raw += static_cast<size_t>(blockIdx.y) * T * M;
   sumsq += static_cast<size_t>(blockIdx.y) * T;
   const int nchunks = (nsteps + KC - 1) / KC;
@@ -109,7 +111,10 @@ __global__ __launch_bounds__(ProjCfg<NT>::kThreads, 1) void proj_mfma_kernel(con
 
   constexpr int WV = (Cfg::kChunkVec + Cfg::kThreads - 1) / Cfg::kThreads;   // u32x4 of W each thread stages per chunk
   constexpr bool kWholeW = Cfg::kChunkVec % Cfg::kThreads == 0;
-  u32x4 a[2][TG][KC], wst[WV];
+  // DIRECT: W is taken as it is; a thread stages (K step, tile, lane) items of eight rows each
+  constexpr int kItems = Cfg::kChunkVec / 2, WI = (kItems + Cfg::kThreads - 1) / Cfg::kThreads;
+  u32x4 a[2][TG][KC], wst[DIRECT ? 1 : WV];
+  float wraw[DIRECT ? WI : 1][8];
   const int wlim = nsteps * NT * 2 * 64 - 1;   // last valid u32x4 of packed W
 
   // Loads never branch: a step past the end re-reads the last step (address
@@ -129,6 +134,21 @@ __global__ __launch_bounds__(ProjCfg<NT>::kThreads, 1) void proj_mfma_kernel(con
     }
   };
   auto load_w = [&](int c) {
+    if constexpr (DIRECT) {
+#pragma unroll
+      for (int i = 0; i < WI; ++i) {
+        int o = i * Cfg::kThreads + threadIdx.x;
+        if (kItems % Cfg::kThreads != 0 && o > kItems - 1) o = kItems - 1;
+        const int blk = o >> 6, j = blk % NT;
+        int step = c * KC + blk / NT;
+        if (step > nsteps - 1) step = nsteps - 1;
+        const int col = 16 * j + (o & 15);
+        const float *row = W + static_cast<size_t>(32 * step + 8 * ((o >> 4) & 3)) * M + (col < M ? col : M - 1);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) wraw[i][e] = row[e * M];
+      }
+      return;
+    }
     const int base = c * Cfg::kChunkVec;
 #pragma unroll
     for (int i = 0; i < WV; ++i) {
@@ -139,6 +159,23 @@ __global__ __launch_bounds__(ProjCfg<NT>::kThreads, 1) void proj_mfma_kernel(con
     }
   };
   auto store_w = [&](int buf) {
+    if constexpr (DIRECT) {
+#pragma unroll
+      for (int i = 0; i < WI; ++i) {
+        int o = i * Cfg::kThreads + threadIdx.x;
+        if (kItems % Cfg::kThreads != 0 && o > kItems - 1) o = kItems - 1;
+        const int blk = o >> 6;
+        if (16 * (blk % NT) + (o & 15) >= M) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) wraw[i][e] = 0.f;
+        }
+        u32x4 hi, lo;
+        split8(wraw[i], std::false_type{}, hi, lo);
+        lds[buf * Cfg::kChunkVec + (blk * 2 + 0) * 64 + (o & 63)] = hi;
+        lds[buf * Cfg::kChunkVec + (blk * 2 + 1) * 64 + (o & 63)] = lo;
+      }
+      return;
+    }
 #pragma unroll
     for (int i = 0; i < WV; ++i) {
       int o = i * Cfg::kThreads + threadIdx.x;
@@ -1630,13 +1667,28 @@ int mfma_ksplit(const mhcl_desc &d) {
   return ks;
 }
 
-hipError_t launch_proj_mfma(const mhcl_desc &d, int M, const void *x, const void *Wp, float *u_raw,
-                            float *sumsq, hipStream_t s) {
+// W staged as it is (split into its two parts on the way to LDS) instead of packed by a launch of its
+// own, 5 to 8 us: up to four logit tiles (with nine the eight loads per item cost more than the
+// launch, 149 against 166 us for mhcl_coeffs at n = 5, C = 2560, 16384 tokens; with five equal), and
+// not for many tokens of very long rows.  mhcl_coeffs, packed / direct: n = 4, C = 1024, 5003
+// tokens 19.9 / 15.7 us, 32768 tokens 75.7 / 70.1; C = 2048, 16384 tokens 87.5 / 72.5, 32768 tokens
+// 141 / 140; C = 4096, 4096 tokens 55.8 / 52.1, 8192 tokens 76.2 / 77.5, 32768 tokens 191 / 220;
+// n = 3, C = 4096, 32768 tokens 165 / 162.
+bool proj_mfma_direct(const mhcl_desc &d) {
+  const int64_t nC = static_cast<int64_t>(d.n) * d.C;
+  return logit_tiles(res_logits(d) + 2 * d.n) <= 4 && (nC < 16384 || d.T <= 4096);
+}
+
+hipError_t launch_proj_mfma(const mhcl_desc &d, int M, const void *x, const void *Wp, const float *W,
+                            float *u_raw, float *sumsq, hipStream_t s) {
   const int K = d.n * d.C;
   const int ks = proj_ksplit(d);
   return dispatch_nt_proj(logit_tiles(M), [&](auto nt) {
     constexpr int NT = decltype(nt)::value;
-    auto kern = proj_mfma_kernel<NT>;
+    auto kern = proj_mfma_kernel<NT, false>;
+    if constexpr (NT <= 4) {
+      if (proj_mfma_direct(d)) kern = proj_mfma_kernel<NT, true>;
+    }
     constexpr int lds = ProjCfg<NT>::kLdsBytes;
     if (lds > 64 * 1024) {
       hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
@@ -1646,7 +1698,7 @@ hipError_t launch_proj_mfma(const mhcl_desc &d, int M, const void *x, const void
     constexpr int kTok = ProjCfg<NT>::kTokens;
     hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>((d.T + kTok - 1) / kTok), ks),
                        dim3(ProjCfg<NT>::kThreads),
-                       lds, s, static_cast<const uint16_t *>(x), static_cast<const u32x4 *>(Wp), K,
+                       lds, s, static_cast<const uint16_t *>(x), static_cast<const u32x4 *>(Wp), W, K,
                        M, d.T, u_raw, sumsq);
     return hipGetLastError();
   });
@@ -1775,8 +1827,8 @@ FastBwdWs::FastBwdWs(const mhcl_desc &d, void *ws) {
 hipError_t launch_pack_w_ab(const mhcl_desc &d, int M, const float *W, const FastBwdWs &w,
                             hipStream_t s) {
   const int K = d.n * d.C, NT = logit_tiles(M), MS = logit_steps(M);
-  // (the B layout has no reader where the wide path recomputes with the fp64 projection)
-  const bool no_b = fast_bwd_wide(d) && proj_fullprec_used(d);
+  // (the B layout has no reader where the wide path's projection takes W as it is)
+  const bool no_b = fast_bwd_wide(d) && (proj_fullprec_used(d) || proj_mfma_direct(d));
   const int nb_b = no_b ? 0 : ((K / 32) * NT * 64 + 255) / 256;
   const int nb_a = ((K / 64) * 4 * MS * 64 + 255) / 256;
   // one fp16 part where the only reader is bwd_out_w16_kernel; its scale needs max |W| first

@@ -117,8 +117,10 @@ size_t packed_w_b_bytes(const mhcl_desc &d, int M);
 // packs W (B layout) and, in the same launch, clears `nzero` floats at `zero`
 hipError_t launch_pack_w_b(const mhcl_desc &d, int M, const float *W, void *Wp, hipStream_t s,
                            float *zero = nullptr, size_t nzero = 0);
-hipError_t launch_proj_mfma(const mhcl_desc &d, int M, const void *x, const void *Wp, float *u_raw,
-                            float *sumsq, hipStream_t s);
+// reads W itself where proj_mfma_direct(d), else Wp (W packed by launch_pack_w_b or launch_pack_w_ab)
+bool proj_mfma_direct(const mhcl_desc &d);
+hipError_t launch_proj_mfma(const mhcl_desc &d, int M, const void *x, const void *Wp, const float *W,
+                            float *u_raw, float *sumsq, hipStream_t s);
 
 // Single-read forward (projection slices, H_pre and h from one read of x): bf16 fast path
 // with at most 32 logits, C a multiple of 256 from 1024 to 8192, enough tokens to fill the pipeline.

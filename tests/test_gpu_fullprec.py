@@ -26,7 +26,8 @@ CASES = [
     # widths that are multiples of 64: the last token count of the fp64 projection, the first of the
     # bf16 one with its row split four ways
     _wl(4, 1024, 2226, "bf16"), _wl(4, 1024, 2227, "bf16"), _wl(5, 320, 833, "bf16"), _wl(5, 320, 834, "bf16"),
-    _wl(8, 128, 2063, "bf16", "subset", 64), _wl(3, 64, 16, "bf16", "sk"), _wl(2, 4096, 3, "bf16"),
+    _wl(8, 128, 2063, "bf16", "subset", 64), _wl(4, 4096, 1600, "bf16"), _wl(7, 64, 4000, "bf16", "subset", 50),
+    _wl(5, 64, 8200, "bf16", "sk"), _wl(2, 64, 65537, "bf16"), _wl(3, 64, 16, "bf16", "sk"), _wl(2, 4096, 3, "bf16"),
     _wl(7, 56, 131, "bf16", "subset", 50), _wl(8, 24, 64, "f32", "subset", 111),
 ]
 
