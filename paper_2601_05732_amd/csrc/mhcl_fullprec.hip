@@ -424,17 +424,16 @@ int gw_columns(const mhcl_desc &d, int M) {
 
 }  // namespace
 
-// Where the bf16 MFMA projection applies too, this one is used for few tokens: it needs no packed W
-// and spreads over the chip by splitting rows, but runs at the fp64 rate.  Its time is about
-// 0.65 us per million of T tiles nC; the other one's, while its blocks do not fill the chip, 5.5 us
-// for packing W and 1.66 us per 1000 columns of a row.  Both sides measured (the mhcl_coeffs call,
-// n = 4): C = 4096 at 16 tokens 15 against 36 us, at 1024 31 / 46, at 2048 54 / 46; C = 1024 at
-// 1024 tokens 15 / 22, at 2048 21 / 22, at 4096 31 / 22; C = 256 at 4096 tokens 14.6 / 16.0.
+// Where the bf16 MFMA projection applies too, this one is used for few tokens: it spreads over the
+// chip by splitting rows into more parts, but runs at the fp64 rate, so its time grows with the
+// tokens and tiles where the other's is flat until its blocks fill the chip.  Both sides, mhcl_coeffs:
+// n = 4, C = 1024, 256 tokens 10.5 / 14.7 us, 1024 tokens 13.6 / 15.1, 2048 tokens 18.7 / 15.2; C = 4096,
+// 64 tokens 13.5 / 37.8, 1024 tokens 29.6 / 39.2, 1500 tokens 40.9 / 39.2; n = 3, C = 1024, 2000 tokens
+// 12.3 / 12.7; n = 5, C = 2560 (nine tiles, where the other one packs W first), 500 tokens 83 / 106.
 bool proj_fullprec_used(const mhcl_desc &d) {
   if (!fast_path_ok(d)) return true;
-  const int64_t nC = static_cast<int64_t>(d.n) * d.C;
   const int tiles = logit_tiles(res_logits(d) + 2 * d.n);
-  return d.T * tiles <= 8000000 / nC + 2500;
+  return d.T * tiles <= (tiles <= 4 ? 2500 : 5000);
 }
 
 // Parts of a row: enough blocks for two per compute unit, each wave with at least one step, at most

@@ -25,9 +25,9 @@ CASES = [
     _wl(5, 64, 70, "bf16", "sk"), _wl(8, 40, 33, "f32", "subset", 20),
     # widths that are multiples of 64: the last token count of the fp64 projection, the first of the
     # bf16 one with its row split four ways
-    _wl(4, 1024, 2226, "bf16"), _wl(4, 1024, 2227, "bf16"), _wl(5, 320, 833, "bf16"), _wl(5, 320, 834, "bf16"),
-    _wl(8, 128, 2063, "bf16", "subset", 64), _wl(4, 4096, 1600, "bf16"), _wl(7, 64, 4000, "bf16", "subset", 50),
-    _wl(5, 64, 8200, "bf16", "sk"), _wl(2, 64, 65537, "bf16"), _wl(3, 64, 16, "bf16", "sk"), _wl(2, 4096, 3, "bf16"),
+    _wl(4, 1024, 1250, "bf16"), _wl(4, 1024, 1251, "bf16"), _wl(5, 320, 555, "bf16"), _wl(5, 320, 556, "bf16"),
+    _wl(8, 128, 1001, "bf16", "subset", 64), _wl(4, 4096, 1300, "bf16"), _wl(7, 64, 700, "bf16", "subset", 50),
+    _wl(5, 64, 900, "bf16", "sk"), _wl(2, 64, 2501, "bf16"), _wl(3, 64, 16, "bf16", "sk"), _wl(2, 4096, 3, "bf16"),
     _wl(7, 56, 131, "bf16", "subset", 50), _wl(8, 24, 64, "f32", "subset", 111),
 ]
 
