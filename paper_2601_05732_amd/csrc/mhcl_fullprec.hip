@@ -1,7 +1,8 @@
-// Thin products at full precision on the matrix cores (v_mfma_f32_16x16x4_f32): f32 streams,
-// bf16 streams whose C is no multiple of 64, and the separable entry points.  Operands enter as
-// they are (x widened, W and the per-token vectors in fp32) and every sum is fp32, so nothing
-// is split or rounded on the way.
+// Thin products at full precision on the matrix cores: f32 streams, bf16 streams whose C is no
+// multiple of 64, the separable entry points, and the projection of few tokens.  Operands enter as
+// they are (x widened, W and the per-token vectors in fp32); the projection sums in fp64
+// (v_mfma_f64_16x16x4_f64), the others in fp32 (v_mfma_f32_16x16x4_f32), so nothing is split or
+// rounded on the way.
 #include "mhcl_common.h"
 #include "mhcl_internal.h"
 #include "mhcl_mfma.h"

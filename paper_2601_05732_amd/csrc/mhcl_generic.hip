@@ -1,7 +1,6 @@
-// Generic kernels of libmhcl: plain fp32 ALU arithmetic, any n in 1..5, bf16
-// or f32 streams.  They serve f32 streams, shapes the MFMA kernels do not
-// cover, and the separable entry points.  Every reduction runs in a fixed
-// order, so results are bitwise reproducible.
+// Stream kernels of libmhcl: plain fp32 arithmetic on bf16 or f32 streams, any n in 1..8 and any C.
+// They are bound by HBM.  Every reduction runs in a fixed order, so results are bitwise
+// reproducible.
 #include "mhcl_common.h"
 #include "mhcl_internal.h"
 

@@ -41,7 +41,7 @@ struct BwdTokenBufs {
   float *gz;      // [gz_rows(d), M+3] sums over a block's tokens of g_z and of the per-group g_z u
 };
 
-// ---- generic (plain ALU) kernels: any n in 1..5, bf16 or f32 streams -----
+// ---- stream kernels: any n in 1..8, bf16 or f32 streams -----
 hipError_t launch_pre(const mhcl_desc &d, const void *x, const float *H_pre, void *h, hipStream_t s);
 hipError_t launch_post(const mhcl_desc &d, const void *x, const void *y, const float *H_res,
                        const float *H_post, void *x_out, hipStream_t s);
