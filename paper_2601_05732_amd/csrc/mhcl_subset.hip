@@ -24,7 +24,7 @@ namespace {
 //     vr   [Tpad][MP32] bf16 hi, lo : vr = r alpha g_z, row per token
 //     vrT  [Tpad/32][MP16][32] bf16 hi, lo : the same, tokens innermost
 //     gzs  [Tpad/64][M+3] f32 : per 64 tokens, the sums of g_z and of the per-group g_z u
-//          (what g_b and g_alpha are summed from), in token order
+//          (what g_b and g_alpha are summed from), added pairwise
 //     Tokens T..Tpad-1 get zero vr so that padded tiles add nothing to g_W.
 //     F16ROWS (the single-kernel wide pass 2): the vr ROWS hold fp16 hi, lo parts of vr / s with
 //     s = max_m |vr_m| of the token (1 if that is 0), so that any gradient scale fits fp16; s
@@ -317,17 +317,16 @@ __global__ __launch_bounds__(kGThreads) void coeffs_group_kernel(
       *reinterpret_cast<u32x4 *>(vrT_lo + off) = lo;
     }
     }
-    // sums over the block's 64 tokens, token order
-    if (tid < M + 3) {
-      float sacc = 0.f;
-      if (tid < M) {
-#pragma unroll 16
-        for (int tk = 0; tk < kGTok; ++tk) sacc += a_s[tk * ld + tid];
-      } else {
-#pragma unroll 16
-        for (int tk = 0; tk < kGTok; ++tk) sacc += t_s[tk * 4 + (tid - M)];
-      }
-      gz_sums[static_cast<int64_t>(blockIdx.x) * (M + 3) + tid] = sacc;
+    // sums over the block's 64 tokens, pairwise: four lanes per column, 16 tokens each (one lane
+    // for all 64 keeps too many loads in flight: 8 us more of 1288 for the n = 5 step)
+    for (int e = tid; e < 4 * (M + 3); e += kGThreads) {
+      const int m = e >> 2, tk0 = 16 * (e & 3);
+      const float *src = m < M ? a_s + tk0 * ld + m : t_s + tk0 * 4 + (m - M);
+      const int step = m < M ? ld : 4;
+      float s = pairwise_sum<16>([&](int tk) { return src[tk * step]; });
+      s += __shfl_xor(s, 1, 64);
+      s += __shfl_xor(s, 2, 64);
+      if ((e & 3) == 0) gz_sums[static_cast<int64_t>(blockIdx.x) * (M + 3) + m] = s;
     }
   }
 }

@@ -466,13 +466,10 @@ __global__ __launch_bounds__(kTokThreads<L>) void token_stage_kernel(TokenIn in,
         }
       }
     }
-    // sums over the block's tokens (zeros past T), in token order, by the last threads
-    for (int m = THREADS - 1 - tid; m < M + 3; m += THREADS) {
-      float s = 0.f;
-#pragma unroll
-      for (int tk = 0; tk < BT; ++tk) s += z_s[tk][m];
-      out.gz_sums[static_cast<int64_t>(blockIdx.x) * (M + 3) + m] = s;
-    }
+    // sums over the block's tokens (zeros past T), pairwise, by the last threads
+    for (int m = THREADS - 1 - tid; m < M + 3; m += THREADS)
+      out.gz_sums[static_cast<int64_t>(blockIdx.x) * (M + 3) + m] =
+          pairwise_sum<BT>([&](int tk) { return z_s[tk][m]; });
   }
 }
 
