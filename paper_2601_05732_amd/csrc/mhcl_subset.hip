@@ -228,8 +228,8 @@ __global__ __launch_bounds__(kGThreads) void coeffs_group_kernel(
       const float uk = ut[kc(kk)];
       const float v = ok ? r * a0 * g : 0.f;
       if (owns(kk)) at[l + 8 * kk] = g;
-      gap[0] += g * (r * uk);
-      dotp += v * uk;
+      gap[0] += ok ? g * (r * uk) : 0.f;   // (selected: uk may be infinite where there is no logit or token)
+      dotp += ok ? v * uk : 0.f;
       vmaxp = fmaxf(vmaxp, fabsf(v));
     }
     if (l < N) {
@@ -254,8 +254,8 @@ __global__ __launch_bounds__(kGThreads) void coeffs_group_kernel(
       at[K + l] = gp;
       at[K + N + l] = gq;
       const float vp = r * a1 * gp, vq = r * a2 * gq;
-      gap[1] = gp * (r * up);
-      gap[2] = gq * (r * uq);
+      gap[1] = live ? gp * (r * up) : 0.f;
+      gap[2] = live ? gq * (r * uq) : 0.f;
       dotp += vp * up + vq * uq;
       vmaxp = fmaxf(vmaxp, fmaxf(fabsf(vp), fabsf(vq)));
     }

@@ -352,7 +352,7 @@ __global__ __launch_bounds__(kTokThreads<L>) void token_stage_kernel(TokenIn in,
           gz[kk] = 0.f;
 #pragma unroll
           for (int i = 0; i < N; ++i) gz[kk] += g[i * N + ((pbits[kk] >> (2 * i)) & 3u)];
-          mean += a[kk] * gz[kk];
+          mean += owns(kk) ? a[kk] * gz[kk] : 0.f;
         }
         mean = group_reduce<L>(mean, Add{});
 #pragma unroll
@@ -386,7 +386,8 @@ __global__ __launch_bounds__(kTokThreads<L>) void token_stage_kernel(TokenIn in,
 #pragma unroll
         for (int c = 0; c < CC; ++c) gz[c] = gh[c] * a[c];
       }
-      // gradient on this lane's gates, vr = r alpha g_z and the sums
+      // gradient on this lane's gates, vr = r alpha g_z and the sums (selected, not multiplied by
+      // zero, where a lane has no logit or a block no token: what stands there may be infinite)
       float dot = 0.f, ga0 = 0.f, ga1 = 0.f, ga2 = 0.f, vmax = 0.f;
 #pragma unroll
       for (int gi = 0; gi < GG; ++gi) {
@@ -396,9 +397,9 @@ __global__ __launch_bounds__(kTokThreads<L>) void token_stage_kernel(TokenIn in,
         const float gzg = !ok ? 0.f : (gt < N ? gg * gate[gi] * (1.f - gate[gi])
                                               : gg * gate[gi] * (1.f - 0.5f * gate[gi]));
         const float v = ok ? r * a_gate[gi] * gzg : 0.f;
-        dot += v * ug[gi];
+        dot += ok ? v * ug[gi] : 0.f;
         vmax = fmaxf(vmax, fabsf(v));
-        const float gag = gzg * (r * ug[gi]);
+        const float gag = ok ? gzg * (r * ug[gi]) : 0.f;
         if (gt < N) ga1 += gag;
         else ga2 += gag;
         if (gt < 2 * N) { z_s[tok][R + gt] = gzg; v_s[tok][R + gt] = v; }
@@ -408,8 +409,8 @@ __global__ __launch_bounds__(kTokThreads<L>) void token_stage_kernel(TokenIn in,
         const bool ok = live && owns(kk);
         if (!ok) gz[kk] = 0.f;
         const float v = ok ? r * a_res * gz[kk] : 0.f;
-        ga0 += gz[kk] * (r * uk[kk]);
-        dot += v * uk[kk];
+        ga0 += ok ? gz[kk] * (r * uk[kk]) : 0.f;
+        dot += ok ? v * uk[kk] : 0.f;
         vmax = fmaxf(vmax, fabsf(v));
         if (owns(kk)) { z_s[tok][logit(kk)] = gz[kk]; v_s[tok][logit(kk)] = v; }
       }
