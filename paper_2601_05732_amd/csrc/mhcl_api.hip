@@ -79,7 +79,7 @@ struct BwdWs {
     sumsq = c.take<float>(parts * T);
     tok.rec = c.take<float>(T * token_rec_floats(n));
     tok.vr = c.take<float>(T * ((M + 15) / 16 * 16));
-    tok.gz = c.take<float>(static_cast<size_t>(gz_rows(d)) * (M + 3));
+    tok.gz = c.take<float>(static_cast<size_t>(gz_rows(d, false)) * (M + 3));
     gH_res = gH_pre = gH_post = nullptr;
     if (need_dots) {
       gH_res = c.take<float>(T * n * n);
@@ -455,7 +455,7 @@ int mhcl_coeffs_bwd(const mhcl_desc *desc, const void *x, const float *W, const 
   MHCL_HIP(launch_gx_fullprec(*desc, M, false, x, W, nullptr, nullptr, w.tok, g_x, nullptr, s));
   MHCL_HIP(launch_gw_fullprec(*desc, M, x, w.tok.vr, w.partials, g_W, s));
   MHCL_HIP(launch_bwd_finish(w.partials, static_cast<size_t>(desc->n) * desc->C * M,
-                             gw_chunks_fullprec(*desc), g_W, w.tok.gz, gz_rows(*desc), M, g_b, g_alpha,
+                             gw_chunks_fullprec(*desc), g_W, w.tok.gz, gz_rows(*desc, false), M, g_b, g_alpha,
                              s));
   return MHCL_OK;
 }
@@ -516,7 +516,7 @@ int mhcl_bwd_fused(const mhcl_desc *desc, const void *x, const void *y, const fl
       MHCL_HIP(launch_bwd_out_gw(*desc, M, x, g_xout, g_h, f, g_x, g_y, g_W, s));
     }
     MHCL_HIP(launch_bwd_finish(f.partials, static_cast<size_t>(desc->n) * desc->C * M,
-                               fast_gw_chunks(*desc), g_W, f.gz, gz_rows(*desc), M, g_b, g_alpha,
+                               fast_gw_chunks(*desc), g_W, f.gz, gz_rows(*desc, true), M, g_b, g_alpha,
                                s));
     return MHCL_OK;
   }
@@ -531,7 +531,7 @@ int mhcl_bwd_fused(const mhcl_desc *desc, const void *x, const void *y, const fl
   }
   MHCL_HIP(launch_gw_fullprec(*desc, M, x, w.tok.vr, w.partials, g_W, s));
   MHCL_HIP(launch_bwd_finish(w.partials, static_cast<size_t>(desc->n) * desc->C * M,
-                             gw_chunks_fullprec(*desc), g_W, w.tok.gz, gz_rows(*desc), M, g_b, g_alpha,
+                             gw_chunks_fullprec(*desc), g_W, w.tok.gz, gz_rows(*desc, false), M, g_b, g_alpha,
                              s));
   return MHCL_OK;
 }

@@ -1805,7 +1805,7 @@ FastBwdWs::FastBwdWs(const mhcl_desc &d, void *ws) {
   gH_pre = c.take<float>(gparts * T * n);
   gH_post = c.take<float>(gparts * T * n);
   cpk = c.take<float>(T * CP);
-  gz = c.take<float>(static_cast<size_t>(gz_rows(d)) * (M + 3));
+  gz = c.take<float>(static_cast<size_t>(gz_rows(d, true)) * (M + 3));
   vr_hi = c.take<uint16_t>(Tpad * MP32);
   vr_lo = c.take<uint16_t>(Tpad * MP32);
   vrT_hi = c.take<uint16_t>(Tpad * MP16);

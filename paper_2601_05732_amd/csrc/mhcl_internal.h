@@ -38,7 +38,7 @@ constexpr int token_rec() { return token_rec_floats(N); }
 struct BwdTokenBufs {
   float *rec;     // [T, token_rec<n>()] H_res | H_pre | H_post | coefx = (r^2 / nC) <vr, u_raw>
   float *vr;      // [T, 16 ceil(M / 16)] r * alpha_g * g_z (the vector multiplied with W and x), zero-padded
-  float *gz;      // [gz_rows(d), M+3] sums over a block's tokens of g_z and of the per-group g_z u
+  float *gz;      // [gz_rows(d, false), M+3] sums over a block's tokens of g_z and of the per-group g_z u
 };
 
 // ---- stream kernels: any n in 1..8, bf16 or f32 streams -----
@@ -77,6 +77,7 @@ hipError_t launch_gx_fullprec(const mhcl_desc &d, int M, bool fused, const void 
 
 // ---- per-token stage of the other forms (n <= 4, Sinkhorn-Knopp) --------------
 bool token_stage_many(const mhcl_desc &d, bool backward);   // the variant for many tokens
+bool sk_token_per_lane(const mhcl_desc &d, bool backward);  // Sinkhorn-Knopp, more tokens still
 hipError_t launch_token_coeffs(const mhcl_desc &d, int parts, const float *u_raw, const float *sumsq,
                                const float *b, const float *alpha, float *H_res, float *H_pre,
                                float *H_post, hipStream_t s);
@@ -88,8 +89,9 @@ hipError_t launch_token_bwd_full(const mhcl_desc &d, int parts, const float *u_r
 // ---- permutation-subset form (run-time table d.perm, n up to 8) --------------
 // eight lanes per token: permutation subsets and the full form at n = 5
 bool coeffs_group_ok(const mhcl_desc &d);
-// rows of the g_z sums that the backward's per-token stage leaves for launch_bwd_finish
-int64_t gz_rows(const mhcl_desc &d);
+// rows of the g_z sums that the per-token stage of the backward (`fast`: of the fast path) leaves
+// for launch_bwd_finish
+int64_t gz_rows(const mhcl_desc &d, bool fast);
 hipError_t launch_coeffs_group(const mhcl_desc &d, int parts, const float *u_raw,
                                const float *sumsq, const float *b, const float *alpha,
                                float *H_res, float *H_pre, float *H_post, hipStream_t s);
@@ -148,7 +150,7 @@ bool fast_bwd_wide(const mhcl_desc &d);   // n >= 5 or a subset: pass 2 split in
 int gw_chunks_fast(const mhcl_desc &d);
 int reduce_parts(const mhcl_desc &d);     // slices that launch_bwd_reduce writes
 struct FastBwdWs {
-  // gz: [gz_rows(d)][M+3] sums of g_z and g_z u over each block's tokens
+  // gz: [gz_rows(d, true)][M+3] sums of g_z and g_z u over each block's tokens
   // wmax_part: partial maxima of |W|; wscale: {scale, 1 / scale} of the fp16 copy of W
   float *u_raw, *sumsq, *gH_res, *gH_pre, *gH_post, *cpk, *gz, *partials, *D, *wmax_part, *wscale;
   uint16_t *vr_hi, *vr_lo, *vrT_hi, *vrT_lo;

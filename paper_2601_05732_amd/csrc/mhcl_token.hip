@@ -485,7 +485,7 @@ hipError_t launch_token_stage(const mhcl_desc &d, const TokenIn &in,
     constexpr int LF = N <= 4 ? 16 : 8;   // lanes per token with few tokens
     auto kern = token_stage_kernel<N, MODE, OUT, LF>;
     int threads = kTokThreads<LF>, per_iter = kSkPerIter<N, MODE, OUT, LF>;
-    if constexpr (N <= 4) {
+    if constexpr (N <= 4 && (MODE == MHCL_RES_LITE || OUT == kOutForward)) {
       if (many) {
         kern = token_stage_kernel<N, MODE, OUT, 4>;
         threads = kTokThreads<4>;
@@ -515,6 +515,263 @@ hipError_t launch_token_stage(const mhcl_desc &d, const TokenIn &in,
   return hipErrorInvalidValue;
 }
 
+// ---------------------------------------------------------------------------
+// Sinkhorn-Knopp with one token per lane, for many tokens.  A group of lanes shortens the chain of one
+// token but repeats its divisions (every lane of a column divides by that column's sum): about 28
+// instructions per iteration in each of 16 lanes at n <= 4 and 90 in each of eight at n = 5, against
+// 24 (n = 1) to 190 (n = 5) in one lane.  Once there are waves enough to hide the chain the count of
+// instructions is what bounds the stage; `sk_token_per_lane` has the line and both sides' times.
+struct SkParams {
+  float alpha_res, alpha_pre, alpha_post, eps;
+  int nC, sk_iters;
+};
+
+// The 2 sk_iters N divisors go to `sums` if that is not null; a = exp(z - max), the input of the
+// iteration; returns r.
+template <int N>
+__device__ __forceinline__ float sk_token(const float *u, float sumsq, const float *b, const SkParams &p,
+                                          float *H_res, float *H_pre, float *H_post, float *a,
+                                          float *sums) {
+  constexpr int R = N * N;
+  const float r = 1.f / sqrtf(sumsq / static_cast<float>(p.nC) + p.eps);
+  float zmax = -INFINITY;
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    a[k] = p.alpha_res * (r * u[k]) + b[k];
+    zmax = fmaxf(zmax, a[k]);
+  }
+#pragma unroll
+  for (int k = 0; k < R; ++k) { a[k] = expf(a[k] - zmax); H_res[k] = a[k]; }
+  for (int it = 0; it < p.sk_iters; ++it) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      float s = 0.f;
+#pragma unroll
+      for (int i = 0; i < N; ++i) s += H_res[i * N + j];
+      const float inv = 1.f / s;
+#pragma unroll
+      for (int i = 0; i < N; ++i) H_res[i * N + j] *= inv;
+      if (sums) sums[(2 * it) * N + j] = s;
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      float s = 0.f;
+#pragma unroll
+      for (int j = 0; j < N; ++j) s += H_res[i * N + j];
+      const float inv = 1.f / s;
+#pragma unroll
+      for (int j = 0; j < N; ++j) H_res[i * N + j] *= inv;
+      if (sums) sums[(2 * it + 1) * N + i] = s;
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    H_pre[j] = sigmoidf(p.alpha_pre * (r * u[R + j]) + b[R + j]);
+    H_post[j] = 2.f * sigmoidf(p.alpha_post * (r * u[R + N + j]) + b[R + N + j]);
+  }
+  return r;
+}
+
+// g_z from the gradients on the coefficients, back through the half steps as in
+// token_stage_kernel.  g and H are used up.
+template <int N>
+__device__ __forceinline__ void sk_token_bwd(float *g, const float *gH_pre, const float *gH_post,
+                                             const float *a, float *H, const float *H_pre,
+                                             const float *H_post, const float *sums, int sk_iters,
+                                             float *g_z) {
+  constexpr int R = N * N;
+  // the divisors of an iteration (private memory: rows, then columns) are fetched one iteration ahead
+  float row[N], col[N], row_next[N], col_next[N];
+  auto fetch = [&](int it, float (&rows)[N], float (&cols)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      cols[i] = sums[(2 * it) * N + i];
+      rows[i] = sums[(2 * it + 1) * N + i];
+    }
+  };
+  fetch(sk_iters - 1, row, col);
+  for (int it = sk_iters - 1; it >= 0; --it) {
+    fetch(it > 0 ? it - 1 : 0, row_next, col_next);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const float inv = 1.f / row[i];
+      float d = 0.f;
+#pragma unroll
+      for (int j = 0; j < N; ++j) d += g[i * N + j] * H[i * N + j];
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        g[i * N + j] = (g[i * N + j] - d) * inv;
+        H[i * N + j] *= row[i];
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const float inv = 1.f / col[j];
+      float d = 0.f;
+#pragma unroll
+      for (int i = 0; i < N; ++i) d += g[i * N + j] * H[i * N + j];
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        g[i * N + j] = (g[i * N + j] - d) * inv;
+        H[i * N + j] *= col[j];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) { row[i] = row_next[i]; col[i] = col_next[i]; }
+  }
+#pragma unroll
+  for (int e = 0; e < R; ++e) g_z[e] = g[e] * a[e];
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    g_z[R + j] = gH_pre[j] * H_pre[j] * (1.f - H_pre[j]);
+    g_z[R + N + j] = gH_post[j] * H_post[j] * (1.f - 0.5f * H_post[j]);
+  }
+}
+
+// the slices of token t's logits and sum of squares, added in order; returns the latter
+template <int M>
+__device__ __forceinline__ float sk_token_logits(const TokenIn &in, int64_t t, float (&u)[M]) {
+  float ssq = in.sumsq[t];
+#pragma unroll
+  for (int m = 0; m < M; ++m) u[m] = in.u_raw[t * M + m];
+  for (int pt = 1; pt < in.parts; ++pt) {
+    ssq += in.sumsq[pt * in.T + t];
+#pragma unroll
+    for (int m = 0; m < M; ++m) u[m] += in.u_raw[(pt * in.T + t) * M + m];
+  }
+  return ssq;
+}
+
+// (blocks of 256: 64 and 128 leave some compute units with a wave more than others, 36 / 44 / 43 us for
+// mhcl_coeffs at n = 4, C = 64, 114688 tokens, 32 iterations)
+constexpr int kSkForwardThreads = 256;
+template <int N>
+__global__ __launch_bounds__(kSkForwardThreads) void sk_coeffs_kernel(TokenIn in, TokenOut out) {
+  constexpr int R = N * N, M = R + 2 * N;
+  const int64_t t = static_cast<int64_t>(blockIdx.x) * kSkForwardThreads + threadIdx.x;
+  if (t >= in.T) return;
+  float u[M], a[R], H[R], Hp[N], Hq[N];
+  const float ssq = sk_token_logits(in, t, u);
+  const SkParams p{in.alpha[0], in.alpha[1], in.alpha[2], in.eps, in.nC, in.sk_iters};
+  sk_token<N>(u, ssq, in.b, p, H, Hp, Hq, a, nullptr);
+#pragma unroll
+  for (int e = 0; e < R; ++e) out.H_res[t * R + e] = H[e];
+#pragma unroll
+  for (int j = 0; j < N; ++j) { out.H_pre[t * N + j] = Hp[j]; out.H_post[t * N + j] = Hq[j]; }
+}
+
+// Outputs as token_stage_kernel<kOutFast>, for one slice of the dot products; one wave per block, the
+// sums over its 64 tokens by a butterfly.
+template <int N>
+__global__ __launch_bounds__(64) void sk_bwd_kernel(TokenIn in, TokenOut out) {
+  constexpr int R = N * N, M = R + 2 * N;
+  constexpr int MP32 = (M + 31) / 32 * 32, MP16 = (M + 15) / 16 * 16;
+  constexpr bool F16ROWS = N == 5;
+  const int64_t t = static_cast<int64_t>(blockIdx.x) * 64 + threadIdx.x;   // up to the next multiple of 64
+  const int64_t blk = t >> 5;
+  const int tin = static_cast<int>(t & 31);
+  const bool live = t < in.T;
+  const int64_t tl = live ? t : in.T - 1;   // (padding lanes go over the last token again and drop it)
+  float u[M], a[R], H[R], Hp[N], Hq[N], gz[M + 3], gr[R], gp[N], gq[N];
+  float sums[2 * kMaxSkIters * N];
+  const float ssq = sk_token_logits(in, tl, u);
+#pragma unroll
+  for (int e = 0; e < R; ++e) gr[e] = in.gH_res[tl * R + e];
+#pragma unroll
+  for (int j = 0; j < N; ++j) { gp[j] = in.gH_pre[tl * N + j]; gq[j] = in.gH_post[tl * N + j]; }
+  const SkParams p{in.alpha[0], in.alpha[1], in.alpha[2], in.eps, in.nC, in.sk_iters};
+  const float r = sk_token<N>(u, ssq, in.b, p, H, Hp, Hq, a, sums);
+  float *rec = out.rec + t * out.rec_ld;
+  if (live) {
+#pragma unroll
+    for (int e = 0; e < R; ++e) rec[e] = H[e];
+#pragma unroll
+    for (int j = 0; j < N; ++j) { rec[R + j] = Hp[j]; rec[R + N + j] = Hq[j]; }
+  }
+  sk_token_bwd<N>(gr, gp, gq, a, H, Hp, Hq, sums, in.sk_iters, gz);
+  auto alpha_of = [&](int m) { return m < R ? p.alpha_res : (m < R + N ? p.alpha_pre : p.alpha_post); };
+  float inv_s = 1.f;
+  if constexpr (F16ROWS) {
+    float vmax = 0.f;
+#pragma unroll
+    for (int m = 0; m < M; ++m) vmax = fmaxf(vmax, fabsf(r * alpha_of(m) * (live ? gz[m] : 0.f)));
+    const float sc = vmax > 0.f ? vmax : 1.f;
+    inv_s = 1.f / sc;
+    if (live) rec[R + 2 * N + 1] = sc;
+  }
+  float ga[3] = {0.f, 0.f, 0.f}, dot = 0.f;
+  u32x4 rows_hi[MP32 / 8], rows_lo[MP32 / 8];   // the token's vr row, eight 16-bit parts per vector
+#pragma unroll
+  for (int v8 = 0; v8 < MP32 / 8; ++v8) {
+    float v[8], vs[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int m = 8 * v8 + e;
+      v[e] = 0.f;
+      if (m < M) {
+        if (!live) gz[m] = 0.f;
+        v[e] = r * alpha_of(m) * gz[m];
+        ga[m < R ? 0 : (m < R + N ? 1 : 2)] += live ? gz[m] * (r * u[m]) : 0.f;
+        dot += v[e] * u[m];
+        if (!live) v[e] = 0.f;
+      }
+      vs[e] = v[e] * inv_s;
+    }
+    u32x4 hi, lo;
+    split8(v, std::false_type{}, hi, lo);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int m = 8 * v8 + e;
+      if (m < MP16) {
+        out.vrT_hi[(blk * MP16 + m) * 32 + tin] = static_cast<uint16_t>(hi[e >> 1] >> (16 * (e & 1)));
+        out.vrT_lo[(blk * MP16 + m) * 32 + tin] = static_cast<uint16_t>(lo[e >> 1] >> (16 * (e & 1)));
+      }
+    }
+    if constexpr (F16ROWS) split8(vs, std::true_type{}, hi, lo);
+    rows_hi[v8] = hi;
+    rows_lo[v8] = lo;
+  }
+#pragma unroll
+  for (int v8 = 0; v8 < MP32 / 8; ++v8) {
+    reinterpret_cast<u32x4 *>(out.vr_hi + t * MP32)[v8] = rows_hi[v8];
+    reinterpret_cast<u32x4 *>(out.vr_lo + t * MP32)[v8] = rows_lo[v8];
+  }
+  if (live) rec[R + 2 * N] = (r * r / static_cast<float>(in.nC)) * dot;
+#pragma unroll
+  for (int g = 0; g < 3; ++g) gz[M + g] = ga[g];
+#pragma unroll
+  for (int m = 0; m < M + 3; ++m) {
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) gz[m] += __shfl_xor(gz[m], off, 64);
+  }
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int m = 0; m < M + 3; ++m) out.gz_sums[static_cast<int64_t>(blockIdx.x) * (M + 3) + m] = gz[m];
+  }
+}
+
+template <bool BWD>
+hipError_t launch_sk_token(const mhcl_desc &d, const TokenIn &in, const TokenOut &out, hipStream_t s) {
+  auto go = [&](auto nn) {
+    constexpr int N = decltype(nn)::value;
+    if constexpr (BWD)
+      hipLaunchKernelGGL(sk_bwd_kernel<N>, dim3(static_cast<unsigned>((d.T + 63) / 64)), dim3(64), 0, s, in, out);
+    else
+      hipLaunchKernelGGL(sk_coeffs_kernel<N>,
+                         dim3(static_cast<unsigned>((d.T + kSkForwardThreads - 1) / kSkForwardThreads)),
+                         dim3(kSkForwardThreads), 0, s, in, out);
+    return hipGetLastError();
+  };
+  switch (d.n) {
+    case 1: return go(std::integral_constant<int, 1>{});
+    case 2: return go(std::integral_constant<int, 2>{});
+    case 3: return go(std::integral_constant<int, 3>{});
+    case 4: return go(std::integral_constant<int, 4>{});
+    case 5: return go(std::integral_constant<int, 5>{});
+  }
+  return hipErrorInvalidValue;
+}
+
 TokenIn token_in(const mhcl_desc &d, int parts, const float *u_raw, const float *sumsq,
                  const float *b, const float *alpha) {
   TokenIn in{};
@@ -534,10 +791,24 @@ bool token_stage_many(const mhcl_desc &d, bool backward) {
   return d.n <= 4 && d.T >= 16384 && !(backward && d.res_mode == MHCL_RES_SK);
 }
 
+// One token per lane from so many token-iterations on (eight iterations' worth is the rest of the stage).
+// Group of lanes / one lane, us per call at C = 64, 20 iterations: mhcl_coeffs n = 4 23.3 / 26.8 at
+// 65536 tokens, 41.2 / 32.4 at 131072; n = 1 13.6 / 16.3 and 18.3 / 13.2; n = 5 18.3 / 22.1 at 16384,
+// 84 / 45 at 131072.  mhcl_bwd_fused n = 1 29.0 / 24.7 at 16384, 103 / 58 at 131072; n = 2 45.8 /
+// 46.4 at 32768, 120 / 85 at 131072; n = 3 70.1 / 72.5 at 49152, 144 / 128 at 131072; n = 4 101 / 109 at
+// 65536, 274 / 263 at 196608; n = 5 112 / 114 at 32768, 344 / 297 at 131072 (with 32 iterations 513 / 329).
+bool sk_token_per_lane(const mhcl_desc &d, bool backward) {
+  constexpr int64_t kForward[] = {0, 1800000, 1500000, 1900000, 2200000, 800000};
+  constexpr int64_t kBackward[] = {0, 450000, 1100000, 1750000, 5500000, 950000};
+  if (d.res_mode != MHCL_RES_SK || d.n < 1 || d.n > 5) return false;
+  return d.T * (d.sk_iters + 8) >= (backward ? kBackward : kForward)[d.n];
+}
+
 // one per block: the blocks cover tokens up to the next multiple of 64, as the readers of vr do
-int64_t gz_rows(const mhcl_desc &d) {
+int64_t gz_rows(const mhcl_desc &d, bool fast) {
   const int64_t blocks64 = (d.T + 63) / 64;
-  return coeffs_group_ok(d) || token_stage_many(d, true) ? blocks64 : 2 * blocks64;
+  if (coeffs_group_ok(d) || token_stage_many(d, true) || (fast && sk_token_per_lane(d, true))) return blocks64;
+  return 2 * blocks64;
 }
 
 hipError_t launch_token_coeffs(const mhcl_desc &d, int parts, const float *u_raw, const float *sumsq,
@@ -545,7 +816,10 @@ hipError_t launch_token_coeffs(const mhcl_desc &d, int parts, const float *u_raw
                                float *H_post, hipStream_t s) {
   TokenOut out{};
   out.H_res = H_res; out.H_pre = H_pre; out.H_post = H_post;
-  return launch_token_stage<kOutForward>(d, token_in(d, parts, u_raw, sumsq, b, alpha), out, s);
+  const TokenIn in = token_in(d, parts, u_raw, sumsq, b, alpha);
+  // (a lane reads its slices one after the other)
+  if (parts < 8 && sk_token_per_lane(d, false)) return launch_sk_token<false>(d, in, out, s);
+  return launch_token_stage<kOutForward>(d, in, out, s);
 }
 
 hipError_t launch_token_bwd_fast(const mhcl_desc &d, const float *b, const float *alpha,
@@ -556,6 +830,10 @@ hipError_t launch_token_bwd_fast(const mhcl_desc &d, const float *b, const float
   out.rec = w.cpk; out.rec_ld = w.CP;
   out.vr_hi = w.vr_hi; out.vr_lo = w.vr_lo; out.vrT_hi = w.vrT_hi; out.vrT_lo = w.vrT_lo;
   out.gz_sums = w.gz;
+  if (sk_token_per_lane(d, true)) {
+    if (w.gparts != 1) return hipErrorInvalidValue;   // (more only up to 8192 tokens)
+    return launch_sk_token<true>(d, in, out, s);
+  }
   return launch_token_stage<kOutFast>(d, in, out, s);
 }
 
