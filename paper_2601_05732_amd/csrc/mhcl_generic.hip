@@ -50,16 +50,38 @@ __device__ __forceinline__ void block_sum(float (&v)[CNT], float *red /* [WAVES 
   __syncthreads();
 }
 
-// The kernels that take one block per token: as many waves as a row of C has 16-byte pieces for, at
-// most four (with 256 threads always, half of them idled at C = 1024: post_bwd_kernel 46 us for 5003
-// tokens of n = 4 in bf16, with two waves 34).
-template <typename F>
-hipError_t dispatch_waves(int C, int vec, F &&f) {
+// The kernels that take one block per token, W: the wave counts a kernel is built for
+template <int... W, typename F>
+hipError_t dispatch_waves(std::integer_sequence<int, W...>, int waves, F &&f) {
+  hipError_t e = hipErrorInvalidValue;
+  ((waves == W ? (void)(e = f(std::integral_constant<int, W>{})) : (void)0), ...);
+  return e;
+}
+// as many waves as a row of C has 16-byte pieces for, at most four
+int waves_that_fit(int C, int vec) {
   const int pieces = C / vec;
-  if (pieces <= 64) return f(std::integral_constant<int, 1>{});
-  if (pieces <= 128) return f(std::integral_constant<int, 2>{});
-  if (pieces <= 192) return f(std::integral_constant<int, 3>{});
-  return f(std::integral_constant<int, 4>{});
+  return pieces <= 64 ? 1 : (pieces <= 128 ? 2 : (pieces <= 192 ? 3 : 4));
+}
+// post_bwd_kernel: waves that fit, against four always (idle waves take registers and wait at the sums;
+// us per call, four / as many as fit): n = 4, C = 64, 4096 tokens 30.1 / 11.6, C = 1024, 32768 tokens 233 /
+// 165, n = 8, f32, C = 768 759 / 584.  Four where all blocks are resident at once anyway (n = 8, C = 64,
+// 512 tokens 20.3 / 22.4, n = 5 10.3 / 11.3), and where HBM bounds the kernel and smaller blocks only
+// spread its rows (n = 2, C = 1024, 65536 tokens 182 / 193; n = 5, f32, C = 768, 32768 tokens 313 / 340).
+int post_bwd_waves(const mhcl_desc &d, int vec) {
+  const int fit = waves_that_fit(d.C, vec);
+  const int64_t resident = 256 * (d.n >= 7 ? 2 : (d.n >= 5 ? 3 : 4));
+  if (d.T <= resident ||
+      (fit == 2 && d.n <= (vec == 4 ? 3 : 2) && d.T > 16384) ||
+      (fit == 3 && vec == 4 && d.n <= 5)) return 4;
+  return fit;
+}
+// pre_bwd_kernel: one wave likewise (n = 4, C = 64, 32768 tokens 60.4 / 24.1; n = 8, 1280 tokens 7.3 / 8.2),
+// two for bf16 rows while the streams stay in cache (n = 8, C = 768, 2048 tokens 17.7 / 14.2; n = 4, C = 768,
+// 65536 tokens 228 / 246), three never (n = 2, f32, C = 768, 16384 tokens 43.9 / 45.2)
+int pre_bwd_waves(const mhcl_desc &d, int vec) {
+  const int fit = waves_that_fit(d.C, vec);
+  if (d.T <= 1536) return 4;
+  return fit == 1 || (fit == 2 && vec == 8 && d.T <= 16384) ? fit : 4;
 }
 
 // ------------------------------------------------------------ stream mixing
@@ -363,7 +385,9 @@ hipError_t launch_post_bwd(const mhcl_desc &d, const void *x, const void *y, con
     return dispatch_n(d.n, [&](auto nn) {
       using IO = decltype(io);
       constexpr int N = decltype(nn)::value;
-      return dispatch_waves(d.C, IO::kVec, [&](auto ww) {
+      using Waves = std::conditional_t<(IO::kVec == 4 && N <= 5), std::integer_sequence<int, 1, 2, 4>,
+                                       std::integer_sequence<int, 1, 2, 3, 4>>;
+      return dispatch_waves(Waves{}, post_bwd_waves(d, IO::kVec), [&](auto ww) {
         constexpr int W = decltype(ww)::value;
         hipLaunchKernelGGL((post_bwd_kernel<IO, N, W>), dim3(static_cast<unsigned>(d.T)), dim3(64 * W), 0, s,
                            x, y, H_res, H_post, g_xout, g_x, g_y, g_H_res, g_H_post, d.C);
@@ -379,7 +403,9 @@ hipError_t launch_pre_bwd(const mhcl_desc &d, const void *x, const float *H_pre,
     return dispatch_n(d.n, [&](auto nn) {
       using IO = decltype(io);
       constexpr int N = decltype(nn)::value;
-      return dispatch_waves(d.C, IO::kVec, [&](auto ww) {
+      using Waves = std::conditional_t<IO::kVec == 8, std::integer_sequence<int, 1, 2, 4>,
+                                       std::integer_sequence<int, 1, 4>>;
+      return dispatch_waves(Waves{}, pre_bwd_waves(d, IO::kVec), [&](auto ww) {
         constexpr int W = decltype(ww)::value;
         hipLaunchKernelGGL((pre_bwd_kernel<IO, N, W>), dim3(static_cast<unsigned>(d.T)), dim3(64 * W), 0, s,
                            x, H_pre, g_h, g_x, g_H_pre, d.C);
@@ -396,7 +422,7 @@ hipError_t launch_bwd_dots(const mhcl_desc &d, const void *x, const void *y, con
     return dispatch_n(d.n, [&](auto nn) {
       using IO = decltype(io);
       constexpr int N = decltype(nn)::value;
-      return dispatch_waves(d.C, IO::kVec, [&](auto ww) {
+      return dispatch_waves(std::integer_sequence<int, 1, 2, 3, 4>{}, waves_that_fit(d.C, IO::kVec), [&](auto ww) {
         constexpr int W = decltype(ww)::value;
         hipLaunchKernelGGL((bwd_dots_kernel<IO, N, W>), dim3(static_cast<unsigned>(d.T)), dim3(64 * W), 0, s,
                            x, y, g_xout, g_h, g_H_res, g_H_post, g_H_pre, d.C);
