@@ -12,15 +12,17 @@ namespace {
 // z[t][m] = alpha_g (r u_raw[t][m]) + b[m], the same expression the coefficient
 // kernels evaluate; spread[t] = max - min of the residual logits, which is
 // log(1/nu) of exp(z_res) (every entry of exp(.) is positive).
-// A block takes 32 tokens, whose logits are one contiguous run of u_raw and of z; the run is
-// kept in LDS, where eight lanes per token look for its extremes.  (One thread per token, each of
-// its logits a strided load and store, took 17.5 us for 8192 tokens of 24 logits; this takes 6.3.)
-constexpr int kLogitTok = 32, kLogitThreads = 256;
+// A block takes 256 / LANES tokens, whose logits are one contiguous run of u_raw and of z; the run is
+// kept in LDS, where LANES lanes per token look for its extremes.  (One thread per token, each of
+// its logits a strided load and store, took 17.5 us for 8192 tokens of 24 logits; eight lanes 6.3.)
+constexpr int kLogitThreads = 256;
+template <int LANES>
 __global__ __launch_bounds__(kLogitThreads) void logits_kernel(
     const float *__restrict__ u_raw, const float *__restrict__ sumsq, int parts,
     const float *__restrict__ b, const float *__restrict__ alpha, int nC, float eps, int64_t T,
     int M, int R, int n, float *__restrict__ z, float *__restrict__ spread) {
-  extern __shared__ float z_s[];   // [32][M | 1]
+  constexpr int kLogitTok = kLogitThreads / LANES;
+  extern __shared__ float z_s[];   // [kLogitTok][M | 1]
   __shared__ float r_s[kLogitTok];
   const int ld = M | 1;
   const int64_t t0 = static_cast<int64_t>(blockIdx.x) * kLogitTok;
@@ -44,16 +46,16 @@ __global__ __launch_bounds__(kLogitThreads) void logits_kernel(
   }
   if (spread == nullptr) return;
   __syncthreads();
-  const int tk = threadIdx.x >> 3, l = threadIdx.x & 7;
+  const int tk = threadIdx.x / LANES, l = threadIdx.x % LANES;
   float zmax = -INFINITY, zmin = INFINITY;
   if (tk < live) {
-    for (int m = l; m < R; m += 8) {
+    for (int m = l; m < R; m += LANES) {
       zmax = fmaxf(zmax, z_s[tk * ld + m]);
       zmin = fminf(zmin, z_s[tk * ld + m]);
     }
   }
 #pragma unroll
-  for (int off = 1; off < 8; off <<= 1) {
+  for (int off = 1; off < LANES; off <<= 1) {
     zmax = fmaxf(zmax, __shfl_xor(zmax, off, 64));
     zmin = fminf(zmin, __shfl_xor(zmin, off, 64));
   }
@@ -134,10 +136,16 @@ inline unsigned blocks128(int64_t items) { return static_cast<unsigned>((items +
 hipError_t launch_logits(const mhcl_desc &d, int M, int parts, const float *u_raw,
                          const float *sumsq, const float *b, const float *alpha, float *z,
                          float *spread, hipStream_t s) {
-  hipLaunchKernelGGL(logits_kernel, dim3(static_cast<unsigned>((d.T + kLogitTok - 1) / kLogitTok)),
-                     dim3(kLogitThreads), kLogitTok * (M | 1) * sizeof(float), s, u_raw, sumsq, parts, b,
-                     alpha, d.n * d.C, d.eps, d.T, M, M - 2 * d.n, d.n, z, spread);
-  return hipGetLastError();
+  auto go = [&](auto lanes) {
+    constexpr int L = decltype(lanes)::value, kTok = kLogitThreads / L;
+    hipLaunchKernelGGL(logits_kernel<L>, dim3(static_cast<unsigned>((d.T + kTok - 1) / kTok)),
+                       dim3(kLogitThreads), kTok * (M | 1) * sizeof(float), s, u_raw, sumsq, parts, b,
+                       alpha, d.n * d.C, d.eps, d.T, M, M - 2 * d.n, d.n, z, spread);
+    return hipGetLastError();
+  };
+  // few logits of many tokens leave seven of eight lanes idle at the extremes (mhcl_logits at C = 64,
+  // eight / one: M = 3, 262144 tokens 22.7 / 17.4 us; M = 15 35.6 / 32.6, 65536 tokens 13.2 / 15.8)
+  return M <= 16 && d.T >= 131072 ? go(std::integral_constant<int, 1>{}) : go(std::integral_constant<int, 8>{});
 }
 
 hipError_t launch_ds_chain(int n, int L, int64_t T, const float *H, float *colsum, float *l1,
