@@ -63,13 +63,17 @@ struct ProjCfg {
   // four-wave blocks (0.23 -> 0.21 ms at n = 4, C = 4096)
   static constexpr int WAVES = 8;
   static constexpr int kThreads = 64 * WAVES;
+  // one logit tile: three blocks per CU hide the start of short rows (n = 1, C = 64, 2^20 tokens: with two,
+  // which two W tiles ahead leave room for, 49 us, with three 44)
+  static constexpr int kAhead = NT == 1 ? 1 : 2;
+  static constexpr int kMinWaves = NT == 1 ? 6 : 1;            // per SIMD
   static constexpr int kTokens = 16 * WAVES * TG;              // tokens per block
   static constexpr int kChunkVec = KC * NT * 2 * 64;           // u32x4 per chunk
   static constexpr int kLdsBytes = 2 * kChunkVec * 16;
 };
 
 template <int NT, bool DIRECT>
-__global__ __launch_bounds__(ProjCfg<NT>::kThreads, 1) void proj_mfma_kernel(const uint16_t *__restrict__ x,
+__global__ __launch_bounds__(ProjCfg<NT>::kThreads, ProjCfg<NT>::kMinWaves) void proj_mfma_kernel(const uint16_t *__restrict__ x,
                                                            const u32x4 *__restrict__ Wp,
                                                            const float *__restrict__ W, int K,
                                                            int M, int64_t T,
@@ -189,7 +193,7 @@ __global__ __launch_bounds__(ProjCfg<NT>::kThreads, 1) void proj_mfma_kernel(con
   // per SIMD in step the matrix cores then wait for LDS at every tile (mhcl_coeffs at n = 5,
   // C = 2560: 137 -> 123 us at 4096 tokens, 279 -> 262 at 32768; n = 4, C = 4096, 32768 tokens
   // 200 -> 191; three or four tiles ahead: the same).
-  constexpr int kTiles = KC * NT, kAhead = 2;
+  constexpr int kTiles = KC * NT, kAhead = Cfg::kAhead;
   auto compute = [&](const u32x4 (&av)[TG][KC], int buf, int c, auto tail) {
     const u32x4 *wb = lds + buf * Cfg::kChunkVec + lane;
     u32x4 w[kAhead + 1][2];
