@@ -77,7 +77,7 @@ hipError_t launch_gx_fullprec(const mhcl_desc &d, int M, bool fused, const void 
 
 // ---- per-token stage of the other forms (n <= 4, Sinkhorn-Knopp) --------------
 bool token_stage_many(const mhcl_desc &d, bool backward);   // the variant for many tokens
-bool sk_token_per_lane(const mhcl_desc &d, bool backward);  // Sinkhorn-Knopp, more tokens still
+bool token_per_lane(const mhcl_desc &d, bool backward);     // more tokens still
 hipError_t launch_token_coeffs(const mhcl_desc &d, int parts, const float *u_raw, const float *sumsq,
                                const float *b, const float *alpha, float *H_res, float *H_pre,
                                float *H_post, hipStream_t s);

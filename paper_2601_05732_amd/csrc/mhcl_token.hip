@@ -516,20 +516,59 @@ hipError_t launch_token_stage(const mhcl_desc &d, const TokenIn &in,
 }
 
 // ---------------------------------------------------------------------------
-// Sinkhorn-Knopp with one token per lane, for many tokens.  A group of lanes shortens the chain of one
+// One token per lane, for many tokens.  In the Sinkhorn-Knopp form a group of lanes shortens the chain of one
 // token but repeats its divisions (every lane of a column divides by that column's sum): about 28
 // instructions per iteration in each of 16 lanes at n <= 4 and 90 in each of eight at n = 5, against
 // 24 (n = 1) to 190 (n = 5) in one lane.  Once there are waves enough to hide the chain the count of
-// instructions is what bounds the stage; `sk_token_per_lane` has the line and both sides' times.
-struct SkParams {
+// instructions is what bounds the stage; so it is, with far more tokens, in the forward of the permutation
+// form.  `token_per_lane` has the lines and both sides' times.
+struct LaneParams {
   float alpha_res, alpha_pre, alpha_post, eps;
   int nC, sk_iters;
 };
 
-// The 2 sk_iters N divisors go to `sums` if that is not null; a = exp(z - max), the input of the
+template <int N>
+__device__ __forceinline__ void lane_gates(const float *u, float r, const float *b, const LaneParams &p,
+                                           float *H_pre, float *H_post) {
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    H_pre[j] = sigmoidf(p.alpha_pre * (r * u[j]) + b[j]);
+    H_post[j] = 2.f * sigmoidf(p.alpha_post * (r * u[N + j]) + b[N + j]);
+  }
+}
+
+// a weight into the entries of permutation K
+template <int N, int K, int... I>
+__device__ __forceinline__ void add_perm(float w, float *H, std::integer_sequence<int, I...>) {
+  ((H[std::integral_constant<int, I * N + Perm<N>::tab.s[K][I]>::value] += w), ...);
+}
+// softmax over all N! logits, a = its weights; H_res = sum_k a_k P_k, k ascending
+template <int N, int... K>
+__device__ __forceinline__ void lite_token(const float *u, float sumsq, const float *b,
+                                           const LaneParams &p, float *H_res, float *H_pre,
+                                           float *H_post, float *a, std::integer_sequence<int, K...>) {
+  constexpr int R = sizeof...(K);
+  const float r = 1.f / sqrtf(sumsq / static_cast<float>(p.nC) + p.eps);
+  float zmax = -INFINITY, s = 0.f;
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    a[k] = p.alpha_res * (r * u[k]) + b[k];
+    zmax = fmaxf(zmax, a[k]);
+  }
+#pragma unroll
+  for (int k = 0; k < R; ++k) { a[k] = expf(a[k] - zmax); s += a[k]; }
+#pragma unroll
+  for (int k = 0; k < R; ++k) a[k] = a[k] / s;
+#pragma unroll
+  for (int e = 0; e < N * N; ++e) H_res[e] = 0.f;
+  (add_perm<N, K>(a[K], H_res, std::make_integer_sequence<int, N>{}), ...);
+  lane_gates<N>(u + R, r, b + R, p, H_pre, H_post);
+}
+
+// Sinkhorn-Knopp: the 2 sk_iters N divisors go to `sums` if that is not null; a = exp(z - max), the input of the
 // iteration; returns r.
 template <int N>
-__device__ __forceinline__ float sk_token(const float *u, float sumsq, const float *b, const SkParams &p,
+__device__ __forceinline__ float sk_token(const float *u, float sumsq, const float *b, const LaneParams &p,
                                           float *H_res, float *H_pre, float *H_post, float *a,
                                           float *sums) {
   constexpr int R = N * N;
@@ -564,11 +603,7 @@ __device__ __forceinline__ float sk_token(const float *u, float sumsq, const flo
       if (sums) sums[(2 * it + 1) * N + i] = s;
     }
   }
-#pragma unroll
-  for (int j = 0; j < N; ++j) {
-    H_pre[j] = sigmoidf(p.alpha_pre * (r * u[R + j]) + b[R + j]);
-    H_post[j] = 2.f * sigmoidf(p.alpha_post * (r * u[R + N + j]) + b[R + N + j]);
-  }
+  lane_gates<N>(u + R, r, b + R, p, H_pre, H_post);
   return r;
 }
 
@@ -630,7 +665,7 @@ __device__ __forceinline__ void sk_token_bwd(float *g, const float *gH_pre, cons
 
 // the slices of token t's logits and sum of squares, added in order; returns the latter
 template <int M>
-__device__ __forceinline__ float sk_token_logits(const TokenIn &in, int64_t t, float (&u)[M]) {
+__device__ __forceinline__ float lane_logits(const TokenIn &in, int64_t t, float (&u)[M]) {
   float ssq = in.sumsq[t];
 #pragma unroll
   for (int m = 0; m < M; ++m) u[m] = in.u_raw[t * M + m];
@@ -644,18 +679,21 @@ __device__ __forceinline__ float sk_token_logits(const TokenIn &in, int64_t t, f
 
 // (blocks of 256: 64 and 128 leave some compute units with a wave more than others, 36 / 44 / 43 us for
 // mhcl_coeffs at n = 4, C = 64, 114688 tokens, 32 iterations)
-constexpr int kSkForwardThreads = 256;
-template <int N>
-__global__ __launch_bounds__(kSkForwardThreads) void sk_coeffs_kernel(TokenIn in, TokenOut out) {
-  constexpr int R = N * N, M = R + 2 * N;
-  const int64_t t = static_cast<int64_t>(blockIdx.x) * kSkForwardThreads + threadIdx.x;
+constexpr int kLaneThreads = 256;
+template <int N, int MODE>
+__global__ __launch_bounds__(kLaneThreads) void lane_coeffs_kernel(TokenIn in, TokenOut out) {
+  constexpr int R = Dims<N, MODE>::R, M = Dims<N, MODE>::M, NN = N * N;
+  const int64_t t = static_cast<int64_t>(blockIdx.x) * kLaneThreads + threadIdx.x;
   if (t >= in.T) return;
-  float u[M], a[R], H[R], Hp[N], Hq[N];
-  const float ssq = sk_token_logits(in, t, u);
-  const SkParams p{in.alpha[0], in.alpha[1], in.alpha[2], in.eps, in.nC, in.sk_iters};
-  sk_token<N>(u, ssq, in.b, p, H, Hp, Hq, a, nullptr);
+  float u[M], a[R], H[NN], Hp[N], Hq[N];
+  const float ssq = lane_logits(in, t, u);
+  const LaneParams p{in.alpha[0], in.alpha[1], in.alpha[2], in.eps, in.nC, in.sk_iters};
+  if constexpr (MODE == MHCL_RES_LITE)
+    lite_token<N>(u, ssq, in.b, p, H, Hp, Hq, a, std::make_integer_sequence<int, R>{});
+  else
+    sk_token<N>(u, ssq, in.b, p, H, Hp, Hq, a, nullptr);
 #pragma unroll
-  for (int e = 0; e < R; ++e) out.H_res[t * R + e] = H[e];
+  for (int e = 0; e < NN; ++e) out.H_res[t * NN + e] = H[e];
 #pragma unroll
   for (int j = 0; j < N; ++j) { out.H_pre[t * N + j] = Hp[j]; out.H_post[t * N + j] = Hq[j]; }
 }
@@ -674,12 +712,12 @@ __global__ __launch_bounds__(64) void sk_bwd_kernel(TokenIn in, TokenOut out) {
   const int64_t tl = live ? t : in.T - 1;   // (padding lanes go over the last token again and drop it)
   float u[M], a[R], H[R], Hp[N], Hq[N], gz[M + 3], gr[R], gp[N], gq[N];
   float sums[2 * kMaxSkIters * N];
-  const float ssq = sk_token_logits(in, tl, u);
+  const float ssq = lane_logits(in, tl, u);
 #pragma unroll
   for (int e = 0; e < R; ++e) gr[e] = in.gH_res[tl * R + e];
 #pragma unroll
   for (int j = 0; j < N; ++j) { gp[j] = in.gH_pre[tl * N + j]; gq[j] = in.gH_post[tl * N + j]; }
-  const SkParams p{in.alpha[0], in.alpha[1], in.alpha[2], in.eps, in.nC, in.sk_iters};
+  const LaneParams p{in.alpha[0], in.alpha[1], in.alpha[2], in.eps, in.nC, in.sk_iters};
   const float r = sk_token<N>(u, ssq, in.b, p, H, Hp, Hq, a, sums);
   float *rec = out.rec + t * out.rec_ld;
   if (live) {
@@ -750,16 +788,30 @@ __global__ __launch_bounds__(64) void sk_bwd_kernel(TokenIn in, TokenOut out) {
   }
 }
 
-template <bool BWD>
-hipError_t launch_sk_token(const mhcl_desc &d, const TokenIn &in, const TokenOut &out, hipStream_t s) {
+hipError_t launch_lane_coeffs(const mhcl_desc &d, const TokenIn &in, const TokenOut &out, hipStream_t s) {
+  auto go = [&](auto nn, auto mm) {
+    hipLaunchKernelGGL((lane_coeffs_kernel<decltype(nn)::value, decltype(mm)::value>),
+                       dim3(static_cast<unsigned>((d.T + kLaneThreads - 1) / kLaneThreads)),
+                       dim3(kLaneThreads), 0, s, in, out);
+    return hipGetLastError();
+  };
+  using L = std::integral_constant<int, MHCL_RES_LITE>;
+  using S = std::integral_constant<int, MHCL_RES_SK>;
+  const bool lite = d.res_mode == MHCL_RES_LITE;
+  switch (d.n) {
+    case 1: return lite ? go(std::integral_constant<int, 1>{}, L{}) : go(std::integral_constant<int, 1>{}, S{});
+    case 2: return lite ? go(std::integral_constant<int, 2>{}, L{}) : go(std::integral_constant<int, 2>{}, S{});
+    case 3: return lite ? go(std::integral_constant<int, 3>{}, L{}) : go(std::integral_constant<int, 3>{}, S{});
+    case 4: return lite ? go(std::integral_constant<int, 4>{}, L{}) : go(std::integral_constant<int, 4>{}, S{});
+    case 5: return lite ? hipErrorInvalidValue : go(std::integral_constant<int, 5>{}, S{});
+  }
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_sk_bwd(const mhcl_desc &d, const TokenIn &in, const TokenOut &out, hipStream_t s) {
   auto go = [&](auto nn) {
-    constexpr int N = decltype(nn)::value;
-    if constexpr (BWD)
-      hipLaunchKernelGGL(sk_bwd_kernel<N>, dim3(static_cast<unsigned>((d.T + 63) / 64)), dim3(64), 0, s, in, out);
-    else
-      hipLaunchKernelGGL(sk_coeffs_kernel<N>,
-                         dim3(static_cast<unsigned>((d.T + kSkForwardThreads - 1) / kSkForwardThreads)),
-                         dim3(kSkForwardThreads), 0, s, in, out);
+    hipLaunchKernelGGL(sk_bwd_kernel<decltype(nn)::value>, dim3(static_cast<unsigned>((d.T + 63) / 64)),
+                       dim3(64), 0, s, in, out);
     return hipGetLastError();
   };
   switch (d.n) {
@@ -797,17 +849,20 @@ bool token_stage_many(const mhcl_desc &d, bool backward) {
 // 84 / 45 at 131072.  mhcl_bwd_fused n = 1 29.0 / 24.7 at 16384, 103 / 58 at 131072; n = 2 45.8 /
 // 46.4 at 32768, 120 / 85 at 131072; n = 3 70.1 / 72.5 at 49152, 144 / 128 at 131072; n = 4 101 / 109 at
 // 65536, 274 / 263 at 196608; n = 5 112 / 114 at 32768, 344 / 297 at 131072 (with 32 iterations 513 / 329).
-bool sk_token_per_lane(const mhcl_desc &d, bool backward) {
+// Permutation form, forward, 2^20 tokens of C = 64, the stage alone: n = 1 18.7 / 7.9 us, n = 4 93 / 68 (equal near 200000).
+bool token_per_lane(const mhcl_desc &d, bool backward) {
   constexpr int64_t kForward[] = {0, 1800000, 1500000, 1900000, 2200000, 800000};
   constexpr int64_t kBackward[] = {0, 450000, 1100000, 1750000, 5500000, 950000};
-  if (d.res_mode != MHCL_RES_SK || d.n < 1 || d.n > 5) return false;
+  if (d.n < 1 || d.n > 5) return false;
+  if (d.res_mode == MHCL_RES_LITE) return d.n <= 4 && !backward && d.T >= 200000;
+  if (d.res_mode != MHCL_RES_SK) return false;
   return d.T * (d.sk_iters + 8) >= (backward ? kBackward : kForward)[d.n];
 }
 
 // one per block: the blocks cover tokens up to the next multiple of 64, as the readers of vr do
 int64_t gz_rows(const mhcl_desc &d, bool fast) {
   const int64_t blocks64 = (d.T + 63) / 64;
-  if (coeffs_group_ok(d) || token_stage_many(d, true) || (fast && sk_token_per_lane(d, true))) return blocks64;
+  if (coeffs_group_ok(d) || token_stage_many(d, true) || (fast && token_per_lane(d, true))) return blocks64;
   return 2 * blocks64;
 }
 
@@ -818,7 +873,7 @@ hipError_t launch_token_coeffs(const mhcl_desc &d, int parts, const float *u_raw
   out.H_res = H_res; out.H_pre = H_pre; out.H_post = H_post;
   const TokenIn in = token_in(d, parts, u_raw, sumsq, b, alpha);
   // (a lane reads its slices one after the other)
-  if (parts < 8 && sk_token_per_lane(d, false)) return launch_sk_token<false>(d, in, out, s);
+  if (parts < 8 && token_per_lane(d, false)) return launch_lane_coeffs(d, in, out, s);
   return launch_token_stage<kOutForward>(d, in, out, s);
 }
 
@@ -830,9 +885,9 @@ hipError_t launch_token_bwd_fast(const mhcl_desc &d, const float *b, const float
   out.rec = w.cpk; out.rec_ld = w.CP;
   out.vr_hi = w.vr_hi; out.vr_lo = w.vr_lo; out.vrT_hi = w.vrT_hi; out.vrT_lo = w.vrT_lo;
   out.gz_sums = w.gz;
-  if (sk_token_per_lane(d, true)) {
+  if (token_per_lane(d, true)) {
     if (w.gparts != 1) return hipErrorInvalidValue;   // (more only up to 8192 tokens)
-    return launch_sk_token<true>(d, in, out, s);
+    return launch_sk_bwd(d, in, out, s);
   }
   return launch_token_stage<kOutFast>(d, in, out, s);
 }
