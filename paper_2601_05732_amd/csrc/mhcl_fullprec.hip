@@ -91,13 +91,15 @@ struct Piece<F32, 4> {
 // 23; one thread per logit and eighth of the row, fp64 on the vector units, took 145).
 constexpr int kProjWaves = 8;
 
-template <typename IO, int NT>
-__global__ __launch_bounds__(64 * kProjWaves, 1) void proj_fullprec_kernel(
+// WAVES == 1: rows of one or two steps, whose other waves would only take part in the sums (n = 2, C = 8,
+// K = 126, bf16, 131072 tokens: 261 us for mhcl_coeffs with eight waves, 97 with one).
+template <typename IO, int NT, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, 1) void proj_fullprec_kernel(
     const void *__restrict__ x, const float *__restrict__ W, int nC, int M, int64_t T,
     int steps_per_part, float *__restrict__ u_raw, float *__restrict__ sumsq) {
   constexpr int V = IO::kVec;
-  __shared__ double red[2][kProjWaves][4][64];
-  __shared__ double red_ss[kProjWaves][16];
+  __shared__ double red[2][WAVES][4][64];
+  __shared__ double red_ss[WAVES][16];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r = lane & 15, q = lane >> 4;
   const int64_t t0 = static_cast<int64_t>(blockIdx.x) * 16;
@@ -147,19 +149,30 @@ __global__ __launch_bounds__(64 * kProjWaves, 1) void proj_fullprec_kernel(
     In a, b;
     int s = s0 + wave;
     load(a, s < s1 ? s : s1 - 1);
-    for (; s + kProjWaves < s1; s += 2 * kProjWaves) {
-      load(b, s + kProjWaves);
+    for (; s + WAVES < s1; s += 2 * WAVES) {
+      load(b, s + WAVES);
       __builtin_amdgcn_sched_barrier(0);
       compute(a, s);
-      load(a, s + 2 * kProjWaves < s1 ? s + 2 * kProjWaves : s1 - 1);
+      load(a, s + 2 * WAVES < s1 ? s + 2 * WAVES : s1 - 1);
       __builtin_amdgcn_sched_barrier(0);
-      compute(b, s + kProjWaves);
+      compute(b, s + WAVES);
     }
     if (s < s1) compute(a, s);
   }
 
   ss += __shfl_xor(ss, 16, 64);   // the four lanes of a token
   ss += __shfl_xor(ss, 32, 64);
+  if constexpr (WAVES == 1) {
+    if (q == 0 && t0 + r < T) sumsq[blockIdx.y * T + t0 + r] = static_cast<float>(ss);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int64_t t = t0 + 4 * i + q;   // (fp64 tiles hold rows 4 i + q)
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+        if (t < T && 16 * j + r < M) u_raw[(blockIdx.y * T + t) * M + 16 * j + r] = static_cast<float>(acc[j][i]);
+    }
+    return;
+  }
   if (q == 0) red_ss[wave][r] = ss;
   // the waves' sums, two logit tiles at a time, in wave order
 #pragma unroll
@@ -176,7 +189,7 @@ __global__ __launch_bounds__(64 * kProjWaves, 1) void proj_fullprec_kernel(
     if (base + j < NT) {
       double sum = red[j][0][i][lane];
 #pragma unroll
-      for (int w = 1; w < kProjWaves; ++w) sum += red[j][w][i][lane];
+      for (int w = 1; w < WAVES; ++w) sum += red[j][w][i][lane];
       // fp64 tiles hold rows 4 i + q: token 4 i + q, logit 16 (base + j) + r
       const int64_t t = t0 + 4 * i + q;
       const int m = 16 * (base + j) + r;
@@ -186,7 +199,7 @@ __global__ __launch_bounds__(64 * kProjWaves, 1) void proj_fullprec_kernel(
   if (threadIdx.x < 16 && t0 + threadIdx.x < T) {   // (red_ss was complete at the barriers above)
     double sum = red_ss[0][threadIdx.x];
 #pragma unroll
-    for (int w = 1; w < kProjWaves; ++w) sum += red_ss[w][threadIdx.x];
+    for (int w = 1; w < WAVES; ++w) sum += red_ss[w][threadIdx.x];
     sumsq[blockIdx.y * T + t0 + threadIdx.x] = static_cast<float>(sum);
   }
 }
@@ -457,8 +470,16 @@ hipError_t launch_proj_fullprec(const mhcl_desc &d, int M, const void *x, const 
   const dim3 grid(static_cast<unsigned>((d.T + 15) / 16), parts);
   return dispatch_io(d.io_dtype, [&](auto io) {
     return dispatch_tiles(logit_tiles(M), [&](auto nt) {
-      hipLaunchKernelGGL((proj_fullprec_kernel<decltype(io), decltype(nt)::value>), grid,
-                         dim3(64 * kProjWaves), 0, s, x, W, nC, M, d.T, spp, u_raw, sumsq);
+      constexpr int NT = decltype(nt)::value;
+      auto kern = proj_fullprec_kernel<decltype(io), NT, kProjWaves>;
+      int waves = kProjWaves;
+      if constexpr (NT >= 4) {   // (with fewer tiles the sums are short)
+        if (nsteps <= 2) {
+          kern = proj_fullprec_kernel<decltype(io), NT, 1>;
+          waves = 1;
+        }
+      }
+      hipLaunchKernelGGL(kern, grid, dim3(64 * waves), 0, s, x, W, nC, M, d.T, spp, u_raw, sumsq);
       return hipGetLastError();
     });
   });
