@@ -117,6 +117,12 @@ int mhcl_validate(const mhcl_desc *desc);
 int32_t mhcl_logit_count(const mhcl_desc *desc);
 
 /* Bytes of workspace `op` needs for `desc`; 0 if desc or op is invalid.
+ * A workspace of the largest batch of a program serves its smaller ones: for the
+ * backward operations, and for the forward ones with f32 streams or C no
+ * multiple of 64, the size never falls as T grows.  The forward of bf16 streams at C a
+ * multiple of 64 splits the projection's rows up to four ways while its blocks
+ * do not fill the chip, and needs less again from the T on at which a split
+ * ends (16384, 32768 or 65536 tokens).
  * Host only. */
 size_t mhcl_workspace_bytes(const mhcl_desc *desc, int op);
 

@@ -45,23 +45,25 @@ struct CoeffsWs {
   char *Wp;   // packed W (fast path only)
   size_t bytes;
   CoeffsWs(const mhcl_desc &d, void *ws) {
-    WsCursor c(ws);
-    const size_t T = static_cast<size_t>(d.T);
-    const size_t parts = static_cast<size_t>(proj_ksplit(d));
-    u_raw = c.take<float>(parts * T * logits(d));
-    sumsq = c.take<float>(parts * T);
-    Wp = proj_fullprec_used(d) ? nullptr : c.take<char>(packed_w_b_bytes(d, logits(d)));
-    bytes = c.off;
-    if (fast_path_ok(d) && proj_fullprec_used(d)) {
-      // never less than the bf16 projection asks for at this shape: the shapes that the static
-      // array takes do not depend on which one runs (its slices alone are at most 10 MB)
-      WsCursor m(nullptr);
-      const size_t mparts = static_cast<size_t>(mfma_ksplit(d));
-      m.take<float>(mparts * T * logits(d));
-      m.take<float>(mparts * T);
-      m.take<char>(packed_w_b_bytes(d, logits(d)));
-      if (m.off > bytes) bytes = m.off;
+    // Sized for both projections where both may run: the shapes that the static array takes are
+    // those of the bf16 one at C a multiple of 64 (the slices of the other are at most 10 MB), of one slice
+    // elsewhere.
+    bytes = carve(d, nullptr, true);
+    if (fast_path_ok(d)) {
+      const size_t packed = carve(d, nullptr, false);
+      if (packed > bytes) bytes = packed;
     }
+    carve(d, ws, proj_fullprec_used(d));
+  }
+
+ private:
+  size_t carve(const mhcl_desc &d, void *ws, bool fullprec) {
+    WsCursor c(ws);
+    const size_t slices = static_cast<size_t>(fullprec ? proj_fullprec_slice_tokens(d) : mfma_ksplit(d) * d.T);
+    u_raw = c.take<float>(slices * logits(d));
+    sumsq = c.take<float>(slices);
+    Wp = fullprec ? nullptr : c.take<char>(packed_w_b_bytes(d, logits(d)));
+    return c.off;
   }
 };
 
@@ -74,12 +76,13 @@ struct BwdWs {
     WsCursor c(ws);
     const size_t T = static_cast<size_t>(d.T);
     const int M = logits(d), n = d.n;
-    const size_t parts = static_cast<size_t>(proj_ksplit(d));
-    u_raw = c.take<float>(parts * T * M);
-    sumsq = c.take<float>(parts * T);
+    int64_t slices = proj_fullprec_slice_tokens(d);
+    if (fast_path_ok(d) && mfma_slice_tokens(d) > slices) slices = mfma_slice_tokens(d);
+    u_raw = c.take<float>(static_cast<size_t>(slices) * M);
+    sumsq = c.take<float>(slices);
     tok.rec = c.take<float>(T * token_rec_floats(n));
     tok.vr = c.take<float>(T * ((M + 15) / 16 * 16));
-    tok.gz = c.take<float>(static_cast<size_t>(gz_rows(d, false)) * (M + 3));
+    tok.gz = c.take<float>(static_cast<size_t>(gz_rows_reserved(d)) * (M + 3));
     gH_res = gH_pre = gH_post = nullptr;
     if (need_dots) {
       gH_res = c.take<float>(T * n * n);

@@ -1655,20 +1655,33 @@ int proj_ksplit(const mhcl_desc &d) {
   return proj_fullprec_used(d) ? proj_fullprec_parts(d) : mfma_ksplit(d);
 }
 
-int mfma_ksplit(const mhcl_desc &d) {
-  const int M = res_logits(d) + 2 * d.n;
-  int kc = 4, tok = 128;
-  const int want = 256;   // one block per CU
-  (void)dispatch_nt_proj(logit_tiles(M), [&](auto nt) {
-    kc = ProjCfg<decltype(nt)::value>::KC;
-    tok = ProjCfg<decltype(nt)::value>::kTokens;
+// K steps per chunk and tokens per block of the projection at d's logits
+static void proj_shape(const mhcl_desc &d, int *kc, int *tok) {
+  (void)dispatch_nt_proj(logit_tiles(res_logits(d) + 2 * d.n), [&](auto nt) {
+    *kc = ProjCfg<decltype(nt)::value>::KC;
+    *tok = ProjCfg<decltype(nt)::value>::kTokens;
     return hipSuccess;
   });
+}
+
+int mfma_ksplit(const mhcl_desc &d) {
+  int kc = 4, tok = 128;
+  const int want = 256;   // one block per CU
+  proj_shape(d, &kc, &tok);
   const int nsteps = d.n * d.C / 32;
   const int64_t blocks = (d.T + tok - 1) / tok;
   int ks = 1;   // enough blocks for one per CU, each part a whole number of chunk pairs
   while (ks < kMaxKSplit && blocks * ks < want && nsteps % (ks * 2 * 2 * kc) == 0) ks *= 2;
   return ks;
+}
+
+// (p > 1 parts only up to 512 / p - 1 blocks)
+int64_t mfma_slice_tokens(const mhcl_desc &d) {
+  int kc = 4, tok = 128;
+  proj_shape(d, &kc, &tok);
+  mhcl_desc one = d;
+  one.T = 1;
+  return slice_tokens(d.T, mfma_ksplit(one), 512 * tok);
 }
 
 // W staged as it is (split into its two parts on the way to LDS) instead of packed by a launch of its
@@ -1760,13 +1773,15 @@ int reduce_parts(const mhcl_desc &d) {
   return (d.C / 64 + spp - 1) / spp;
 }
 
-int out_gw_tokens_per_block(const mhcl_desc &d) {
-  // Token chunks: as many as make the grid one round of resident blocks (all blocks
-  // then start together and the blocks of a chunk walk down the same rows side by
-  // side), never more than 64 MiB of partial g_W copies, and blocks of a whole
-  // number of 64-token iterations.  With few tokens a block is down to one of them: filling the
-  // chip is worth more than sharing a block's copy of W among tokens (the fused backward at n = 4,
-  // C = 1024, 2048 tokens: 126 us with at least 256 tokens per block, 109 with 128, 102 with 64).
+// slices x tokens of the dot products, at most, of T tokens or fewer (256 / ceil(T / 64) parts)
+static int64_t reduce_slice_tokens(const mhcl_desc &d) {
+  mhcl_desc one = d;
+  one.T = 1;
+  return slice_tokens(d.T, reduce_parts(one), 256 * 64);
+}
+
+// token chunks of pass 2 as far as T does not limit them
+static int64_t out_gw_max_chunks(const mhcl_desc &d) {
   const int64_t M = res_logits(d) + 2 * d.n;
   const int64_t copy_bytes = static_cast<int64_t>(d.n) * d.C * M * 4;
   const bool pair = (d.C / 64) % 2 == 0;            // two 64-column steps per block
@@ -1776,6 +1791,17 @@ int out_gw_tokens_per_block(const mhcl_desc &d) {
   if (chunks < 1) chunks = 1;
   const int64_t cap = (64ll << 20) / copy_bytes;
   if (chunks > cap) chunks = cap < 1 ? 1 : cap;
+  return chunks;
+}
+
+int out_gw_tokens_per_block(const mhcl_desc &d) {
+  // Token chunks: as many as make the grid one round of resident blocks (all blocks
+  // then start together and the blocks of a chunk walk down the same rows side by
+  // side), never more than 64 MiB of partial g_W copies, and blocks of a whole
+  // number of 64-token iterations.  With few tokens a block is down to one of them: filling the
+  // chip is worth more than sharing a block's copy of W among tokens (the fused backward at n = 4,
+  // C = 1024, 2048 tokens: 126 us with at least 256 tokens per block, 109 with 128, 102 with 64).
+  const int64_t chunks = out_gw_max_chunks(d);
   const int64_t tpb = ((d.T + chunks - 1) / chunks + 63) / 64 * 64;
   return tpb > 0 ? static_cast<int>(tpb) : 64;   // (no tokens: workspace queries still divide by it)
 }
@@ -1803,13 +1829,20 @@ FastBwdWs::FastBwdWs(const mhcl_desc &d, void *ws) {
   // takes the projection from the forward's kernels
   parts = fast_bwd_wide(d) ? proj_ksplit(d) : reduce_parts(d);
   gparts = reduce_parts(d);
-  u_raw = c.take<float>(static_cast<size_t>(parts) * T * M);
-  sumsq = c.take<float>(static_cast<size_t>(parts) * T);
-  gH_res = c.take<float>(gparts * T * n * n);
-  gH_pre = c.take<float>(gparts * T * n);
-  gH_post = c.take<float>(gparts * T * n);
+  const int64_t gcap = reduce_slice_tokens(d);
+  int64_t ucap = gcap;
+  if (fast_bwd_wide(d)) {
+    const int64_t few = proj_fullprec_slice_tokens(d);
+    ucap = mfma_slice_tokens(d);
+    if (few > ucap) ucap = few;
+  }
+  u_raw = c.take<float>(static_cast<size_t>(ucap) * M);
+  sumsq = c.take<float>(ucap);
+  gH_res = c.take<float>(gcap * n * n);
+  gH_pre = c.take<float>(gcap * n);
+  gH_post = c.take<float>(gcap * n);
   cpk = c.take<float>(T * CP);
-  gz = c.take<float>(static_cast<size_t>(gz_rows(d, true)) * (M + 3));
+  gz = c.take<float>(static_cast<size_t>(gz_rows_reserved(d)) * (M + 3));
   vr_hi = c.take<uint16_t>(Tpad * MP32);
   vr_lo = c.take<uint16_t>(Tpad * MP32);
   vrT_hi = c.take<uint16_t>(Tpad * MP16);
@@ -1818,12 +1851,12 @@ FastBwdWs::FastBwdWs(const mhcl_desc &d, void *ws) {
   Wa = c.take<char>(packed_a_bytes(K, M));
   wmax_part = c.take<float>(256);   // kWmaxBlocks
   wscale = c.take<float>(2);
-  {
-    const int64_t tpb = out_gw_tokens_per_block(d);
-    const size_t fused_chunks = static_cast<size_t>((d.T + tpb - 1) / tpb);
-    const size_t chunks = fused_chunks > static_cast<size_t>(gw_chunks_fast(d)) ? fused_chunks : gw_chunks_fast(d);
-    partials = c.take<float>(chunks * K * M);
+  int64_t chunks = gw_chunks_fast(d);
+  if (!fast_bwd_wide(d)) {   // (blocks of a whole number of 64 tokens: sometimes fewer than this for more tokens)
+    chunks = out_gw_max_chunks(d);
+    if (chunks > (d.T + 63) / 64) chunks = (d.T + 63) / 64;
   }
+  partials = c.take<float>(static_cast<size_t>(chunks) * K * M);
   D = fast_bwd_wide(d) ? c.take<float>(T * K) : nullptr;
   bytes = c.off;
 }

@@ -444,11 +444,11 @@ int gw_columns(const mhcl_desc &d, int M) {
 // n = 4, C = 1024, 256 tokens 10.5 / 14.7 us, 1024 tokens 13.6 / 15.1, 2048 tokens 18.7 / 15.2; C = 4096,
 // 64 tokens 13.5 / 37.8, 1024 tokens 29.6 / 39.2, 1500 tokens 40.9 / 39.2; n = 3, C = 1024, 2000 tokens
 // 12.3 / 12.7; n = 5, C = 2560 (nine tiles, where the other one packs W first), 500 tokens 83 / 106.
-bool proj_fullprec_used(const mhcl_desc &d) {
-  if (!fast_path_ok(d)) return true;
+static int64_t few_tokens(const mhcl_desc &d) {
   const int tiles = logit_tiles(res_logits(d) + 2 * d.n);
-  return d.T * tiles <= (tiles <= 4 ? 2500 : 5000);
+  return (tiles <= 4 ? 2500 : 5000) / tiles;
 }
+bool proj_fullprec_used(const mhcl_desc &d) { return !fast_path_ok(d) || d.T <= few_tokens(d); }
 
 // Parts of a row: enough blocks for two per compute unit, each wave with at least one step, at most
 // 16 (the coefficient stages add the slices; 32 gained 1 us for 16 tokens and lost 2 for 256 at
@@ -460,6 +460,18 @@ int proj_fullprec_parts(const mhcl_desc &d) {
   int parts = 1;
   while (parts < 16 && groups * parts < 512 && nsteps >= 2 * parts * kProjWaves) parts *= 2;
   return parts;
+}
+
+// (p > 1 parts only up to 16 (1024 / p - 1) tokens, see above)
+int64_t proj_fullprec_slice_tokens(const mhcl_desc &d) {
+  mhcl_desc one = d;
+  one.T = 1;
+  int64_t T = d.T;
+  if (fast_path_ok(d)) {   // above few_tokens the bf16 projection runs
+    const int64_t few = few_tokens(d);
+    if (T > few) T = few;
+  }
+  return slice_tokens(T, proj_fullprec_parts(one), 16 * 1024);
 }
 
 hipError_t launch_proj_fullprec(const mhcl_desc &d, int M, const void *x, const float *W,

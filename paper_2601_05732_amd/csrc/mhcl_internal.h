@@ -14,6 +14,13 @@ inline int res_logits(const mhcl_desc &d) {
   if (d.res_mode == MHCL_RES_SUBSET) return d.n_perm;
   return d.n * d.n;
 }
+// A workspace is sized for every token count up to T, so that one made for a caller's largest batch serves
+// its smaller ones: the number of slices rises as T falls.  `parts1` slices at one token, and never
+// more than `most` slices times tokens while there is more than one.
+inline int64_t slice_tokens(int64_t T, int parts1, int64_t most) {
+  const int64_t split = parts1 * T < most ? parts1 * T : most;
+  return split > T ? split : T;
+}
 inline size_t align_up(size_t v, size_t a = 256) { return (v + a - 1) / a * a; }
 
 // Carves a caller-provided workspace into 256-byte aligned pieces.
@@ -38,7 +45,7 @@ constexpr int token_rec() { return token_rec_floats(N); }
 struct BwdTokenBufs {
   float *rec;     // [T, token_rec<n>()] H_res | H_pre | H_post | coefx = (r^2 / nC) <vr, u_raw>
   float *vr;      // [T, 16 ceil(M / 16)] r * alpha_g * g_z (the vector multiplied with W and x), zero-padded
-  float *gz;      // [gz_rows(d, false), M+3] sums over a block's tokens of g_z and of the per-group g_z u
+  float *gz;      // [gz_rows(d), M+3] sums over a block's tokens of g_z and of the per-group g_z u
 };
 
 // ---- stream kernels: any n in 1..8, bf16 or f32 streams -----
@@ -62,6 +69,7 @@ hipError_t launch_fill_zero(float *p, size_t count, hipStream_t s);
 // whether u_raw, sumsq come from the fp64 projection below (else from launch_proj_mfma)
 bool proj_fullprec_used(const mhcl_desc &d);
 int proj_fullprec_parts(const mhcl_desc &d);   // slices it writes
+int64_t proj_fullprec_slice_tokens(const mhcl_desc &d);   // slices x tokens, at most, of T tokens or fewer
 hipError_t launch_proj_fullprec(const mhcl_desc &d, int M, const void *x, const float *W,
                                 float *u_raw, float *sumsq, hipStream_t s);
 // g_W from x and vr (rows as in BwdTokenBufs); `partials` holds gw_chunks_fullprec(d) results
@@ -92,6 +100,7 @@ bool coeffs_group_ok(const mhcl_desc &d);
 // rows of the g_z sums that the per-token stage of the backward (`fast`: of the fast path) leaves
 // for launch_bwd_finish
 int64_t gz_rows(const mhcl_desc &d, bool fast);
+int64_t gz_rows_reserved(const mhcl_desc &d);   // at most, of T tokens or fewer
 hipError_t launch_coeffs_group(const mhcl_desc &d, int parts, const float *u_raw,
                                const float *sumsq, const float *b, const float *alpha,
                                float *H_res, float *H_pre, float *H_post, hipStream_t s);
@@ -115,6 +124,7 @@ bool fast_path_ok(const mhcl_desc &d);
 constexpr int kMaxKSplit = 4;
 int proj_ksplit(const mhcl_desc &d);
 int mfma_ksplit(const mhcl_desc &d);   // slices of launch_proj_mfma
+int64_t mfma_slice_tokens(const mhcl_desc &d);   // slices x tokens, at most, of T tokens or fewer
 size_t packed_w_b_bytes(const mhcl_desc &d, int M);
 // packs W (B layout) and, in the same launch, clears `nzero` floats at `zero`
 hipError_t launch_pack_w_b(const mhcl_desc &d, int M, const float *W, void *Wp, hipStream_t s,
@@ -150,7 +160,7 @@ bool fast_bwd_wide(const mhcl_desc &d);   // n >= 5 or a subset: pass 2 split in
 int gw_chunks_fast(const mhcl_desc &d);
 int reduce_parts(const mhcl_desc &d);     // slices that launch_bwd_reduce writes
 struct FastBwdWs {
-  // gz: [gz_rows(d, true)][M+3] sums of g_z and g_z u over each block's tokens
+  // gz: [gz_rows(d)][M+3] sums of g_z and g_z u over each block's tokens
   // wmax_part: partial maxima of |W|; wscale: {scale, 1 / scale} of the fp16 copy of W
   float *u_raw, *sumsq, *gH_res, *gH_pre, *gH_post, *cpk, *gz, *partials, *D, *wmax_part, *wscale;
   uint16_t *vr_hi, *vr_lo, *vrT_hi, *vrT_lo;

@@ -866,6 +866,11 @@ int64_t gz_rows(const mhcl_desc &d, bool fast) {
   return 2 * blocks64;
 }
 
+int64_t gz_rows_reserved(const mhcl_desc &d) {
+  const int64_t blocks64 = (d.T + 63) / 64;
+  return coeffs_group_ok(d) ? blocks64 : 2 * blocks64;
+}
+
 hipError_t launch_token_coeffs(const mhcl_desc &d, int parts, const float *u_raw, const float *sumsq,
                                const float *b, const float *alpha, float *H_res, float *H_pre,
                                float *H_post, hipStream_t s) {
