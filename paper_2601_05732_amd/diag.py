@@ -39,7 +39,7 @@ def layer_stack(wl, L: int, inputs, device: str = "cuda"):
     spread = torch.empty(L, wl.T, device=device, dtype=f)
     # the library wants 16-byte aligned pointers: a layer's slice where that holds for all of
     # them, else a buffer of its own, copied into the stack afterwards
-    own = [None if t[0].numel() % 4 == 0 else torch.empty_like(t[0]) for t in (H, z, spread)]
+    own = [None if t.shape[1:].numel() % 4 == 0 else t.new_empty(t.shape[1:]) for t in (H, z, spread)]
     Hp = torch.empty(wl.T, wl.n, device=device, dtype=f)
     Hq = torch.empty(wl.T, wl.n, device=device, dtype=f)
     ws = mhcl.new_workspace(d, mhcl.OP_COEFFS, device)
