@@ -165,8 +165,11 @@ def _ptr(t, dtype, shape, name):
 
 def _stream():
     """Handle of the current stream of the current device."""
-    if torch.cuda.is_initialized():     # (without building a Stream object: 4 us a call)
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    # (without building a Stream object, 4 us a call, where torch has these two)
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    device = getattr(torch._C, "_cuda_getDevice", None)
+    if raw is not None and device is not None and torch.cuda.is_initialized():
+        return raw(device())
     return torch.cuda.current_stream().cuda_stream
 
 
