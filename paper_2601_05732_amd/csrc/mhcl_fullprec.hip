@@ -550,9 +550,10 @@ hipError_t launch_gx_fullprec(const mhcl_desc &d, int M, bool fused, const void 
       using IO = decltype(io);
       constexpr int N = decltype(nn)::value;
       auto kern = fused ? gx_fullprec_kernel<IO, N, true> : gx_fullprec_kernel<IO, N, false>;
-      if (lds > 64 * 1024) {
+      if (lds > 64 * 1024) {   // (one window then; the limit of the kernel, whatever thread launches it with how many logits)
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+                                           hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           N * (IO::kVec / 4) * 9 * 1024);
         if (e != hipSuccess) return e;
       }
       hipLaunchKernelGGL(kern, grid, dim3(64 * kGxWaves), lds, s, x, W, g_xout, g_h, o.rec, o.vr, M, S,

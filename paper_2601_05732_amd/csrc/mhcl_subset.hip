@@ -370,11 +370,12 @@ bool group_table(const mhcl_desc &d, GroupTable &g) {
   return false;
 }
 
+// lds: this call's need, most: the kernel's (the limit is the kernel's, also for other threads' calls)
 template <typename Kern>
-hipError_t allow_lds(Kern kern, size_t lds) {
+hipError_t allow_lds(Kern kern, size_t lds, size_t most) {
   if (lds <= 64 * 1024) return hipSuccess;
   return hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+                             hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(most));
 }
 
 }  // namespace
@@ -393,7 +394,7 @@ hipError_t launch_coeffs_group(const mhcl_desc &d, int parts, const float *u_raw
     auto kern = g.K <= 64 ? coeffs_group_kernel<N, kGroupForward, false, 8>
                           : coeffs_group_kernel<N, kGroupForward, false, 16>;
     const size_t lds = group_lds_bytes(N, g.K, false);
-    hipError_t e = allow_lds(kern, lds);
+    hipError_t e = allow_lds(kern, lds, group_lds_bytes(N, kMaxPerm, false));
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>((d.T + kGTok - 1) / kGTok)),
                        dim3(kGThreads), lds, s, u_raw, sumsq, parts, b, alpha, nullptr, nullptr,
@@ -415,7 +416,7 @@ hipError_t launch_coeffs_bwd_group(const mhcl_desc &d, int parts, const float *u
     auto kern = g.K <= 64 ? coeffs_group_kernel<N, kGroupFull, false, 8>
                           : coeffs_group_kernel<N, kGroupFull, false, 16>;
     const size_t lds = group_lds_bytes(N, g.K, true);
-    hipError_t e = allow_lds(kern, lds);
+    hipError_t e = allow_lds(kern, lds, group_lds_bytes(N, kMaxPerm, true));
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>((d.T + kGTok - 1) / kGTok)),
                        dim3(kGThreads), lds, s, u_raw, sumsq, parts, b, alpha, g_H_res, g_H_pre,
@@ -439,7 +440,7 @@ hipError_t launch_bwd_epilogue_group(const mhcl_desc &d, const float *b, const f
     constexpr int N = decltype(nn)::value;
     auto launch = [&](auto kern) {
       const size_t lds = group_lds_bytes(N, g.K, true);
-      hipError_t e = allow_lds(kern, lds);
+      hipError_t e = allow_lds(kern, lds, group_lds_bytes(N, kMaxPerm, true));
       if (e != hipSuccess) return e;
       hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(Tpad / kGTok)), dim3(kGThreads), lds, s,
                          w.u_raw, w.sumsq, w.parts, b, alpha, w.gH_res, w.gH_pre, w.gH_post,

@@ -494,9 +494,10 @@ hipError_t launch_token_stage(const mhcl_desc &d, const TokenIn &in,
     }
     const size_t lds = static_cast<size_t>(per_iter) * d.sk_iters * sizeof(float);
     if (MODE == MHCL_RES_SK && lds > 16 * 1024) {   // (with the static arrays it may pass 64 KiB)
+      // the kernel's limit, not this call's need: another thread may be about to launch with more iterations
+      const int most = per_iter * kMaxSkIters * static_cast<int>(sizeof(float));
       hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize,
-                                         static_cast<int>(lds));
+                                         hipFuncAttributeMaxDynamicSharedMemorySize, most);
       if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(threads), MODE == MHCL_RES_SK ? lds : 0, s, in, out);
