@@ -885,6 +885,12 @@ hipError_t launch_token_coeffs(const mhcl_desc &d, int parts, const float *u_raw
 
 hipError_t launch_token_bwd_fast(const mhcl_desc &d, const float *b, const float *alpha,
                                  const FastBwdWs &w, hipStream_t s) {
+  // what the kernels fix at compile time against what pass 2 reads: row lengths, and fp16 rows with
+  // their scale at n = 5 exactly where bwd_out_w16_kernel takes them
+  const int M = res_logits(d) + 2 * d.n, record = d.n * d.n + 2 * d.n + (d.n == 5 ? 2 : 1);
+  if (w.MP32 != (M + 31) / 32 * 32 || w.MP16 != (M + 15) / 16 * 16 || w.CP < record ||
+      (d.n == 5) != fast_bwd_whi(d))
+    return hipErrorInvalidValue;
   TokenIn in = token_in(d, w.parts, w.u_raw, w.sumsq, b, alpha);
   in.gH_res = w.gH_res; in.gH_pre = w.gH_pre; in.gH_post = w.gH_post; in.gparts = w.gparts;
   TokenOut out{};
