@@ -44,8 +44,17 @@
  *    and 512 past a 1 KiB boundary), than when they are equally aligned.
  *  - Stream tensors (x, y, h, x_out and their gradients) have the element
  *    type desc->io_dtype.  Coefficients, parameters and parameter gradients
- *    are always fp32.  All arithmetic accumulates in fp32; bf16 results are
- *    rounded to nearest-even once, from the fp32 value.
+ *    are always fp32.  All arithmetic accumulates in fp32 or wider; bf16 results
+ *    are rounded to nearest-even once, from the fp32 value.
+ *  - The projection x_hat W takes W as it is and sums in fp64 for f32 streams,
+ *    for C no multiple of 64, and for few tokens (T * ceil(M / 16) <= 2500, or
+ *    5000 above 64 logits).  Otherwise, and in mhcl_bwd_fused at n <= 4 (full
+ *    forms) with any T, bf16 streams take W as the sum of two bf16 numbers (16
+ *    significant bits, 2^-17 of each product) and sum in fp32.  So the same token's
+ *    H_*, z and h may differ at that level between a small batch and a large one,
+ *    and between the forward and what mhcl_bwd_fused recomputes; bf16 results
+ *    then differ by single roundings.  Each is within the other's error of the
+ *    exact value, and any one call gives the same bits every time.
  *  - x is [T, n, C] and is flattened stream-major: x_hat[j*C + c] = x[j][c].
  *  - W is one [n*C, M] matrix, b is [M]; columns are [res | pre | post] with
  *    M = n! + 2n (MHCL_RES_LITE; res column k belongs to permutation k) or
