@@ -43,7 +43,6 @@ __device__ __forceinline__ void split_bf16(float w, uint16_t &hi, uint16_t &lo) 
 // A 16-byte chunk of a stream tensor held as fp32 lanes.
 struct BF16 {
   static constexpr int kVec = 8;      // elements per 16 bytes
-  static constexpr int kBytes = 2;
   __device__ static __forceinline__ void load(const void *p, size_t elem, float (&v)[8]) {
     const uint4 q = *reinterpret_cast<const uint4 *>(static_cast<const uint16_t *>(p) + elem);
     v[0] = bf16lo(q.x); v[1] = bf16hi(q.x); v[2] = bf16lo(q.y); v[3] = bf16hi(q.y);
@@ -55,13 +54,9 @@ struct BF16 {
     q.z = pack_bf16x2(v[4], v[5]); q.w = pack_bf16x2(v[6], v[7]);
     *reinterpret_cast<uint4 *>(static_cast<uint16_t *>(p) + elem) = q;
   }
-  __device__ static __forceinline__ float load1(const void *p, size_t elem) {
-    return bf16_to_f32(static_cast<const uint16_t *>(p)[elem]);
-  }
 };
 struct F32 {
   static constexpr int kVec = 4;
-  static constexpr int kBytes = 4;
   __device__ static __forceinline__ void load(const void *p, size_t elem, float (&v)[4]) {
     const float4 q = *reinterpret_cast<const float4 *>(static_cast<const float *>(p) + elem);
     v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
@@ -69,10 +64,28 @@ struct F32 {
   __device__ static __forceinline__ void store(void *p, size_t elem, const float (&v)[4]) {
     *reinterpret_cast<float4 *>(static_cast<float *>(p) + elem) = make_float4(v[0], v[1], v[2], v[3]);
   }
-  __device__ static __forceinline__ float load1(const void *p, size_t elem) {
-    return static_cast<const float *>(p)[elem];
-  }
 };
+
+// ------------------------------------------------- host: run-time values as types
+template <typename F>
+inline hipError_t dispatch_n(int n, F &&f) {
+  switch (n) {
+    case 1: return f(std::integral_constant<int, 1>{});
+    case 2: return f(std::integral_constant<int, 2>{});
+    case 3: return f(std::integral_constant<int, 3>{});
+    case 4: return f(std::integral_constant<int, 4>{});
+    case 5: return f(std::integral_constant<int, 5>{});
+    case 6: return f(std::integral_constant<int, 6>{});
+    case 7: return f(std::integral_constant<int, 7>{});
+    case 8: return f(std::integral_constant<int, 8>{});
+  }
+  return hipErrorInvalidValue;
+}
+template <typename F>
+inline hipError_t dispatch_io(int io, F &&f) {
+  if (io == MHCL_BF16) return f(BF16{});
+  return f(F32{});
+}
 
 // ------------------------------------------------- permutation table
 constexpr int factorial(int n) { return n <= 1 ? 1 : n * factorial(n - 1); }
@@ -118,9 +131,8 @@ struct Dims {
 
 __device__ __forceinline__ float sigmoidf(float t) { return 1.f / (1.f + expf(-t)); }
 
-// ------------------------------------------------- block reduction
-// Sum of `v` over the 256 threads of a block, result valid in every thread.
-// `red` is shared scratch of at least 4 floats (one per wave).
+// ------------------------------------------------- sums in a fixed order
+// sum of `v` over the 64 lanes of a wave, in every lane
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);

@@ -11,25 +11,6 @@ namespace mhcl {
 
 namespace {
 
-template <typename F>
-hipError_t dispatch_n(int n, F &&f) {
-  switch (n) {
-    case 1: return f(std::integral_constant<int, 1>{});
-    case 2: return f(std::integral_constant<int, 2>{});
-    case 3: return f(std::integral_constant<int, 3>{});
-    case 4: return f(std::integral_constant<int, 4>{});
-    case 5: return f(std::integral_constant<int, 5>{});
-    case 6: return f(std::integral_constant<int, 6>{});
-    case 7: return f(std::integral_constant<int, 7>{});
-    case 8: return f(std::integral_constant<int, 8>{});
-  }
-  return hipErrorInvalidValue;
-}
-template <typename F>
-hipError_t dispatch_io(int io, F &&f) {
-  if (io == MHCL_BF16) return f(BF16{});
-  return f(F32{});
-}
 // logit tiles of 16: 1 ... 9
 template <typename F>
 hipError_t dispatch_tiles(int NT, F &&f) {
@@ -497,8 +478,8 @@ hipError_t launch_proj_fullprec(const mhcl_desc &d, int M, const void *x, const 
   });
 }
 
-// Token chunks: one round of blocks on the 256 compute units, each with at least two steps
-// of its loop (128 tokens each) to run ahead in.
+// Token chunks: one round of blocks on the 256 compute units, and no more than one per 256 tokens (two
+// steps of its loop to run ahead in, four above three logit tiles).
 int gw_chunks_fullprec(const mhcl_desc &d) {
   const int M = res_logits(d) + 2 * d.n, cols = gw_columns(d, M);
   const int64_t xblocks = (static_cast<int64_t>(d.n) * d.C + cols - 1) / cols;
@@ -535,7 +516,7 @@ hipError_t launch_gx_fullprec(const mhcl_desc &d, int M, bool fused, const void 
                               const void *g_xout, const void *g_h, const BwdTokenBufs &o, void *g_x,
                               void *g_y, hipStream_t s) {
   const int V = d.io_dtype == MHCL_BF16 ? BF16::kVec : F32::kVec, S = logit_tiles(M);
-  const int per_win = d.n * (V / 4) * S * 1024;   // bytes of W in LDS per window (147 KiB at most)
+  const int per_win = d.n * (V / 4) * S * 1024;   // bytes of W in LDS per window (144 KiB at most)
   const int windows = (d.C + 4 * V - 1) / (4 * V);
   int win = kGxWaves;   // adjacent windows per block: two blocks per compute unit where possible
   while (win > 1 && (win * per_win > 64 * 1024 || win > windows)) win /= 2;

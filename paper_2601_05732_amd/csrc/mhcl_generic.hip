@@ -10,26 +10,6 @@ namespace {
 
 constexpr int kBlock = 256;
 
-template <typename F>
-hipError_t dispatch_n(int n, F &&f) {
-  switch (n) {
-    case 1: return f(std::integral_constant<int, 1>{});
-    case 2: return f(std::integral_constant<int, 2>{});
-    case 3: return f(std::integral_constant<int, 3>{});
-    case 4: return f(std::integral_constant<int, 4>{});
-    case 5: return f(std::integral_constant<int, 5>{});
-    case 6: return f(std::integral_constant<int, 6>{});
-    case 7: return f(std::integral_constant<int, 7>{});
-    case 8: return f(std::integral_constant<int, 8>{});
-  }
-  return hipErrorInvalidValue;
-}
-template <typename F>
-hipError_t dispatch_io(int io, F &&f) {
-  if (io == MHCL_BF16) return f(BF16{});
-  return f(F32{});
-}
-
 // Sum over the block of CNT per-thread values; the totals land in red[0..CNT).  Fixed order:
 // butterfly inside each wave, then the waves in order.
 template <int WAVES, int CNT>

@@ -331,21 +331,6 @@ __global__ __launch_bounds__(kGThreads) void coeffs_group_kernel(
   }
 }
 
-template <typename F>
-hipError_t dispatch_n8(int n, F &&f) {
-  switch (n) {
-    case 1: return f(std::integral_constant<int, 1>{});
-    case 2: return f(std::integral_constant<int, 2>{});
-    case 3: return f(std::integral_constant<int, 3>{});
-    case 4: return f(std::integral_constant<int, 4>{});
-    case 5: return f(std::integral_constant<int, 5>{});
-    case 6: return f(std::integral_constant<int, 6>{});
-    case 7: return f(std::integral_constant<int, 7>{});
-    case 8: return f(std::integral_constant<int, 8>{});
-  }
-  return hipErrorInvalidValue;
-}
-
 // table of the launch: the caller's subset, or all 120 permutations of n = 5 in
 // lexicographic order (full form), passed by value
 struct GroupTable {
@@ -389,7 +374,7 @@ hipError_t launch_coeffs_group(const mhcl_desc &d, int parts, const float *u_raw
                                float *H_res, float *H_pre, float *H_post, hipStream_t s) {
   GroupTable g;
   if (!group_table(d, g)) return hipErrorInvalidValue;
-  return dispatch_n8(d.n, [&](auto nn) {
+  return dispatch_n(d.n, [&](auto nn) {
     constexpr int N = decltype(nn)::value;
     auto kern = g.K <= 64 ? coeffs_group_kernel<N, kGroupForward, false, 8>
                           : coeffs_group_kernel<N, kGroupForward, false, 16>;
@@ -411,7 +396,7 @@ hipError_t launch_coeffs_bwd_group(const mhcl_desc &d, int parts, const float *u
   GroupTable g;
   if (!group_table(d, g)) return hipErrorInvalidValue;
   const int M = g.K + 2 * d.n;
-  return dispatch_n8(d.n, [&](auto nn) {
+  return dispatch_n(d.n, [&](auto nn) {
     constexpr int N = decltype(nn)::value;
     auto kern = g.K <= 64 ? coeffs_group_kernel<N, kGroupFull, false, 8>
                           : coeffs_group_kernel<N, kGroupFull, false, 16>;
@@ -436,7 +421,7 @@ hipError_t launch_bwd_epilogue_group(const mhcl_desc &d, const float *b, const f
   if (w.MP32 != (M + 31) / 32 * 32 || w.MP16 != (M + 15) / 16 * 16) return hipErrorInvalidValue;
   const bool f16 = fast_bwd_whi(d);   // rows for bwd_out_w16_kernel
   if (f16 && w.CP < d.n * d.n + 2 * d.n + 2) return hipErrorInvalidValue;
-  return dispatch_n8(d.n, [&](auto nn) {
+  return dispatch_n(d.n, [&](auto nn) {
     constexpr int N = decltype(nn)::value;
     auto launch = [&](auto kern) {
       const size_t lds = group_lds_bytes(N, g.K, true);

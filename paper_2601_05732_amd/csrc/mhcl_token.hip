@@ -2,7 +2,8 @@
 // from the raw projection to the coefficients, and in the backward on to g_z and the operands of
 // what follows.  The work of one token is a few hundred dependent instructions, so it is spread
 // over a group of lanes: 16 for n <= 4 (lane 4 i + j owns entry (i, j) of H_res, and the
-// residual logits l, l + 16), 64 for n = 5 (8 i + j).  Sums over the group are DPP steps.
+// residual logits l, l + 16), four where there are many tokens (a row of H_res each), eight for n = 5
+// (likewise).  Sums over the group are DPP steps.  With more tokens still, one lane per token.
 #include "mhcl_common.h"
 #include "mhcl_internal.h"
 #include "mhcl_mfma.h"

@@ -1,5 +1,5 @@
-"""The per-token stage against the oracle at the edges of its blocks (32 or 64 tokens, four, sixteen
-or sixty-four lanes per token): every n and form, Sinkhorn-Knopp iteration counts from one to the
+"""The per-token stage against the oracle at the edges of its blocks (32 or 64 tokens, four, eight
+or sixteen lanes per token): every n and form, Sinkhorn-Knopp iteration counts from one to the
 largest (whose divisors take the most LDS), and the token count at which the lanes per token
 change.  C = 64 keeps the rest small.  Tolerances as in gpu_harness.py."""
 import pytest

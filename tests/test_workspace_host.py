@@ -1,4 +1,5 @@
-"""Workspace sizes are answered on the host for every form and operation, also for an empty batch."""
+"""Workspace sizes are answered on the host, also for an empty batch (what they have to hold:
+test_workspace_reuse_host.py), and the shapes the static array takes do not depend on the projection."""
 import pytest
 
 import paper_2601_05732_amd as mhcl

@@ -42,8 +42,9 @@ def _same_bits(a, b):
 
 def test_static_scratch_matches_workspace_call_twice_second_smaller():
     big = si.Workload("static_big", n=4, C=1024, T=4133, io="bf16")       # MFMA path, ragged tail
-    small = si.Workload("static_small", n=4, C=1024, T=517, io="bf16")    # fewer tokens: K split differs
-    for wl, seed in ((big, 11), (small, 12)):
+    split = si.Workload("static_split", n=4, C=1024, T=1300, io="bf16")   # fewer tokens: the row split four ways
+    small = si.Workload("static_small", n=4, C=1024, T=517, io="bf16")    # fewer still: the fp64 projection
+    for wl, seed in ((big, 11), (split, 13), (small, 12)):
         inp, ref, got = _run_both(wl, seed)
         for name, a, b in zip(("H_res", "H_pre", "H_post", "h"), ref, got):
             assert _same_bits(a, b), f"{wl.name}: {name} differs from the workspace call"
@@ -54,7 +55,7 @@ def test_static_scratch_matches_workspace_call_twice_second_smaller():
 
 
 def test_static_scratch_other_forms_and_plain_path():
-    cases = [si.Workload("static_f32", n=3, C=40, T=300, io="f32"),                       # plain ALU kernels
+    cases = [si.Workload("static_f32", n=3, C=40, T=300, io="f32"),                       # fp64 projection
              si.Workload("static_sk", n=4, C=256, T=1000, io="bf16", res_mode="sk"),
              si.Workload("static_n5", n=5, C=128, T=70, io="bf16")]
     for k, wl in enumerate(cases):
