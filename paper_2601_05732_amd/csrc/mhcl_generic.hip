@@ -264,8 +264,10 @@ __global__ __launch_bounds__(64 * WAVES) void bwd_dots_kernel(
 // The end of a backward in one launch.  Blocks [0, nbW): g_W = sum over the token chunks' partial
 // sums, in a fixed association: the GR groups of threads of a block each add every GR-th chunk for
 // the same 256 / GR elements (eight independent loads in flight), then the groups' sums in order.
-// Many chunks take more groups, or a thread would walk down them one round trip after another
-// (256 chunks of n = 3, C = 64: 11 -> 6 us with 16 groups instead of 4).
+// Many chunks of few elements take more groups, or a thread would walk down them one round trip after
+// another (256 chunks of n = 3, C = 64: 11 -> 6 us with 16 groups instead of 4); with blocks enough for the
+// chip they do not, since a group's loads are then 64 bytes long instead of 256 (64 chunks of n = 4, C = 512:
+// 8.2 us with 16 groups, 4.3 with 4).
 // Block nbW + c: column c of the [rows, ld] matrix of g_z sums per 32 or 64 tokens, added in a
 // fixed order (thread i takes rows i, i + 256, ... in turn, then a pairwise tree over the
 // threads); columns below nA go to dstA (g_b), the others to dstB (g_alpha).
@@ -422,7 +424,7 @@ hipError_t launch_bwd_finish(const float *partials, size_t size, int chunks, flo
                        chunks, nbW, g_W, gz_rows, rows, M + 3, M, g_b, g_alpha);
     return hipGetLastError();
   };
-  return chunks > 32 ? go(std::integral_constant<int, 16>{}) : go(std::integral_constant<int, 4>{});
+  return chunks > 32 && size < 64 * 256 ? go(std::integral_constant<int, 16>{}) : go(std::integral_constant<int, 4>{});
 }
 
 hipError_t launch_copy(void *dst, const void *src, size_t bytes, hipStream_t s) {
