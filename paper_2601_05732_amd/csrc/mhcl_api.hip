@@ -46,7 +46,7 @@ struct CoeffsWs {
   size_t bytes;
   CoeffsWs(const mhcl_desc &d, void *ws) {
     // Sized for both projections where both may run: the shapes that the static array takes are
-    // those of the bf16 one at C a multiple of 64 (the slices of the other are at most 10 MB), of one slice
+    // those of the bf16 one at C a multiple of 64 (the slices of the other are 10 MB or less), of one slice
     // elsewhere.
     bytes = carve(d, nullptr, true);
     if (fast_path_ok(d)) {
@@ -59,7 +59,7 @@ struct CoeffsWs {
  private:
   size_t carve(const mhcl_desc &d, void *ws, bool fullprec) {
     WsCursor c(ws);
-    const size_t slices = static_cast<size_t>(fullprec ? proj_fullprec_slice_tokens(d) : mfma_ksplit(d) * d.T);
+    const size_t slices = static_cast<size_t>(fullprec ? proj_fullprec_slice_floats(d) : mfma_ksplit(d) * d.T);
     u_raw = c.take<float>(slices * logits(d));
     sumsq = c.take<float>(slices);
     Wp = fullprec ? nullptr : c.take<char>(packed_w_b_bytes(d, logits(d)));
@@ -76,7 +76,7 @@ struct BwdWs {
     WsCursor c(ws);
     const size_t T = static_cast<size_t>(d.T);
     const int M = logits(d), n = d.n;
-    int64_t slices = proj_fullprec_slice_tokens(d);
+    int64_t slices = proj_fullprec_slice_floats(d);
     if (fast_path_ok(d) && mfma_slice_tokens(d) > slices) slices = mfma_slice_tokens(d);
     u_raw = c.take<float>(static_cast<size_t>(slices) * M);
     sumsq = c.take<float>(slices);
@@ -137,22 +137,18 @@ hipError_t run_projection(const mhcl_desc &d, const void *x, const float *W, flo
 
 // per-token coefficients from the projection: compile-time tables for the full
 // permutation and Sinkhorn-Knopp forms, the run-time table for a subset
-hipError_t run_coeffs_epilogue(const mhcl_desc &d, int parts, const float *u_raw,
-                               const float *sumsq, const float *b, const float *alpha,
-                               float *H_res, float *H_pre, float *H_post, hipStream_t s) {
-  if (coeffs_group_ok(d))
-    return launch_coeffs_group(d, parts, u_raw, sumsq, b, alpha, H_res, H_pre, H_post, s);
-  return launch_token_coeffs(d, parts, u_raw, sumsq, b, alpha, H_res, H_pre, H_post, s);
+hipError_t run_coeffs_epilogue(const mhcl_desc &d, const RawSums &raw, const float *b,
+                               const float *alpha, float *H_res, float *H_pre, float *H_post,
+                               hipStream_t s) {
+  if (coeffs_group_ok(d)) return launch_coeffs_group(d, raw, b, alpha, H_res, H_pre, H_post, s);
+  return launch_token_coeffs(d, raw, b, alpha, H_res, H_pre, H_post, s);
 }
-hipError_t run_coeffs_bwd_epilogue(const mhcl_desc &d, const float *u_raw, const float *sumsq,
-                                   const float *b, const float *alpha, const float *g_H_res,
-                                   const float *g_H_pre, const float *g_H_post,
-                                   const BwdTokenBufs &o, hipStream_t s) {
+hipError_t run_coeffs_bwd_epilogue(const mhcl_desc &d, const RawSums &raw, const float *b,
+                                   const float *alpha, const float *g_H_res, const float *g_H_pre,
+                                   const float *g_H_post, const BwdTokenBufs &o, hipStream_t s) {
   if (coeffs_group_ok(d))
-    return launch_coeffs_bwd_group(d, proj_ksplit(d), u_raw, sumsq, b, alpha, g_H_res, g_H_pre,
-                                   g_H_post, o, s);
-  return launch_token_bwd_full(d, proj_ksplit(d), u_raw, sumsq, b, alpha, g_H_res, g_H_pre, g_H_post,
-                               o, s);
+    return launch_coeffs_bwd_group(d, raw, b, alpha, g_H_res, g_H_pre, g_H_post, o, s);
+  return launch_token_bwd_full(d, raw, b, alpha, g_H_res, g_H_pre, g_H_post, o, s);
 }
 
 // argument checks of mhcl_fwd_coeffs_pre and its allocation-free variant
@@ -193,14 +189,14 @@ int run_fwd_coeffs_pre(const mhcl_desc &d, const void *x, const float *W, const 
         StageBracket br(MHCL_STAGE_FWD_PROJ, s);
         MHCL_HIP(launch_fwd_once(d, logits(d), x, b, alpha, w, h, s));
       }
-      MHCL_HIP(run_coeffs_epilogue(d, w.parts, w.u_part, w.sumsq_part, b, alpha, H_res, H_pre,
+      MHCL_HIP(run_coeffs_epilogue(d, {w.u_part, w.sumsq_part, w.parts, false}, b, alpha, H_res, H_pre,
                                    H_post, s));
       return MHCL_OK;
     }
   }
   CoeffsWs w(d, ws);
   MHCL_HIP(run_projection(d, x, W, w.u_raw, w.sumsq, w.Wp, MHCL_STAGE_FWD_PROJ, s));
-  MHCL_HIP(run_coeffs_epilogue(d, proj_ksplit(d), w.u_raw, w.sumsq, b, alpha, H_res, H_pre, H_post, s));
+  MHCL_HIP(run_coeffs_epilogue(d, projected(d, w.u_raw, w.sumsq), b, alpha, H_res, H_pre, H_post, s));
   {
     StageBracket br(MHCL_STAGE_FWD_PRE, s);
     MHCL_HIP(launch_pre(d, x, H_pre, h, s));
@@ -314,7 +310,7 @@ int mhcl_coeffs(const mhcl_desc *desc, const void *x, const float *W, const floa
   CoeffsWs w(*desc, ws);
   Disarm disarm;
   MHCL_HIP(run_projection(*desc, x, W, w.u_raw, w.sumsq, w.Wp, MHCL_STAGE_FWD_PROJ, s));
-  MHCL_HIP(run_coeffs_epilogue(*desc, proj_ksplit(*desc), w.u_raw, w.sumsq, b, alpha, H_res, H_pre,
+  MHCL_HIP(run_coeffs_epilogue(*desc, projected(*desc, w.u_raw, w.sumsq), b, alpha, H_res, H_pre,
                                H_post, s));
   return MHCL_OK;
 }
@@ -333,7 +329,7 @@ int mhcl_logits(const mhcl_desc *desc, const void *x, const float *W, const floa
   CoeffsWs w(*desc, ws);
   Disarm disarm;
   MHCL_HIP(run_projection(*desc, x, W, w.u_raw, w.sumsq, w.Wp, MHCL_STAGE_FWD_PROJ, s));
-  MHCL_HIP(launch_logits(*desc, mhcl_logit_count(desc), proj_ksplit(*desc), w.u_raw, w.sumsq, b,
+  MHCL_HIP(launch_logits(*desc, mhcl_logit_count(desc), projected(*desc, w.u_raw, w.sumsq), b,
                          alpha, z, log_inv_nu, s));
   return MHCL_OK;
 }
@@ -453,7 +449,7 @@ int mhcl_coeffs_bwd(const mhcl_desc *desc, const void *x, const float *W, const 
   BwdWs w(*desc, ws, false);
   Disarm disarm;
   MHCL_HIP(run_projection(*desc, x, W, w.u_raw, w.sumsq, w.Wp, MHCL_STAGE_BWD_REDUCE, s));
-  MHCL_HIP(run_coeffs_bwd_epilogue(*desc, w.u_raw, w.sumsq, b, alpha, g_H_res, g_H_pre, g_H_post,
+  MHCL_HIP(run_coeffs_bwd_epilogue(*desc, projected(*desc, w.u_raw, w.sumsq), b, alpha, g_H_res, g_H_pre, g_H_post,
                                    w.tok, s));
   MHCL_HIP(launch_gx_fullprec(*desc, M, false, x, W, nullptr, nullptr, w.tok, g_x, nullptr, s));
   MHCL_HIP(launch_gw_fullprec(*desc, M, x, w.tok.vr, w.partials, g_W, s));
@@ -526,7 +522,7 @@ int mhcl_bwd_fused(const mhcl_desc *desc, const void *x, const void *y, const fl
   BwdWs w(*desc, ws, true);
   MHCL_HIP(run_projection(*desc, x, W, w.u_raw, w.sumsq, w.Wp, MHCL_STAGE_BWD_REDUCE, s));
   MHCL_HIP(launch_bwd_dots(*desc, x, y, g_xout, g_h, w.gH_res, w.gH_post, w.gH_pre, s));
-  MHCL_HIP(run_coeffs_bwd_epilogue(*desc, w.u_raw, w.sumsq, b, alpha, w.gH_res, w.gH_pre,
+  MHCL_HIP(run_coeffs_bwd_epilogue(*desc, projected(*desc, w.u_raw, w.sumsq), b, alpha, w.gH_res, w.gH_pre,
                                    w.gH_post, w.tok, s));
   {
     StageBracket br(MHCL_STAGE_BWD_OUT, s);

@@ -151,4 +151,18 @@ __device__ __forceinline__ float pairwise_sum(F at, int first = 0) {
   }
 }
 
+// src[at] + src[at + stride] + ..., one element of each slice, in order; in fp64 and rounded once if the
+// slices are fp64 (`wide`)
+__device__ __forceinline__ float slice_sum(const float *src, int slices, int wide, int64_t stride, int64_t at) {
+  if (wide) {
+    const double *p = reinterpret_cast<const double *>(src);
+    double s = p[at];
+    for (int k = 1; k < slices; ++k) s += p[k * stride + at];
+    return static_cast<float>(s);
+  }
+  float s = src[at];
+  for (int k = 1; k < slices; ++k) s += src[k * stride + at];
+  return s;
+}
+
 }  // namespace mhcl

@@ -1829,10 +1829,11 @@ FastBwdWs::FastBwdWs(const mhcl_desc &d, void *ws) {
   // takes the projection from the forward's kernels
   parts = fast_bwd_wide(d) ? proj_ksplit(d) : reduce_parts(d);
   gparts = reduce_parts(d);
+  wide_sums = fast_bwd_wide(d) && projected(d, nullptr, nullptr).wide;
   const int64_t gcap = reduce_slice_tokens(d);
   int64_t ucap = gcap;
   if (fast_bwd_wide(d)) {
-    const int64_t few = proj_fullprec_slice_tokens(d);
+    const int64_t few = proj_fullprec_slice_floats(d);
     ucap = mfma_slice_tokens(d);
     if (few > ucap) ucap = few;
   }

@@ -77,7 +77,7 @@ constexpr int kProjWaves = 8;
 template <typename IO, int NT, int WAVES>
 __global__ __launch_bounds__(64 * WAVES, 1) void proj_fullprec_kernel(
     const void *__restrict__ x, const float *__restrict__ W, int nC, int M, int64_t T,
-    int steps_per_part, float *__restrict__ u_raw, float *__restrict__ sumsq) {
+    int steps_per_part, float *__restrict__ u_raw, float *__restrict__ sumsq) {   // (fp64 if gridDim.y > 1)
   constexpr int V = IO::kVec;
   __shared__ double red[2][WAVES][4][64];
   __shared__ double red_ss[WAVES][16];
@@ -143,17 +143,25 @@ __global__ __launch_bounds__(64 * WAVES, 1) void proj_fullprec_kernel(
 
   ss += __shfl_xor(ss, 16, 64);   // the four lanes of a token
   ss += __shfl_xor(ss, 32, 64);
-  if constexpr (WAVES == 1) {
-    if (q == 0 && t0 + r < T) sumsq[blockIdx.y * T + t0 + r] = static_cast<float>(ss);
+  if constexpr (WAVES == 1) {   // (one part)
+    if (q == 0 && t0 + r < T) sumsq[t0 + r] = static_cast<float>(ss);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int64_t t = t0 + 4 * i + q;   // (fp64 tiles hold rows 4 i + q)
 #pragma unroll
       for (int j = 0; j < NT; ++j)
-        if (t < T && 16 * j + r < M) u_raw[(blockIdx.y * T + t) * M + 16 * j + r] = static_cast<float>(acc[j][i]);
+        if (t < T && 16 * j + r < M) u_raw[t * M + 16 * j + r] = static_cast<float>(acc[j][i]);
     }
     return;
   }
+  // A row's one part is rounded to fp32 here; parts stay in fp64 and are rounded when they are added.
+  // (Relative error of H_pre against 64 bits, f32, n = 4, C = 4096, 16 tokens: 5.7e-8 with fp32 slices, 4.0e-8.)
+  auto put = [&](float *dst, int64_t at, double v) {
+    if (gridDim.y > 1)
+      reinterpret_cast<double *>(dst)[at] = v;
+    else
+      dst[at] = static_cast<float>(v);
+  };
   if (q == 0) red_ss[wave][r] = ss;
   // the waves' sums, two logit tiles at a time, in wave order
 #pragma unroll
@@ -174,15 +182,34 @@ __global__ __launch_bounds__(64 * WAVES, 1) void proj_fullprec_kernel(
       // fp64 tiles hold rows 4 i + q: token 4 i + q, logit 16 (base + j) + r
       const int64_t t = t0 + 4 * i + q;
       const int m = 16 * (base + j) + r;
-      if (t < T && m < M) u_raw[(blockIdx.y * T + t) * M + m] = static_cast<float>(sum);
+      if (t < T && m < M) put(u_raw, (blockIdx.y * T + t) * M + m, sum);
     }
   }
   if (threadIdx.x < 16 && t0 + threadIdx.x < T) {   // (red_ss was complete at the barriers above)
     double sum = red_ss[0][threadIdx.x];
 #pragma unroll
     for (int w = 1; w < WAVES; ++w) sum += red_ss[w][threadIdx.x];
-    sumsq[blockIdx.y * T + t0 + threadIdx.x] = static_cast<float>(sum);
+    put(sumsq, blockIdx.y * T + t0 + threadIdx.x, sum);
   }
+}
+
+// Element e of [u_raw | sumsq] in fp64 slices: its sum over the slices, left in the first one.  For the stages
+// whose blocks take 64 tokens or whose threads add serially (measured there).
+template <int S>
+__global__ __launch_bounds__(256) void add_slices_kernel(double *__restrict__ u_raw, double *__restrict__ sumsq,
+                                                         int64_t n_u, int64_t T) {
+  int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  if (e >= n_u + T) return;
+  double *p = u_raw;
+  int64_t stride = n_u;
+  if (e >= n_u) { p = sumsq; stride = T; e -= n_u; }
+  double v[S], s;
+#pragma unroll
+  for (int k = 0; k < S; ++k) v[k] = p[k * stride + e];
+  s = v[0];
+#pragma unroll
+  for (int k = 1; k < S; ++k) s += v[k];
+  p[e] = s;
 }
 
 // ---------------------------------------------------------------------------
@@ -434,17 +461,47 @@ bool proj_fullprec_used(const mhcl_desc &d) { return !fast_path_ok(d) || d.T <= 
 // Parts of a row: enough blocks for two per compute unit, each wave with at least one step, at most
 // 16 (the coefficient stages add the slices; 32 gained 1 us for 16 tokens and lost 2 for 256 at
 // C = 4096; 4 instead of 16 for n = 5, C = 2560, 256 tokens: 105 us for mhcl_coeffs against 57).
+// Eight or nine tiles: 448 blocks are enough, so that the fp64 slices of any T fit in
+// MHCL_STATIC_SCRATCH_BYTES (14304 slice-tokens of 143 logits and a sum of squares).
+static int64_t enough_blocks(const mhcl_desc &d) {
+  return logit_tiles(res_logits(d) + 2 * d.n) >= 8 ? 448 : 512;
+}
 int proj_fullprec_parts(const mhcl_desc &d) {
   const int V = d.io_dtype == MHCL_BF16 ? BF16::kVec : F32::kVec;
   const int nsteps = (d.n * d.C + 4 * V - 1) / (4 * V);
   const int64_t groups = (d.T + 15) / 16;
   int parts = 1;
-  while (parts < 16 && groups * parts < 512 && nsteps >= 2 * parts * kProjWaves) parts *= 2;
+  while (parts < 16 && groups * parts < enough_blocks(d) && nsteps >= 2 * parts * kProjWaves) parts *= 2;
   return parts;
 }
 
-// (p > 1 parts only up to 16 (1024 / p - 1) tokens, see above)
-int64_t proj_fullprec_slice_tokens(const mhcl_desc &d) {
+RawSums projected(const mhcl_desc &d, const float *u_raw, const float *sumsq) {
+  const int parts = proj_ksplit(d);
+  return {u_raw, sumsq, parts, proj_fullprec_used(d) && parts > 1};
+}
+
+hipError_t add_wide_slices(const mhcl_desc &d, RawSums &raw, hipStream_t s) {
+  if (!raw.wide) return hipErrorInvalidValue;
+  const int64_t n_u = d.T * (res_logits(d) + 2 * d.n);
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>((n_u + d.T + 255) / 256)), dim3(256), 0, s,
+                       reinterpret_cast<double *>(const_cast<float *>(raw.u_raw)),
+                       reinterpret_cast<double *>(const_cast<float *>(raw.sumsq)), n_u, d.T);
+    return hipGetLastError();
+  };
+  const int parts = raw.parts;
+  raw.parts = 1;
+  switch (parts) {
+    case 2: return go(add_slices_kernel<2>);
+    case 4: return go(add_slices_kernel<4>);
+    case 8: return go(add_slices_kernel<8>);
+    case 16: return go(add_slices_kernel<16>);
+  }
+  return hipErrorInvalidValue;
+}
+
+// (p > 1 parts only up to 16 (2 enough_blocks / p - 1) tokens, see above)
+int64_t proj_fullprec_slice_floats(const mhcl_desc &d) {
   mhcl_desc one = d;
   one.T = 1;
   int64_t T = d.T;
@@ -452,7 +509,8 @@ int64_t proj_fullprec_slice_tokens(const mhcl_desc &d) {
     const int64_t few = few_tokens(d);
     if (T > few) T = few;
   }
-  return slice_tokens(T, proj_fullprec_parts(one), 16 * 1024);
+  const int parts = proj_fullprec_parts(one);
+  return parts > 1 ? slice_tokens(T, 2 * parts, 2 * 16 * 2 * enough_blocks(d)) : T;
 }
 
 hipError_t launch_proj_fullprec(const mhcl_desc &d, int M, const void *x, const float *W,

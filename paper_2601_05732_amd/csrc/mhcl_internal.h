@@ -68,10 +68,22 @@ hipError_t launch_fill_zero(float *p, size_t count, hipStream_t s);
 // ---- full-precision products on the matrix cores: any C, bf16 or f32 streams -----
 // whether u_raw, sumsq come from the fp64 projection below (else from launch_proj_mfma)
 bool proj_fullprec_used(const mhcl_desc &d);
-int proj_fullprec_parts(const mhcl_desc &d);   // slices it writes
-int64_t proj_fullprec_slice_tokens(const mhcl_desc &d);   // slices x tokens, at most, of T tokens or fewer
+int proj_fullprec_parts(const mhcl_desc &d);   // slices it writes: one in fp32, 2, 4, 8 or 16 in fp64
+// floats that the slices of one logit take, at most, of T tokens or fewer
+int64_t proj_fullprec_slice_floats(const mhcl_desc &d);
 hipError_t launch_proj_fullprec(const mhcl_desc &d, int M, const void *x, const float *W,
                                 float *u_raw, float *sumsq, hipStream_t s);
+// What a projection leaves for the per-token stage, where the slices are added in order: u_raw
+// [parts][T][M] and sumsq [parts][T], in fp64 if `wide`.
+struct RawSums {
+  const float *u_raw, *sumsq;
+  int parts;
+  bool wide;
+};
+// the sums over fp64 slices take the place of the first one, which alone is left
+hipError_t add_wide_slices(const mhcl_desc &d, RawSums &raw, hipStream_t s);
+// as launch_proj_fullprec or launch_proj_mfma left them
+RawSums projected(const mhcl_desc &d, const float *u_raw, const float *sumsq);
 // g_W from x and vr (rows as in BwdTokenBufs); `partials` holds gw_chunks_fullprec(d) results
 // of [nC, M] when that is more than one
 int gw_chunks_fullprec(const mhcl_desc &d);
@@ -86,13 +98,12 @@ hipError_t launch_gx_fullprec(const mhcl_desc &d, int M, bool fused, const void 
 // ---- per-token stage of the other forms (n <= 4, Sinkhorn-Knopp) --------------
 bool token_stage_many(const mhcl_desc &d, bool backward);   // the variant for many tokens
 bool token_per_lane(const mhcl_desc &d, bool backward);     // more tokens still
-hipError_t launch_token_coeffs(const mhcl_desc &d, int parts, const float *u_raw, const float *sumsq,
-                               const float *b, const float *alpha, float *H_res, float *H_pre,
-                               float *H_post, hipStream_t s);
-hipError_t launch_token_bwd_full(const mhcl_desc &d, int parts, const float *u_raw,
-                                 const float *sumsq, const float *b, const float *alpha,
-                                 const float *g_H_res, const float *g_H_pre, const float *g_H_post,
-                                 const BwdTokenBufs &o, hipStream_t s);
+hipError_t launch_token_coeffs(const mhcl_desc &d, const RawSums &raw, const float *b,
+                               const float *alpha, float *H_res, float *H_pre, float *H_post,
+                               hipStream_t s);
+hipError_t launch_token_bwd_full(const mhcl_desc &d, const RawSums &raw, const float *b,
+                                 const float *alpha, const float *g_H_res, const float *g_H_pre,
+                                 const float *g_H_post, const BwdTokenBufs &o, hipStream_t s);
 
 // ---- permutation-subset form (run-time table d.perm, n up to 8) --------------
 // eight lanes per token: permutation subsets and the full form at n = 5
@@ -101,19 +112,17 @@ bool coeffs_group_ok(const mhcl_desc &d);
 // for launch_bwd_finish
 int64_t gz_rows(const mhcl_desc &d, bool fast);
 int64_t gz_rows_reserved(const mhcl_desc &d);   // at most, of T tokens or fewer
-hipError_t launch_coeffs_group(const mhcl_desc &d, int parts, const float *u_raw,
-                               const float *sumsq, const float *b, const float *alpha,
-                               float *H_res, float *H_pre, float *H_post, hipStream_t s);
-hipError_t launch_coeffs_bwd_group(const mhcl_desc &d, int parts, const float *u_raw,
-                                   const float *sumsq, const float *b, const float *alpha,
-                                   const float *g_H_res, const float *g_H_pre, const float *g_H_post,
-                                   const BwdTokenBufs &o, hipStream_t s);
+hipError_t launch_coeffs_group(const mhcl_desc &d, const RawSums &raw, const float *b,
+                               const float *alpha, float *H_res, float *H_pre, float *H_post,
+                               hipStream_t s);
+hipError_t launch_coeffs_bwd_group(const mhcl_desc &d, const RawSums &raw, const float *b,
+                                   const float *alpha, const float *g_H_res, const float *g_H_pre,
+                                   const float *g_H_post, const BwdTokenBufs &o, hipStream_t s);
 
 // ---- diagnostics ----------------------------------------------------------
 // z [T,M] and spread [T] (max - min of the residual logits); either may be null
-hipError_t launch_logits(const mhcl_desc &d, int M, int parts, const float *u_raw,
-                         const float *sumsq, const float *b, const float *alpha, float *z,
-                         float *spread, hipStream_t s);
+hipError_t launch_logits(const mhcl_desc &d, int M, const RawSums &raw, const float *b,
+                         const float *alpha, float *z, float *spread, hipStream_t s);
 hipError_t launch_ds_chain(int n, int L, int64_t T, const float *H, float *colsum, float *l1,
                            float *prod, float *prod_colsum, float *prod_l1, hipStream_t s);
 
@@ -166,6 +175,8 @@ struct FastBwdWs {
   uint16_t *vr_hi, *vr_lo, *vrT_hi, *vrT_lo;
   char *Wp, *Wa;
   int CP, MP32, MP16, parts, gparts;   // slices of u_raw, sumsq and of gH_*
+  bool wide_sums;                      // the former are fp64
+  RawSums raw() const { return {u_raw, sumsq, parts, wide_sums}; }
   size_t bytes;
   FastBwdWs(const mhcl_desc &d, void *ws);
 };

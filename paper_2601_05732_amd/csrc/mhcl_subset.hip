@@ -62,12 +62,13 @@ inline size_t group_lds_bytes(int N, int K, bool bwd) {
 // last one: some valid element again), slices in order.  Eight elements per thread and three more
 // slices of each are on their way together: with one slice of four elements at a time the
 // block, alone on its CU, spent 20 us in round trips at n = 5.
-__device__ __forceinline__ void stage_run(const float *__restrict__ src, int slices, int64_t T,
+template <typename F>
+__device__ __forceinline__ void stage_run(const F *__restrict__ src, int slices, int64_t T,
                                           int64_t t0, int W, float *dst, int ld) {
-  constexpr int E = 8, S = 3;
+  constexpr int E = 8, S = sizeof(F) == 4 ? 3 : 1;
   const int64_t stride = T * W, base = t0 * W;
   for (int e0 = threadIdx.x; e0 < kGTok * W; e0 += E * kGThreads) {
-    float s[E];
+    F s[E];
     int64_t at[E];
 #pragma unroll
     for (int v = 0; v < E; ++v) {
@@ -77,10 +78,10 @@ __device__ __forceinline__ void stage_run(const float *__restrict__ src, int sli
       s[v] = src[at[v]];
     }
     for (int p0 = 1; p0 < slices; p0 += S) {
-      float w[S][E];
+      F w[S][E];
 #pragma unroll
       for (int k = 0; k < S; ++k) {
-        const float *slice = src + (p0 + k < slices ? p0 + k : slices - 1) * stride;
+        const F *slice = src + (p0 + k < slices ? p0 + k : slices - 1) * stride;
 #pragma unroll
         for (int v = 0; v < E; ++v) w[k][v] = slice[at[v]];
       }
@@ -93,7 +94,7 @@ __device__ __forceinline__ void stage_run(const float *__restrict__ src, int sli
 #pragma unroll
     for (int v = 0; v < E; ++v) {
       const int e = e0 + v * kGThreads;
-      if (e < kGTok * W) dst[(e / W) * ld + e % W] = s[v];
+      if (e < kGTok * W) dst[(e / W) * ld + e % W] = static_cast<float>(s[v]);
     }
   }
 }
@@ -101,7 +102,7 @@ __device__ __forceinline__ void stage_run(const float *__restrict__ src, int sli
 // OWN: residual logits per lane, 8 OWN >= K
 template <int N, int OUT, bool F16ROWS, int OWN>
 __global__ __launch_bounds__(kGThreads) void coeffs_group_kernel(
-    const float *__restrict__ u_raw, const float *__restrict__ sumsq, int parts,
+    const float *__restrict__ u_raw, const float *__restrict__ sumsq, int parts, int wide,
     const float *__restrict__ b, const float *__restrict__ alpha,
     const float *__restrict__ gH_res, const float *__restrict__ gH_pre,
     const float *__restrict__ gH_post, int gparts, int nC, float eps, int64_t T, int K,
@@ -137,12 +138,14 @@ __global__ __launch_bounds__(kGThreads) void coeffs_group_kernel(
   float bk[OWN];
 #pragma unroll
   for (int kk = 0; kk < OWN; ++kk) bk[kk] = b[kc(kk)];
-  stage_run(u_raw, parts, T, t0, M, u_s, ld);
+  if (wide)
+    stage_run(reinterpret_cast<const double *>(u_raw), parts, T, t0, M, u_s, ld);
+  else
+    stage_run(u_raw, parts, T, t0, M, u_s, ld);
   if (tid < kGTok) {
     int64_t tt = t0 + tid;
     if (tt > T - 1) tt = T - 1;
-    float ssq = sumsq[tt];
-    for (int pt = 1; pt < parts; ++pt) ssq += sumsq[pt * T + tt];
+    const float ssq = slice_sum(sumsq, parts, wide, T, tt);
     r_s[tid] = 1.f / sqrtf(ssq / static_cast<float>(nC) + eps);
   }
   if constexpr (BWD) stage_run(gH_res, gparts, T, t0, NN, g_s, gld);
@@ -363,17 +366,27 @@ hipError_t allow_lds(Kern kern, size_t lds, size_t most) {
                              hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(most));
 }
 
+// Slices that are added by a launch of their own: a block here takes 64 tokens and would read 16 slices of
+// 64 x 130 fp64 logits through its one compute unit.  mhcl_coeffs, f32, inside / before (n = 5, C = 1024: 16 parts at
+// 16 tokens 42.5 / 30.3 us, 512 tokens 63.3 / 52.0; two parts, C = 256, 4096 tokens 52.7 / 55.6).
+bool add_first(const RawSums &raw) { return raw.wide && raw.parts > 2; }
+
 }  // namespace
 
 bool coeffs_group_ok(const mhcl_desc &d) {
   return d.res_mode == MHCL_RES_SUBSET || (d.res_mode == MHCL_RES_LITE && d.n == 5);
 }
 
-hipError_t launch_coeffs_group(const mhcl_desc &d, int parts, const float *u_raw,
-                               const float *sumsq, const float *b, const float *alpha,
-                               float *H_res, float *H_pre, float *H_post, hipStream_t s) {
+hipError_t launch_coeffs_group(const mhcl_desc &d, const RawSums &raw, const float *b,
+                               const float *alpha, float *H_res, float *H_pre, float *H_post,
+                               hipStream_t s) {
   GroupTable g;
   if (!group_table(d, g)) return hipErrorInvalidValue;
+  RawSums r = raw;
+  if (add_first(r)) {
+    hipError_t e = add_wide_slices(d, r, s);
+    if (e != hipSuccess) return e;
+  }
   return dispatch_n(d.n, [&](auto nn) {
     constexpr int N = decltype(nn)::value;
     auto kern = g.K <= 64 ? coeffs_group_kernel<N, kGroupForward, false, 8>
@@ -382,19 +395,23 @@ hipError_t launch_coeffs_group(const mhcl_desc &d, int parts, const float *u_raw
     hipError_t e = allow_lds(kern, lds, group_lds_bytes(N, kMaxPerm, false));
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>((d.T + kGTok - 1) / kGTok)),
-                       dim3(kGThreads), lds, s, u_raw, sumsq, parts, b, alpha, nullptr, nullptr,
+                       dim3(kGThreads), lds, s, r.u_raw, r.sumsq, r.parts, r.wide, b, alpha, nullptr, nullptr,
                        nullptr, 1, d.n * d.C, d.eps, d.T, g.K, g.sigma, g.tab, g.use_tab, H_res, H_pre,
                        H_post, 0, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
     return hipGetLastError();
   });
 }
 
-hipError_t launch_coeffs_bwd_group(const mhcl_desc &d, int parts, const float *u_raw,
-                                   const float *sumsq, const float *b, const float *alpha,
-                                   const float *g_H_res, const float *g_H_pre, const float *g_H_post,
-                                   const BwdTokenBufs &o, hipStream_t s) {
+hipError_t launch_coeffs_bwd_group(const mhcl_desc &d, const RawSums &raw, const float *b,
+                                   const float *alpha, const float *g_H_res, const float *g_H_pre,
+                                   const float *g_H_post, const BwdTokenBufs &o, hipStream_t s) {
   GroupTable g;
   if (!group_table(d, g)) return hipErrorInvalidValue;
+  RawSums r = raw;
+  if (add_first(r)) {
+    hipError_t e = add_wide_slices(d, r, s);
+    if (e != hipSuccess) return e;
+  }
   const int M = g.K + 2 * d.n;
   return dispatch_n(d.n, [&](auto nn) {
     constexpr int N = decltype(nn)::value;
@@ -404,7 +421,7 @@ hipError_t launch_coeffs_bwd_group(const mhcl_desc &d, int parts, const float *u
     hipError_t e = allow_lds(kern, lds, group_lds_bytes(N, kMaxPerm, true));
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>((d.T + kGTok - 1) / kGTok)),
-                       dim3(kGThreads), lds, s, u_raw, sumsq, parts, b, alpha, g_H_res, g_H_pre,
+                       dim3(kGThreads), lds, s, r.u_raw, r.sumsq, r.parts, r.wide, b, alpha, g_H_res, g_H_pre,
                        g_H_post, 1, d.n * d.C, d.eps, d.T, g.K, g.sigma, g.tab, g.use_tab, nullptr, nullptr,
                        nullptr, token_rec<N>(), 0, (M + 15) / 16 * 16, o.rec, nullptr, nullptr, nullptr,
                        nullptr, o.vr, o.gz);
@@ -421,6 +438,11 @@ hipError_t launch_bwd_epilogue_group(const mhcl_desc &d, const float *b, const f
   if (w.MP32 != (M + 31) / 32 * 32 || w.MP16 != (M + 15) / 16 * 16) return hipErrorInvalidValue;
   const bool f16 = fast_bwd_whi(d);   // rows for bwd_out_w16_kernel
   if (f16 && w.CP < d.n * d.n + 2 * d.n + 2) return hipErrorInvalidValue;
+  RawSums r = w.raw();
+  if (add_first(r)) {
+    hipError_t e = add_wide_slices(d, r, s);
+    if (e != hipSuccess) return e;
+  }
   return dispatch_n(d.n, [&](auto nn) {
     constexpr int N = decltype(nn)::value;
     auto launch = [&](auto kern) {
@@ -428,7 +450,7 @@ hipError_t launch_bwd_epilogue_group(const mhcl_desc &d, const float *b, const f
       hipError_t e = allow_lds(kern, lds, group_lds_bytes(N, kMaxPerm, true));
       if (e != hipSuccess) return e;
       hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(Tpad / kGTok)), dim3(kGThreads), lds, s,
-                         w.u_raw, w.sumsq, w.parts, b, alpha, w.gH_res, w.gH_pre, w.gH_post,
+                         r.u_raw, r.sumsq, r.parts, r.wide, b, alpha, w.gH_res, w.gH_pre, w.gH_post,
                          w.gparts, d.n * d.C, d.eps, d.T, g.K, g.sigma, g.tab, g.use_tab, nullptr, nullptr,
                          nullptr, w.CP, w.MP32, w.MP16, w.cpk, w.vr_hi, w.vr_lo, w.vrT_hi, w.vrT_lo,
                          nullptr, w.gz);

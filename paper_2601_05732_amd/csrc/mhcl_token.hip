@@ -108,8 +108,9 @@ __device__ __forceinline__ uint32_t select_perm(int k, std::integer_sequence<int
 }
 
 struct TokenIn {
-  const float *u_raw, *sumsq;              // [parts][T][M], [parts][T]
+  const float *u_raw, *sumsq;              // [parts][T][M], [parts][T], in fp64 if `wide`
   int parts;
+  bool wide;
   const float *gH_res, *gH_pre, *gH_post;  // backward: [gparts][T][n*n], [gparts][T][n]
   int gparts;
   const float *b, *alpha;
@@ -169,6 +170,43 @@ struct StageSums {
   }
 };
 
+// the same for slices in fp64, rounded once: a row that was split sums as a whole one does.  E elements per
+// thread and all their slices are on their way together.
+template <int W, int L, int S, int E>
+__device__ __forceinline__ void stage_wide_pass(const double *src, int64_t T, int64_t t0, float *dst, int ld) {
+  constexpr int THREADS = kTokThreads<L>, ALL = kTokBlock<L> * W;
+  const int64_t stride = T * W;
+  for (int e0 = threadIdx.x; e0 < ALL; e0 += E * THREADS) {
+    double v[E][S];
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+      const int64_t at = t0 * W + e0 + i * THREADS, e = at < stride ? at : stride - 1;
+#pragma unroll
+      for (int k = 0; k < S; ++k) v[i][k] = src[k * stride + e];
+    }
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+      double s = v[i][0];
+#pragma unroll
+      for (int k = 1; k < S; ++k) s += v[i][k];
+      const int e = e0 + i * THREADS;
+      if (e < ALL) dst[(e / W) * ld + e % W] = static_cast<float>(s);
+    }
+  }
+}
+// slices: 2, 4, 8 or 16 (proj_fullprec_parts)
+template <int W, int L>
+__device__ __forceinline__ void stage_wide(const float *src, int slices, int64_t T, int64_t t0, float *dst, int ld) {
+  constexpr int IT = (kTokBlock<L> * W + kTokThreads<L> - 1) / kTokThreads<L>;
+  const double *p = reinterpret_cast<const double *>(src);
+  switch (slices) {
+    case 2: stage_wide_pass<W, L, 2, IT>(p, T, t0, dst, ld); break;
+    case 4: stage_wide_pass<W, L, 4, IT>(p, T, t0, dst, ld); break;
+    case 8: stage_wide_pass<W, L, 8, IT < 4 ? IT : 4>(p, T, t0, dst, ld); break;
+    default: stage_wide_pass<W, L, 16, IT < 2 ? IT : 2>(p, T, t0, dst, ld);
+  }
+}
+
 // floats of dynamic LDS per Sinkhorn-Knopp iteration: the divisors of its two half steps and their
 // reciprocals, one pair per line and token of a pass (backward only)
 template <int N, int L>
@@ -204,7 +242,8 @@ __global__ __launch_bounds__(kTokThreads<L>) void token_stage_kernel(TokenIn in,
   StageSums<1, L> ss;
   StageSums<NN, L> sr;
   StageSums<N, L> sp, sq;
-  su.begin(in.u_raw, T, t0);
+  constexpr bool WIDE = L != 4;   // (the fp64 slices are those of few tokens)
+  su.begin(in.u_raw, T, t0);      // (of fp64 slices: some of their halves, not used)
   ss.begin(in.sumsq, T, t0);
   if constexpr (BWD) {
     sr.begin(in.gH_res, T, t0);
@@ -237,8 +276,13 @@ __global__ __launch_bounds__(kTokThreads<L>) void token_stage_kernel(TokenIn in,
     for (int kk = 0; kk < KK; ++kk)
       pbits[kk] = BWD ? select_perm<N>(l + L * kk, std::make_integer_sequence<int, R>{}) : 0u;
   }
-  su.finish(in.parts, &u_s[0][0], UL);
-  ss.finish(in.parts, &u_s[0][M], UL);
+  if (WIDE && in.wide) {
+    stage_wide<M, L>(in.u_raw, in.parts, T, t0, &u_s[0][0], UL);
+    stage_wide<1, L>(in.sumsq, in.parts, T, t0, &u_s[0][M], UL);
+  } else {
+    su.finish(in.parts, &u_s[0][0], UL);
+    ss.finish(in.parts, &u_s[0][M], UL);
+  }
   if constexpr (BWD) {
     constexpr int GL = (NN + 2 * N) | 1, PAD = MP32 - M > 0 ? MP32 - M : 1;
     sr.finish(in.gparts, &g_s[0][0], GL);
@@ -826,10 +870,9 @@ hipError_t launch_sk_bwd(const mhcl_desc &d, const TokenIn &in, const TokenOut &
   return hipErrorInvalidValue;
 }
 
-TokenIn token_in(const mhcl_desc &d, int parts, const float *u_raw, const float *sumsq,
-                 const float *b, const float *alpha) {
+TokenIn token_in(const mhcl_desc &d, const RawSums &raw, const float *b, const float *alpha) {
   TokenIn in{};
-  in.u_raw = u_raw; in.sumsq = sumsq; in.parts = parts;
+  in.u_raw = raw.u_raw; in.sumsq = raw.sumsq; in.parts = raw.parts; in.wide = raw.wide;
   in.b = b; in.alpha = alpha;
   in.nC = d.n * d.C; in.eps = d.eps; in.sk_iters = d.sk_iters; in.T = d.T;
   return in;
@@ -873,14 +916,14 @@ int64_t gz_rows_reserved(const mhcl_desc &d) {
   return coeffs_group_ok(d) ? blocks64 : 2 * blocks64;
 }
 
-hipError_t launch_token_coeffs(const mhcl_desc &d, int parts, const float *u_raw, const float *sumsq,
-                               const float *b, const float *alpha, float *H_res, float *H_pre,
-                               float *H_post, hipStream_t s) {
+hipError_t launch_token_coeffs(const mhcl_desc &d, const RawSums &raw, const float *b,
+                               const float *alpha, float *H_res, float *H_pre, float *H_post,
+                               hipStream_t s) {
   TokenOut out{};
   out.H_res = H_res; out.H_pre = H_pre; out.H_post = H_post;
-  const TokenIn in = token_in(d, parts, u_raw, sumsq, b, alpha);
-  // (a lane reads its slices one after the other)
-  if (parts < 8 && token_per_lane(d, false)) return launch_lane_coeffs(d, in, out, s);
+  const TokenIn in = token_in(d, raw, b, alpha);
+  // (a lane reads its slices one after the other, in fp32)
+  if (raw.parts < 8 && !raw.wide && token_per_lane(d, false)) return launch_lane_coeffs(d, in, out, s);
   return launch_token_stage<kOutForward>(d, in, out, s);
 }
 
@@ -892,24 +935,23 @@ hipError_t launch_token_bwd_fast(const mhcl_desc &d, const float *b, const float
   if (w.MP32 != (M + 31) / 32 * 32 || w.MP16 != (M + 15) / 16 * 16 || w.CP < record ||
       (d.n == 5) != fast_bwd_whi(d))
     return hipErrorInvalidValue;
-  TokenIn in = token_in(d, w.parts, w.u_raw, w.sumsq, b, alpha);
+  TokenIn in = token_in(d, w.raw(), b, alpha);
   in.gH_res = w.gH_res; in.gH_pre = w.gH_pre; in.gH_post = w.gH_post; in.gparts = w.gparts;
   TokenOut out{};
   out.rec = w.cpk; out.rec_ld = w.CP;
   out.vr_hi = w.vr_hi; out.vr_lo = w.vr_lo; out.vrT_hi = w.vrT_hi; out.vrT_lo = w.vrT_lo;
   out.gz_sums = w.gz;
   if (token_per_lane(d, true)) {
-    if (w.gparts != 1) return hipErrorInvalidValue;   // (more only up to 8192 tokens)
+    if (w.gparts != 1 || w.wide_sums) return hipErrorInvalidValue;   // (more only up to 8192 tokens)
     return launch_sk_bwd(d, in, out, s);
   }
   return launch_token_stage<kOutFast>(d, in, out, s);
 }
 
-hipError_t launch_token_bwd_full(const mhcl_desc &d, int parts, const float *u_raw,
-                                 const float *sumsq, const float *b, const float *alpha,
-                                 const float *g_H_res, const float *g_H_pre, const float *g_H_post,
-                                 const BwdTokenBufs &o, hipStream_t s) {
-  TokenIn in = token_in(d, parts, u_raw, sumsq, b, alpha);
+hipError_t launch_token_bwd_full(const mhcl_desc &d, const RawSums &raw, const float *b,
+                                 const float *alpha, const float *g_H_res, const float *g_H_pre,
+                                 const float *g_H_post, const BwdTokenBufs &o, hipStream_t s) {
+  TokenIn in = token_in(d, raw, b, alpha);
   in.gH_res = g_H_res; in.gH_pre = g_H_pre; in.gH_post = g_H_post; in.gparts = 1;
   TokenOut out{};
   out.rec = o.rec; out.rec_ld = token_rec_floats(d.n); out.vr = o.vr; out.gz_sums = o.gz;

@@ -1,6 +1,7 @@
 """Workspace sizes are answered on the host, also for an empty batch (what they have to hold:
 test_workspace_reuse_host.py), and the shapes the static array takes do not depend on the projection."""
 import pytest
+import torch
 
 import paper_2601_05732_amd as mhcl
 
@@ -43,3 +44,16 @@ def test_static_array_takes_the_same_shapes_whichever_projection_runs(n):
                         want = up(T * d.M * 4) + up(T * 4)
                     got = mhcl.workspace_bytes(d, mhcl.OP_COEFFS)
                     assert (got > mhcl.STATIC_SCRATCH_BYTES) == (want > mhcl.STATIC_SCRATCH_BYTES), (n, C, T, io, mode)
+
+
+@pytest.mark.parametrize("n,K", [(8, 96), (8, 112), (8, 128), (6, 128), (5, 110)])
+def test_static_array_takes_the_longest_logit_rows_too(n, K):
+    """One slice of these fits up to 29000 tokens and more, so split rows of few tokens have to."""
+    d = mhcl.Desc(n, 4096, 0, mhcl.F32, mhcl.RES_SUBSET, perm=torch.zeros(K, n, dtype=torch.int8))
+    for C in (256, 1000, 4096, 20480):
+        d.c.C = C
+        for T in list(range(1, 4000, 13)) + list(range(4000, 9000, 5)) + [16 * g + k for g in range(300) for k in (0, 1)][1:]:
+            d.c.T = T
+            for io in (mhcl.BF16, mhcl.F32) if C % 64 else (mhcl.F32,):
+                d.c.io_dtype = io
+                assert mhcl.workspace_bytes(d, mhcl.OP_COEFFS) <= mhcl.STATIC_SCRATCH_BYTES, (C, T, io)
