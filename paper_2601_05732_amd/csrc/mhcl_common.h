@@ -132,6 +132,13 @@ struct Dims {
 __device__ __forceinline__ float sigmoidf(float t) { return 1.f / (1.f + expf(-t)); }
 
 // ------------------------------------------------- sums in a fixed order
+// a + b, of two lanes' values: never fused with a product that a lane's own value is.  (Fused, either lane adds
+// its unrounded product to the other's rounded one, and the lanes get different sums.)
+__device__ __forceinline__ float lane_add(float a, float b) {
+#pragma clang fp contract(off)
+  return a + b;
+}
+
 // sum of `v` over the 64 lanes of a wave, in every lane
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll

@@ -38,9 +38,9 @@ constexpr int kGTok = 64, kGThreads = 512;
 enum { kGroupForward, kGroupFast, kGroupFull };
 
 __device__ __forceinline__ float group_sum(float v) {
-  v += __shfl_xor(v, 1, 64);
-  v += __shfl_xor(v, 2, 64);
-  v += __shfl_xor(v, 4, 64);
+  v = lane_add(v, __shfl_xor(v, 1, 64));
+  v = lane_add(v, __shfl_xor(v, 2, 64));
+  v = lane_add(v, __shfl_xor(v, 4, 64));
   return v;
 }
 __device__ __forceinline__ float group_max(float v) {

@@ -45,7 +45,7 @@ __device__ __forceinline__ float group_reduce(float v, OP op) {
   return v;
 }
 struct Add {
-  __device__ __forceinline__ float operator()(float a, float b) const { return a + b; }
+  __device__ __forceinline__ float operator()(float a, float b) const { return lane_add(a, b); }
 };
 struct Max {
   __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); }
@@ -58,12 +58,12 @@ __device__ __forceinline__ void column_sums(const float (&v)[CC], float (&s)[CC]
   for (int c = 0; c < CC; ++c) {
     s[c] = v[c];
     if constexpr (L == 16) {
-      s[c] += dpp<kRor8>(s[c]);
-      s[c] += dpp<kRor4>(s[c]);
+      s[c] = lane_add(s[c], dpp<kRor8>(s[c]));
+      s[c] = lane_add(s[c], dpp<kRor4>(s[c]));
     } else {
-      s[c] += dpp<kXor2>(s[c]);
-      s[c] += dpp<kXor1>(s[c]);
-      if constexpr (L == 8) s[c] += dpp<kHalfMirror>(s[c]);
+      s[c] = lane_add(s[c], dpp<kXor2>(s[c]));
+      s[c] = lane_add(s[c], dpp<kXor1>(s[c]));
+      if constexpr (L == 8) s[c] = lane_add(s[c], dpp<kHalfMirror>(s[c]));
     }
   }
 }
@@ -73,8 +73,8 @@ __device__ __forceinline__ float row_sum(const float (&v)[CC]) {
 #pragma unroll
   for (int c = 1; c < CC; ++c) s += v[c];
   if constexpr (L == 16) {
-    s += dpp<kXor1>(s);
-    s += dpp<kXor2>(s);
+    s = lane_add(s, dpp<kXor1>(s));
+    s = lane_add(s, dpp<kXor2>(s));
   }
   return s;
 }
