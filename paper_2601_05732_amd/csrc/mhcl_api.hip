@@ -46,8 +46,8 @@ struct CoeffsWs {
   size_t bytes;
   CoeffsWs(const mhcl_desc &d, void *ws) {
     // Sized for both projections where both may run: the shapes that the static array takes are
-    // those of the bf16 one at C a multiple of 64 (the slices of the other are 10 MB or less), of one slice
-    // elsewhere.
+    // those of the bf16 one at C a multiple of 64, of one slice elsewhere (the slices of split rows fit the array
+    // at any T).
     bytes = carve(d, nullptr, true);
     if (fast_path_ok(d)) {
       const size_t packed = carve(d, nullptr, false);
