@@ -59,7 +59,7 @@ struct CoeffsWs {
  private:
   size_t carve(const mhcl_desc &d, void *ws, bool fullprec) {
     WsCursor c(ws);
-    const size_t slices = static_cast<size_t>(fullprec ? proj_fullprec_slice_floats(d) : mfma_ksplit(d) * d.T);
+    const size_t slices = static_cast<size_t>(fullprec ? proj_fullprec_slice_floats(d) : mfma_slices(d));
     u_raw = c.take<float>(slices * logits(d));
     sumsq = c.take<float>(slices);
     Wp = fullprec ? nullptr : c.take<char>(packed_w_b_bytes(d, logits(d)));

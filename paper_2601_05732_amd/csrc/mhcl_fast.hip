@@ -72,15 +72,15 @@ struct ProjCfg {
   static constexpr int kLdsBytes = 2 * kChunkVec * 16;
 };
 
-template <int NT, bool DIRECT>
+template <int NT, bool DIRECT, bool TURNED>
 __global__ __launch_bounds__(ProjCfg<NT>::kThreads, ProjCfg<NT>::kMinWaves) void proj_mfma_kernel(const uint16_t *__restrict__ x,
                                                            const u32x4 *__restrict__ Wp,
                                                            const float *__restrict__ W, int K,
-                                                           int M, int64_t T,
+                                                           int M, int64_t T, int steps_per_part,
                                                            float *__restrict__ u_raw,
                                                            float *__restrict__ sumsq) {
   // gridDim.y blocks share the K range of the same tokens (K split): block
-  // (bx, part) walks K steps [part * nsteps, (part + 1) * nsteps) and writes its
+  // (bx, part) walks K steps [part * steps_per_part, ...) and writes its
   // partial u_raw / sumsq to slice `part`; the consumer adds the slices in order.
   using Cfg = ProjCfg<NT>;
   constexpr int KC = Cfg::KC, TG = Cfg::TG;
@@ -95,8 +95,8 @@ __global__ __launch_bounds__(ProjCfg<NT>::kThreads, ProjCfg<NT>::kMinWaves) void
     if (t > T - 1) t = T - 1;
     row[g] = x + t * K + q * 8;
   }
-  const int nsteps = K / 32 / gridDim.y;          // K steps of this block
-  const int step0 = blockIdx.y * nsteps;
+  const int step0 = blockIdx.y * steps_per_part;
+  const int nsteps = step0 + steps_per_part < K / 32 ? steps_per_part : K / 32 - step0;   // of this block
 #pragma unroll
   for (int g = 0; g < TG; ++g) row[g] += static_cast<size_t>(step0) * 32;
   if constexpr (DIRECT) W += static_cast<size_t>(step0) * 32 * M;
@@ -124,13 +124,16 @@ __global__ __launch_bounds__(ProjCfg<NT>::kThreads, ProjCfg<NT>::kMinWaves) void
   // Loads never branch: a step past the end re-reads the last step (address
   // clamped); compute() zeroes such a tile where it is consumed, so it adds
   // nothing and the load itself is never waited for early.
-  // (All blocks walk K in the same order: they then read the same W chunk at about the
-  // same time, which keeps W in L2; starting each block elsewhere, as bwd_reduce_kernel
-  // does, cost 20 % with nine logit tiles and gained nothing with two.)
+  // TURNED: each block starts its walk at another chunk, as in bwd_reduce_kernel (a part with a tail keeps it last)
+  const int rot = TURNED && nsteps % KC == 0 ? static_cast<int>((blockIdx.x * 13u) % static_cast<unsigned>(nchunks)) : 0;
+  auto turn = [&](int c) {
+    if constexpr (!TURNED) return c;
+    return c + rot < nchunks ? c + rot : c + rot - nchunks;
+  };
   auto load_a = [&](u32x4 (&dst)[TG][KC], int c) {
 #pragma unroll
     for (int s = 0; s < KC; ++s) {
-      const int step = c * KC + s;
+      const int step = turn(c) * KC + s;
       const int sc = step < nsteps ? step : nsteps - 1;
 #pragma unroll
       for (int g = 0; g < TG; ++g)
@@ -144,7 +147,7 @@ __global__ __launch_bounds__(ProjCfg<NT>::kThreads, ProjCfg<NT>::kMinWaves) void
         int o = i * Cfg::kThreads + threadIdx.x;
         if (kItems % Cfg::kThreads != 0 && o > kItems - 1) o = kItems - 1;
         const int blk = o >> 6, j = blk % NT;
-        int step = c * KC + blk / NT;
+        int step = turn(c) * KC + blk / NT;
         if (step > nsteps - 1) step = nsteps - 1;
         const int col = 16 * j + (o & 15);
         const float *row = W + static_cast<size_t>(32 * step + 8 * ((o >> 4) & 3)) * M + (col < M ? col : M - 1);
@@ -153,7 +156,7 @@ __global__ __launch_bounds__(ProjCfg<NT>::kThreads, ProjCfg<NT>::kMinWaves) void
       }
       return;
     }
-    const int base = c * Cfg::kChunkVec;
+    const int base = turn(c) * Cfg::kChunkVec;
 #pragma unroll
     for (int i = 0; i < WV; ++i) {
       int o = i * Cfg::kThreads + threadIdx.x;
@@ -1664,24 +1667,68 @@ static void proj_shape(const mhcl_desc &d, int *kc, int *tok) {
   });
 }
 
-int mfma_ksplit(const mhcl_desc &d) {
+// K steps per part.  A part costs its share of the walk times the blocks that a CU gets one after the other,
+// plus a slice that the per-token stage adds; more parts only where that gains a tenth.  mhcl_coeffs in us, with
+// powers of two up to four that divide the steps / with this: n = 4, C = 4096, 3000 tokens (24 blocks: 8 parts) 50 / 31,
+// 9000 tokens (71 blocks: 3) 106 / 73; C = 2048, 20000 tokens (157 blocks: 3) 105 / 75; C = 1024, 5003 tokens
+// (40 blocks: 6) 15.3 / 14.2; n = 5, C = 2560, 3000 tokens (12 blocks: 16) 118 / 67, 10000 tokens (40 blocks: 6)
+// 125 / 112; n = 8, K = 64, C = 1024, 5000 tokens (20 blocks: 12) 70 / 50.
+constexpr int kMaxMfmaBlocks = 768;   // of a projection that is split
+static int mfma_steps(const mhcl_desc &d) {
   int kc = 4, tok = 128;
-  const int want = 256;   // one block per CU
   proj_shape(d, &kc, &tok);
-  const int nsteps = d.n * d.C / 32;
+  const int M = res_logits(d) + 2 * d.n, K = d.n * d.C;
+  const int chunks = (K / 32 + kc - 1) / kc;
   const int64_t blocks = (d.T + tok - 1) / tok;
-  int ks = 1;   // enough blocks for one per CU, each part a whole number of chunk pairs
-  while (ks < kMaxKSplit && blocks * ks < want && nsteps % (ks * 2 * 2 * kc) == 0) ks *= 2;
-  return ks;
+  int64_t most = d.T > 0 ? mfma_slices(d) / d.T : 1;   // (what the workspace has room for)
+  if (most > kMaxMfmaParts) most = kMaxMfmaParts;
+  int best = chunks;
+  double best_cost = 0.0;
+  for (int p = 1; p <= most; ++p) {
+    const int cpp = (chunks + p - 1) / p;               // chunks per part: two at least
+    if (p > 1 && (cpp < 2 || blocks * p > kMaxMfmaBlocks)) break;
+    const double cost = static_cast<double>((blocks * p + 255) / 256 * cpp) / chunks +
+                        static_cast<double>(p * blocks) / 256 * 4 * M / K;
+    if (p == 1 || cost < 0.9 * best_cost) { best = cpp; best_cost = cost; }
+  }
+  return best * kc;
+}
+int mfma_ksplit(const mhcl_desc &d) {
+  const int spp = mfma_steps(d);
+  return (d.n * d.C / 32 + spp - 1) / spp;
 }
 
-// (p > 1 parts only up to 512 / p - 1 blocks)
+// slices x tokens of a split projection, at most, of T tokens or fewer
 int64_t mfma_slice_tokens(const mhcl_desc &d) {
   int kc = 4, tok = 128;
   proj_shape(d, &kc, &tok);
-  mhcl_desc one = d;
-  one.T = 1;
-  return slice_tokens(d.T, mfma_ksplit(one), 512 * tok);
+  return slice_tokens(d.T, kMaxMfmaParts, static_cast<int64_t>(kMaxMfmaBlocks) * tok);
+}
+
+// Slices x tokens that the forward's workspace holds.  The shapes that the static array takes are those whose
+// rows fit in parts of a power of two up to four; more parts only as far as they fit in the array too.
+int64_t mfma_slices(const mhcl_desc &d) {
+  int kc = 4, tok = 128;
+  proj_shape(d, &kc, &tok);
+  const int nsteps = d.n * d.C / 32, M = res_logits(d) + 2 * d.n;
+  const int64_t blocks = (d.T + tok - 1) / tok;
+  int ks = 1;
+  while (ks < 4 && blocks * ks < 256 && nsteps % (ks * 4 * kc) == 0) ks *= 2;
+  const int64_t room = static_cast<int64_t>(MHCL_STATIC_SCRATCH_BYTES) - align_up(packed_w_b_bytes(d, M)) - 512;
+  const int64_t fit = room > 0 ? room / (4 * (M + 1)) : 0;
+  int64_t more = mfma_slice_tokens(d);
+  if (more > fit) more = fit;
+  return ks * d.T > more ? ks * d.T : more;
+}
+
+// Each block starts its walk along the rows at another place, as in bwd_reduce_kernel: in step, all requests
+// differ only in address bits above the row length and crowd a few memory channels.  mhcl_coeffs, in step /
+// turned: n = 8, K = 64, C = 1024, 16384 tokens 102 / 86 us; n = 4, C = 2048, 16384 tokens 73 / 58, C = 1024, 32768
+// tokens 70 / 60, C = 768 31 / 30.  Not where the part of W that a block walks through is larger than what then
+// stays in L2 next to the stream: n = 4, C = 4096, 32768 tokens (2 MB) 192 / 203; n = 5, C = 2560, 16384 tokens (1.8 MB) 149 /
+// 158, 32768 tokens (3.6 MB) 268 / 282; at 1 MB (n = 4, C = 4096, 9000 tokens in two parts) 106 / 93.
+static bool proj_turned(const mhcl_desc &d, int M, int steps) {
+  return static_cast<size_t>(steps) * logit_tiles(M) * 2 * 1024 <= 1536 * 1024;
 }
 
 // W staged as it is (split into its two parts on the way to LDS) instead of packed by a launch of its
@@ -1699,12 +1746,13 @@ bool proj_mfma_direct(const mhcl_desc &d) {
 hipError_t launch_proj_mfma(const mhcl_desc &d, int M, const void *x, const void *Wp, const float *W,
                             float *u_raw, float *sumsq, hipStream_t s) {
   const int K = d.n * d.C;
-  const int ks = proj_ksplit(d);
+  const int spp = mfma_steps(d), ks = mfma_ksplit(d);
   return dispatch_nt_proj(logit_tiles(M), [&](auto nt) {
     constexpr int NT = decltype(nt)::value;
-    auto kern = proj_mfma_kernel<NT, false>;
+    const bool turned = proj_turned(d, M, spp);
+    auto kern = turned ? proj_mfma_kernel<NT, false, true> : proj_mfma_kernel<NT, false, false>;
     if constexpr (NT <= 4) {
-      if (proj_mfma_direct(d)) kern = proj_mfma_kernel<NT, true>;
+      if (proj_mfma_direct(d)) kern = turned ? proj_mfma_kernel<NT, true, true> : proj_mfma_kernel<NT, true, false>;
     }
     constexpr int lds = ProjCfg<NT>::kLdsBytes;
     if (lds > 64 * 1024) {
@@ -1716,7 +1764,7 @@ hipError_t launch_proj_mfma(const mhcl_desc &d, int M, const void *x, const void
     hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>((d.T + kTok - 1) / kTok), ks),
                        dim3(ProjCfg<NT>::kThreads),
                        lds, s, static_cast<const uint16_t *>(x), static_cast<const u32x4 *>(Wp), W, K,
-                       M, d.T, u_raw, sumsq);
+                       M, d.T, spp, u_raw, sumsq);
     return hipGetLastError();
   });
 }

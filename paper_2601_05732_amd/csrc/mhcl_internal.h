@@ -129,10 +129,11 @@ hipError_t launch_ds_chain(int n, int L, int64_t T, const float *H, float *colsu
 // ---- bf16 fast path (MFMA projections); needs fast_path_ok(desc) ---------
 bool fast_path_ok(const mhcl_desc &d);
 // Either projection may split K over several blocks per token tile (the MFMA one over up to
-// kMaxKSplit); u_raw and sumsq then hold that many slices ([parts][T][M], [parts][T]).
-constexpr int kMaxKSplit = 4;
+// kMaxMfmaParts); u_raw and sumsq then hold that many slices ([parts][T][M], [parts][T]).
+constexpr int kMaxMfmaParts = 16;
 int proj_ksplit(const mhcl_desc &d);
 int mfma_ksplit(const mhcl_desc &d);   // slices of launch_proj_mfma
+int64_t mfma_slices(const mhcl_desc &d);         // slices x tokens that the forward's workspace holds
 int64_t mfma_slice_tokens(const mhcl_desc &d);   // slices x tokens, at most, of T tokens or fewer
 size_t packed_w_b_bytes(const mhcl_desc &d, int M);
 // packs W (B layout) and, in the same launch, clears `nzero` floats at `zero`
