@@ -263,6 +263,12 @@ int mhcl_logits(const mhcl_desc *desc, const void *x, const float *W, const floa
                 const float *alpha, float *z, float *log_inv_nu, void *ws, size_t ws_bytes,
                 void *stream);
 
+/* mhcl_coeffs and mhcl_logits of the same inputs in one call (one projection).
+ * All outputs are required.  Workspace as for MHCL_OP_COEFFS. */
+int mhcl_coeffs_logits(const mhcl_desc *desc, const void *x, const float *W, const float *b,
+                       const float *alpha, float *H_res, float *H_pre, float *H_post, float *z,
+                       float *log_inv_nu, void *ws, size_t ws_bytes, void *stream);
+
 /* Column sums and l1 errors of L layers' per-token residual matrices and of
  * their running product over the layers (Sec. 3.1 footnote 1 and last
  * paragraph; Sec. 4.3, "per-matrix" and "prod").  n in 1..8, L >= 1, T >= 0.

@@ -25,7 +25,7 @@ _SYMBOLS = [
     "mhcl_perm_table", "mhcl_coeffs", "mhcl_pre", "mhcl_post", "mhcl_fwd_coeffs_pre",
     "mhcl_post_bwd", "mhcl_pre_bwd", "mhcl_coeffs_bwd", "mhcl_bwd_fused",
     "mhcl_logits", "mhcl_ds_chain", "mhcl_profile_next_call", "mhcl_debug_copy",
-    "mhcl_fwd_coeffs_pre_static",
+    "mhcl_fwd_coeffs_pre_static", "mhcl_coeffs_logits",
 ]
 STATIC_SCRATCH_BYTES = 16 << 20   # MHCL_STATIC_SCRATCH_BYTES
 
@@ -112,6 +112,7 @@ def lib():
         L.mhcl_coeffs_bwd.argtypes = [P] + [V] * 12 + [Z, V]
         L.mhcl_bwd_fused.argtypes = [P] + [V] * 13 + [Z, V]
         L.mhcl_logits.argtypes = [P] + [V] * 7 + [Z, V]
+        L.mhcl_coeffs_logits.argtypes = [P] + [V] * 10 + [Z, V]
         L.mhcl_ds_chain.argtypes = [ctypes.c_int32, ctypes.c_int32, ctypes.c_int64] + [V] * 7
         _lib = L
     return _lib
@@ -280,6 +281,17 @@ def mhcl_logits(d, x, W, b, alpha, z, log_inv_nu, ws):
         ctypes.byref(d.c), _ptr(x, io, (d.T, d.n, d.C), "x"), _ptr(W, f, (d.n * d.C, d.M), "W"),
         _ptr(b, f, (d.M,), "b"), _ptr(alpha, f, (3,), "alpha"), _ptr(z, f, (d.T, d.M), "z"),
         _ptr(log_inv_nu, f, (d.T,), "log_inv_nu"), wp, wb, _stream()), "mhcl_logits")
+
+
+def mhcl_coeffs_logits(d, x, W, b, alpha, H_res, H_pre, H_post, z, log_inv_nu, ws):
+    f, io = torch.float32, d.torch_dtype
+    wp, wb = _ws(ws)
+    _check(lib().mhcl_coeffs_logits(
+        ctypes.byref(d.c), _ptr(x, io, (d.T, d.n, d.C), "x"), _ptr(W, f, (d.n * d.C, d.M), "W"),
+        _ptr(b, f, (d.M,), "b"), _ptr(alpha, f, (3,), "alpha"),
+        _ptr(H_res, f, (d.T, d.n, d.n), "H_res"), _ptr(H_pre, f, (d.T, d.n), "H_pre"),
+        _ptr(H_post, f, (d.T, d.n), "H_post"), _ptr(z, f, (d.T, d.M), "z"),
+        _ptr(log_inv_nu, f, (d.T,), "log_inv_nu"), wp, wb, _stream()), "mhcl_coeffs_logits")
 
 
 def mhcl_ds_chain(n, L, T, H, colsum, l1, prod, prod_colsum, prod_l1):

@@ -101,6 +101,11 @@ bool token_per_lane(const mhcl_desc &d, bool backward);     // more tokens still
 hipError_t launch_token_coeffs(const mhcl_desc &d, const RawSums &raw, const float *b,
                                const float *alpha, float *H_res, float *H_pre, float *H_post,
                                hipStream_t s);
+// the same with the logits z [T,M] and spread [T] (see launch_logits) where token_logits_ok
+bool token_logits_ok(const mhcl_desc &d, const RawSums &raw);
+hipError_t launch_token_coeffs_logits(const mhcl_desc &d, const RawSums &raw, const float *b,
+                                      const float *alpha, float *H_res, float *H_pre, float *H_post,
+                                      float *z, float *spread, hipStream_t s);
 hipError_t launch_token_bwd_full(const mhcl_desc &d, const RawSums &raw, const float *b,
                                  const float *alpha, const float *g_H_res, const float *g_H_pre,
                                  const float *g_H_post, const BwdTokenBufs &o, hipStream_t s);

@@ -121,6 +121,7 @@ struct TokenIn {
 };
 struct TokenOut {
   float *H_res, *H_pre, *H_post;                     // forward
+  float *z, *spread;                                 // forward, optional: logits, max - min of the residual ones
   float *rec;                                        // backward: records of `rec_ld` floats
   int rec_ld;
   uint16_t *vr_hi, *vr_lo, *vrT_hi, *vrT_lo;         // fast
@@ -309,6 +310,18 @@ __global__ __launch_bounds__(kTokThreads<L>) void token_stage_kernel(TokenIn in,
       zmax = fmaxf(zmax, a[kk]);
     }
     zmax = group_reduce<L>(zmax, Max{});
+    if constexpr (!BWD) {
+      if (out.z != nullptr) {   // (all lanes take part in the minimum)
+        float zneg = -INFINITY;
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) {
+          zneg = fmaxf(zneg, owns(kk) ? -a[kk] : -INFINITY);
+          if (live && owns(kk)) out.z[t * M + logit(kk)] = a[kk];
+        }
+        zneg = group_reduce<L>(zneg, Max{});
+        if (live && l == 0) out.spread[t] = zmax + zneg;
+      }
+    }
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) a[kk] = owns(kk) ? expf(a[kk] - zmax) : 0.f;
     // Sinkhorn-Knopp: one pair of floats per line, columns in the even half steps, rows in the odd
@@ -359,8 +372,11 @@ __global__ __launch_bounds__(kTokThreads<L>) void token_stage_kernel(TokenIn in,
     for (int gi = 0; gi < GG; ++gi) {
       const int gt = l + L * gi < 2 * N ? l + L * gi : 0;
       ug[gi] = u[R + gt];
-      const float sg = sigmoidf(a_gate[gi] * (r * ug[gi]) + bg[gi]);
+      const float zg = a_gate[gi] * (r * ug[gi]) + bg[gi], sg = sigmoidf(zg);
       gate[gi] = gt < N ? sg : 2.f * sg;
+      if constexpr (!BWD) {
+        if (out.z != nullptr && live && l + L * gi < 2 * N) out.z[t * M + R + gt] = zg;
+      }
     }
 
     if constexpr (!BWD) {
@@ -925,6 +941,17 @@ hipError_t launch_token_coeffs(const mhcl_desc &d, const RawSums &raw, const flo
   // (a lane reads its slices one after the other, in fp32)
   if (raw.parts < 8 && !raw.wide && token_per_lane(d, false)) return launch_lane_coeffs(d, in, out, s);
   return launch_token_stage<kOutForward>(d, in, out, s);
+}
+
+bool token_logits_ok(const mhcl_desc &d, const RawSums &raw) {
+  return !coeffs_group_ok(d) && !(raw.parts < 8 && !raw.wide && token_per_lane(d, false));
+}
+hipError_t launch_token_coeffs_logits(const mhcl_desc &d, const RawSums &raw, const float *b,
+                                      const float *alpha, float *H_res, float *H_pre, float *H_post,
+                                      float *z, float *spread, hipStream_t s) {
+  TokenOut out{};
+  out.H_res = H_res; out.H_pre = H_pre; out.H_post = H_post; out.z = z; out.spread = spread;
+  return launch_token_stage<kOutForward>(d, token_in(d, raw, b, alpha), out, s);
 }
 
 hipError_t launch_token_bwd_fast(const mhcl_desc &d, const float *b, const float *alpha,

@@ -5,7 +5,7 @@ matrices H_res of every layer (permutation form or 20-step Sinkhorn-Knopp),
 the relative range log(1/nu) of the Sinkhorn-Knopp input (Eq. 3), the column
 sums and l1 errors of each matrix ("per-matrix" in Fig. 2) and of the product
 over the layers ("prod").  All arithmetic runs in ``libmhcl.so``
-(``mhcl_coeffs``, ``mhcl_logits``, ``mhcl_ds_chain``); this module only
+(``mhcl_coeffs_logits``, ``mhcl_ds_chain``); this module only
 allocates, draws inputs and summarises.
 
 The paper takes these statistics from trained models; those weights are not
@@ -46,8 +46,7 @@ def layer_stack(wl, L: int, inputs, device: str = "cuda"):
     for l in range(L):
         inp = inputs(l) if callable(inputs) else inputs[l]
         into = [t[l] if o is None else o for t, o in zip((H, z, spread), own)]
-        mhcl.mhcl_coeffs(d, inp["x"], inp["W"], inp["b"], inp["alpha"], into[0], Hp, Hq, ws)
-        mhcl.mhcl_logits(d, inp["x"], inp["W"], inp["b"], inp["alpha"], into[1], into[2], ws)
+        mhcl.mhcl_coeffs_logits(d, inp["x"], inp["W"], inp["b"], inp["alpha"], into[0], Hp, Hq, into[1], into[2], ws)
         for t, o in zip((H, z, spread), own):
             if o is not None:
                 t[l].copy_(o)
