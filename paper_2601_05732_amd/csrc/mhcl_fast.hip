@@ -441,8 +441,8 @@ struct ReduceCfg {
   static constexpr int kLdsBytes = 2 * kStageVec * 16;
 };
 
-template <int N, int NT, int WAVES>
-__global__ __launch_bounds__(64 * WAVES, (WAVES == 4 || N <= 3) ? 2 : 1) void bwd_reduce_kernel(
+template <int N, int NT, int WAVES, bool AHEAD>
+__global__ __launch_bounds__(64 * WAVES, AHEAD ? 1 : 2) void bwd_reduce_kernel(
     const uint16_t *__restrict__ x, const uint16_t *__restrict__ y,
     const uint16_t *__restrict__ g, const uint16_t *__restrict__ gh,
     const u32x4 *__restrict__ Wp, int C, int M, int64_t T, int steps_per_part,
@@ -547,15 +547,18 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 4 || N <= 3) ? 2 : 1) void bw
   const int rot = static_cast<int>((blockIdx.x * 13u) % static_cast<unsigned>(nst));
   auto turn = [&](int c) { const int v = c + rot; return cs0 + (v >= nst ? v - nst : v); };
   load_w(turn(0));
-  store_w(0);
-  __syncthreads();
-  if constexpr (WAVES == 8 && N >= 4) {
+  if constexpr (AHEAD) {
     // One block per CU: nothing else keeps HBM busy while the block's waves, held in step by the
     // barrier, compute.  So the NEXT step's tile is requested before this step's arithmetic
     // (two tiles in registers); requests go out in the order W(next), tile(next), so that parking
     // W in LDS waits for the W loads alone and computing on the current tile waits for nothing.
+    // (Four-wave blocks likewise while there is one per CU at most: this kernel at n = 4, C = 768, 3001 tokens
+    // 17.8 -> 15.4 us, 6000 tokens 30.0 -> 27.0.)
     Tile ta, tb2;
     load_tile(ta, turn(0));
+    __builtin_amdgcn_sched_barrier(0);
+    store_w(0);
+    __syncthreads();
     auto step = [&](const Tile &cur, Tile &nxt, int cs) {
       const int nx = cs + 1 < nst ? cs + 1 : cs;   // the last step re-requests itself (unused)
       load_w(turn(nx));
@@ -573,6 +576,8 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 4 || N <= 3) ? 2 : 1) void bw
     }
     if (cs < nst) step(ta, tb2, cs);
   } else {
+    store_w(0);
+    __syncthreads();
     Tile tile;
     for (int cs = 0; cs < nst; ++cs) {
       const int nx = cs + 1 < nst ? cs + 1 : cs;   // last step re-stages itself (unused)
@@ -740,9 +745,11 @@ __global__ __launch_bounds__(256 * SLABS, SLABS == 1 ? 2 : 1) void bwd_out_gw_ke
   const int S = blockIdx.x * SLABS + slab;
   const int c0 = S * 64 + q * 8;
   const int nS = C / 64;
-  for (int e = threadIdx.x & 255; e < kSliceVec; e += 256) {
-    const int j = e / 512, rem = e % 512;
-    lds[e] = Wa[static_cast<size_t>(j * nS + S) * 512 + rem];
+  u32x4 wst[kSliceVec / 256];   // this thread's share of the slice: on its way while the first tiles are requested
+#pragma unroll
+  for (int i = 0; i < kSliceVec / 256; ++i) {
+    const int e = (threadIdx.x & 255) + 256 * i;
+    wst[i] = Wa[static_cast<size_t>(e / 512 * nS + S) * 512 + e % 512];
   }
   const u32x4 *wl = lds + lane;
 
@@ -881,8 +888,8 @@ __global__ __launch_bounds__(256 * SLABS, SLABS == 1 ? 2 : 1) void bwd_out_gw_ke
   };
   // g_W rows of stream `wave` from the 64 tokens whose x tiles sit in LDS.  The vrT operands
   // (two 32-token blocks: wave pairs (0,1) and (2,3)) are fetched by gw_fetch, which the main
-  // loop issues BEFORE the next iteration's x tiles: loads return in order, so requested after
-  // them these small L2 hits would wait for a whole HBM round trip.
+  // loop issues BEFORE this iteration's other operands and the next one's x tiles: loads return in order, so
+  // requested after them these small L2 hits would wait for a whole HBM round trip.
   auto gw_fetch = [&](int64_t t0blk, u32x4 (&va)[2][NT][2]) {
     const int64_t blk0 = t0blk >> 5;
 #pragma unroll
@@ -930,8 +937,13 @@ __global__ __launch_bounds__(256 * SLABS, SLABS == 1 ? 2 : 1) void bwd_out_gw_ke
   In in;
   const int niter = static_cast<int>((te - tb + 63) / 64);   // same for all four waves
   load_x(in, tb + wave * 16);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < kSliceVec / 256; ++i) lds[(threadIdx.x & 255) + 256 * i] = wst[i];
   for (int it = 0; it < niter; ++it) {
     const int64_t t0 = tb + static_cast<int64_t>(it) * 64 + wave * 16;
+    u32x4 va[2][NT][2];
+    if (wave < N) gw_fetch(tb + static_cast<int64_t>(it) * 64, va);
     load_rest(in, t0);
     __syncthreads();   // everyone is done with the previous iteration's x tiles (and W is staged)
 #pragma unroll
@@ -939,8 +951,6 @@ __global__ __launch_bounds__(256 * SLABS, SLABS == 1 ? 2 : 1) void bwd_out_gw_ke
 #pragma unroll
       for (int u = 0; u < 2; ++u) xch[((j * 4 + wave) * 2 + u) * 64 + lane] = in.X[j][u];
     __syncthreads();
-    u32x4 va[2][NT][2];
-    if (wave < N) gw_fetch(tb + static_cast<int64_t>(it) * 64, va);
     __builtin_amdgcn_sched_barrier(0);
     load_x(in, t0 + 64);   // clamped to the block's last token when past the end
     __builtin_amdgcn_sched_barrier(0);
@@ -1842,6 +1852,21 @@ static int64_t out_gw_max_chunks(const mhcl_desc &d) {
   return chunks;
 }
 
+// 64-token iterations of a block where each CU has one 64-column step, in as many chunks as that allows
+static int64_t out_gw_iterations_spread(const mhcl_desc &d) {
+  int64_t chunks = 256 / (d.C / 64);
+  if (chunks > out_gw_max_chunks(d)) chunks = out_gw_max_chunks(d);
+  return chunks < 1 ? d.T : ((d.T + 63) / 64 + chunks - 1) / chunks;
+}
+// One step per CU instead of two where that takes one iteration, or three instead of twice two (the fused backward at
+// n = 4, us with two / one: C = 768, 64 tokens 36 / 30, 1000 tokens 41 / 36, 3001 tokens 56 / 53; C = 256, 3000 tokens 38 / 33;
+// two instead of twice one, 1500 tokens 44.6 / 44.4; five instead of twice three, 6000 tokens 81.5 / 83.2).
+static bool out_gw_spread(const mhcl_desc &d) {
+  const int64_t two = ((d.T + 63) / 64 + out_gw_max_chunks(d) - 1) / out_gw_max_chunks(d);
+  const int64_t one = out_gw_iterations_spread(d);
+  return one <= 3 && one < 2 * two;
+}
+
 int out_gw_tokens_per_block(const mhcl_desc &d) {
   // Token chunks: as many as make the grid one round of resident blocks (all blocks
   // then start together and the blocks of a chunk walk down the same rows side by
@@ -1849,9 +1874,10 @@ int out_gw_tokens_per_block(const mhcl_desc &d) {
   // number of 64-token iterations.  With few tokens a block is down to one of them: filling the
   // chip is worth more than sharing a block's copy of W among tokens (the fused backward at n = 4,
   // C = 1024, 2048 tokens: 126 us with at least 256 tokens per block, 109 with 128, 102 with 64).
+  if (d.T <= 0) return 64;   // (no tokens: workspace queries still divide by it)
+  if (out_gw_spread(d)) return static_cast<int>(64 * out_gw_iterations_spread(d));
   const int64_t chunks = out_gw_max_chunks(d);
-  const int64_t tpb = ((d.T + chunks - 1) / chunks + 63) / 64 * 64;
-  return tpb > 0 ? static_cast<int>(tpb) : 64;   // (no tokens: workspace queries still divide by it)
+  return static_cast<int>(((d.T + chunks - 1) / chunks + 63) / 64 * 64);
 }
 
 int gw_chunks_fast(const mhcl_desc &d) {
@@ -1937,9 +1963,9 @@ hipError_t launch_bwd_reduce(const mhcl_desc &d, int M, const void *x, const voi
                              hipStream_t s) {
   auto go = [&](auto nn, auto nt) {
     constexpr int N = decltype(nn)::value, NT = decltype(nt)::value;
-    auto launch = [&](auto wv) {
+    auto launch = [&](auto wv, auto ahead) {
       constexpr int WAVES = decltype(wv)::value;
-      auto kern = bwd_reduce_kernel<N, NT, WAVES>;
+      auto kern = bwd_reduce_kernel<N, NT, WAVES, decltype(ahead)::value>;
       hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>((d.T + 16 * WAVES - 1) / (16 * WAVES)),
                                     reduce_parts(d)),
                          dim3(64 * WAVES), (ReduceCfg<N, NT, WAVES>::kLdsBytes), s,
@@ -1949,8 +1975,10 @@ hipError_t launch_bwd_reduce(const mhcl_desc &d, int M, const void *x, const voi
                          w.u_raw, w.sumsq, w.gH_res, w.gH_post, w.gH_pre);
       return hipGetLastError();
     };
-    return reduce_wide_blocks(d) ? launch(std::integral_constant<int, 8>{})
-                                 : launch(std::integral_constant<int, 4>{});
+    if (reduce_wide_blocks(d))
+      return launch(std::integral_constant<int, 8>{}, std::bool_constant<(N >= 4)>{});
+    return (d.T + 63) / 64 * reduce_parts(d) <= 256 ? launch(std::integral_constant<int, 4>{}, std::true_type{})
+                                                    : launch(std::integral_constant<int, 4>{}, std::false_type{});
   };
   const int NT = logit_tiles(M);
   using I1 = std::integral_constant<int, 1>;
@@ -2127,7 +2155,7 @@ hipError_t launch_bwd_out_gw(const mhcl_desc &d, int M, const void *x, const voi
   const int chunks = static_cast<int>((d.T + tpb - 1) / tpb);
   float *dst = chunks == 1 ? g_W : w.partials;
   // two adjacent 64-column steps per block where C allows it
-  const bool pair = (d.C / 64) % 2 == 0;
+  const bool pair = !out_gw_spread(d) && (d.C / 64) % 2 == 0;
   auto go = [&](auto nn, auto nt) {
     constexpr int N = decltype(nn)::value, NT = decltype(nt)::value;
     constexpr int lds = (N * 4 * 2 * 64) * 2 * 16;
