@@ -291,7 +291,7 @@ int mhcl_ds_chain(int32_t n, int32_t L, int64_t T, const float *H, float *colsum
 enum {
   MHCL_STAGE_NONE = 0,
   MHCL_STAGE_FWD_PROJ = 1,   /* projection + coefficients kernel of the forward          */
-  MHCL_STAGE_FWD_PRE = 2,    /* h = H_pre x                                              */
+  MHCL_STAGE_FWD_PRE = 2,    /* h = H_pre x (with the coefficients where one launch takes both) */
   MHCL_STAGE_POST = 3,       /* x_out = H_res x + H_post y                               */
   MHCL_STAGE_BWD_REDUCE = 4, /* backward pass 1: all per-token reductions + coefficients */
   MHCL_STAGE_BWD_OUT = 5,    /* backward pass 2: g_x and g_y                             */

@@ -196,7 +196,14 @@ int run_fwd_coeffs_pre(const mhcl_desc &d, const void *x, const float *W, const 
   }
   CoeffsWs w(d, ws);
   MHCL_HIP(run_projection(d, x, W, w.u_raw, w.sumsq, w.Wp, MHCL_STAGE_FWD_PROJ, s));
-  MHCL_HIP(run_coeffs_epilogue(d, projected(d, w.u_raw, w.sumsq), b, alpha, H_res, H_pre, H_post, s));
+  const RawSums raw = projected(d, w.u_raw, w.sumsq);
+  if (group_coeffs_pre_ok(d) || token_coeffs_pre_ok(d, raw)) {
+    StageBracket br(MHCL_STAGE_FWD_PRE, s);
+    MHCL_HIP(coeffs_group_ok(d) ? launch_coeffs_pre_group(d, raw, b, alpha, x, H_res, H_pre, H_post, h, s)
+                                : launch_token_coeffs_pre(d, raw, b, alpha, x, H_res, H_pre, H_post, h, s));
+    return MHCL_OK;
+  }
+  MHCL_HIP(run_coeffs_epilogue(d, raw, b, alpha, H_res, H_pre, H_post, s));
   {
     StageBracket br(MHCL_STAGE_FWD_PRE, s);
     MHCL_HIP(launch_pre(d, x, H_pre, h, s));

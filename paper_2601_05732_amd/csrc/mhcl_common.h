@@ -164,10 +164,12 @@ __device__ __forceinline__ float slice_sum(const float *src, int slices, int wid
   if (wide) {
     const double *p = reinterpret_cast<const double *>(src);
     double s = p[at];
+#pragma unroll 4
     for (int k = 1; k < slices; ++k) s += p[k * stride + at];
     return static_cast<float>(s);
   }
   float s = src[at];
+#pragma unroll 4
   for (int k = 1; k < slices; ++k) s += src[k * stride + at];
   return s;
 }

@@ -101,6 +101,11 @@ bool token_per_lane(const mhcl_desc &d, bool backward);     // more tokens still
 hipError_t launch_token_coeffs(const mhcl_desc &d, const RawSums &raw, const float *b,
                                const float *alpha, float *H_res, float *H_pre, float *H_post,
                                hipStream_t s);
+// the coefficients and, in the same launch, h = H_pre x, where token_coeffs_pre_ok
+bool token_coeffs_pre_ok(const mhcl_desc &d, const RawSums &raw);
+hipError_t launch_token_coeffs_pre(const mhcl_desc &d, const RawSums &raw, const float *b, const float *alpha,
+                                   const void *x, float *H_res, float *H_pre, float *H_post, void *h,
+                                   hipStream_t s);
 // the same with the logits z [T,M] and spread [T] (see launch_logits) where token_logits_ok
 bool token_logits_ok(const mhcl_desc &d, const RawSums &raw);
 hipError_t launch_token_coeffs_logits(const mhcl_desc &d, const RawSums &raw, const float *b,
@@ -120,6 +125,10 @@ int64_t gz_rows_reserved(const mhcl_desc &d);   // at most, of T tokens or fewer
 hipError_t launch_coeffs_group(const mhcl_desc &d, const RawSums &raw, const float *b,
                                const float *alpha, float *H_res, float *H_pre, float *H_post,
                                hipStream_t s);
+bool group_coeffs_pre_ok(const mhcl_desc &d);   // with h in the same launch
+hipError_t launch_coeffs_pre_group(const mhcl_desc &d, const RawSums &raw, const float *b, const float *alpha,
+                                   const void *x, float *H_res, float *H_pre, float *H_post, void *h,
+                                   hipStream_t s);
 hipError_t launch_coeffs_bwd_group(const mhcl_desc &d, const RawSums &raw, const float *b,
                                    const float *alpha, const float *g_H_res, const float *g_H_pre,
                                    const float *g_H_post, const BwdTokenBufs &o, hipStream_t s);

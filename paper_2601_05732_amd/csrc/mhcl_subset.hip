@@ -8,6 +8,7 @@
 #include "mhcl_common.h"
 #include "mhcl_internal.h"
 #include "mhcl_mfma.h"
+#include "mhcl_pre.h"
 
 namespace mhcl {
 
@@ -101,12 +102,12 @@ __device__ __forceinline__ void stage_run(const F *__restrict__ src, int slices,
 
 // OWN: residual logits per lane, 8 OWN >= K
 template <int N, int OUT, bool F16ROWS, int OWN>
-__global__ __launch_bounds__(kGThreads) void coeffs_group_kernel(
+__device__ __forceinline__ void coeffs_group(
     const float *__restrict__ u_raw, const float *__restrict__ sumsq, int parts, int wide,
     const float *__restrict__ b, const float *__restrict__ alpha,
     const float *__restrict__ gH_res, const float *__restrict__ gH_pre,
     const float *__restrict__ gH_post, int gparts, int nC, float eps, int64_t T, int K,
-    const int8_t *__restrict__ sigma, const TableArg tab, int use_tab,
+    const int8_t *__restrict__ sigma, const TableArg &tab, int use_tab,
     float *__restrict__ H_res, float *__restrict__ H_pre, float *__restrict__ H_post, int CP,
     int MP32, int MP16, float *__restrict__ cpk, uint16_t *__restrict__ vr_hi,
     uint16_t *__restrict__ vr_lo, uint16_t *__restrict__ vrT_hi, uint16_t *__restrict__ vrT_lo,
@@ -334,6 +335,35 @@ __global__ __launch_bounds__(kGThreads) void coeffs_group_kernel(
   }
 }
 
+template <int N, int OUT, bool F16ROWS, int OWN>
+__global__ __launch_bounds__(kGThreads) void coeffs_group_kernel(
+    const float *__restrict__ u_raw, const float *__restrict__ sumsq, int parts, int wide,
+    const float *__restrict__ b, const float *__restrict__ alpha,
+    const float *__restrict__ gH_res, const float *__restrict__ gH_pre,
+    const float *__restrict__ gH_post, int gparts, int nC, float eps, int64_t T, int K,
+    const int8_t *__restrict__ sigma, const TableArg tab, int use_tab,
+    float *__restrict__ H_res, float *__restrict__ H_pre, float *__restrict__ H_post, int CP,
+    int MP32, int MP16, float *__restrict__ cpk, uint16_t *__restrict__ vr_hi,
+    uint16_t *__restrict__ vr_lo, uint16_t *__restrict__ vrT_hi, uint16_t *__restrict__ vrT_lo,
+    float *__restrict__ vr32, float *__restrict__ gz_sums) {
+  coeffs_group<N, OUT, F16ROWS, OWN>(
+      u_raw, sumsq, parts, wide, b, alpha, gH_res, gH_pre, gH_post, gparts, nC, eps, T, K, sigma, tab, use_tab, H_res, H_pre, H_post, CP, MP32, MP16, cpk, vr_hi, vr_lo, vrT_hi, vrT_lo, vr32, gz_sums);
+}
+// the forward's coefficients, and from block p.first on the pre-aggregate
+template <int N, int OWN, typename IO>
+__global__ __launch_bounds__(kGThreads) void coeffs_group_pre_kernel(
+    const float *__restrict__ u_raw, const float *__restrict__ sumsq, int parts, int wide,
+    const float *__restrict__ b, const float *__restrict__ alpha, float eps, int64_t T, int K,
+    const int8_t *__restrict__ sigma, const TableArg tab, int use_tab, float *__restrict__ H_res,
+    float *__restrict__ H_pre, float *__restrict__ H_post, PreArgs p) {
+  if (blockIdx.x < p.first)
+    coeffs_group<N, kGroupForward, false, OWN>(u_raw, sumsq, parts, wide, b, alpha, nullptr, nullptr, nullptr, 1,
+                                               N * p.C, eps, T, K, sigma, tab, use_tab, H_res, H_pre, H_post, 0, 0,
+                                               0, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
+  else
+    pre_from_slices<IO, N, kGThreads>(p, blockIdx.x - p.first, u_raw, sumsq, parts, wide, b, alpha, eps, T, K);
+}
+
 // table of the launch: the caller's subset, or all 120 permutations of n = 5 in
 // lexicographic order (full form), passed by value
 struct GroupTable {
@@ -399,6 +429,43 @@ hipError_t launch_coeffs_group(const mhcl_desc &d, const RawSums &raw, const flo
                        nullptr, 1, d.n * d.C, d.eps, d.T, g.K, g.sigma, g.tab, g.use_tab, H_res, H_pre,
                        H_post, 0, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
     return hipGetLastError();
+  });
+}
+
+// Two launches / one, us for both forward calls: n = 5, C = 1024, 16 tokens 36.7 / 34.7, C = 2560, 1500 tokens
+// (480 thousand 16-byte chunks of h) 88.9 / 82.2, 4000 tokens (1.3 million) 164 / 163, 16384 tokens 389 / 421, C = 320,
+// 32768 tokens 131 / 145: two blocks per compute unit fit its LDS, too few to stream.  n = 8, K = 64: C = 1024, 4000 tokens 79.4 / 71.5,
+// 16384 tokens (2.1 million chunks) 234 / 232.
+bool group_coeffs_pre_ok(const mhcl_desc &d) {
+  const bool three = 3 * group_lds_bytes(d.n, res_logits(d), false) <= 150 * 1024;
+  if (!coeffs_group_ok(d)) return false;
+  return three ? pre_chunks(d) <= (1 << 21) : pre_chunks(d) <= (1 << 19) && d.T <= 128 * kGTok;
+}
+hipError_t launch_coeffs_pre_group(const mhcl_desc &d, const RawSums &raw, const float *b, const float *alpha,
+                                   const void *x, float *H_res, float *H_pre, float *H_post, void *h,
+                                   hipStream_t s) {
+  GroupTable g;
+  if (!group_table(d, g)) return hipErrorInvalidValue;
+  const PreArgs p{x, h, static_cast<unsigned>((d.T + kGTok - 1) / kGTok), d.C};
+  RawSums r = raw;
+  if (add_first(r)) {
+    hipError_t e = add_wide_slices(d, r, s);
+    if (e != hipSuccess) return e;
+  }
+  return dispatch_io(d.io_dtype, [&](auto io) {
+    return dispatch_n(d.n, [&](auto nn) {
+      constexpr int N = decltype(nn)::value;
+      using IO = decltype(io);
+      auto kern = g.K <= 64 ? coeffs_group_pre_kernel<N, 8, IO> : coeffs_group_pre_kernel<N, 16, IO>;
+      const size_t lds = group_lds_bytes(N, g.K, false);
+      // (with the static arrays it may pass 64 KiB before it does by itself)
+      hipError_t e = allow_lds(kern, lds + sizeof(float) * (kGThreads + 1) * N + sizeof(double) * kGThreads,
+                                group_lds_bytes(N, kMaxPerm, false));
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL(kern, dim3(p.first + pre_blocks(d, kGThreads)), dim3(kGThreads), lds, s, r.u_raw, r.sumsq,
+                         r.parts, r.wide, b, alpha, d.eps, d.T, g.K, g.sigma, g.tab, g.use_tab, H_res, H_pre, H_post, p);
+      return hipGetLastError();
+    });
   });
 }
 

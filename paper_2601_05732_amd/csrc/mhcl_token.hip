@@ -7,6 +7,7 @@
 #include "mhcl_common.h"
 #include "mhcl_internal.h"
 #include "mhcl_mfma.h"
+#include "mhcl_pre.h"
 
 namespace mhcl {
 
@@ -217,7 +218,7 @@ constexpr int kSkPerIter = (MODE == MHCL_RES_SK && OUT != kOutForward)
                                ? 2 * 2 * kTokBlock<L> * kLines<N, L> : 0;
 
 template <int N, int MODE, int OUT, int L>
-__global__ __launch_bounds__(kTokThreads<L>) void token_stage_kernel(TokenIn in, TokenOut out) {
+__device__ __forceinline__ void token_stage(const TokenIn &in, const TokenOut &out) {
   constexpr int R = Dims<N, MODE>::R, M = Dims<N, MODE>::M, NN = N * N;
   constexpr int THREADS = kTokThreads<L>, BT = kTokBlock<L>, NP = kLines<N, L>;
   constexpr int CC = L == 16 ? 1 : N;                          // entries of H_res per lane
@@ -535,6 +536,20 @@ __global__ __launch_bounds__(kTokThreads<L>) void token_stage_kernel(TokenIn in,
   }
 }
 
+template <int N, int MODE, int OUT, int L>
+__global__ __launch_bounds__(kTokThreads<L>) void token_stage_kernel(TokenIn in, TokenOut out) {
+  token_stage<N, MODE, OUT, L>(in, out);
+}
+// the forward's stage, and from block p.first on the pre-aggregate
+template <int N, int MODE, int L, typename IO>
+__global__ __launch_bounds__(kTokThreads<L>) void token_pre_kernel(TokenIn in, TokenOut out, PreArgs p) {
+  if (blockIdx.x < p.first)
+    token_stage<N, MODE, kOutForward, L>(in, out);
+  else
+    pre_from_slices<IO, N, kTokThreads<L>>(p, blockIdx.x - p.first, in.u_raw, in.sumsq, in.parts, in.wide, in.b,
+                                           in.alpha, in.eps, in.T, Dims<N, MODE>::R);
+}
+
 template <int OUT>
 hipError_t launch_token_stage(const mhcl_desc &d, const TokenIn &in,
                               const TokenOut &out, hipStream_t s) {
@@ -850,6 +865,39 @@ __global__ __launch_bounds__(64) void sk_bwd_kernel(TokenIn in, TokenOut out) {
   }
 }
 
+hipError_t launch_token_pre(const mhcl_desc &d, const TokenIn &in, const TokenOut &out, const void *x, void *h,
+                            hipStream_t s) {
+  const bool many = token_stage_many(d, false);
+  const int64_t blocks64 = (d.T + 63) / 64;
+  auto go = [&](auto nn, auto mm) {
+    constexpr int N = decltype(nn)::value, MODE = decltype(mm)::value;
+    constexpr int LF = N <= 4 ? 16 : 8;
+    auto with = [&](auto ll, auto io) {
+      constexpr int L = decltype(ll)::value;
+      const PreArgs p{x, h, static_cast<unsigned>(many ? blocks64 : 2 * blocks64), d.C};
+      hipLaunchKernelGGL((token_pre_kernel<N, MODE, L, decltype(io)>),
+                         dim3(p.first + pre_blocks(d, kTokThreads<L>)), dim3(kTokThreads<L>), 0, s, in, out, p);
+      return hipGetLastError();
+    };
+    return dispatch_io(d.io_dtype, [&](auto io) {
+      if constexpr (N <= 4)
+        if (many) return with(std::integral_constant<int, 4>{}, io);
+      return with(std::integral_constant<int, LF>{}, io);
+    });
+  };
+  using L = std::integral_constant<int, MHCL_RES_LITE>;
+  using S = std::integral_constant<int, MHCL_RES_SK>;
+  const bool lite = d.res_mode == MHCL_RES_LITE;
+  switch (d.n) {
+    case 1: return lite ? go(std::integral_constant<int, 1>{}, L{}) : go(std::integral_constant<int, 1>{}, S{});
+    case 2: return lite ? go(std::integral_constant<int, 2>{}, L{}) : go(std::integral_constant<int, 2>{}, S{});
+    case 3: return lite ? go(std::integral_constant<int, 3>{}, L{}) : go(std::integral_constant<int, 3>{}, S{});
+    case 4: return lite ? go(std::integral_constant<int, 4>{}, L{}) : go(std::integral_constant<int, 4>{}, S{});
+    case 5: return lite ? hipErrorInvalidValue : go(std::integral_constant<int, 5>{}, S{});
+  }
+  return hipErrorInvalidValue;
+}
+
 hipError_t launch_lane_coeffs(const mhcl_desc &d, const TokenIn &in, const TokenOut &out, hipStream_t s) {
   auto go = [&](auto nn, auto mm) {
     hipLaunchKernelGGL((lane_coeffs_kernel<decltype(nn)::value, decltype(mm)::value>),
@@ -941,6 +989,26 @@ hipError_t launch_token_coeffs(const mhcl_desc &d, const RawSums &raw, const flo
   // (a lane reads its slices one after the other, in fp32)
   if (raw.parts < 8 && !raw.wide && token_per_lane(d, false)) return launch_lane_coeffs(d, in, out, s);
   return launch_token_stage<kOutForward>(d, in, out, s);
+}
+
+// Two launches / one, us for both forward calls, by the 16-byte chunks of h.  Permutation form, n = 4: 16 tokens of
+// C = 4096 19.7 / 17.0, C = 768, 1000 tokens 19.9 / 17.4, 3001 23.9 / 23.7, C = 1024, 5003 tokens (640 thousand
+// chunks) 39.1 / 37.6, C = 768, 8192 tokens 44.7 / 45.1; n = 2, C = 512, 9000 tokens 23.3 / 23.8; fp64 slices, f32, 4096 tokens (786 thousand) 51.6 / 50.3,
+// 20000 tokens 228 / 230; four lanes per token, C = 64, 16384 tokens (131 thousand) 19.2 / 16.5, 65536 tokens
+// 36.8 / 37.6.  Sinkhorn-Knopp, whose stage is the longer, C = 768: 3001 tokens 25.3 / 23.5, 65536 344 / 340.
+bool token_coeffs_pre_ok(const mhcl_desc &d, const RawSums &raw) {
+  if (coeffs_group_ok(d) || (raw.parts < 8 && !raw.wide && token_per_lane(d, false))) return false;
+  const int64_t chunks = pre_chunks(d);
+  if (d.res_mode == MHCL_RES_SK) return chunks <= (1 << 23);
+  if (token_stage_many(d, false) || d.n <= 2) return chunks <= (1 << 18);
+  return chunks <= (raw.wide ? 3 << 18 : 5 << 17);
+}
+hipError_t launch_token_coeffs_pre(const mhcl_desc &d, const RawSums &raw, const float *b, const float *alpha,
+                                   const void *x, float *H_res, float *H_pre, float *H_post, void *h,
+                                   hipStream_t s) {
+  TokenOut out{};
+  out.H_res = H_res; out.H_pre = H_pre; out.H_post = H_post;
+  return launch_token_pre(d, token_in(d, raw, b, alpha), out, x, h, s);
 }
 
 bool token_logits_ok(const mhcl_desc &d, const RawSums &raw) {

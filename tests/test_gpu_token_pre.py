@@ -1,0 +1,45 @@
+"""mhcl_fwd_coeffs_pre where one launch takes the coefficients and h, against the separate calls, which test_gpu_parity.py
+holds against the oracle: each lane count, blocks whose chunks of h start and end inside rows, rows of one chunk,
+gates that one thread adds (many tokens a block) and ones that many stage, both sides of the rule's lines.
+H_pre of either comes from the same sums in the same order, so h differs by fp32 rounding of the gates at most: one
+step of the stream type (2^-8 of a bf16 value, 2^-21 of its largest term for f32)."""
+import pytest
+import torch
+
+import paper_2601_05732_amd as mhcl
+import synth_inputs as si
+from gpu_harness import GpuLayer, desc_for
+
+pytestmark = pytest.mark.gpu
+
+
+def _wl(n, C, T, io="bf16", mode="lite", K=0):
+    return si.Workload(f"n{n}_c{C}_t{T}_{io}_{mode}{K}", n=n, C=C, T=T, io=io, res_mode=mode, n_perm=K, backward=False)
+
+
+CASES = [_wl(4, 4096, 1), _wl(4, 4096, 17), _wl(3, 200, 7), _wl(4, 768, 683), _wl(2, 8, 1030), _wl(1, 8, 511, "f32"),
+         _wl(4, 72, 2049, "f32"), _wl(4, 1024, 5120), _wl(4, 1024, 5121), _wl(4, 64, 16384), _wl(2, 128, 20011),
+         _wl(4, 768, 3001, mode="sk"), _wl(5, 136, 333, mode="sk"), _wl(1, 64, 70000, mode="sk"),
+         _wl(5, 1024, 16), _wl(5, 64, 65, "f32"), _wl(8, 512, 33, "bf16", "subset", 30), _wl(8, 8, 700, "bf16", "subset", 100),
+         _wl(6, 256, 2000, "f32", "subset", 20), _wl(7, 64, 3000, "bf16", "subset", 128)]
+
+
+@pytest.mark.parametrize("wl", CASES, ids=lambda w: w.name)
+def test_h_of_the_fused_call(wl):
+    print(f"case {wl}", flush=True)
+    inp = si.make_inputs(wl, seed=31, device="cuda")
+    L = GpuLayer(desc_for(wl, perm=inp.get("perm")), inp)
+    for k in ("H_res", "H_pre", "H_post", "h"):
+        getattr(L, k).fill_(float("nan"))
+    mhcl.mhcl_fwd_coeffs_pre(L.d, inp["x"], inp["W"], inp["b"], inp["alpha"], L.H_res, L.H_pre, L.H_post, L.h,
+                             mhcl.binding.new_workspace(L.d, mhcl.OP_FWD_COEFFS_PRE))
+    got = {k: getattr(L, k).clone() for k in ("H_res", "H_pre", "H_post", "h")}
+    mhcl.mhcl_coeffs(L.d, inp["x"], inp["W"], inp["b"], inp["alpha"], L.H_res, L.H_pre, L.H_post,
+                     mhcl.binding.new_workspace(L.d, mhcl.OP_COEFFS))
+    mhcl.mhcl_pre(L.d, inp["x"], L.H_pre, L.h)
+    torch.cuda.synchronize()
+    for k in ("H_res", "H_pre", "H_post"):   # (the compiler may fuse a product in one kernel and not in the other)
+        assert torch.allclose(got[k], getattr(L, k), rtol=2.0 ** -20, atol=2.0 ** -24), k
+    terms = (L.H_pre.double().unsqueeze(-1) * inp["x"].double().abs()).sum(dim=1)
+    step = 2.0 ** -8 if wl.io == "bf16" else 2.0 ** -21
+    assert bool(((got["h"].double() - L.h.double()).abs() <= step * terms).all())
