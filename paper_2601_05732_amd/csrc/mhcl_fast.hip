@@ -1695,8 +1695,8 @@ static int mfma_steps(const mhcl_desc &d) {
   int best = chunks;
   double best_cost = 0.0;
   for (int p = 1; p <= most; ++p) {
-    const int cpp = (chunks + p - 1) / p;               // chunks per part: two at least
-    if (p > 1 && (cpp < 2 || blocks * p > kMaxMfmaBlocks)) break;
+    const int cpp = (chunks + p - 1) / p;               // chunks per part: two at least, also of the last one of two
+    if (p > 1 && (chunks < 4 || cpp < 2 || blocks * p > kMaxMfmaBlocks)) break;
     const double cost = static_cast<double>((blocks * p + 255) / 256 * cpp) / chunks +
                         static_cast<double>(p * blocks) / 256 * 4 * M / K;
     if (p == 1 || cost < 0.9 * best_cost) { best = cpp; best_cost = cost; }
@@ -1736,9 +1736,10 @@ int64_t mfma_slices(const mhcl_desc &d) {
 // turned: n = 8, K = 64, C = 1024, 16384 tokens 102 / 86 us; n = 4, C = 2048, 16384 tokens 73 / 58, C = 1024, 32768
 // tokens 70 / 60, C = 768 31 / 30.  Not where the part of W that a block walks through is larger than what then
 // stays in L2 next to the stream: n = 4, C = 4096, 32768 tokens (2 MB) 192 / 203; n = 5, C = 2560, 16384 tokens (1.8 MB) 149 /
-// 158, 32768 tokens (3.6 MB) 268 / 282; at 1 MB (n = 4, C = 4096, 9000 tokens in two parts) 106 / 93.
+// 158, 32768 tokens (3.6 MB) 268 / 282; at 1 MB (n = 4, C = 4096, 9000 tokens in two parts) 106 / 93.  Nor for rows of
+// less than 2 KB, whose few chunks leave little to turn: a token's logits do not depend on its block there.
 static bool proj_turned(const mhcl_desc &d, int M, int steps) {
-  return static_cast<size_t>(steps) * logit_tiles(M) * 2 * 1024 <= 1536 * 1024;
+  return d.n * d.C >= 1024 && static_cast<size_t>(steps) * logit_tiles(M) * 2 * 1024 <= 1536 * 1024;
 }
 
 // W staged as it is (split into its two parts on the way to LDS) instead of packed by a launch of its
