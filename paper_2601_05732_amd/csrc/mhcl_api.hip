@@ -103,7 +103,9 @@ thread_local hipEvent_t t_ev_start = nullptr, t_ev_stop = nullptr;
 struct StageBracket {
   bool on;
   hipStream_t s;
-  StageBracket(int stage, hipStream_t stream) : on(stage == t_stage && t_ev_start), s(stream) {
+  // (MHCL_STAGE_NONE: no bracket, also where disarmed events are still known here, which their owner may have freed)
+  StageBracket(int stage, hipStream_t stream)
+      : on(stage != MHCL_STAGE_NONE && stage == t_stage && t_ev_start), s(stream) {
     if (on) (void)hipEventRecord(t_ev_start, s);
   }
   ~StageBracket() {
@@ -149,6 +151,32 @@ hipError_t run_coeffs_bwd_epilogue(const mhcl_desc &d, const RawSums &raw, const
   if (coeffs_group_ok(d))
     return launch_coeffs_bwd_group(d, raw, b, alpha, g_H_res, g_H_pre, g_H_post, o, s);
   return launch_token_bwd_full(d, raw, b, alpha, g_H_res, g_H_pre, g_H_post, o, s);
+}
+
+// the end of a full-precision backward: g_x (g_y), g_W, g_b, g_alpha from the per-token stage's results
+int run_bwd_out_fullprec(const mhcl_desc &d, bool fused, const void *x, const float *W, const void *g_xout,
+                         const void *g_h, const BwdWs &w, void *g_x, void *g_y, float *g_W, float *g_b,
+                         float *g_alpha, hipStream_t s) {
+  const int M = logits(d), chunks = gw_chunks_fullprec(d);
+  const size_t size = static_cast<size_t>(d.n) * d.C * M;
+  int64_t rows = gz_rows(d, false);
+  if (joint_fullprec_ok(d)) {
+    {
+      StageBracket br(fused ? MHCL_STAGE_BWD_OUT : MHCL_STAGE_NONE, s);
+      MHCL_HIP(launch_gx_gw_fullprec(d, M, fused, x, W, g_xout, g_h, w.tok, g_x, g_y, w.partials, g_W, rows, g_b,
+                                     g_alpha, s));
+    }
+    if (chunks == 1) return MHCL_OK;
+    rows = 0;
+  } else {
+    {
+      StageBracket br(fused ? MHCL_STAGE_BWD_OUT : MHCL_STAGE_NONE, s);
+      MHCL_HIP(launch_gx_fullprec(d, M, fused, x, W, g_xout, g_h, w.tok, g_x, g_y, s));
+    }
+    MHCL_HIP(launch_gw_fullprec(d, M, x, w.tok.vr, w.partials, g_W, s));
+  }
+  MHCL_HIP(launch_bwd_finish(w.partials, size, chunks, g_W, w.tok.gz, rows, M, g_b, g_alpha, s));
+  return MHCL_OK;
 }
 
 // argument checks of mhcl_fwd_coeffs_pre and its allocation-free variant
@@ -479,18 +507,12 @@ int mhcl_coeffs_bwd(const mhcl_desc *desc, const void *x, const float *W, const 
   if (!ws || !aligned16(ws) || ws_bytes < mhcl_workspace_bytes(desc, MHCL_OP_COEFFS_BWD))
     return MHCL_ERR_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int M = logits(*desc);
   BwdWs w(*desc, ws, false);
   Disarm disarm;
   MHCL_HIP(run_projection(*desc, x, W, w.u_raw, w.sumsq, w.Wp, MHCL_STAGE_BWD_REDUCE, s));
   MHCL_HIP(run_coeffs_bwd_epilogue(*desc, projected(*desc, w.u_raw, w.sumsq), b, alpha, g_H_res, g_H_pre, g_H_post,
                                    w.tok, s));
-  MHCL_HIP(launch_gx_fullprec(*desc, M, false, x, W, nullptr, nullptr, w.tok, g_x, nullptr, s));
-  MHCL_HIP(launch_gw_fullprec(*desc, M, x, w.tok.vr, w.partials, g_W, s));
-  MHCL_HIP(launch_bwd_finish(w.partials, static_cast<size_t>(desc->n) * desc->C * M,
-                             gw_chunks_fullprec(*desc), g_W, w.tok.gz, gz_rows(*desc, false), M, g_b, g_alpha,
-                             s));
-  return MHCL_OK;
+  return run_bwd_out_fullprec(*desc, false, x, W, nullptr, nullptr, w, g_x, nullptr, g_W, g_b, g_alpha, s);
 }
 
 int mhcl_bwd_fused(const mhcl_desc *desc, const void *x, const void *y, const float *W,
@@ -554,19 +576,16 @@ int mhcl_bwd_fused(const mhcl_desc *desc, const void *x, const void *y, const fl
     return MHCL_OK;
   }
   BwdWs w(*desc, ws, true);
-  MHCL_HIP(run_projection(*desc, x, W, w.u_raw, w.sumsq, w.Wp, MHCL_STAGE_BWD_REDUCE, s));
-  MHCL_HIP(launch_bwd_dots(*desc, x, y, g_xout, g_h, w.gH_res, w.gH_post, w.gH_pre, s));
+  if (joint_fullprec_ok(*desc)) {
+    StageBracket br(MHCL_STAGE_BWD_REDUCE, s);
+    MHCL_HIP(launch_proj_dots(*desc, M, x, W, y, g_xout, g_h, w.u_raw, w.sumsq, w.gH_res, w.gH_post, w.gH_pre, s));
+  } else {
+    MHCL_HIP(run_projection(*desc, x, W, w.u_raw, w.sumsq, w.Wp, MHCL_STAGE_BWD_REDUCE, s));
+    MHCL_HIP(launch_bwd_dots(*desc, x, y, g_xout, g_h, w.gH_res, w.gH_post, w.gH_pre, s));
+  }
   MHCL_HIP(run_coeffs_bwd_epilogue(*desc, projected(*desc, w.u_raw, w.sumsq), b, alpha, w.gH_res, w.gH_pre,
                                    w.gH_post, w.tok, s));
-  {
-    StageBracket br(MHCL_STAGE_BWD_OUT, s);
-    MHCL_HIP(launch_gx_fullprec(*desc, M, true, x, W, g_xout, g_h, w.tok, g_x, g_y, s));
-  }
-  MHCL_HIP(launch_gw_fullprec(*desc, M, x, w.tok.vr, w.partials, g_W, s));
-  MHCL_HIP(launch_bwd_finish(w.partials, static_cast<size_t>(desc->n) * desc->C * M,
-                             gw_chunks_fullprec(*desc), g_W, w.tok.gz, gz_rows(*desc, false), M, g_b, g_alpha,
-                             s));
-  return MHCL_OK;
+  return run_bwd_out_fullprec(*desc, true, x, W, g_xout, g_h, w, g_x, g_y, g_W, g_b, g_alpha, s);
 }
 
 }  // extern "C"

@@ -174,4 +174,35 @@ __device__ __forceinline__ float slice_sum(const float *src, int slices, int wid
   return s;
 }
 
+// Column c of the [rows, ld] matrix of g_z sums per 32 or 64 tokens, by a block's first 256 threads in a fixed order
+// (thread i takes rows i, i + 256, ... in turn, then a pairwise tree over the threads, in red[256]); columns below
+// nA go to dstA (g_b), the others to dstB (g_alpha).
+__device__ __forceinline__ void column_sum(const float *__restrict__ src, int64_t rows, int ld, int c, int nA,
+                                           float *__restrict__ dstA, float *__restrict__ dstB, float *red) {
+  const int tid = threadIdx.x;
+  float s = 0.f;
+  if (tid < 256) {
+#pragma unroll 4
+    for (int64_t r = tid; r < rows; r += 256) s += src[r * ld + c];
+    red[tid] = s;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int w = 128; w > 0; w >>= 1) {
+    if (tid < w) red[tid] += red[tid + w];
+    __syncthreads();
+  }
+  if (tid == 0) {
+    if (c < nA) dstA[c] = red[0];
+    else dstB[c - nA] = red[0];
+  }
+}
+
+// ------------------------------------------------- host: blocks of one token
+// as many waves as a row of C has 16-byte pieces for, at most four
+inline int waves_that_fit(int C, int vec) {
+  const int pieces = C / vec;
+  return pieces <= 64 ? 1 : (pieces <= 128 ? 2 : (pieces <= 192 ? 3 : 4));
+}
+
 }  // namespace mhcl

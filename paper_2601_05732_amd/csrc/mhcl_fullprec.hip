@@ -74,20 +74,21 @@ constexpr int kProjWaves = 8;
 
 // WAVES == 1: rows of one or two steps, whose other waves would only take part in the sums (n = 2, C = 8,
 // K = 126, bf16, 131072 tokens: 261 us for mhcl_coeffs with eight waves, 97 with one).
+// Block bx of `part`, of parts (fp64 slices if more than one).
 template <typename IO, int NT, int WAVES>
-__global__ __launch_bounds__(64 * WAVES, 1) void proj_fullprec_kernel(
+__device__ __forceinline__ void proj_fullprec(
     const void *__restrict__ x, const float *__restrict__ W, int nC, int M, int64_t T,
-    int steps_per_part, float *__restrict__ u_raw, float *__restrict__ sumsq) {   // (fp64 if gridDim.y > 1)
+    int steps_per_part, float *__restrict__ u_raw, float *__restrict__ sumsq, int bx, int part, int parts) {
   constexpr int V = IO::kVec;
   __shared__ double red[2][WAVES][4][64];
   __shared__ double red_ss[WAVES][16];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r = lane & 15, q = lane >> 4;
-  const int64_t t0 = static_cast<int64_t>(blockIdx.x) * 16;
+  const int64_t t0 = static_cast<int64_t>(bx) * 16;
   const int64_t tl = t0 + r < T ? t0 + r : T - 1;
   const size_t row = static_cast<size_t>(tl) * nC;
   const int nsteps = (nC + 4 * V - 1) / (4 * V);
-  const int s0 = blockIdx.y * steps_per_part;
+  const int s0 = part * steps_per_part;
   const int s1 = s0 + steps_per_part < nsteps ? s0 + steps_per_part : nsteps;
   int mj[NT];   // this lane's logit of tile j (past the last one: the last again, not stored)
 #pragma unroll
@@ -157,7 +158,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void proj_fullprec_kernel(
   // A row's one part is rounded to fp32 here; parts stay in fp64 and are rounded when they are added.
   // (Relative error of H_pre against 64 bits, f32, n = 4, C = 4096, 16 tokens: 5.7e-8 with fp32 slices, 4.0e-8.)
   auto put = [&](float *dst, int64_t at, double v) {
-    if (gridDim.y > 1)
+    if (parts > 1)
       reinterpret_cast<double *>(dst)[at] = v;
     else
       dst[at] = static_cast<float>(v);
@@ -182,15 +183,93 @@ __global__ __launch_bounds__(64 * WAVES, 1) void proj_fullprec_kernel(
       // fp64 tiles hold rows 4 i + q: token 4 i + q, logit 16 (base + j) + r
       const int64_t t = t0 + 4 * i + q;
       const int m = 16 * (base + j) + r;
-      if (t < T && m < M) put(u_raw, (blockIdx.y * T + t) * M + m, sum);
+      if (t < T && m < M) put(u_raw, (part * T + t) * M + m, sum);
     }
   }
   if (threadIdx.x < 16 && t0 + threadIdx.x < T) {   // (red_ss was complete at the barriers above)
     double sum = red_ss[0][threadIdx.x];
 #pragma unroll
     for (int w = 1; w < WAVES; ++w) sum += red_ss[w][threadIdx.x];
-    put(sumsq, blockIdx.y * T + t0 + threadIdx.x, sum);
+    put(sumsq, part * T + t0 + threadIdx.x, sum);
   }
+}
+
+template <typename IO, int NT, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, 1) void proj_fullprec_kernel(
+    const void *__restrict__ x, const float *__restrict__ W, int nC, int M, int64_t T,
+    int steps_per_part, float *__restrict__ u_raw, float *__restrict__ sumsq) {
+  proj_fullprec<IO, NT, WAVES>(x, W, nC, M, T, steps_per_part, u_raw, sumsq, blockIdx.x, blockIdx.y, gridDim.y);
+}
+
+// The n^2 + 2n reductions over C of the backward, as bwd_dots_kernel has them: `waves` waves per token, the block's
+// eight take 8 / waves tokens.  They need nothing of the projection, so one launch has blocks of both: the
+// products run at the fp64 rate and these at that of HBM, and x comes from the caches the second time.
+struct DotsArgs {
+  const void *y, *g_xout, *g_h;
+  float *g_H_res, *g_H_post, *g_H_pre;
+  int C, waves;
+};
+template <typename IO, int N>
+__device__ __forceinline__ void dots_of_tokens(const DotsArgs &p, const void *__restrict__ x, int64_t T, int block) {
+  constexpr int V = IO::kVec, D = N * N + 2 * N;
+  __shared__ float red[kProjWaves][D];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, W = p.waves, C = p.C;
+  const int per_block = kProjWaves / W, sub = wave / W;
+  const int64_t t = static_cast<int64_t>(block) * per_block + sub;
+  float dots[D];
+#pragma unroll
+  for (int e = 0; e < D; ++e) dots[e] = 0.f;
+  if (sub < per_block && t < T) {
+    for (int c = ((wave - sub * W) * 64 + lane) * V; c < C; c += 64 * W * V) {
+      float xv[N][V], gv[N][V], yv[V], gh[V];
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        IO::load(x, (t * N + j) * C + c, xv[j]);
+        IO::load(p.g_xout, (t * N + j) * C + c, gv[j]);
+      }
+      IO::load(p.y, t * C + c, yv);
+      IO::load(p.g_h, t * C + c, gh);
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+          dots[N * N + i] += gv[i][e] * yv[e];
+          dots[N * N + N + i] += gh[e] * xv[i][e];
+        }
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+#pragma unroll
+          for (int e = 0; e < V; ++e) dots[i * N + j] += gv[i][e] * xv[j][e];
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < D; ++e) {
+      const float s = wave_sum(dots[e]);
+      if (lane == 0) red[wave][e] = s;
+    }
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < per_block * D; i += 64 * kProjWaves) {
+    const int k = i / D, e = i - k * D;
+    const int64_t tt = static_cast<int64_t>(block) * per_block + k;
+    if (tt >= T) continue;
+    float s = red[k * W][e];
+    for (int w = 1; w < W; ++w) s += red[k * W + w][e];
+    if (e < N * N) p.g_H_res[tt * N * N + e] = s;
+    else if (e < N * N + N) p.g_H_post[tt * N + e - N * N] = s;
+    else p.g_H_pre[tt * N + e - N * N - N] = s;
+  }
+}
+
+template <typename IO, int N, int NT>
+__global__ __launch_bounds__(64 * kProjWaves, 1) void proj_dots_kernel(
+    const void *__restrict__ x, const float *__restrict__ W, int nC, int M, int64_t T, int steps_per_part,
+    float *__restrict__ u_raw, float *__restrict__ sumsq, int groups, int parts, DotsArgs p) {
+  const int b = static_cast<int>(blockIdx.x);
+  if (b < groups * parts)
+    proj_fullprec<IO, NT, kProjWaves>(x, W, nC, M, T, steps_per_part, u_raw, sumsq, b % groups, b / groups, parts);
+  else
+    dots_of_tokens<IO, N>(p, x, T, b - groups * parts);
 }
 
 // Element e of [u_raw | sumsq] in fp64 slices: its sum over the slices, left in the first one.  For the stages
@@ -225,18 +304,26 @@ __global__ __launch_bounds__(256) void add_slices_kernel(double *__restrict__ u_
 // 572 -> 18.5 us for bf16 n = 4, C = 1024, 5003 tokens, 301 -> 14.8 us for f32 C = 768, 4096 tokens.
 constexpr int kGwWaves = 8;
 
+// columns per lane: 16-byte pieces, 8-byte ones where the accumulators of a 16-byte bf16
+// piece (8 NT x 4 registers) no longer fit
+template <typename IO, int NT>
+constexpr int gw_piece() { return IO::kVec == 8 && NT <= 3 ? 8 : 4; }
+
+constexpr int kGwLds = 8 * kGwWaves * 64 * sizeof(f32x4);
+extern __shared__ f32x4 fullprec_lds[];   // of either role
+
 template <typename IO, int NT, int V>
-__global__ __launch_bounds__(64 * kGwWaves, 1) void gw_fullprec_kernel(
+__device__ __forceinline__ void gw_fullprec(
     const void *__restrict__ x, const float *__restrict__ vr, int nC, int M, int64_t T,
-    int64_t chunk, float *__restrict__ out) {
+    int64_t chunk, float *__restrict__ out, int bx, int by) {
   constexpr int U = NT <= 3 ? 4 : 2;   // groups per step (registers: 4 V NT are accumulators)
   constexpr int TILES = V * NT;
-  __shared__ f32x4 red[8][kGwWaves][64];
+  f32x4(*red)[kGwWaves][64] = reinterpret_cast<f32x4(*)[kGwWaves][64]>(fullprec_lds);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r = lane & 15, q = lane >> 4;
-  const int k0 = blockIdx.x * 16 * V;
+  const int k0 = bx * 16 * V;
   const int kr = k0 + V * r < nC ? k0 + V * r : nC - V;   // (lanes past the row re-read its end)
-  const int64_t tb = static_cast<int64_t>(blockIdx.y) * chunk;
+  const int64_t tb = static_cast<int64_t>(by) * chunk;
   const int64_t te = tb + chunk < T ? tb + chunk : T;
   f32x4 acc[V][NT];
 #pragma unroll
@@ -289,7 +376,7 @@ __global__ __launch_bounds__(64 * kGwWaves, 1) void gw_fullprec_kernel(
   }
 
   // the waves' sums, eight tiles at a time: wave w adds tile w over the waves, in order
-  float *dst = out + static_cast<size_t>(blockIdx.y) * nC * M;
+  float *dst = out + static_cast<size_t>(by) * nC * M;
 #pragma unroll
   for (int base = 0; base < TILES; base += 8) {
     __syncthreads();
@@ -312,6 +399,13 @@ __global__ __launch_bounds__(64 * kGwWaves, 1) void gw_fullprec_kernel(
   }
 }
 
+template <typename IO, int NT, int V>
+__global__ __launch_bounds__(64 * kGwWaves, 1) void gw_fullprec_kernel(
+    const void *__restrict__ x, const float *__restrict__ vr, int nC, int M, int64_t T,
+    int64_t chunk, float *__restrict__ out) {
+  gw_fullprec<IO, NT, V>(x, vr, nC, M, T, chunk, out, blockIdx.x, blockIdx.y);
+}
+
 // ---------------------------------------------------------------------------
 // Gradient on x.  With vr = r alpha g_z and coefx = (r^2/nC) <vr, u_raw>, the RMSNorm +
 // projection part is  W vr - x_hat coefx.
@@ -325,19 +419,30 @@ __global__ __launch_bounds__(64 * kGwWaves, 1) void gw_fullprec_kernel(
 // group s covers the logits 16 s + 4 q + i.  The block's slice of W sits in LDS for its whole
 // walk down the tokens; `win` of the eight waves take adjacent windows (so that a row visit covers
 // win x 64 contiguous bytes), the others the next tokens.
-// Bound by HBM (bf16, n = 4, C = 1024, 5003 tokens: 123 MB in 40 us; f32, C = 768, 4096 tokens,
-// FUSED: 176 MB in 45 us).  A block per token, every thread re-reading its rows of W from L2
+// Bound by HBM (by itself, bf16, n = 4, C = 1024, 5003 tokens: 123 MB in 40 us; f32, C = 768, 4096 tokens,
+// FUSED: 176 MB in 45 us; together with g_W: see gx_gw_kernel).  A block per token, every thread re-reading its rows of W from L2
 // for each token, took 340 and 218 us.
 constexpr int kGxWaves = 8;
 
-template <typename IO, int N, bool FUSED>
-__global__ __launch_bounds__(64 * kGxWaves, 1) void gx_fullprec_kernel(
+struct GxArgs {
+  const void *x;
+  const float *W;
+  const void *g_xout, *g_h;
+  const float *rec, *vr;
+  int M, S, C;
+  int64_t T;
+  int win, tokens_per_block;
+  void *g_x, *g_y;
+};
+
+template <typename IO, int N, int SC, bool FUSED>   // SC: the groups of 16 logits, 0: as S says
+__device__ __forceinline__ void gx_fullprec(
     const void *__restrict__ x, const float *__restrict__ W, const void *__restrict__ g_xout,
     const void *__restrict__ g_h, const float *__restrict__ rec, const float *__restrict__ vr, int M,
     int S, int C, int64_t T, int win, int tokens_per_block, void *__restrict__ g_x,
-    void *__restrict__ g_y) {
+    void *__restrict__ g_y, int bx, int by) {
   constexpr int V = IO::kVec, TL = V / 4, CP = token_rec<N>();
-  extern __shared__ f32x4 wl_all[];   // [window][stream][tile][group of 16 logits][lane]
+  f32x4 *wl_all = fullprec_lds;   // [window][stream][tile][group of 16 logits][lane]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r = lane & 15, q = lane >> 4;
   const int per_win = N * TL * S * 64;
@@ -347,7 +452,7 @@ __global__ __launch_bounds__(64 * kGxWaves, 1) void gx_fullprec_kernel(
     const int s = idx % S; idx /= S;
     const int h = idx % TL; idx /= TL;
     const int j = idx % N, w = idx / N;
-    const int col = (blockIdx.x * win + w) * (4 * V) + V * (lr >> 2) + 4 * h + (lr & 3);
+    const int col = (bx * win + w) * (4 * V) + V * (lr >> 2) + 4 * h + (lr & 3);
     const int m = 16 * s + 4 * lq;
     f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
     if (col < C) {
@@ -365,39 +470,44 @@ __global__ __launch_bounds__(64 * kGxWaves, 1) void gx_fullprec_kernel(
   __syncthreads();
   const int wi = wave % win, sub = wave / win, subs = kGxWaves / win;
   const f32x4 *wl = wl_all + wi * per_win + lane;
-  const int c0 = (blockIdx.x * win + wi) * (4 * V) + V * q;
+  const int c0 = (bx * win + wi) * (4 * V) + V * q;
   const bool col_ok = c0 < C;
   const int cl = col_ok ? c0 : C - V;
-  const int64_t tb = static_cast<int64_t>(blockIdx.y) * tokens_per_block;
+  const int64_t tb = static_cast<int64_t>(by) * tokens_per_block;
   const int64_t te = tb + tokens_per_block < T ? tb + tokens_per_block : T;
-  for (int64_t t0 = tb + 16 * sub; t0 < te; t0 += 16 * subs) {
-    const int64_t t = t0 + r;
-    const bool live = t < te && col_ok;
-    const int64_t tl = t < te ? t : te - 1;
-    // g: g_xout (FUSED) or the g_x so far
-    Piece<IO, V> xp[N], gp[N], hp;
+  // g: g_xout (FUSED) or the g_x so far
+  struct In {
+    Piece<IO, V> x[N], g[N], h;
+    f32x4 rc[CP / 4], b[SC > 0 ? SC : 1];
+  };
+  auto load = [&](In &in, int64_t t0) {
+    const int64_t tl = t0 + r < te ? t0 + r : te - 1;
+    // (vr ahead of the streams: loads return in order, and W vr is done while these are on their way)
+#pragma unroll
+    for (int s = 0; s < SC; ++s) in.b[s] = *reinterpret_cast<const f32x4 *>(vr + tl * (16 * S) + 16 * s + 4 * q);
+    if constexpr (SC > 0) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int j = 0; j < N; ++j) {
-      xp[j].load(x, (static_cast<size_t>(tl) * N + j) * C + cl);
-      gp[j].load(FUSED ? g_xout : g_x, (static_cast<size_t>(tl) * N + j) * C + cl);
+      in.x[j].load(x, (static_cast<size_t>(tl) * N + j) * C + cl);
+      in.g[j].load(FUSED ? g_xout : g_x, (static_cast<size_t>(tl) * N + j) * C + cl);
     }
-    if constexpr (FUSED) hp.load(g_h, static_cast<size_t>(tl) * C + cl);
-    f32x4 rc[CP / 4];
+    if constexpr (FUSED) in.h.load(g_h, static_cast<size_t>(tl) * C + cl);
 #pragma unroll
     for (int e = 0; e < CP / 4; ++e)
       if (FUSED || e == (N * N + 2 * N) / 4)
-        rc[e] = *reinterpret_cast<const f32x4 *>(rec + tl * CP + 4 * e);
-    auto cf = [&](int e) { return rc[e >> 2][e & 3]; };
+        in.rc[e] = *reinterpret_cast<const f32x4 *>(rec + tl * CP + 4 * e);
+  };
+  auto compute = [&](const In &in, int64_t t0) {
+    const int64_t t = t0 + r;
+    const bool live = t < te && col_ok;
+    auto cf = [&](int e) { return in.rc[e >> 2][e & 3]; };
     const float cx = cf(N * N + 2 * N);
-
     f32x4 acc[N][TL];
 #pragma unroll
     for (int j = 0; j < N; ++j)
 #pragma unroll
       for (int h = 0; h < TL; ++h) acc[j][h] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const float *vrow = vr + tl * (16 * S) + 4 * q;
-    for (int s = 0; s < S; ++s) {
-      const f32x4 b = *reinterpret_cast<const f32x4 *>(vrow + 16 * s);
+    auto group = [&](int s, const f32x4 &b) {
 #pragma unroll
       for (int j = 0; j < N; ++j)
 #pragma unroll
@@ -406,6 +516,15 @@ __global__ __launch_bounds__(64 * kGxWaves, 1) void gx_fullprec_kernel(
 #pragma unroll
           for (int i = 0; i < 4; ++i) acc[j][h] = mfma_f32(a[i], b[i], acc[j][h]);
         }
+    };
+    if constexpr (SC > 0) {
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int s = 0; s < SC; ++s) group(s, in.b[s]);
+      __builtin_amdgcn_sched_barrier(0);
+    } else {
+      const float *vrow = vr + (t < te ? t : te - 1) * (16 * S) + 4 * q;
+      for (int s = 0; s < S; ++s) group(s, *reinterpret_cast<const f32x4 *>(vrow + 16 * s));
     }
     if constexpr (FUSED) {
       if (g_y != nullptr && live) {   // (optional output)
@@ -414,7 +533,7 @@ __global__ __launch_bounds__(64 * kGxWaves, 1) void gx_fullprec_kernel(
         for (int e = 0; e < V; ++e) {
           gy[e] = 0.f;
 #pragma unroll
-          for (int i = 0; i < N; ++i) gy[e] += cf(N * N + N + i) * gp[i].at(e);
+          for (int i = 0; i < N; ++i) gy[e] += cf(N * N + N + i) * in.g[i].at(e);
         }
         IO::store(g_y, t * C + c0, gy);
       }
@@ -424,22 +543,69 @@ __global__ __launch_bounds__(64 * kGxWaves, 1) void gx_fullprec_kernel(
       float o[V];
 #pragma unroll
       for (int e = 0; e < V; ++e) {
-        o[e] = acc[j][e >> 2][e & 3] - xp[j].at(e) * cx;
+        o[e] = acc[j][e >> 2][e & 3] - in.x[j].at(e) * cx;
         if constexpr (FUSED) {
 #pragma unroll
-          for (int i = 0; i < N; ++i) o[e] += cf(i * N + j) * gp[i].at(e);
-          o[e] += cf(N * N + j) * hp.at(e);
+          for (int i = 0; i < N; ++i) o[e] += cf(i * N + j) * in.g[i].at(e);
+          o[e] += cf(N * N + j) * in.h.at(e);
         } else {
-          o[e] += gp[j].at(e);
+          o[e] += in.g[j].at(e);
         }
       }
       if (live) IO::store(g_x, (t * N + j) * C + c0, o);
     }
+  };
+  const int64_t step = 16 * subs;
+  int64_t t0 = tb + 16 * sub;
+  // (the next tokens' loads ahead of these tokens' work: 2 us slower at n = 4, C = 1024, bf16 and f32)
+  for (; t0 < te; t0 += step) {
+    In in;
+    load(in, t0);
+    compute(in, t0);
   }
 }
 
-// columns per wave: 16-byte pieces, 8-byte ones where the accumulators of a 16-byte bf16
-// piece (8 NT x 4 registers) no longer fit
+template <typename IO, int N, bool FUSED>
+__global__ __launch_bounds__(64 * kGxWaves, 1) void gx_fullprec_kernel(GxArgs p) {
+  gx_fullprec<IO, N, 0, FUSED>(p.x, p.W, p.g_xout, p.g_h, p.rec, p.vr, p.M, p.S, p.C, p.T, p.win, p.tokens_per_block,
+                               p.g_x, p.g_y, blockIdx.x, blockIdx.y);
+}
+
+// What is left of a backward once vr is there, in one launch: g_W (blocks [0, gw_blocks)), the columns of the g_z
+// sums (g_b and g_alpha, one block each) and g_x, g_y.  None needs another's result, and all but the columns read x.
+// With launch_proj_dots, steps in us, five launches / two or three: f32, n = 4, C = 64, 256 tokens 41.2 / 29.7; C = 768, 33
+// tokens 44.1 / 34.0, 4096 tokens 166 / 150; bf16, n = 3, C = 200, 2000 tokens 41.4 / 34.5, n = 4, 10000 tokens 136 / 113;
+// separable calls n = 4, C = 1024, 300 tokens 68 / 59, 5003 tokens 168 / 157.
+struct GwArgs {
+  int64_t chunk;
+  float *out;
+  int xblocks, blocks;
+};
+struct ColumnArgs {
+  const float *rows;   // [rows][M + 3]
+  int64_t count;
+  float *g_b, *g_alpha;
+};
+template <typename IO, int N, int NT, bool FUSED>
+__global__ __launch_bounds__(64 * kGxWaves, 1) void gx_gw_kernel(GxArgs p, GwArgs w, ColumnArgs z, int gx_xblocks) {
+  static_assert(kGxWaves == kGwWaves, "one block size");
+  int b = static_cast<int>(blockIdx.x);
+  if (b < w.blocks) {
+    gw_fullprec<IO, NT, gw_piece<IO, NT>()>(p.x, p.vr, N * p.C, p.M, p.T, w.chunk, w.out, b % w.xblocks,
+                                            b / w.xblocks);
+    return;
+  }
+  b -= w.blocks;
+  if (b < p.M + 3) {
+    column_sum(z.rows, z.count, p.M + 3, b, p.M, z.g_b, z.g_alpha, reinterpret_cast<float *>(fullprec_lds));
+    return;
+  }
+  b -= p.M + 3;
+  gx_fullprec<IO, N, NT, FUSED>(p.x, p.W, p.g_xout, p.g_h, p.rec, p.vr, p.M, NT, p.C, p.T, p.win, p.tokens_per_block,
+                            p.g_x, p.g_y, b % gx_xblocks, b / gx_xblocks);
+}
+
+// columns per wave
 int gw_columns(const mhcl_desc &d, int M) {
   return d.io_dtype == MHCL_BF16 && logit_tiles(M) <= 3 ? 128 : 64;
 }
@@ -546,26 +712,108 @@ int gw_chunks_fullprec(const mhcl_desc &d) {
   return c < 1 ? 1 : static_cast<int>(c);
 }
 
+// (n, logit tiles) of the forms whose two roles are built as one launch: the full permutation form up to n = 4 and
+// Sinkhorn-Knopp; at more tiles the products' registers would leave the other role short of waves
+template <typename F>
+static hipError_t dispatch_joint(const mhcl_desc &d, F &&f) {
+  const int NT = logit_tiles(res_logits(d) + 2 * d.n);
+  auto go = [&](auto nn, auto nt) { return NT == decltype(nt)::value ? f(nn, nt) : hipErrorInvalidValue; };
+  using std::integral_constant;
+  switch (d.n) {
+    case 1: return go(integral_constant<int, 1>{}, integral_constant<int, 1>{});
+    case 2: return go(integral_constant<int, 2>{}, integral_constant<int, 1>{});
+    case 3: return go(integral_constant<int, 3>{}, integral_constant<int, 1>{});
+    case 4: return go(integral_constant<int, 4>{}, integral_constant<int, 2>{});
+    case 5: return go(integral_constant<int, 5>{}, integral_constant<int, 3>{});
+  }
+  return hipErrorInvalidValue;
+}
+// (the bound keeps the joint grid below 2^32 threads)
+bool joint_fullprec_ok(const mhcl_desc &d) { return !coeffs_group_ok(d) && d.T <= (1 << 22); }
+
+hipError_t launch_proj_dots(const mhcl_desc &d, int M, const void *x, const float *W, const void *y,
+                            const void *g_xout, const void *g_h, float *u_raw, float *sumsq, float *g_H_res,
+                            float *g_H_post, float *g_H_pre, hipStream_t s) {
+  const int V = d.io_dtype == MHCL_BF16 ? BF16::kVec : F32::kVec;
+  const int nC = d.n * d.C, parts = proj_fullprec_parts(d);
+  const int nsteps = (nC + 4 * V - 1) / (4 * V), spp = (nsteps + parts - 1) / parts;
+  const int groups = static_cast<int>((d.T + 15) / 16);
+  const DotsArgs p{y, g_xout, g_h, g_H_res, g_H_post, g_H_pre, d.C, waves_that_fit(d.C, V)};
+  const int per_block = kProjWaves / p.waves;
+  const int64_t blocks = groups * static_cast<int64_t>(parts) + (d.T + per_block - 1) / per_block;
+  return dispatch_io(d.io_dtype, [&](auto io) {
+    return dispatch_joint(d, [&](auto nn, auto nt) {
+      hipLaunchKernelGGL((proj_dots_kernel<decltype(io), decltype(nn)::value, decltype(nt)::value>),
+                         dim3(static_cast<unsigned>(blocks)), dim3(64 * kProjWaves), 0, s, x, W, nC, M, d.T, spp,
+                         u_raw, sumsq, groups, parts, p);
+      return hipGetLastError();
+    });
+  });
+}
+
 hipError_t launch_gw_fullprec(const mhcl_desc &d, int M, const void *x, const float *vr,
                               float *partials, float *g_W, hipStream_t s) {
   const int chunks = gw_chunks_fullprec(d), cols = gw_columns(d, M), nC = d.n * d.C;
   const int64_t chunk = (d.T + chunks - 1) / chunks;
   float *dst = chunks == 1 ? g_W : partials;
   const dim3 grid((nC + cols - 1) / cols, chunks);
-  auto go = [&](auto io, auto nt, auto vv) {
-    using IO = decltype(io);
-    constexpr int NT = decltype(nt)::value, V = decltype(vv)::value;
-    hipLaunchKernelGGL((gw_fullprec_kernel<IO, NT, V>), grid, dim3(64 * kGwWaves), 0, s, x, vr, nC,
-                       M, d.T, chunk, dst);
-    return hipGetLastError();
-  };
   return dispatch_io(d.io_dtype, [&](auto io) {   // (the chunks are added by launch_bwd_finish)
     return dispatch_tiles(logit_tiles(M), [&](auto nt) {
       using IO = decltype(io);
-      if constexpr (IO::kVec == 8 && decltype(nt)::value <= 3)
-        return go(io, nt, std::integral_constant<int, 8>{});
-      else
-        return go(io, nt, std::integral_constant<int, 4>{});
+      constexpr int NT = decltype(nt)::value;
+      hipLaunchKernelGGL((gw_fullprec_kernel<IO, NT, gw_piece<IO, NT>()>), grid, dim3(64 * kGwWaves), kGwLds, s, x,
+                         vr, nC, M, d.T, chunk, dst);
+      return hipGetLastError();
+    });
+  });
+}
+
+// Windows of W per block, blocks along C and tokens per block: one round of resident blocks, two per compute unit,
+// or one beside that of launch_gw_fullprec's role (whole step or separable calls, two / one: f32, n = 4, C = 768,
+// 4096 tokens 153 / 150 us; bf16, C = 1024, 5003 tokens 162 / 156, C = 200, 10000 tokens 123 / 113)
+struct GxShape {
+  int win, lds, xblocks, tokens_per_block, chunks;
+};
+static GxShape gx_shape(const mhcl_desc &d, int S, bool joint) {
+  const int V = d.io_dtype == MHCL_BF16 ? BF16::kVec : F32::kVec;
+  const int per_win = d.n * (V / 4) * S * 1024;   // bytes of W in LDS per window (144 KiB at most)
+  const int windows = (d.C + 4 * V - 1) / (4 * V);
+  GxShape g;
+  g.win = kGxWaves;   // adjacent windows per block: two blocks per compute unit where possible
+  while (g.win > 1 && (g.win * per_win > 64 * 1024 || g.win > windows)) g.win /= 2;
+  g.lds = g.win * per_win;
+  g.xblocks = (windows + g.win - 1) / g.win;
+  const int64_t step = 16 * (kGxWaves / g.win);     // tokens of one round of the block's waves
+  int64_t chunks = (!joint && g.lds <= 80 * 1024 ? 512 : 256) / g.xblocks;
+  if (chunks < 1) chunks = 1;
+  g.tokens_per_block = static_cast<int>(((d.T + chunks - 1) / chunks + step - 1) / step * step);
+  g.chunks = static_cast<int>((d.T + g.tokens_per_block - 1) / g.tokens_per_block);
+  return g;
+}
+
+hipError_t launch_gx_gw_fullprec(const mhcl_desc &d, int M, bool fused, const void *x, const float *W,
+                                 const void *g_xout, const void *g_h, const BwdTokenBufs &o, void *g_x, void *g_y,
+                                 float *partials, float *g_W, int64_t gz_count, float *g_b, float *g_alpha,
+                                 hipStream_t s) {
+  const GxShape g = gx_shape(d, logit_tiles(M), true);
+  const int cols = gw_columns(d, M), chunks = gw_chunks_fullprec(d);
+  GwArgs w;
+  w.chunk = (d.T + chunks - 1) / chunks;
+  w.out = chunks == 1 ? g_W : partials;
+  w.xblocks = (d.n * d.C + cols - 1) / cols;
+  w.blocks = w.xblocks * chunks;
+  const ColumnArgs z{o.gz, gz_count, g_b, g_alpha};
+  const GxArgs p{x, W, g_xout, g_h, o.rec, o.vr, M, logit_tiles(M), d.C, d.T, g.win, g.tokens_per_block, g_x, g_y};
+  const unsigned blocks = w.blocks + M + 3 + g.xblocks * g.chunks;
+  return dispatch_io(d.io_dtype, [&](auto io) {
+    return dispatch_joint(d, [&](auto nn, auto nt) {
+      using IO = decltype(io);
+      constexpr int N = decltype(nn)::value, NT = decltype(nt)::value;
+      auto kern = fused ? gx_gw_kernel<IO, N, NT, true> : gx_gw_kernel<IO, N, NT, false>;
+      // (up to three tiles a window of W is at most 64 KiB)
+      hipLaunchKernelGGL(kern, dim3(blocks), dim3(64 * kGxWaves), g.lds > kGwLds ? g.lds : kGwLds, s, p, w, z,
+                         g.xblocks);
+      return hipGetLastError();
     });
   });
 }
@@ -573,30 +821,22 @@ hipError_t launch_gw_fullprec(const mhcl_desc &d, int M, const void *x, const fl
 hipError_t launch_gx_fullprec(const mhcl_desc &d, int M, bool fused, const void *x, const float *W,
                               const void *g_xout, const void *g_h, const BwdTokenBufs &o, void *g_x,
                               void *g_y, hipStream_t s) {
-  const int V = d.io_dtype == MHCL_BF16 ? BF16::kVec : F32::kVec, S = logit_tiles(M);
-  const int per_win = d.n * (V / 4) * S * 1024;   // bytes of W in LDS per window (144 KiB at most)
-  const int windows = (d.C + 4 * V - 1) / (4 * V);
-  int win = kGxWaves;   // adjacent windows per block: two blocks per compute unit where possible
-  while (win > 1 && (win * per_win > 64 * 1024 || win > windows)) win /= 2;
-  const int lds = win * per_win, xb = (windows + win - 1) / win;
-  const int64_t step = 16 * (kGxWaves / win);     // tokens of one round of the block's waves
-  int64_t chunks = (lds <= 80 * 1024 ? 512 : 256) / xb;   // one round of resident blocks
-  if (chunks < 1) chunks = 1;
-  int64_t tpb = ((d.T + chunks - 1) / chunks + step - 1) / step * step;
-  const dim3 grid(xb, static_cast<unsigned>((d.T + tpb - 1) / tpb));
+  const int S = logit_tiles(M);
+  const GxShape g = gx_shape(d, S, false);
+  const GxArgs p{x, W, g_xout, g_h, o.rec, o.vr, M, S, d.C, d.T, g.win, g.tokens_per_block, g_x, g_y};
+  const dim3 grid(g.xblocks, g.chunks);
   return dispatch_io(d.io_dtype, [&](auto io) {
     return dispatch_n(d.n, [&](auto nn) {
       using IO = decltype(io);
       constexpr int N = decltype(nn)::value;
       auto kern = fused ? gx_fullprec_kernel<IO, N, true> : gx_fullprec_kernel<IO, N, false>;
-      if (lds > 64 * 1024) {   // (one window then; the limit of the kernel, whatever thread launches it with how many logits)
+      if (g.lds > 64 * 1024) {   // (one window then; the limit of the kernel, whatever thread launches it with how many logits)
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize,
                                            N * (IO::kVec / 4) * 9 * 1024);
         if (e != hipSuccess) return e;
       }
-      hipLaunchKernelGGL(kern, grid, dim3(64 * kGxWaves), lds, s, x, W, g_xout, g_h, o.rec, o.vr, M, S,
-                         d.C, d.T, win, static_cast<int>(tpb), g_x, g_y);
+      hipLaunchKernelGGL(kern, grid, dim3(64 * kGxWaves), g.lds, s, p);
       return hipGetLastError();
     });
   });

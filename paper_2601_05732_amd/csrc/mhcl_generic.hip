@@ -37,11 +37,6 @@ hipError_t dispatch_waves(std::integer_sequence<int, W...>, int waves, F &&f) {
   ((waves == W ? (void)(e = f(std::integral_constant<int, W>{})) : (void)0), ...);
   return e;
 }
-// as many waves as a row of C has 16-byte pieces for, at most four
-int waves_that_fit(int C, int vec) {
-  const int pieces = C / vec;
-  return pieces <= 64 ? 1 : (pieces <= 128 ? 2 : (pieces <= 192 ? 3 : 4));
-}
 // post_bwd_kernel: waves that fit, against four always (idle waves take registers and wait at the sums;
 // us per call, four / as many as fit): n = 4, C = 64, 4096 tokens 30.1 / 11.6, C = 1024, 32768 tokens 233 /
 // 165, n = 8, f32, C = 768 759 / 584.  Four where all blocks are resident at once anyway (n = 8, C = 64,
@@ -268,9 +263,7 @@ __global__ __launch_bounds__(64 * WAVES) void bwd_dots_kernel(
 // another (256 chunks of n = 3, C = 64: 11 -> 6 us with 16 groups instead of 4); with blocks enough for the
 // chip they do not, since a group's loads are then 64 bytes long instead of 256 (64 chunks of n = 4, C = 512:
 // 8.2 us with 16 groups, 4.3 with 4).
-// Block nbW + c: column c of the [rows, ld] matrix of g_z sums per 32 or 64 tokens, added in a
-// fixed order (thread i takes rows i, i + 256, ... in turn, then a pairwise tree over the
-// threads); columns below nA go to dstA (g_b), the others to dstB (g_alpha).
+// Block nbW + c: column c of the [rows, ld] matrix of g_z sums per 32 or 64 tokens (none if its launch has had them).
 template <int GR>
 __global__ __launch_bounds__(kBlock) void bwd_finish_kernel(const float *__restrict__ part,
                                                             size_t size, int chunks, int nbW,
@@ -298,21 +291,7 @@ __global__ __launch_bounds__(kBlock) void bwd_finish_kernel(const float *__restr
     }
     return;
   }
-  const int c = static_cast<int>(blockIdx.x) - nbW;
-  float s = 0.f;
-#pragma unroll 4
-  for (int64_t r = threadIdx.x; r < rows; r += kBlock) s += src[r * ld + c];
-  red[threadIdx.x] = s;
-  __syncthreads();
-#pragma unroll
-  for (int w = kBlock / 2; w > 0; w >>= 1) {
-    if (static_cast<int>(threadIdx.x) < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    if (c < nA) dstA[c] = red[0];
-    else dstB[c - nA] = red[0];
-  }
+  column_sum(src, rows, ld, static_cast<int>(blockIdx.x) - nbW, nA, dstA, dstB, red);
 }
 
 __global__ __launch_bounds__(kBlock) void fill_zero_kernel(float *__restrict__ p, size_t count) {
@@ -420,7 +399,7 @@ hipError_t launch_bwd_finish(const float *partials, size_t size, int chunks, flo
   auto go = [&](auto gr) {
     constexpr int GR = decltype(gr)::value;
     const int nbW = chunks > 1 ? static_cast<int>(blocks_for(size, kBlock / GR)) : 0;
-    hipLaunchKernelGGL(bwd_finish_kernel<GR>, dim3(nbW + M + 3), dim3(kBlock), 0, s, partials, size,
+    hipLaunchKernelGGL(bwd_finish_kernel<GR>, dim3(nbW + (rows > 0 ? M + 3 : 0)), dim3(kBlock), 0, s, partials, size,
                        chunks, nbW, g_W, gz_rows, rows, M + 3, M, g_b, g_alpha);
     return hipGetLastError();
   };

@@ -95,6 +95,17 @@ hipError_t launch_gx_fullprec(const mhcl_desc &d, int M, bool fused, const void 
                              const void *g_xout, const void *g_h, const BwdTokenBufs &o, void *g_x,
                              void *g_y, hipStream_t s);
 
+// What does not wait for each other, as one launch, where joint_fullprec_ok: launch_proj_fullprec with
+// launch_bwd_dots; launch_gx_fullprec with launch_gw_fullprec and the sums behind g_b and g_alpha (gz_count rows)
+bool joint_fullprec_ok(const mhcl_desc &d);
+hipError_t launch_proj_dots(const mhcl_desc &d, int M, const void *x, const float *W, const void *y,
+                            const void *g_xout, const void *g_h, float *u_raw, float *sumsq, float *g_H_res,
+                            float *g_H_post, float *g_H_pre, hipStream_t s);
+hipError_t launch_gx_gw_fullprec(const mhcl_desc &d, int M, bool fused, const void *x, const float *W,
+                                 const void *g_xout, const void *g_h, const BwdTokenBufs &o, void *g_x, void *g_y,
+                                 float *partials, float *g_W, int64_t gz_count, float *g_b, float *g_alpha,
+                                 hipStream_t s);
+
 // ---- per-token stage of the other forms (n <= 4, Sinkhorn-Knopp) --------------
 bool token_stage_many(const mhcl_desc &d, bool backward);   // the variant for many tokens
 bool token_per_lane(const mhcl_desc &d, bool backward);     // more tokens still
@@ -217,7 +228,7 @@ hipError_t launch_bwd_out_gw(const mhcl_desc &d, int M, const void *x, const voi
 hipError_t launch_bwd_gw(const mhcl_desc &d, int M, const void *x, const FastBwdWs &w, float *g_W,
                          hipStream_t s);
 // g_W from the chunks' partial sums (none if chunks == 1) and g_b, g_alpha from the
-// [rows, M+3] sums of g_z, in one launch
+// [rows, M+3] sums of g_z (none if rows == 0), in one launch
 hipError_t launch_bwd_finish(const float *partials, size_t size, int chunks, float *g_W,
                              const float *gz_rows, int64_t rows, int M, float *g_b, float *g_alpha,
                              hipStream_t s);
