@@ -542,7 +542,7 @@ int mhcl_bwd_fused(const mhcl_desc *desc, const void *x, const void *y, const fl
   if (fast_bwd_ok(*desc)) {
     FastBwdWs f(*desc, ws);
     const bool wide = fast_bwd_wide(*desc);
-    MHCL_HIP(launch_pack_w_ab(*desc, M, W, f, s));
+    if (!narrow_direct(*desc)) MHCL_HIP(launch_pack_w_ab(*desc, M, W, f, s));
     {
       StageBracket br(MHCL_STAGE_BWD_REDUCE, s);
       if (wide) {
@@ -552,7 +552,7 @@ int mhcl_bwd_fused(const mhcl_desc *desc, const void *x, const void *y, const fl
           MHCL_HIP(launch_proj_mfma(*desc, M, x, f.Wp, W, f.u_raw, f.sumsq, s));
         MHCL_HIP(launch_bwd_dots_fast(*desc, x, y, g_xout, g_h, f, s));
       } else {
-        MHCL_HIP(launch_bwd_reduce(*desc, M, x, y, g_xout, g_h, f, s));
+        MHCL_HIP(launch_bwd_reduce(*desc, M, x, y, W, g_xout, g_h, f, s));
       }
     }
     if (coeffs_group_ok(*desc))
@@ -568,7 +568,8 @@ int mhcl_bwd_fused(const mhcl_desc *desc, const void *x, const void *y, const fl
       MHCL_HIP(launch_bwd_gw(*desc, M, x, f, g_W, s));
     } else {
       StageBracket br(MHCL_STAGE_BWD_OUT, s);
-      MHCL_HIP(launch_bwd_out_gw(*desc, M, x, g_xout, g_h, f, g_x, g_y, g_W, s));
+      MHCL_HIP(launch_bwd_out_gw(*desc, M, x, W, g_xout, g_h, f, g_x, g_y, g_W, gz_rows(*desc, true), g_b, g_alpha, s));
+      if (fast_gw_chunks(*desc) == 1) return MHCL_OK;
     }
     MHCL_HIP(launch_bwd_finish(f.partials, static_cast<size_t>(desc->n) * desc->C * M,
                                fast_gw_chunks(*desc), g_W, f.gz, gz_rows(*desc, true), M, g_b, g_alpha,

@@ -174,16 +174,20 @@ __device__ __forceinline__ float slice_sum(const float *src, int slices, int wid
   return s;
 }
 
-// Column c of the [rows, ld] matrix of g_z sums per 32 or 64 tokens, by a block's first 256 threads in a fixed order
-// (thread i takes rows i, i + 256, ... in turn, then a pairwise tree over the threads, in red[256]); columns below
-// nA go to dstA (g_b), the others to dstB (g_alpha).
-__device__ __forceinline__ void column_sum(const float *__restrict__ src, int64_t rows, int ld, int c, int nA,
-                                           float *__restrict__ dstA, float *__restrict__ dstB, float *red) {
+// Columns of the [count, ld] matrix of g_z sums per 32 or 64 tokens, which add up to g_b and g_alpha.
+struct ColumnArgs {
+  const float *rows;
+  int64_t count;
+  float *g_b, *g_alpha;
+};
+// Column c, by a block's first 256 threads in a fixed order (thread i takes rows i, i + 256, ... in turn, then a
+// pairwise tree over the threads, in red[256]); columns below M go to g_b, the others to g_alpha.
+__device__ __forceinline__ void column_sum(const ColumnArgs &p, int ld, int c, int M, float *red) {
   const int tid = threadIdx.x;
   float s = 0.f;
   if (tid < 256) {
 #pragma unroll 4
-    for (int64_t r = tid; r < rows; r += 256) s += src[r * ld + c];
+    for (int64_t r = tid; r < p.count; r += 256) s += p.rows[r * ld + c];
     red[tid] = s;
   }
   __syncthreads();
@@ -193,8 +197,8 @@ __device__ __forceinline__ void column_sum(const float *__restrict__ src, int64_
     __syncthreads();
   }
   if (tid == 0) {
-    if (c < nA) dstA[c] = red[0];
-    else dstB[c - nA] = red[0];
+    if (c < M) p.g_b[c] = red[0];
+    else p.g_alpha[c - M] = red[0];
   }
 }
 

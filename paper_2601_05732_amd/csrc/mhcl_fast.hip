@@ -441,11 +441,13 @@ struct ReduceCfg {
   static constexpr int kLdsBytes = 2 * kStageVec * 16;
 };
 
-template <int N, int NT, int WAVES, bool AHEAD>
+// DIRECT: W is taken as it is and split into its two parts on the way to LDS, as in proj_mfma_kernel
+// (narrow_direct).
+template <int N, int NT, int WAVES, bool AHEAD, bool DIRECT>
 __global__ __launch_bounds__(64 * WAVES, AHEAD ? 1 : 2) void bwd_reduce_kernel(
     const uint16_t *__restrict__ x, const uint16_t *__restrict__ y,
     const uint16_t *__restrict__ g, const uint16_t *__restrict__ gh,
-    const u32x4 *__restrict__ Wp, int C, int M, int64_t T, int steps_per_part,
+    const u32x4 *__restrict__ Wp, const float *__restrict__ W, int C, int M, int64_t T, int steps_per_part,
     float *__restrict__ u_raw, float *__restrict__ sumsq, float *__restrict__ gH_res,
     float *__restrict__ gH_post, float *__restrict__ gH_pre) {
   // gridDim.y blocks share the columns of the same tokens: block (bx, part) walks the 64-column
@@ -466,7 +468,14 @@ __global__ __launch_bounds__(64 * WAVES, AHEAD ? 1 : 2) void bwd_reduce_kernel(
   const int ncs = C / 64;   // 64-column steps; also per-stream stride of W in such steps
 
   struct Tile { u32x4 X[N][2], G[N][2], Y[2], H[2]; };
-  u32x4 wst[Cfg::WV];
+  constexpr int kItems = Cfg::kStageVec / 2, WI = (kItems + Cfg::kThreads - 1) / Cfg::kThreads;
+  u32x4 wst[DIRECT ? 1 : Cfg::WV];
+  float wraw[DIRECT ? WI : 1][8];
+  // item i of this thread: eight rows of a logit, (stream, u, tile) block and lane
+  auto item = [&](int i) {
+    const int o = i * Cfg::kThreads + threadIdx.x;
+    return o < kItems ? o : kItems - 1;   // surplus threads repeat the last one
+  };
   f32x4 acc[NT], ss = f32x4{0.f, 0.f, 0.f, 0.f};
   float dots[D];
 #pragma unroll
@@ -490,8 +499,20 @@ __global__ __launch_bounds__(64 * WAVES, AHEAD ? 1 : 2) void bwd_reduce_kernel(
   };
   // W blocks of step cs: for stream j the 2 K steps 2 (j ncs + cs) + u, NT tiles, hi/lo
   auto load_w = [&](int cs) {
+    if constexpr (DIRECT) {
 #pragma unroll
-    for (int i = 0; i < Cfg::WV; ++i) {
+      for (int i = 0; i < WI; ++i) {
+        const int o = item(i), blk = o >> 6, jt = blk % NT, u = blk / NT % 2, j = blk / NT / 2;
+        const int col = 16 * jt + (o & 15);
+        const float *from = W + (static_cast<size_t>(j * ncs + cs) * 64 + 32 * u + 8 * ((o >> 4) & 3)) * M +
+                            (col < M ? col : M - 1);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) wraw[i][e] = from[e * M];
+      }
+      return;
+    }
+#pragma unroll
+    for (int i = 0; i < (DIRECT ? 0 : Cfg::WV); ++i) {
       int e = i * Cfg::kThreads + threadIdx.x;
       if (e > Cfg::kStageVec - 1) e = Cfg::kStageVec - 1;   // surplus threads repeat the last one
       const int j = e / (NT * 256), rem = e % (NT * 256);
@@ -499,8 +520,23 @@ __global__ __launch_bounds__(64 * WAVES, AHEAD ? 1 : 2) void bwd_reduce_kernel(
     }
   };
   auto store_w = [&](int buf) {
+    if constexpr (DIRECT) {
 #pragma unroll
-    for (int i = 0; i < Cfg::WV; ++i) {
+      for (int i = 0; i < WI; ++i) {
+        const int o = item(i), blk = o >> 6;
+        if (16 * (blk % NT) + (o & 15) >= M) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) wraw[i][e] = 0.f;
+        }
+        u32x4 hi, lo;
+        split8(wraw[i], std::false_type{}, hi, lo);
+        lds[buf * Cfg::kStageVec + (blk * 2 + 0) * 64 + (o & 63)] = hi;
+        lds[buf * Cfg::kStageVec + (blk * 2 + 1) * 64 + (o & 63)] = lo;
+      }
+      return;
+    }
+#pragma unroll
+    for (int i = 0; i < (DIRECT ? 0 : Cfg::WV); ++i) {
       int e = i * Cfg::kThreads + threadIdx.x;
       if (e > Cfg::kStageVec - 1) e = Cfg::kStageVec - 1;
       lds[buf * Cfg::kStageVec + e] = wst[i];
@@ -724,10 +760,14 @@ __global__ __launch_bounds__(256) void bwd_dots_fast_kernel(
 // with x^T obtained by an MFMA against a 0/1 selection matrix (exact) as in
 // bwd_gw_kernel.  Accumulators stay in registers over the block's token chunk;
 // partial sums per chunk go to `gw_part` and are added in chunk order.
-template <int N, int NT, int SLABS>
+// Blocks of the first `xblocks` along x; where there is one chunk of tokens, the others sum the columns of g_z (g_b and
+// g_alpha), which then need no launch of their own (steps of 1 to 64 tokens 37 to 39 us / 30 to 34).
+// DIRECT: W is taken as it is and split into its two parts on the way to LDS (narrow_direct).
+template <int N, int NT, int SLABS, bool DIRECT>
 __global__ __launch_bounds__(256 * SLABS, SLABS == 1 ? 2 : 1) void bwd_out_gw_kernel(
     const uint16_t *__restrict__ x, const uint16_t *__restrict__ g,
-    const uint16_t *__restrict__ gh, const u32x4 *__restrict__ Wa, const float *__restrict__ cpk,
+    const uint16_t *__restrict__ gh, const u32x4 *__restrict__ Wa, const float *__restrict__ W, int xblocks,
+    ColumnArgs columns, const float *__restrict__ cpk,
     const uint16_t *__restrict__ vr_hi, const uint16_t *__restrict__ vr_lo,
     const uint16_t *__restrict__ vrT_hi, const uint16_t *__restrict__ vrT_lo, int MP16, int M, int C,
     int64_t T, int tokens_per_block, int CP, uint16_t *__restrict__ g_x,
@@ -738,6 +778,10 @@ __global__ __launch_bounds__(256 * SLABS, SLABS == 1 ? 2 : 1) void bwd_out_gw_ke
   // SLABS adjacent 64-column steps per block, four waves each, all on the same tokens at
   // the same time: a row visit of the block then covers SLABS x 128 contiguous bytes
   extern __shared__ u32x4 lds_all[];
+  if (static_cast<int>(blockIdx.x) >= xblocks) {
+    column_sum(columns, M + 3, static_cast<int>(blockIdx.x) - xblocks, M, reinterpret_cast<float *>(lds_all));
+    return;
+  }
   const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) & 3, slab = threadIdx.x >> 8;
   u32x4 *lds = lds_all + slab * (2 * kSliceVec);
   u32x4 *xch = lds + kSliceVec;               // x tiles of one iteration: [stream][wave][u][lane]
@@ -745,11 +789,31 @@ __global__ __launch_bounds__(256 * SLABS, SLABS == 1 ? 2 : 1) void bwd_out_gw_ke
   const int S = blockIdx.x * SLABS + slab;
   const int c0 = S * 64 + q * 8;
   const int nS = C / 64;
-  u32x4 wst[kSliceVec / 256];   // this thread's share of the slice: on its way while the first tiles are requested
+  // this thread's share of the slice: on its way while the first tiles are requested
+  u32x4 wst[DIRECT ? 1 : kSliceVec / 256];
+  float wraw[DIRECT ? N : 1][8];   // of stream i: eight logits of a row (those past the last one are zeroed below)
+  const int wlane = threadIdx.x & 63, wh4 = (threadIdx.x >> 6) & 3, wcol = 8 * (wlane >> 4);
+  if constexpr (DIRECT) {
+    const int row = 64 * S + 32 * (wh4 >> 1) + 8 * ((wlane & 15) >> 2) + 4 * (wh4 & 1) + (wlane & 3);
 #pragma unroll
-  for (int i = 0; i < kSliceVec / 256; ++i) {
-    const int e = (threadIdx.x & 255) + 256 * i;
-    wst[i] = Wa[static_cast<size_t>(e / 512 * nS + S) * 512 + e % 512];
+    for (int i = 0; i < N; ++i) {
+      const float *from = W + (static_cast<size_t>(i) * C + row) * M;
+      if (M % 8 == 0) {
+        const float *at = from + (wcol < M ? wcol : M - 8);
+        const f32x4 a = *reinterpret_cast<const f32x4 *>(at), b = *reinterpret_cast<const f32x4 *>(at + 4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { wraw[i][e] = a[e]; wraw[i][4 + e] = b[e]; }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) wraw[i][e] = from[wcol + e < M ? wcol + e : M - 1];
+      }
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < kSliceVec / 256; ++i) {
+      const int e = (threadIdx.x & 255) + 256 * i;
+      wst[i] = Wa[static_cast<size_t>(e / 512 * nS + S) * 512 + e % 512];
+    }
   }
   const u32x4 *wl = lds + lane;
 
@@ -938,8 +1002,21 @@ __global__ __launch_bounds__(256 * SLABS, SLABS == 1 ? 2 : 1) void bwd_out_gw_ke
   const int niter = static_cast<int>((te - tb + 63) / 64);   // same for all four waves
   load_x(in, tb + wave * 16);
   __builtin_amdgcn_sched_barrier(0);
+  if constexpr (DIRECT) {
 #pragma unroll
-  for (int i = 0; i < kSliceVec / 256; ++i) lds[(threadIdx.x & 255) + 256 * i] = wst[i];
+    for (int i = 0; i < N; ++i) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (wcol + e >= M) wraw[i][e] = 0.f;
+      u32x4 hi, lo;
+      split8(wraw[i], std::false_type{}, hi, lo);
+      lds[i * 512 + (wh4 * 2 + 0) * 64 + wlane] = hi;
+      lds[i * 512 + (wh4 * 2 + 1) * 64 + wlane] = lo;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < kSliceVec / 256; ++i) lds[(threadIdx.x & 255) + 256 * i] = wst[i];
+  }
   for (int it = 0; it < niter; ++it) {
     const int64_t t0 = tb + static_cast<int64_t>(it) * 64 + wave * 16;
     u32x4 va[2][NT][2];
@@ -1959,20 +2036,29 @@ hipError_t launch_pack_w_ab(const mhcl_desc &d, int M, const float *W, const Fas
   return hipGetLastError();
 }
 
-hipError_t launch_bwd_reduce(const mhcl_desc &d, int M, const void *x, const void *y,
+// Few tokens: the launch that packs W is a tenth of the step; with more, every block splits W again.  Steps, us, packed /
+// as it is: n = 4, C = 768, 100 tokens 43.7 / 41.4, 3001 (Sinkhorn-Knopp) 74.4 / 72.6, 8000 124.5 / 125.3, 16384 239 / 242;
+// C = 4096, 200 tokens 66.5 / 65.2, 2000 159.5 / 159.6; n = 2, C = 1024, 3000 tokens 52.9 / 51.3; n = 3, C = 1024, 500 tokens
+// 38.8 / 39.0, 4000 73.2 / 75.1 (rows of 12 or 15 logits: eight of them are no aligned vectors).
+bool narrow_direct(const mhcl_desc &d) { return !fast_bwd_wide(d) && d.T <= (d.n == 3 ? 1024 : 4096); }
+
+hipError_t launch_bwd_reduce(const mhcl_desc &d, int M, const void *x, const void *y, const float *W,
                              const void *g_xout, const void *g_h, const FastBwdWs &w,
                              hipStream_t s) {
   auto go = [&](auto nn, auto nt) {
     constexpr int N = decltype(nn)::value, NT = decltype(nt)::value;
     auto launch = [&](auto wv, auto ahead) {
       constexpr int WAVES = decltype(wv)::value;
-      auto kern = bwd_reduce_kernel<N, NT, WAVES, decltype(ahead)::value>;
+      auto kern = bwd_reduce_kernel<N, NT, WAVES, decltype(ahead)::value, false>;
+      if constexpr (WAVES == 4) {
+        if (narrow_direct(d)) kern = bwd_reduce_kernel<N, NT, WAVES, decltype(ahead)::value, true>;
+      }
       hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>((d.T + 16 * WAVES - 1) / (16 * WAVES)),
                                     reduce_parts(d)),
                          dim3(64 * WAVES), (ReduceCfg<N, NT, WAVES>::kLdsBytes), s,
                          static_cast<const uint16_t *>(x), static_cast<const uint16_t *>(y),
                          static_cast<const uint16_t *>(g_xout), static_cast<const uint16_t *>(g_h),
-                         reinterpret_cast<const u32x4 *>(w.Wp), d.C, M, d.T, reduce_steps(d),
+                         reinterpret_cast<const u32x4 *>(w.Wp), W, d.C, M, d.T, reduce_steps(d),
                          w.u_raw, w.sumsq, w.gH_res, w.gH_post, w.gH_pre);
       return hipGetLastError();
     };
@@ -2149,12 +2235,13 @@ hipError_t launch_bwd_out_wide(const mhcl_desc &d, int M, const void *x, const v
 }
 
 // g_x, g_y and g_W from one pass (n <= 4)
-hipError_t launch_bwd_out_gw(const mhcl_desc &d, int M, const void *x, const void *g_xout,
+hipError_t launch_bwd_out_gw(const mhcl_desc &d, int M, const void *x, const float *W, const void *g_xout,
                              const void *g_h, const FastBwdWs &w, void *g_x, void *g_y, float *g_W,
-                             hipStream_t s) {
+                             int64_t gz_count, float *g_b, float *g_alpha, hipStream_t s) {
   const int tpb = out_gw_tokens_per_block(d);
   const int chunks = static_cast<int>((d.T + tpb - 1) / tpb);
   float *dst = chunks == 1 ? g_W : w.partials;
+  const ColumnArgs columns{w.gz, gz_count, g_b, g_alpha};
   // two adjacent 64-column steps per block where C allows it
   const bool pair = !out_gw_spread(d) && (d.C / 64) % 2 == 0;
   auto go = [&](auto nn, auto nt) {
@@ -2162,16 +2249,17 @@ hipError_t launch_bwd_out_gw(const mhcl_desc &d, int M, const void *x, const voi
     constexpr int lds = (N * 4 * 2 * 64) * 2 * 16;
     auto launch = [&](auto sl) {
       constexpr int SL = decltype(sl)::value;
-      auto kern = bwd_out_gw_kernel<N, NT, SL>;
+      auto kern = narrow_direct(d) ? bwd_out_gw_kernel<N, NT, SL, true> : bwd_out_gw_kernel<N, NT, SL, false>;
       if (lds * SL > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, lds * SL);
         if (e != hipSuccess) return e;
       }
-      hipLaunchKernelGGL(kern, dim3(d.C / 64 / SL, chunks), dim3(256 * SL), lds * SL, s,
+      const int xblocks = d.C / 64 / SL;
+      hipLaunchKernelGGL(kern, dim3(xblocks + (chunks == 1 ? M + 3 : 0), chunks), dim3(256 * SL), lds * SL, s,
                          static_cast<const uint16_t *>(x), static_cast<const uint16_t *>(g_xout),
-                         static_cast<const uint16_t *>(g_h), reinterpret_cast<const u32x4 *>(w.Wa),
-                         w.cpk, w.vr_hi, w.vr_lo, w.vrT_hi, w.vrT_lo, w.MP16, M, d.C, d.T, tpb,
+                         static_cast<const uint16_t *>(g_h), reinterpret_cast<const u32x4 *>(w.Wa), W, xblocks,
+                         columns, w.cpk, w.vr_hi, w.vr_lo, w.vrT_hi, w.vrT_lo, w.MP16, M, d.C, d.T, tpb,
                          w.CP, static_cast<uint16_t *>(g_x), static_cast<uint16_t *>(g_y), dst);
       return hipGetLastError();
     };

@@ -581,11 +581,6 @@ struct GwArgs {
   float *out;
   int xblocks, blocks;
 };
-struct ColumnArgs {
-  const float *rows;   // [rows][M + 3]
-  int64_t count;
-  float *g_b, *g_alpha;
-};
 template <typename IO, int N, int NT, bool FUSED>
 __global__ __launch_bounds__(64 * kGxWaves, 1) void gx_gw_kernel(GxArgs p, GwArgs w, ColumnArgs z, int gx_xblocks) {
   static_assert(kGxWaves == kGwWaves, "one block size");
@@ -597,7 +592,7 @@ __global__ __launch_bounds__(64 * kGxWaves, 1) void gx_gw_kernel(GxArgs p, GwArg
   }
   b -= w.blocks;
   if (b < p.M + 3) {
-    column_sum(z.rows, z.count, p.M + 3, b, p.M, z.g_b, z.g_alpha, reinterpret_cast<float *>(fullprec_lds));
+    column_sum(z, p.M + 3, b, p.M, reinterpret_cast<float *>(fullprec_lds));
     return;
   }
   b -= p.M + 3;

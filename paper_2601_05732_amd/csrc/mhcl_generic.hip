@@ -267,11 +267,7 @@ __global__ __launch_bounds__(64 * WAVES) void bwd_dots_kernel(
 template <int GR>
 __global__ __launch_bounds__(kBlock) void bwd_finish_kernel(const float *__restrict__ part,
                                                             size_t size, int chunks, int nbW,
-                                                            float *__restrict__ out,
-                                                            const float *__restrict__ src,
-                                                            int64_t rows, int ld, int nA,
-                                                            float *__restrict__ dstA,
-                                                            float *__restrict__ dstB) {
+                                                            float *__restrict__ out, ColumnArgs columns, int M) {
   constexpr int EB = kBlock / GR;
   __shared__ float red[kBlock];
   if (static_cast<int>(blockIdx.x) < nbW) {
@@ -291,7 +287,7 @@ __global__ __launch_bounds__(kBlock) void bwd_finish_kernel(const float *__restr
     }
     return;
   }
-  column_sum(src, rows, ld, static_cast<int>(blockIdx.x) - nbW, nA, dstA, dstB, red);
+  column_sum(columns, M + 3, static_cast<int>(blockIdx.x) - nbW, M, red);
 }
 
 __global__ __launch_bounds__(kBlock) void fill_zero_kernel(float *__restrict__ p, size_t count) {
@@ -400,7 +396,7 @@ hipError_t launch_bwd_finish(const float *partials, size_t size, int chunks, flo
     constexpr int GR = decltype(gr)::value;
     const int nbW = chunks > 1 ? static_cast<int>(blocks_for(size, kBlock / GR)) : 0;
     hipLaunchKernelGGL(bwd_finish_kernel<GR>, dim3(nbW + (rows > 0 ? M + 3 : 0)), dim3(kBlock), 0, s, partials, size,
-                       chunks, nbW, g_W, gz_rows, rows, M + 3, M, g_b, g_alpha);
+                       chunks, nbW, g_W, ColumnArgs{gz_rows, rows, g_b, g_alpha}, M);
     return hipGetLastError();
   };
   return chunks > 32 && size < 64 * 256 ? go(std::integral_constant<int, 16>{}) : go(std::integral_constant<int, 4>{});

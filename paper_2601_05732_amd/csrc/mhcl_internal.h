@@ -208,7 +208,9 @@ struct FastBwdWs {
 };
 hipError_t launch_pack_w_ab(const mhcl_desc &d, int M, const float *W, const FastBwdWs &w,
                             hipStream_t s);
-hipError_t launch_bwd_reduce(const mhcl_desc &d, int M, const void *x, const void *y,
+// whether the two passes of n <= 4 take W as it is (else packed by launch_pack_w_ab)
+bool narrow_direct(const mhcl_desc &d);
+hipError_t launch_bwd_reduce(const mhcl_desc &d, int M, const void *x, const void *y, const float *W,
                              const void *g_xout, const void *g_h, const FastBwdWs &w,
                              hipStream_t s);
 hipError_t launch_bwd_dots_fast(const mhcl_desc &d, const void *x, const void *y, const void *g_xout,
@@ -222,9 +224,10 @@ hipError_t launch_bwd_epilogue_group(const mhcl_desc &d, const float *b, const f
 hipError_t launch_bwd_out_wide(const mhcl_desc &d, int M, const void *x, const void *g_xout,
                                const void *g_h, const FastBwdWs &w, void *g_x, void *g_y,
                                hipStream_t s);
-hipError_t launch_bwd_out_gw(const mhcl_desc &d, int M, const void *x, const void *g_xout,
+// (with one chunk of tokens also g_b and g_alpha, from the gz_count rows of g_z sums)
+hipError_t launch_bwd_out_gw(const mhcl_desc &d, int M, const void *x, const float *W, const void *g_xout,
                              const void *g_h, const FastBwdWs &w, void *g_x, void *g_y, float *g_W,
-                             hipStream_t s);
+                             int64_t gz_count, float *g_b, float *g_alpha, hipStream_t s);
 hipError_t launch_bwd_gw(const mhcl_desc &d, int M, const void *x, const FastBwdWs &w, float *g_W,
                          hipStream_t s);
 // g_W from the chunks' partial sums (none if chunks == 1) and g_b, g_alpha from the
