@@ -18,7 +18,11 @@ namespace {
 // Block = 64 tokens, 512 threads (one token per lane leaves a single wave per CU walking K-long
 // dependent loops over strided global loads).  The block first stages its tokens' logits, summed over the
 // K-split slices, with contiguous loads into LDS; lane l of a token then owns
-// the logits k = l, l + 8, ... (softmax, g_a, g_z) and row l of H_res.
+// the logits k = l, l + 8, ... (softmax, g_a, g_z).  Bound by a chain of short phases with one block per compute unit; of
+// 91 thousand cycles at n = 5, backward, 14 were the rows of H_res (matrix cores now), 32 vr read eight logits or tokens
+// at a time with bank conflicts, divisions and a factor per element (vr stands in LDS now, rows an odd number of 16-byte
+// pieces long).  Steps, us before / now: n = 5, C = 512, 16 tokens 112 / 98, 3000 tokens 179 / 164, C = 2560, 16384 tokens 1255 /
+// 1239; n = 8, K = 64, C = 1024, 16384 tokens 805 / 799; forward n = 5, C = 512, 4000 tokens 52.8 / 48.7.
 //   kGroupForward: H_res, H_pre, H_post
 //   kGroupFast   : for the bf16 backward, in the layouts its MFMAs read:
 //     cpk  [T][CP] f32 : H_res (N*N) | H_pre (N) | H_post (N) | coefx
@@ -51,22 +55,25 @@ __device__ __forceinline__ float group_max(float v) {
   return v;
 }
 
-// floats of dynamic LDS the kernel needs (plus K * N table bytes)
+// row length of the LDS arrays of M logits: whole 16-byte pieces, an odd number of them
+__host__ __device__ constexpr int group_ld(int M) { return 4 * (((M + 3) / 4) | 1); }
+
+// dynamic LDS the kernel needs, eight table bytes per permutation among it
 inline size_t group_lds_bytes(int N, int K, bool bwd) {
-  const int M = K + 2 * N, ld = M | 1;
-  size_t fl = 2 * static_cast<size_t>(kGTok) * ld + kGTok;
+  size_t fl = 2 * static_cast<size_t>(kGTok) * group_ld(K + 2 * N) + kGTok;
   if (bwd) fl += static_cast<size_t>(kGTok) * (N * N + 1) + 4 * kGTok;
-  return fl * sizeof(float) + static_cast<size_t>(K) * N;
+  return fl * sizeof(float) + static_cast<size_t>(K) * 8;
 }
 
 // dst[tok][0..W) = the sums over the slices of src [slices][T][W] for the block's 64 tokens (past the
-// last one: some valid element again), slices in order.  Eight elements per thread and three more
+// last one: some valid element again), slices in order.  Nine elements per thread and three more
 // slices of each are on their way together: with one slice of four elements at a time the
 // block, alone on its CU, spent 20 us in round trips at n = 5.
 template <typename F>
 __device__ __forceinline__ void stage_run(const F *__restrict__ src, int slices, int64_t T,
                                           int64_t t0, int W, float *dst, int ld) {
-  constexpr int E = 8, S = sizeof(F) == 4 ? 3 : 1;
+  constexpr int E = 9, S = sizeof(F) == 4 ? 3 : 1;
+  const unsigned per = 0xffffffffu / static_cast<unsigned>(W) + 1;   // e / W is the high word of e per
   const int64_t stride = T * W, base = t0 * W;
   for (int e0 = threadIdx.x; e0 < kGTok * W; e0 += E * kGThreads) {
     F s[E];
@@ -95,7 +102,8 @@ __device__ __forceinline__ void stage_run(const F *__restrict__ src, int slices,
 #pragma unroll
     for (int v = 0; v < E; ++v) {
       const int e = e0 + v * kGThreads;
-      if (e < kGTok * W) dst[(e / W) * ld + e % W] = static_cast<float>(s[v]);
+      const int row = W == 1 ? e : static_cast<int>(__umulhi(static_cast<unsigned>(e), per));
+      if (e < kGTok * W) dst[row * ld + e - row * W] = static_cast<float>(s[v]);
     }
   }
 }
@@ -113,21 +121,22 @@ __device__ __forceinline__ void coeffs_group(
     uint16_t *__restrict__ vr_lo, uint16_t *__restrict__ vrT_hi, uint16_t *__restrict__ vrT_lo,
     float *__restrict__ vr32, float *__restrict__ gz_sums) {
   constexpr bool BWD = OUT != kGroupForward;
-  extern __shared__ float smem[];
-  const int M = K + 2 * N, ld = M | 1;
+  extern __shared__ __align__(16) float smem[];
+  const int M = K + 2 * N, ld = group_ld(M);
   constexpr int NN = N * N, gld = NN + 1;
-  float *u_s = smem;                              // [64][ld]  raw logits
+  float *u_s = smem;                              // [64][ld]  raw logits, later vr
   float *a_s = u_s + kGTok * ld;                  // [64][ld]  softmax weights, later g_z
   float *g_s = a_s + kGTok * ld;                  // [64][gld] g_H_res            (BWD)
   float *r_s = g_s + (BWD ? kGTok * gld : 0);     // [64]      RMSNorm scale
   float *t_s = r_s + kGTok;                       // [64][4]   sums of g_z u per group, row scale (BWD)
-  int8_t *sig = reinterpret_cast<int8_t *>(t_s + (BWD ? 4 * kGTok : 0));   // [K][N]
+  int8_t *sig = reinterpret_cast<int8_t *>(t_s + (BWD ? 4 * kGTok : 0));   // [K][8], N of them used
   const int tid = threadIdx.x;
   const int64_t t0 = static_cast<int64_t>(blockIdx.x) * kGTok;
 
   // stage: table (entries clamped to 0..N-1), logits, scale, g_H_res
-  for (int i = tid; i < K * N; i += kGThreads) {
-    int v = use_tab ? tab.s[i] : sigma[i];
+  for (int i = tid; i < K * 8; i += kGThreads) {
+    const int at = (i >> 3) * N + ((i & 7) < N ? i & 7 : 0);
+    int v = use_tab ? tab.s[at] : sigma[at];
     v = v < 0 ? 0 : (v > N - 1 ? N - 1 : v);
     sig[i] = static_cast<int8_t>(v);
   }
@@ -157,7 +166,7 @@ __device__ __forceinline__ void coeffs_group(
   const int64_t tl = live ? t : T - 1;
   const float r = r_s[tok];
   const float a0 = alpha[0], a1 = alpha[1], a2 = alpha[2];
-  const float *ut = u_s + tok * ld;
+  float *ut = u_s + tok * ld;
   float *at = a_s + tok * ld;
 
   // softmax over the K residual logits; own[] = this lane's weights
@@ -184,22 +193,27 @@ __device__ __forceinline__ void coeffs_group(
   }
   __syncthreads();
 
-  // row l of H_res = sum_k a_k P_k, k ascending
-  if (l < N) {
-    float row[N];
+  // H_res = sum_k a_k P_k: the weights of 16 tokens times the 0/1 matrix of the table, in fp32 on the matrix cores (a
+  // lane per row that walked the K permutations took 14 thousand cycles of 90 at n = 5)
+  {
+    constexpr int CT = (NN + 15) / 16;   // tiles of 16 entries
+    const int lane = tid & 63, rr = lane & 15, q = lane >> 4;
+    for (int tile = tid >> 6; tile < kGTok / 16 * CT; tile += kGThreads / 64) {
+      const int tk0 = 16 * (tile / CT), cell = 16 * (tile % CT) + rr;
+      const int ci = cell < NN ? cell / N : 0, cj = cell < NN ? cell % N : -1;
+      const float *aw = a_s + (tk0 + rr) * ld;
+      f32x4 h = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+      for (int k0 = 0; k0 < K; k0 += 4) {
+        const int k = k0 + q < K ? k0 + q : K - 1;
+        const float w = k0 + q < K ? aw[k] : 0.f;
+        h = mfma_f32(w, sig[k * 8 + ci] == cj ? 1.f : 0.f, h);
+      }
 #pragma unroll
-    for (int j = 0; j < N; ++j) row[j] = 0.f;
-#pragma unroll 8
-    for (int k = 0; k < K; ++k) {
-      const float w = at[k];
-      const int sj = sig[k * N + l];
-#pragma unroll
-      for (int j = 0; j < N; ++j) row[j] += (j == sj) ? w : 0.f;
-    }
-    if (live) {
-      float *dst = BWD ? cpk + t * CP + l * N : H_res + t * NN + l * N;
-#pragma unroll
-      for (int j = 0; j < N; ++j) dst[j] = row[j];
+      for (int i = 0; i < 4; ++i) {
+        const int64_t tt = t0 + tk0 + 4 * q + i;
+        if (tt < T && cell < NN) (BWD ? cpk + tt * CP : H_res + tt * NN)[cell] = h[i];
+      }
     }
   }
 
@@ -216,9 +230,10 @@ __device__ __forceinline__ void coeffs_group(
     float meanp = 0.f;
 #pragma unroll
     for (int kk = 0; kk < OWN; ++kk) {
+      const u32x2 row = *reinterpret_cast<const u32x2 *>(sig + kc(kk) * 8);
       float sg = 0.f;
 #pragma unroll
-      for (int i = 0; i < N; ++i) sg += gt[i * N + sig[kc(kk) * N + i]];
+      for (int i = 0; i < N; ++i) sg += gt[i * N + ((row[i >> 2] >> (8 * (i & 3))) & 0xffu)];
       gown[kk] = sg;
       meanp += owns(kk) ? own[kk] * sg : 0.f;
     }
@@ -231,7 +246,10 @@ __device__ __forceinline__ void coeffs_group(
       const float g = ok ? own[kk] * (gown[kk] - mean) : 0.f;
       const float uk = ut[kc(kk)];
       const float v = ok ? r * a0 * g : 0.f;
-      if (owns(kk)) at[l + 8 * kk] = g;
+      if (owns(kk)) {   // (a lane that has no logit kk re-reads the last one's place, and drops it)
+        at[l + 8 * kk] = g;
+        ut[l + 8 * kk] = v;
+      }
       gap[0] += ok ? g * (r * uk) : 0.f;   // (selected: uk may be infinite where there is no logit or token)
       dotp += ok ? v * uk : 0.f;
       vmaxp = fmaxf(vmaxp, fabsf(v));
@@ -257,10 +275,12 @@ __device__ __forceinline__ void coeffs_group(
       }
       at[K + l] = gp;
       at[K + N + l] = gq;
-      const float vp = r * a1 * gp, vq = r * a2 * gq;
+      const float vp = live ? r * a1 * gp : 0.f, vq = live ? r * a2 * gq : 0.f;
+      ut[K + l] = vp;
+      ut[K + N + l] = vq;
       gap[1] = live ? gp * (r * up) : 0.f;
       gap[2] = live ? gq * (r * uq) : 0.f;
-      dotp += vp * up + vq * uq;
+      dotp += live ? vp * up + vq * uq : 0.f;
       vmaxp = fmaxf(vmaxp, fmaxf(fabsf(vp), fabsf(vq)));
     }
     const float dot = group_sum(dotp);
@@ -280,41 +300,34 @@ __device__ __forceinline__ void coeffs_group(
     }
     __syncthreads();
 
-    // vr = r alpha_g g_z of logit m of block token tk (zero past the last logit)
-    auto vr_of = [&](int tk, int m) {
-      if (m >= M) return 0.f;
-      const float al = m < K ? a0 : (m < K + N ? a1 : a2);
-      return r_s[tk] * al * a_s[tk * ld + m];
-    };
+    // vr = r alpha_g g_z, zero past the last logit
     if constexpr (OUT == kGroupFull) {
-      for (int e = tid; e < kGTok * MP16; e += kGThreads) {
-        const int tk = e / MP16, m = e - tk * MP16;
-        if (t0 + tk < T) vr32[(t0 + tk) * MP16 + m] = vr_of(tk, m);
-      }
+      if (live)
+        for (int m = l; m < MP16; m += 8) vr32[t * MP16 + m] = m < M ? ut[m] : 0.f;
     } else {
-    // rows [Tpad][MP32]: eight consecutive logits of one token per thread
-    const int nvec = MP32 / 8;
-    for (int e = tid; e < kGTok * nvec; e += kGThreads) {
-      const int tk = e / nvec, v8 = e - tk * nvec;
-      const float inv = F16ROWS ? t_s[tk * 4 + 3] : 1.f;
+    // rows [Tpad][MP32]: eight consecutive logits at a time, by the token's lanes
+    const float inv = F16ROWS ? t_s[tok * 4 + 3] : 1.f;
+    for (int v8 = l; v8 < MP32 / 8; v8 += 8) {
+      const f32x4 lo4 = *reinterpret_cast<const f32x4 *>(ut + 8 * v8);   // (past the row: another one's, not used)
+      const f32x4 hi4 = *reinterpret_cast<const f32x4 *>(ut + 8 * v8 + 4);
       float v[8];
       u32x4 hi, lo;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = vr_of(tk, 8 * v8 + i) * inv;
+      for (int i = 0; i < 8; ++i) v[i] = 8 * v8 + i < M ? (i < 4 ? lo4[i] : hi4[i - 4]) * inv : 0.f;
       split8(v, std::bool_constant<F16ROWS>{}, hi, lo);
-      const size_t off = static_cast<size_t>(t0 + tk) * MP32 + 8 * v8;
+      const size_t off = static_cast<size_t>(t) * MP32 + 8 * v8;
       *reinterpret_cast<u32x4 *>(vr_hi + off) = hi;
       *reinterpret_cast<u32x4 *>(vr_lo + off) = lo;
     }
     // tokens innermost [Tpad/32][MP16][32]: eight consecutive tokens of one logit per thread
     const int64_t blk0 = t0 >> 5;
-    for (int e = tid; e < 2 * MP16 * 4; e += kGThreads) {
-      const int half = e / (MP16 * 4), rem = e - half * (MP16 * 4);
-      const int m = rem >> 2, tg = rem & 3;
+    for (int e = tid; e < 8 * MP16; e += kGThreads) {
+      const int m = e >> 3, half = (e >> 2) & 1, tg = e & 3;
+      const float *src = u_s + (half * 32 + tg * 8) * ld + (m < M ? m : M - 1);
       float v[8];
       u32x4 hi, lo;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = vr_of(half * 32 + tg * 8 + i, m);
+      for (int i = 0; i < 8; ++i) v[i] = m < M ? src[i * ld] : 0.f;
       split8(v, std::false_type{}, hi, lo);
       const size_t off = (static_cast<size_t>(blk0 + half) * MP16 + m) * 32 + tg * 8;
       *reinterpret_cast<u32x4 *>(vrT_hi + off) = hi;
