@@ -264,30 +264,33 @@ __global__ __launch_bounds__(64 * WAVES) void bwd_dots_kernel(
 // chip they do not, since a group's loads are then 64 bytes long instead of 256 (64 chunks of n = 4, C = 512:
 // 8.2 us with 16 groups, 4.3 with 4).
 // Block nbW + c: column c of the [rows, ld] matrix of g_z sums per 32 or 64 tokens (none if its launch has had them).
-template <int GR>
+// V: elements of a thread, four where that leaves blocks for the chip (steps, us, one / four: n = 5, C = 2560, 16384 tokens
+// 1239 / 1232, C = 2048, 100 tokens 146.7 / 142.6; n = 7, K = 100 755 / 751; n = 4, C = 2048, 4000 tokens 154.9 / 154.0).
+template <int GR, int V>
 __global__ __launch_bounds__(kBlock) void bwd_finish_kernel(const float *__restrict__ part,
                                                             size_t size, int chunks, int nbW,
                                                             float *__restrict__ out, ColumnArgs columns, int M) {
+  using Vec = float __attribute__((ext_vector_type(V)));
   constexpr int EB = kBlock / GR;
-  __shared__ float red[kBlock];
+  __shared__ Vec red[kBlock];
   if (static_cast<int>(blockIdx.x) < nbW) {
     const int el = threadIdx.x % EB, grp = threadIdx.x / EB;
-    const size_t i = static_cast<size_t>(blockIdx.x) * EB + el;
-    float s = 0.f;
+    const size_t i = (static_cast<size_t>(blockIdx.x) * EB + el) * V;   // (size is a multiple of V)
+    Vec s = 0.f;
     if (i < size) {
 #pragma unroll 8
-      for (int c = grp; c < chunks; c += GR) s += part[c * size + i];
+      for (int c = grp; c < chunks; c += GR) s += *reinterpret_cast<const Vec *>(part + c * size + i);
     }
     red[threadIdx.x] = s;
     __syncthreads();
     if (grp == 0 && i < size) {
 #pragma unroll
       for (int w = 1; w < GR; ++w) s += red[w * EB + el];
-      out[i] = s;
+      *reinterpret_cast<Vec *>(out + i) = s;
     }
     return;
   }
-  column_sum(columns, M + 3, static_cast<int>(blockIdx.x) - nbW, M, red);
+  column_sum(columns, M + 3, static_cast<int>(blockIdx.x) - nbW, M, reinterpret_cast<float *>(red));
 }
 
 __global__ __launch_bounds__(kBlock) void fill_zero_kernel(float *__restrict__ p, size_t count) {
@@ -392,14 +395,17 @@ hipError_t launch_bwd_dots(const mhcl_desc &d, const void *x, const void *y, con
 hipError_t launch_bwd_finish(const float *partials, size_t size, int chunks, float *g_W,
                              const float *gz_rows, int64_t rows, int M, float *g_b, float *g_alpha,
                              hipStream_t s) {
-  auto go = [&](auto gr) {
-    constexpr int GR = decltype(gr)::value;
-    const int nbW = chunks > 1 ? static_cast<int>(blocks_for(size, kBlock / GR)) : 0;
-    hipLaunchKernelGGL(bwd_finish_kernel<GR>, dim3(nbW + (rows > 0 ? M + 3 : 0)), dim3(kBlock), 0, s, partials, size,
-                       chunks, nbW, g_W, ColumnArgs{gz_rows, rows, g_b, g_alpha}, M);
+  auto go = [&](auto gr, auto vv) {
+    constexpr int GR = decltype(gr)::value, V = decltype(vv)::value;
+    const int nbW = chunks > 1 ? static_cast<int>(blocks_for(size, kBlock / GR * V)) : 0;
+    hipLaunchKernelGGL((bwd_finish_kernel<GR, V>), dim3(nbW + (rows > 0 ? M + 3 : 0)), dim3(kBlock), 0, s, partials,
+                       size, chunks, nbW, g_W, ColumnArgs{gz_rows, rows, g_b, g_alpha}, M);
     return hipGetLastError();
   };
-  return chunks > 32 && size < 64 * 256 ? go(std::integral_constant<int, 16>{}) : go(std::integral_constant<int, 4>{});
+  using One = std::integral_constant<int, 1>;
+  using Four = std::integral_constant<int, 4>;
+  if (size % 4 == 0 && size >= (1 << 17)) return go(Four{}, Four{});
+  return chunks > 32 && size < 64 * 256 ? go(std::integral_constant<int, 16>{}, One{}) : go(Four{}, One{});
 }
 
 hipError_t launch_copy(void *dst, const void *src, size_t bytes, hipStream_t s) {
