@@ -1185,14 +1185,20 @@ __global__ __launch_bounds__(512, 1) void bwd_out_w16_kernel(
     const int64_t t = t0 + r;
     const bool live = t < te;
     const int64_t tl = live ? t : te - 1;
-    u32x4 X[N][2], G[N][2], H[2], vbh[MS], vbl[MS];
+    // Where the registers do not hold both halves of all lines (n = 8 spilled up to 164 bytes a lane), the second half of
+    // an x row takes the first one's once that is used.  Steps, us, both at once / so: n = 8, C = 512, K = 20, 30000 tokens
+    // 751 / 708, C = 1024, K = 64, 16384 tokens 807 / 802; n = 7, K = 100 765 / 754, but K = 30, C = 2048, 5000 tokens 426 / 429;
+    // n = 6 570 / 575.  (The same with g_xout: slower, 730 and 769.)
+    constexpr int XU = N == 8 || (N == 7 && MS >= 3) ? 1 : 2;
+    u32x4 X[N][XU], G[N][2], H[2], vbh[MS], vbl[MS];
+    auto load_x = [&](int j, int u) { return *reinterpret_cast<const u32x4 *>(x + (tl * N + j) * C + c0 + u * 32); };
     float4 rec[NV];
 #pragma unroll
     for (int j = 0; j < N; ++j)
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         G[j][u] = *reinterpret_cast<const u32x4 *>(g + (tl * N + j) * C + c0 + u * 32);
-        X[j][u] = *reinterpret_cast<const u32x4 *>(x + (tl * N + j) * C + c0 + u * 32);
+        if (u < XU) X[j][u < XU ? u : 0] = load_x(j, u);
       }
 #pragma unroll
     for (int u = 0; u < 2; ++u) H[u] = *reinterpret_cast<const u32x4 *>(gh + tl * C + c0 + u * 32);
@@ -1271,7 +1277,7 @@ __global__ __launch_bounds__(512, 1) void bwd_out_w16_kernel(
             }
           }
           float xv[8], hv[8], o[8];
-          unpack(X[j][u], xv);
+          unpack(X[j][u < XU ? u : 0], xv);
           unpack(H[u], hv);
 #pragma unroll
           for (int e = 0; e < 8; ++e) o[e] = vscale * wv[e >> 2][e & 3] - xv[e] * cx + hp * hv[e];
@@ -1326,7 +1332,8 @@ __global__ __launch_bounds__(512, 1) void bwd_out_w16_kernel(
           }
           const float hp = cpr[NN + j];
           float xv[8], o[8];
-          unpack(X[j][u], xv);
+          unpack(X[j][u < XU ? u : 0], xv);
+          if (XU == 1 && u == 0) X[j][0] = load_x(j, 1);
 #pragma unroll
           for (int e = 0; e < 8; ++e) o[e] = vscale * wv[e >> 2][e & 3] - xv[e] * cx + hp * hv[e];
 #pragma unroll
