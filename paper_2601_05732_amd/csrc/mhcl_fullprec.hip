@@ -620,8 +620,10 @@ static int64_t few_tokens(const mhcl_desc &d) {
 bool proj_fullprec_used(const mhcl_desc &d) { return !fast_path_ok(d) || d.T <= few_tokens(d); }
 
 // Parts of a row: enough blocks for two per compute unit, each wave with at least one step, at most
-// 16 (the coefficient stages add the slices; 32 gained 1 us for 16 tokens and lost 2 for 256 at
-// C = 4096; 4 instead of 16 for n = 5, C = 2560, 256 tokens: 105 us for mhcl_coeffs against 57).
+// 16 (the coefficient stages add the slices; 4 instead of 16 for n = 5, C = 2560, 256 tokens: 105 us for mhcl_coeffs
+// against 57), or 32 for a block or two of tokens with many products: forward, us, 16 / 32 parts at 16 tokens: n = 4, C = 4096
+// 17.1 / 16.4, n = 5, C = 2048 36.6 / 32.9, n = 8, K = 64, C = 2048 34.9 / 29.6; but n = 3, C = 4096 15.8 / 16.4, n = 4, C = 2048
+// 15.9 / 16.2, and for 256 tokens at n = 4, C = 4096 2 us more; f32 step at n = 4, C = 4096 41.3 / 42.6.
 // Eight or nine tiles: 448 blocks are enough, so that the fp64 slices of any T fit in
 // MHCL_STATIC_SCRATCH_BYTES (14304 slice-tokens of 143 logits and a sum of squares).
 static int64_t enough_blocks(const mhcl_desc &d) {
@@ -631,8 +633,11 @@ int proj_fullprec_parts(const mhcl_desc &d) {
   const int V = d.io_dtype == MHCL_BF16 ? BF16::kVec : F32::kVec;
   const int nsteps = (d.n * d.C + 4 * V - 1) / (4 * V);
   const int64_t groups = (d.T + 15) / 16;
+  // 32 where 16 leave a wave with 64 products or more of 32 tokens or fewer (128 for f32 streams)
+  const int products = nsteps / (16 * kProjWaves) * V * logit_tiles(res_logits(d) + 2 * d.n);
+  const int most = groups <= 2 && products >= (d.io_dtype == MHCL_BF16 ? 64 : 128) ? 32 : 16;
   int parts = 1;
-  while (parts < 16 && groups * parts < enough_blocks(d) && nsteps >= 2 * parts * kProjWaves) parts *= 2;
+  while (parts < most && groups * parts < enough_blocks(d) && nsteps >= 2 * parts * kProjWaves) parts *= 2;
   return parts;
 }
 
@@ -657,6 +662,7 @@ hipError_t add_wide_slices(const mhcl_desc &d, RawSums &raw, hipStream_t s) {
     case 4: return go(add_slices_kernel<4>);
     case 8: return go(add_slices_kernel<8>);
     case 16: return go(add_slices_kernel<16>);
+    case 32: return go(add_slices_kernel<32>);
   }
   return hipErrorInvalidValue;
 }

@@ -68,7 +68,7 @@ hipError_t launch_fill_zero(float *p, size_t count, hipStream_t s);
 // ---- full-precision products on the matrix cores: any C, bf16 or f32 streams -----
 // whether u_raw, sumsq come from the fp64 projection below (else from launch_proj_mfma)
 bool proj_fullprec_used(const mhcl_desc &d);
-int proj_fullprec_parts(const mhcl_desc &d);   // slices it writes: one in fp32, 2, 4, 8 or 16 in fp64
+int proj_fullprec_parts(const mhcl_desc &d);   // slices it writes: one in fp32, 2, 4, 8, 16 or 32 in fp64
 // floats that the slices of one logit take, at most, of T tokens or fewer
 int64_t proj_fullprec_slice_floats(const mhcl_desc &d);
 hipError_t launch_proj_fullprec(const mhcl_desc &d, int M, const void *x, const float *W,

@@ -196,7 +196,7 @@ __device__ __forceinline__ void stage_wide_pass(const double *src, int64_t T, in
     }
   }
 }
-// slices: 2, 4, 8 or 16 (proj_fullprec_parts)
+// slices: 2, 4, 8, 16 or 32 (proj_fullprec_parts)
 template <int W, int L>
 __device__ __forceinline__ void stage_wide(const float *src, int slices, int64_t T, int64_t t0, float *dst, int ld) {
   constexpr int IT = (kTokBlock<L> * W + kTokThreads<L> - 1) / kTokThreads<L>;
@@ -205,7 +205,8 @@ __device__ __forceinline__ void stage_wide(const float *src, int slices, int64_t
     case 2: stage_wide_pass<W, L, 2, IT>(p, T, t0, dst, ld); break;
     case 4: stage_wide_pass<W, L, 4, IT>(p, T, t0, dst, ld); break;
     case 8: stage_wide_pass<W, L, 8, IT < 4 ? IT : 4>(p, T, t0, dst, ld); break;
-    default: stage_wide_pass<W, L, 16, IT < 2 ? IT : 2>(p, T, t0, dst, ld);
+    case 16: stage_wide_pass<W, L, 16, IT < 2 ? IT : 2>(p, T, t0, dst, ld); break;
+    default: stage_wide_pass<W, L, 32, 1>(p, T, t0, dst, ld);
   }
 }
 
