@@ -72,7 +72,7 @@ struct ProjCfg {
   static constexpr int kLdsBytes = 2 * kChunkVec * 16;
 };
 
-template <int NT, bool DIRECT, bool TURNED>
+template <int NT, bool DIRECT>
 __global__ __launch_bounds__(ProjCfg<NT>::kThreads, ProjCfg<NT>::kMinWaves) void proj_mfma_kernel(const uint16_t *__restrict__ x,
                                                            const u32x4 *__restrict__ Wp,
                                                            const float *__restrict__ W, int K,
@@ -124,16 +124,14 @@ __global__ __launch_bounds__(ProjCfg<NT>::kThreads, ProjCfg<NT>::kMinWaves) void
   // Loads never branch: a step past the end re-reads the last step (address
   // clamped); compute() zeroes such a tile where it is consumed, so it adds
   // nothing and the load itself is never waited for early.
-  // TURNED: each block starts its walk at another chunk, as in bwd_reduce_kernel (a part with a tail keeps it last)
-  const int rot = TURNED && nsteps % KC == 0 ? static_cast<int>((blockIdx.x * 13u) % static_cast<unsigned>(nchunks)) : 0;
-  auto turn = [&](int c) {
-    if constexpr (!TURNED) return c;
-    return c + rot < nchunks ? c + rot : c + rot - nchunks;
-  };
+  // (All blocks walk K in the same order: equal tokens of a call then get equal logits wherever they stand.
+  // With the walk begun at another chunk in each block, as in bwd_reduce_kernel, a token's sums depended on
+  // its block.  That spread the requests over more memory channels: mhcl_coeffs, in step / turned, n = 8, K = 64,
+  // C = 1024, 16384 tokens 102 / 86 us, n = 4, C = 2048, 16384 tokens 73 / 58, C = 4096, 32768 tokens 192 / 203.)
   auto load_a = [&](u32x4 (&dst)[TG][KC], int c) {
 #pragma unroll
     for (int s = 0; s < KC; ++s) {
-      const int step = turn(c) * KC + s;
+      const int step = c * KC + s;
       const int sc = step < nsteps ? step : nsteps - 1;
 #pragma unroll
       for (int g = 0; g < TG; ++g)
@@ -147,7 +145,7 @@ __global__ __launch_bounds__(ProjCfg<NT>::kThreads, ProjCfg<NT>::kMinWaves) void
         int o = i * Cfg::kThreads + threadIdx.x;
         if (kItems % Cfg::kThreads != 0 && o > kItems - 1) o = kItems - 1;
         const int blk = o >> 6, j = blk % NT;
-        int step = turn(c) * KC + blk / NT;
+        int step = c * KC + blk / NT;
         if (step > nsteps - 1) step = nsteps - 1;
         const int col = 16 * j + (o & 15);
         const float *row = W + static_cast<size_t>(32 * step + 8 * ((o >> 4) & 3)) * M + (col < M ? col : M - 1);
@@ -156,7 +154,7 @@ __global__ __launch_bounds__(ProjCfg<NT>::kThreads, ProjCfg<NT>::kMinWaves) void
       }
       return;
     }
-    const int base = turn(c) * Cfg::kChunkVec;
+    const int base = c * Cfg::kChunkVec;
 #pragma unroll
     for (int i = 0; i < WV; ++i) {
       int o = i * Cfg::kThreads + threadIdx.x;
@@ -1815,17 +1813,6 @@ int64_t mfma_slices(const mhcl_desc &d) {
   return ks * d.T > more ? ks * d.T : more;
 }
 
-// Each block starts its walk along the rows at another place, as in bwd_reduce_kernel: in step, all requests
-// differ only in address bits above the row length and crowd a few memory channels.  mhcl_coeffs, in step /
-// turned: n = 8, K = 64, C = 1024, 16384 tokens 102 / 86 us; n = 4, C = 2048, 16384 tokens 73 / 58, C = 1024, 32768
-// tokens 70 / 60, C = 768 31 / 30.  Not where the part of W that a block walks through is larger than what then
-// stays in L2 next to the stream: n = 4, C = 4096, 32768 tokens (2 MB) 192 / 203; n = 5, C = 2560, 16384 tokens (1.8 MB) 149 /
-// 158, 32768 tokens (3.6 MB) 268 / 282; at 1 MB (n = 4, C = 4096, 9000 tokens in two parts) 106 / 93.  Nor for rows of
-// less than 2 KB, whose few chunks leave little to turn: a token's logits do not depend on its block there.
-static bool proj_turned(const mhcl_desc &d, int M, int steps) {
-  return d.n * d.C >= 1024 && static_cast<size_t>(steps) * logit_tiles(M) * 2 * 1024 <= 1536 * 1024;
-}
-
 // W staged as it is (split into its two parts on the way to LDS) instead of packed by a launch of its
 // own, 5 to 8 us: up to four logit tiles (with nine the eight loads per item cost more than the
 // launch, 149 against 166 us for mhcl_coeffs at n = 5, C = 2560, 16384 tokens; with five equal), and
@@ -1844,10 +1831,9 @@ hipError_t launch_proj_mfma(const mhcl_desc &d, int M, const void *x, const void
   const int spp = mfma_steps(d), ks = mfma_ksplit(d);
   return dispatch_nt_proj(logit_tiles(M), [&](auto nt) {
     constexpr int NT = decltype(nt)::value;
-    const bool turned = proj_turned(d, M, spp);
-    auto kern = turned ? proj_mfma_kernel<NT, false, true> : proj_mfma_kernel<NT, false, false>;
+    auto kern = proj_mfma_kernel<NT, false>;
     if constexpr (NT <= 4) {
-      if (proj_mfma_direct(d)) kern = turned ? proj_mfma_kernel<NT, true, true> : proj_mfma_kernel<NT, true, false>;
+      if (proj_mfma_direct(d)) kern = proj_mfma_kernel<NT, true>;
     }
     constexpr int lds = ProjCfg<NT>::kLdsBytes;
     if (lds > 64 * 1024) {

@@ -1,5 +1,5 @@
 """The bf16 projection where it splits rows into uneven parts (the last one shorter, or with a tail that is no
-whole chunk of K steps) and where its blocks start their walk at different chunks, against the oracle;
+whole chunk of K steps), against the oracle;
 tolerances as in gpu_harness.py."""
 import pytest
 import torch
