@@ -129,9 +129,10 @@ int32_t mhcl_logit_count(const mhcl_desc *desc);
  * A workspace of the largest batch of a program serves its smaller ones: for the
  * backward operations, and for the forward ones with f32 streams or C no
  * multiple of 64, the size never falls as T grows.  The forward of bf16 streams at C a
- * multiple of 64 splits the projection's rows up to four ways while its blocks
- * do not fill the chip, and needs less again from the T on at which a split
- * ends (16384, 32768 or 65536 tokens).
+ * multiple of 64 splits the projection's rows while its blocks do not fill the chip: up to
+ * sixteen ways as far as the slices fit MHCL_STATIC_SCRATCH_BYTES (the size never falls
+ * there either), and up to four ways anyway, where it may need less again from the
+ * T on at which such a split ends (16384, 32768 or 65536 tokens).
  * Host only. */
 size_t mhcl_workspace_bytes(const mhcl_desc *desc, int op);
 
@@ -192,9 +193,10 @@ int mhcl_fwd_coeffs_pre(const mhcl_desc *desc, const void *x, const float *W, co
  * kernels of mhcl_coeffs followed by mhcl_pre, with their results bit for bit
  * (the single-read kernel needs more scratch than the array at the shapes where
  * it pays).  Returns MHCL_ERR_WORKSPACE, and enqueues nothing, when
- * mhcl_workspace_bytes(desc, MHCL_OP_COEFFS) exceeds the array (at
- * n = 4, bf16 streams that is about T * 132 bytes + 2 MiB: the array covers
- * n = 4, C = 4096 up to 100 000 tokens).  The first call on a GPU looks up the
+ * mhcl_workspace_bytes(desc, MHCL_OP_COEFFS) exceeds the array (at n = 4, bf16
+ * streams that is 132 bytes per token and part of a split row, and 512 C bytes of packed W;
+ * rows are split into no more than four parts beyond what fits: the array
+ * covers n = 4, C = 4096 up to 100 000 tokens).  The first call on a GPU looks up the
  * array's device address (hipGetSymbolAddress; make that call outside graph
  * capture).  All calls on one GPU share the array: two such calls that overlap
  * in time on one GPU (different streams or host threads) race; calls on one

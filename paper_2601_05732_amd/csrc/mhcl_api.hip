@@ -48,19 +48,23 @@ struct CoeffsWs {
     // Sized for both projections where both may run: the shapes that the static array takes are
     // those of the bf16 one at C a multiple of 64, of one slice elsewhere (the slices of split rows fit the array
     // at any T).
-    bytes = carve(d, nullptr, true);
-    if (fast_path_ok(d)) {
-      const size_t packed = carve(d, nullptr, false);
-      if (packed > bytes) bytes = packed;
+    const int64_t wide = proj_fullprec_slice_floats(d);
+    bytes = carve(d, nullptr, true, wide);
+    if (!fast_path_ok(d)) {
+      carve(d, ws, true, wide);
+      return;
     }
-    carve(d, ws, proj_fullprec_used(d));
+    const int64_t bf16 = mfma_slices(d);
+    const size_t packed = carve(d, nullptr, false, bf16);
+    if (packed > bytes) bytes = packed;
+    const bool fullprec = proj_fullprec_used(d);
+    carve(d, ws, fullprec, fullprec ? wide : bf16);
   }
 
  private:
-  size_t carve(const mhcl_desc &d, void *ws, bool fullprec) {
+  size_t carve(const mhcl_desc &d, void *ws, bool fullprec, int64_t slices) {
     WsCursor c(ws);
-    const size_t slices = static_cast<size_t>(fullprec ? proj_fullprec_slice_floats(d) : mfma_slices(d));
-    u_raw = c.take<float>(slices * logits(d));
+    u_raw = c.take<float>(static_cast<size_t>(slices) * logits(d));
     sumsq = c.take<float>(slices);
     Wp = fullprec ? nullptr : c.take<char>(packed_w_b_bytes(d, logits(d)));
     return c.off;
@@ -77,7 +81,10 @@ struct BwdWs {
     const size_t T = static_cast<size_t>(d.T);
     const int M = logits(d), n = d.n;
     int64_t slices = proj_fullprec_slice_floats(d);
-    if (fast_path_ok(d) && mfma_slice_tokens(d) > slices) slices = mfma_slice_tokens(d);
+    if (fast_path_ok(d)) {
+      const int64_t bf16 = mfma_slice_tokens(d);
+      if (bf16 > slices) slices = bf16;
+    }
     u_raw = c.take<float>(static_cast<size_t>(slices) * M);
     sumsq = c.take<float>(slices);
     tok.rec = c.take<float>(T * token_rec_floats(n));

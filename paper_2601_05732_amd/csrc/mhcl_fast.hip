@@ -1766,51 +1766,81 @@ static void proj_shape(const mhcl_desc &d, int *kc, int *tok) {
 // (40 blocks: 6) 15.3 / 14.2; n = 5, C = 2560, 3000 tokens (12 blocks: 16) 118 / 67, 10000 tokens (40 blocks: 6)
 // 125 / 112; n = 8, K = 64, C = 1024, 5000 tokens (20 blocks: 12) 70 / 50.
 constexpr int kMaxMfmaBlocks = 768;   // of a projection that is split
-static int mfma_steps(const mhcl_desc &d) {
-  int kc = 4, tok = 128;
-  proj_shape(d, &kc, &tok);
-  const int M = res_logits(d) + 2 * d.n, K = d.n * d.C;
-  const int chunks = (K / 32 + kc - 1) / kc;
-  const int64_t blocks = (d.T + tok - 1) / tok;
-  int64_t most = d.T > 0 ? mfma_slices(d) / d.T : 1;   // (what the workspace has room for)
-  if (most > kMaxMfmaParts) most = kMaxMfmaParts;
-  int best = chunks;
-  double best_cost = 0.0;
-  for (int p = 1; p <= most; ++p) {
-    const int cpp = (chunks + p - 1) / p;               // chunks per part: two at least, also of the last one of two
-    if (p > 1 && (chunks < 4 || cpp < 2 || blocks * p > kMaxMfmaBlocks)) break;
-    const double cost = static_cast<double>((blocks * p + 255) / 256 * cpp) / chunks +
-                        static_cast<double>(p * blocks) / 256 * 4 * M / K;
-    if (p == 1 || cost < 0.9 * best_cost) { best = cpp; best_cost = cost; }
+namespace {
+struct MfmaSplit {
+  int kc = 4, tok = 128;        // K steps per chunk, tokens per block
+  int nsteps, chunks, most_parts;
+  int64_t fit;                  // slices x tokens that the static array has room for
+  int per_part[kMaxMfmaParts + 1];        // chunks of each of so many parts
+  double walk[kMaxMfmaParts + 1], add[kMaxMfmaParts + 1];   // the cost of a round of blocks, and of the slices per block
+
+  explicit MfmaSplit(const mhcl_desc &d) {
+    proj_shape(d, &kc, &tok);
+    const int M = res_logits(d) + 2 * d.n, K = d.n * d.C;
+    nsteps = K / 32;
+    chunks = (nsteps + kc - 1) / kc;
+    const int64_t room = static_cast<int64_t>(MHCL_STATIC_SCRATCH_BYTES) - align_up(packed_w_b_bytes(d, M)) - 512;
+    fit = room > 0 ? room / (4 * (M + 1)) : 0;
+    // two chunks per part at least, also of the last one of two
+    most_parts = chunks < 4 ? 1 : (chunks - 1 < kMaxMfmaParts ? chunks - 1 : kMaxMfmaParts);
+    for (int p = 1; p <= most_parts; ++p) {
+      per_part[p] = (chunks + p - 1) / p;
+      walk[p] = static_cast<double>(per_part[p]) / chunks;
+      add[p] = static_cast<double>(p) / 256 * 4 * M / K;
+    }
   }
-  return best * kc;
-}
-int mfma_ksplit(const mhcl_desc &d) {
-  const int spp = mfma_steps(d);
-  return (d.n * d.C / 32 + spp - 1) / spp;
-}
+  // The shapes that the static array takes are those whose rows fit in so many parts (a power of two up to
+  // four); more parts only as far as they fit in the array too.
+  int static_parts(int64_t blocks) const {
+    int ks = 1;
+    while (ks < 4 && blocks * ks < 256 && nsteps % (ks * 4 * kc) == 0) ks *= 2;
+    return ks;
+  }
+  int64_t blocks_of(int64_t T) const { return (T + tok - 1) / tok; }
+  int steps(int64_t T) const {   // K steps per part
+    const int64_t blocks = blocks_of(T);
+    int64_t most = static_parts(blocks);
+    if (T > 0 && fit / T > most) most = fit / T;
+    if (most > most_parts) most = most_parts;
+    int best = chunks;
+    double best_cost = 0.0;
+    for (int p = 1; p <= most && (p == 1 || blocks * p <= kMaxMfmaBlocks); ++p) {
+      const double cost = static_cast<double>((blocks * p + 255) / 256) * walk[p] + static_cast<double>(blocks) * add[p];
+      if (p == 1 || cost < 0.9 * best_cost) { best = per_part[p]; best_cost = cost; }
+    }
+    return best * kc;
+  }
+  int parts(int64_t T) const {
+    const int spp = steps(T);
+    return (nsteps + spp - 1) / spp;
+  }
+  // Slices x tokens that a call of more than `few` and up to T tokens writes, at most.  From the last block on:
+  // within a block's tokens the parts can only fall, and only where the room in the static array ends them.
+  int64_t slice_tokens(int64_t T, int64_t few) const {
+    const int64_t row_most = (chunks + 1) / 2 < most_parts ? (chunks + 1) / 2 : most_parts;
+    int64_t most = T, b = blocks_of(T) < kMaxMfmaBlocks ? blocks_of(T) : kMaxMfmaBlocks;
+    for (; b > 0; --b) {
+      const int64_t last = b * tok < T ? b * tok : T, first = (b - 1) * tok > few ? (b - 1) * tok + 1 : few + 1;
+      if (last <= few || row_most * last <= most) break;
+      if (kMaxMfmaBlocks / b * last <= most) continue;
+      const int at_last = parts(last), at_first = fit / last >= most_parts ? at_last : parts(first);
+      int64_t here = at_last * last;
+      if (at_first > at_last) here = at_first * last < fit ? at_first * last : (here > fit ? here : fit);
+      if (here > most) most = here;
+    }
+    return most;
+  }
+};
+}  // namespace
 
-// slices x tokens of a split projection, at most, of T tokens or fewer
-int64_t mfma_slice_tokens(const mhcl_desc &d) {
-  int kc = 4, tok = 128;
-  proj_shape(d, &kc, &tok);
-  return slice_tokens(d.T, kMaxMfmaParts, static_cast<int64_t>(kMaxMfmaBlocks) * tok);
-}
-
-// Slices x tokens that the forward's workspace holds.  The shapes that the static array takes are those whose
-// rows fit in parts of a power of two up to four; more parts only as far as they fit in the array too.
+static int mfma_steps(const mhcl_desc &d) { return MfmaSplit(d).steps(d.T); }
+int mfma_ksplit(const mhcl_desc &d) { return MfmaSplit(d).parts(d.T); }
+int64_t mfma_slice_tokens(const mhcl_desc &d) { return MfmaSplit(d).slice_tokens(d.T, few_tokens(d)); }
 int64_t mfma_slices(const mhcl_desc &d) {
-  int kc = 4, tok = 128;
-  proj_shape(d, &kc, &tok);
-  const int nsteps = d.n * d.C / 32, M = res_logits(d) + 2 * d.n;
-  const int64_t blocks = (d.T + tok - 1) / tok;
-  int ks = 1;
-  while (ks < 4 && blocks * ks < 256 && nsteps % (ks * 4 * kc) == 0) ks *= 2;
-  const int64_t room = static_cast<int64_t>(MHCL_STATIC_SCRATCH_BYTES) - align_up(packed_w_b_bytes(d, M)) - 512;
-  const int64_t fit = room > 0 ? room / (4 * (M + 1)) : 0;
-  int64_t more = mfma_slice_tokens(d);
-  if (more > fit) more = fit;
-  return ks * d.T > more ? ks * d.T : more;
+  const MfmaSplit split(d);
+  const int64_t room = split.static_parts(split.blocks_of(d.T)) * d.T, most = split.slice_tokens(d.T, few_tokens(d));
+  const int64_t more = most < split.fit ? most : split.fit;
+  return room > more ? room : more;
 }
 
 // W staged as it is (split into its two parts on the way to LDS) instead of packed by a launch of its

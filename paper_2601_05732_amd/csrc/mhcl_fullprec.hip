@@ -613,7 +613,7 @@ int gw_columns(const mhcl_desc &d, int M) {
 // n = 4, C = 1024, 256 tokens 10.5 / 14.7 us, 1024 tokens 13.6 / 15.1, 2048 tokens 18.7 / 15.2; C = 4096,
 // 64 tokens 13.5 / 37.8, 1024 tokens 29.6 / 39.2, 1500 tokens 40.9 / 39.2; n = 3, C = 1024, 2000 tokens
 // 12.3 / 12.7; n = 5, C = 2560 (nine tiles, where the other one packs W first), 500 tokens 83 / 106.
-static int64_t few_tokens(const mhcl_desc &d) {
+int64_t few_tokens(const mhcl_desc &d) {
   const int tiles = logit_tiles(res_logits(d) + 2 * d.n);
   return (tiles <= 4 ? 2500 : 5000) / tiles;
 }
@@ -677,7 +677,10 @@ int64_t proj_fullprec_slice_floats(const mhcl_desc &d) {
     if (T > few) T = few;
   }
   const int parts = proj_fullprec_parts(one);
-  return parts > 1 ? slice_tokens(T, 2 * parts, 2 * 16 * 2 * enough_blocks(d)) : T;
+  if (parts == 1) return T;
+  const int64_t slices = slice_tokens(T, 2 * (parts < 16 ? parts : 16), 2 * 16 * 2 * enough_blocks(d));
+  const int64_t first = 2 * parts * (T < 32 ? T : 32);   // (32 parts: of 32 tokens or fewer)
+  return slices > first ? slices : first;
 }
 
 hipError_t launch_proj_fullprec(const mhcl_desc &d, int M, const void *x, const float *W,

@@ -68,6 +68,7 @@ hipError_t launch_fill_zero(float *p, size_t count, hipStream_t s);
 // ---- full-precision products on the matrix cores: any C, bf16 or f32 streams -----
 // whether u_raw, sumsq come from the fp64 projection below (else from launch_proj_mfma)
 bool proj_fullprec_used(const mhcl_desc &d);
+int64_t few_tokens(const mhcl_desc &d);   // up to so many where the other could run too
 int proj_fullprec_parts(const mhcl_desc &d);   // slices it writes: one in fp32, 2, 4, 8, 16 or 32 in fp64
 // floats that the slices of one logit take, at most, of T tokens or fewer
 int64_t proj_fullprec_slice_floats(const mhcl_desc &d);
@@ -159,7 +160,7 @@ constexpr int kMaxMfmaParts = 16;
 int proj_ksplit(const mhcl_desc &d);
 int mfma_ksplit(const mhcl_desc &d);   // slices of launch_proj_mfma
 int64_t mfma_slices(const mhcl_desc &d);         // slices x tokens that the forward's workspace holds
-int64_t mfma_slice_tokens(const mhcl_desc &d);   // slices x tokens, at most, of T tokens or fewer
+int64_t mfma_slice_tokens(const mhcl_desc &d);   // slices x tokens of launch_proj_mfma, at most, of T tokens or fewer
 size_t packed_w_b_bytes(const mhcl_desc &d, int M);
 // packs W (B layout) and, in the same launch, clears `nzero` floats at `zero`
 hipError_t launch_pack_w_b(const mhcl_desc &d, int M, const float *W, void *Wp, hipStream_t s,
