@@ -172,8 +172,9 @@ int mhcl_post(const mhcl_desc *desc, const void *x, const void *y, const float *
  * The projection's sum over n C terms is then split differently from
  * mhcl_coeffs, so H_* agree with it to fp32 rounding of the logits and h to
  * one bf16 step.  Every other shape, or a device that cannot hold the 256
- * blocks at once: mhcl_coeffs followed by mhcl_pre, bit for bit (x is then
- * read twice: h needs H_pre, which needs the token's whole row).
+ * blocks at once: the results of mhcl_coeffs followed by mhcl_pre, bit for bit (x is
+ * then read twice: h needs H_pre, which needs the token's whole row; with few
+ * tokens one launch takes the coefficients and h).
  * Results are reproducible bit for bit from call to call either way.
  * MHCL_FWD_ONCE=0 in the environment keeps the two-kernel form everywhere (for
  * a process that shares the device with other long-running work: the one
@@ -189,10 +190,10 @@ int mhcl_fwd_coeffs_pre(const mhcl_desc *desc, const void *x, const float *W, co
  * a workspace argument.  Its scratch is a static device array of
  * MHCL_STATIC_SCRATCH_BYTES that every GPU the library runs on holds from the
  * first use of the library on it until the process ends; the call allocates
- * and frees nothing (no hipMalloc, no library allocator).  It always runs the
- * kernels of mhcl_coeffs followed by mhcl_pre, with their results bit for bit
- * (the single-read kernel needs more scratch than the array at the shapes where
- * it pays).  Returns MHCL_ERR_WORKSPACE, and enqueues nothing, when
+ * and frees nothing (no hipMalloc, no library allocator).  Its results
+ * are those of mhcl_coeffs followed by mhcl_pre, bit for bit, at every shape (the
+ * single-read kernel, which needs more scratch than the array where it pays, is never
+ * taken).  Returns MHCL_ERR_WORKSPACE, and enqueues nothing, when
  * mhcl_workspace_bytes(desc, MHCL_OP_COEFFS) exceeds the array (at n = 4, bf16
  * streams that is 132 bytes per token and part of a split row, and 512 C bytes of packed W;
  * rows are split into no more than four parts beyond what fits: the array

@@ -131,6 +131,14 @@ struct Dims {
 
 __device__ __forceinline__ float sigmoidf(float t) { return 1.f / (1.f + expf(-t)); }
 
+// RMSNorm's factor of a token and a logit from its projection u.  Several kernels compute the same ones (the gates of
+// h are computed apart from those handed out where one launch takes both) and must get the same bits: which product
+// is fused with which sum is fixed here and not left to each kernel's compilation.
+__device__ __forceinline__ float rms_factor(float sumsq, int nC, float eps) {
+  return 1.f / sqrtf(sumsq / static_cast<float>(nC) + eps);
+}
+__device__ __forceinline__ float logit_of(float alpha, float r, float u, float b) { return fmaf(alpha, r * u, b); }
+
 // ------------------------------------------------- sums in a fixed order
 // a + b, of two lanes' values: never fused with a product that a lane's own value is.  (Fused, either lane adds
 // its unrounded product to the other's rounded one, and the lanes get different sums.)

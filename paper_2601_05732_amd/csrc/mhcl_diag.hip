@@ -29,7 +29,7 @@ __global__ __launch_bounds__(kLogitThreads) void logits_kernel(
   const int live = T - t0 < kLogitTok ? static_cast<int>(T - t0) : kLogitTok;
   if (static_cast<int>(threadIdx.x) < live) {
     const float ssq = slice_sum(sumsq, parts, wide, T, t0 + threadIdx.x);
-    r_s[threadIdx.x] = 1.f / sqrtf(ssq / static_cast<float>(nC) + eps);
+    r_s[threadIdx.x] = rms_factor(ssq, nC, eps);
   }
   const float a0 = alpha[0], a1 = alpha[1], a2 = alpha[2];
   __syncthreads();
@@ -38,7 +38,7 @@ __global__ __launch_bounds__(kLogitThreads) void logits_kernel(
     const int tk = e / M, m = e - tk * M;
     const float u = slice_sum(u_raw, parts, wide, T * M, t0 * M + e);
     const float al = m < R ? a0 : (m < R + n ? a1 : a2);
-    const float v = al * (r_s[tk] * u) + b[m];
+    const float v = logit_of(al, r_s[tk], u, b[m]);
     if (z) z[t0 * M + e] = v;
     z_s[tk * ld + m] = v;
   }

@@ -80,7 +80,7 @@ __global__ __launch_bounds__(kBlock) void pre_kernel(const void *__restrict__ x,
     IO::load(x, (t * N + j) * C + c, v);
     const float w = H_pre[t * N + j];
 #pragma unroll
-    for (int e = 0; e < V; ++e) acc[e] += w * v[e];
+    for (int e = 0; e < V; ++e) acc[e] = fmaf(w, v[e], acc[e]);
   }
   IO::store(h, t * C + c, acc);
 }

@@ -123,7 +123,6 @@ __global__ __launch_bounds__(512, 1) void fwd_once_kernel(
   const int niter = cluster < ngroups ? static_cast<int>((ngroups - 1 - cluster) / nclusters) + 1 : 0;
   if (niter == 0) return;   // (the whole cluster: its blocks exchange only with each other)
   const int col0 = part * kOnceCB + wave * 32 + q * 8;
-  const float nC = static_cast<float>(N) * static_cast<float>(C);
 
   // the block's slice of packed W: rows part*256 .. +255 of every stream
   for (int i = threadIdx.x; i < Cfg::kWVec; i += 512) {
@@ -273,8 +272,7 @@ __global__ __launch_bounds__(512, 1) void fwd_once_kernel(
         }
       }
       if (bpub) {
-        const float rr = 1.f / sqrtf(ssq / nC + eps);
-        const float hv = sigmoidf(alpha_pre * (rr * u) + b_pre);
+        const float hv = sigmoidf(logit_of(alpha_pre, rms_factor(ssq, N * C, eps), u, b_pre));
         put_word(l2_at(ib, btok) + bj, hv, static_cast<unsigned>(ib) + 1u);
       }
     }
@@ -291,7 +289,7 @@ __global__ __launch_bounds__(512, 1) void fwd_once_kernel(
         const float v[8] = {bf16lo(pv.x), bf16hi(pv.x), bf16lo(pv.y), bf16hi(pv.y),
                             bf16lo(pv.z), bf16hi(pv.z), bf16lo(pv.w), bf16hi(pv.w)};
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] += w * v[e];
+        for (int e = 0; e < 8; ++e) acc[e] = fmaf(w, v[e], acc[e]);   // (as pre_kernel)
       }
       const int64_t t = group_of(ic) * kOnceGT + r;
       if (t < T) {

@@ -34,8 +34,7 @@ __device__ __forceinline__ void pre_from_slices(const PreArgs &p, unsigned block
   int tokens = static_cast<int>((static_cast<unsigned>(rem) + THREADS - 1) / static_cast<unsigned>(vpr)) + 1;
   if (tokens > T - t0) tokens = static_cast<int>(T - t0);
   auto gate = [&](int i, float u, float ssq) {
-    const float r = 1.f / sqrtf(ssq / static_cast<float>(nC) + eps);
-    gate_s[i] = sigmoidf(alpha[1] * (r * u) + b[R + i % N]);
+    gate_s[i] = sigmoidf(logit_of(alpha[1], rms_factor(ssq, nC, eps), u, b[R + i % N]));
   };
   float v[N][V];
   auto load_x = [&]() {
@@ -89,7 +88,7 @@ __device__ __forceinline__ void pre_from_slices(const PreArgs &p, unsigned block
   for (int j = 0; j < N; ++j) {
     const float w = gate_s[tok * N + j];
 #pragma unroll
-    for (int e = 0; e < V; ++e) acc[e] += w * v[j][e];
+    for (int e = 0; e < V; ++e) acc[e] = fmaf(w, v[j][e], acc[e]);   // (as pre_kernel)
   }
   IO::store(p.h, t * p.C + c, acc);
 }

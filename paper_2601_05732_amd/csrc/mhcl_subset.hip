@@ -156,7 +156,7 @@ __device__ __forceinline__ void coeffs_group(
     int64_t tt = t0 + tid;
     if (tt > T - 1) tt = T - 1;
     const float ssq = slice_sum(sumsq, parts, wide, T, tt);
-    r_s[tid] = 1.f / sqrtf(ssq / static_cast<float>(nC) + eps);
+    r_s[tid] = rms_factor(ssq, nC, eps);
   }
   if constexpr (BWD) stage_run(gH_res, gparts, T, t0, NN, g_s, gld);
   __syncthreads();
@@ -174,7 +174,7 @@ __device__ __forceinline__ void coeffs_group(
   float zmax = -INFINITY;
 #pragma unroll
   for (int kk = 0; kk < OWN; ++kk) {
-    const float z = a0 * (r * ut[kc(kk)]) + bk[kk];
+    const float z = logit_of(a0, r, ut[kc(kk)], bk[kk]);
     own[kk] = owns(kk) ? z : -INFINITY;
     zmax = fmaxf(zmax, own[kk]);
   }
@@ -219,8 +219,8 @@ __device__ __forceinline__ void coeffs_group(
 
   if constexpr (!BWD) {
     if (l < N && live) {
-      H_pre[t * N + l] = sigmoidf(a1 * (r * ut[K + l]) + b[K + l]);
-      H_post[t * N + l] = 2.f * sigmoidf(a2 * (r * ut[K + N + l]) + b[K + N + l]);
+      H_pre[t * N + l] = sigmoidf(logit_of(a1, r, ut[K + l], b[K + l]));
+      H_post[t * N + l] = 2.f * sigmoidf(logit_of(a2, r, ut[K + N + l], b[K + N + l]));
     }
     return;
   } else {
@@ -256,8 +256,8 @@ __device__ __forceinline__ void coeffs_group(
     }
     if (l < N) {
       const float up = ut[K + l], uq = ut[K + N + l];
-      const float hp = sigmoidf(a1 * (r * up) + b[K + l]);
-      const float hq = 2.f * sigmoidf(a2 * (r * uq) + b[K + N + l]);
+      const float hp = sigmoidf(logit_of(a1, r, up, b[K + l]));
+      const float hq = 2.f * sigmoidf(logit_of(a2, r, uq, b[K + N + l]));
       float dp = gH_pre[tl * N + l], dq = gH_post[tl * N + l];
 #pragma unroll 4
       for (int pt = 1; pt < gparts; ++pt) {

@@ -300,7 +300,7 @@ __device__ __forceinline__ void token_stage(const TokenIn &in, const TokenOut &o
     const int64_t t = t0 + tok;
     const bool live = t < T;
     const float *u = u_s[tok];
-    const float r = 1.f / sqrtf(u[M] / static_cast<float>(in.nC) + in.eps);
+    const float r = rms_factor(u[M], in.nC, in.eps);
 
     // residual logits of this lane, softmax weights / Sinkhorn-Knopp input a, entries H of H_res
     float a[KK], uk[KK], H[CC];
@@ -308,7 +308,7 @@ __device__ __forceinline__ void token_stage(const TokenIn &in, const TokenOut &o
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
       uk[kk] = u[owns(kk) ? logit(kk) : 0];
-      a[kk] = owns(kk) ? a_res * (r * uk[kk]) + bk[kk] : -INFINITY;
+      a[kk] = owns(kk) ? logit_of(a_res, r, uk[kk], bk[kk]) : -INFINITY;
       zmax = fmaxf(zmax, a[kk]);
     }
     zmax = group_reduce<L>(zmax, Max{});
@@ -374,7 +374,7 @@ __device__ __forceinline__ void token_stage(const TokenIn &in, const TokenOut &o
     for (int gi = 0; gi < GG; ++gi) {
       const int gt = l + L * gi < 2 * N ? l + L * gi : 0;
       ug[gi] = u[R + gt];
-      const float zg = a_gate[gi] * (r * ug[gi]) + bg[gi], sg = sigmoidf(zg);
+      const float zg = logit_of(a_gate[gi], r, ug[gi], bg[gi]), sg = sigmoidf(zg);
       gate[gi] = gt < N ? sg : 2.f * sg;
       if constexpr (!BWD) {
         if (out.z != nullptr && live && l + L * gi < 2 * N) out.z[t * M + R + gt] = zg;
@@ -610,8 +610,8 @@ __device__ __forceinline__ void lane_gates(const float *u, float r, const float 
                                            float *H_pre, float *H_post) {
 #pragma unroll
   for (int j = 0; j < N; ++j) {
-    H_pre[j] = sigmoidf(p.alpha_pre * (r * u[j]) + b[j]);
-    H_post[j] = 2.f * sigmoidf(p.alpha_post * (r * u[N + j]) + b[N + j]);
+    H_pre[j] = sigmoidf(logit_of(p.alpha_pre, r, u[j], b[j]));
+    H_post[j] = 2.f * sigmoidf(logit_of(p.alpha_post, r, u[N + j], b[N + j]));
   }
 }
 
@@ -626,11 +626,11 @@ __device__ __forceinline__ void lite_token(const float *u, float sumsq, const fl
                                            const LaneParams &p, float *H_res, float *H_pre,
                                            float *H_post, float *a, std::integer_sequence<int, K...>) {
   constexpr int R = sizeof...(K);
-  const float r = 1.f / sqrtf(sumsq / static_cast<float>(p.nC) + p.eps);
+  const float r = rms_factor(sumsq, p.nC, p.eps);
   float zmax = -INFINITY, s = 0.f;
 #pragma unroll
   for (int k = 0; k < R; ++k) {
-    a[k] = p.alpha_res * (r * u[k]) + b[k];
+    a[k] = logit_of(p.alpha_res, r, u[k], b[k]);
     zmax = fmaxf(zmax, a[k]);
   }
 #pragma unroll
@@ -650,11 +650,11 @@ __device__ __forceinline__ float sk_token(const float *u, float sumsq, const flo
                                           float *H_res, float *H_pre, float *H_post, float *a,
                                           float *sums) {
   constexpr int R = N * N;
-  const float r = 1.f / sqrtf(sumsq / static_cast<float>(p.nC) + p.eps);
+  const float r = rms_factor(sumsq, p.nC, p.eps);
   float zmax = -INFINITY;
 #pragma unroll
   for (int k = 0; k < R; ++k) {
-    a[k] = p.alpha_res * (r * u[k]) + b[k];
+    a[k] = logit_of(p.alpha_res, r, u[k], b[k]);
     zmax = fmaxf(zmax, a[k]);
   }
 #pragma unroll

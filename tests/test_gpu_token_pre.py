@@ -1,8 +1,7 @@
 """mhcl_fwd_coeffs_pre where one launch takes the coefficients and h, against the separate calls, which test_gpu_parity.py
 holds against the oracle: each lane count, blocks whose chunks of h start and end inside rows, rows of one chunk,
 gates that one thread adds (many tokens a block) and ones that many stage, both sides of the rule's lines.
-H_pre of either comes from the same sums in the same order, so h differs by fp32 rounding of the gates at most: one
-step of the stream type (2^-8 of a bf16 value, 2^-21 of its largest term for f32)."""
+Either computes the same sums in the same order and the same products fused, so the results are the same in every bit."""
 import pytest
 import torch
 
@@ -38,8 +37,6 @@ def test_h_of_the_fused_call(wl):
                      mhcl.binding.new_workspace(L.d, mhcl.OP_COEFFS))
     mhcl.mhcl_pre(L.d, inp["x"], L.H_pre, L.h)
     torch.cuda.synchronize()
-    for k in ("H_res", "H_pre", "H_post"):   # (the compiler may fuse a product in one kernel and not in the other)
-        assert torch.allclose(got[k], getattr(L, k), rtol=2.0 ** -20, atol=2.0 ** -24), k
-    terms = (L.H_pre.double().unsqueeze(-1) * inp["x"].double().abs()).sum(dim=1)
-    step = 2.0 ** -8 if wl.io == "bf16" else 2.0 ** -21
-    assert bool(((got["h"].double() - L.h.double()).abs() <= step * terms).all())
+    for k in got:
+        other = int((got[k] != getattr(L, k)).sum())
+        assert other == 0, f"{k}: {other} values differ"
