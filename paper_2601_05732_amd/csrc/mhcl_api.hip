@@ -584,7 +584,7 @@ int mhcl_bwd_fused(const mhcl_desc *desc, const void *x, const void *y, const fl
     return MHCL_OK;
   }
   BwdWs w(*desc, ws, true);
-  if (joint_fullprec_ok(*desc)) {
+  if (joint_proj_dots_ok(*desc)) {
     StageBracket br(MHCL_STAGE_BWD_REDUCE, s);
     MHCL_HIP(launch_proj_dots(*desc, M, x, W, y, g_xout, g_h, w.u_raw, w.sumsq, w.gH_res, w.gH_post, w.gH_pre, s));
   } else {

@@ -735,6 +735,18 @@ static hipError_t dispatch_joint(const mhcl_desc &d, F &&f) {
 // (the bound keeps the joint grid below 2^32 threads)
 bool joint_fullprec_ok(const mhcl_desc &d) { return !coeffs_group_ok(d) && d.T <= (1 << 22); }
 
+// Up to so many tokens: the dot products' blocks have eight waves and the registers of the projection's role, so with many tokens
+// fewer waves stream than bwd_dots_kernel has on a compute unit (n = 5, bf16: 8 against 12).  The fused backward,
+// us, two launches / one: n = 5, bf16, C = 1000, 400 tokens 56.1 / 51.6, 800 74.0 / 73.6, 1000 76.8 / 79.2, 8000 304 / 337, C = 200,
+// 50000 533 / 631; n = 5, f32, C = 1000, 14000 tokens 704 / 699, 30000 1460 / 1482; n = 4, f32, C = 768, 4096 tokens 115 / 98 with
+// gx_gw_kernel, 10000 255 / 245, 16000 380 / 391, bf16, C = 1000, 10000 238 / 226, 20000 448 / 454 (C = 4096 and C = 200 still gain
+// there, 3 %); n = 3, f32, C = 768, 9000 tokens 148 / 144, 12000 195 / 197, bf16, C = 1000 122 / 116 and 155 / 158; n = 2, C = 768, 50000 tokens
+// 648 / 629, C = 128, 150000 tokens 370 / 374; n = 1 likewise.
+bool joint_proj_dots_ok(const mhcl_desc &d) {
+  constexpr int64_t kMost[] = {0, 1 << 17, 1 << 17, 10240, 10240, 16384};
+  return joint_fullprec_ok(d) && d.T <= (d.n == 5 && d.io_dtype == MHCL_BF16 ? 800 : kMost[d.n]);
+}
+
 hipError_t launch_proj_dots(const mhcl_desc &d, int M, const void *x, const float *W, const void *y,
                             const void *g_xout, const void *g_h, float *u_raw, float *sumsq, float *g_H_res,
                             float *g_H_post, float *g_H_pre, hipStream_t s) {

@@ -96,8 +96,9 @@ hipError_t launch_gx_fullprec(const mhcl_desc &d, int M, bool fused, const void 
                              const void *g_xout, const void *g_h, const BwdTokenBufs &o, void *g_x,
                              void *g_y, hipStream_t s);
 
-// What does not wait for each other, as one launch, where joint_fullprec_ok: launch_proj_fullprec with
-// launch_bwd_dots; launch_gx_fullprec with launch_gw_fullprec and the sums behind g_b and g_alpha (gz_count rows)
+// What does not wait for each other, as one launch: launch_proj_fullprec with launch_bwd_dots where joint_proj_dots_ok;
+// launch_gx_fullprec with launch_gw_fullprec and the sums behind g_b and g_alpha (gz_count rows) where joint_fullprec_ok
+bool joint_proj_dots_ok(const mhcl_desc &d);
 bool joint_fullprec_ok(const mhcl_desc &d);
 hipError_t launch_proj_dots(const mhcl_desc &d, int M, const void *x, const float *W, const void *y,
                             const void *g_xout, const void *g_h, float *u_raw, float *sumsq, float *g_H_res,

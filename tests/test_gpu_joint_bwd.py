@@ -22,7 +22,10 @@ def _wl(n, C, T, io="f32", mode="lite"):
 CASES = [_wl(1, 8, 9), _wl(2, 264, 35), _wl(3, 520, 7), _wl(4, 776, 17), _wl(4, 768, 300), _wl(4, 64, 257),
          _wl(5, 520, 3, mode="sk"), _wl(5, 1032, 33, mode="sk"), _wl(1, 520, 513, mode="sk"),
          _wl(4, 1032, 5, "bf16"), _wl(4, 1544, 301, "bf16"), _wl(3, 2056, 65, "bf16", "sk"), _wl(5, 72, 530, "bf16", "sk"),
-         _wl(2, 1032, 1, "bf16")]
+         _wl(2, 1032, 1, "bf16"),
+         # both sides of the line up to which the projection and the dot products share a launch
+         _wl(5, 40, 800, "bf16", "sk"), _wl(5, 40, 801, "bf16", "sk"), _wl(5, 8, 16384, mode="sk"), _wl(5, 8, 16385, mode="sk"),
+         _wl(4, 8, 10240), _wl(4, 8, 10241, "bf16"), _wl(3, 8, 10240, "bf16"), _wl(3, 8, 10241), _wl(2, 8, 131073), _wl(1, 8, 131073, mode="sk")]
 
 
 @pytest.mark.parametrize("wl", CASES, ids=lambda w: w.name)
