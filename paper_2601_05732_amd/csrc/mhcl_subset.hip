@@ -445,14 +445,16 @@ hipError_t launch_coeffs_group(const mhcl_desc &d, const RawSums &raw, const flo
   });
 }
 
-// Two launches / one, us for both forward calls: n = 5, C = 1024, 16 tokens 36.7 / 34.7, C = 2560, 1500 tokens
-// (480 thousand 16-byte chunks of h) 88.9 / 82.2, 4000 tokens (1.3 million) 164 / 163, 16384 tokens 389 / 421, C = 320,
-// 32768 tokens 131 / 145: two blocks per compute unit fit its LDS, too few to stream.  n = 8, K = 64: C = 1024, 4000 tokens 79.4 / 71.5,
-// 16384 tokens (2.1 million chunks) 234 / 232.
+// Up to 64 permutations (eight residual logits per lane) the kernel has 110 registers and at most 64 KB of LDS, so two of its
+// blocks stream on a compute unit; with more it has 133, and one does, which is too few for many tokens.  Two launches /
+// one, us for mhcl_fwd_coeffs_pre.  n = 8, K = 64, C = 1024, 4000 tokens 51.8 / 46.1, 16384 (2.1 million 16-byte chunks of h) 121 / 116,
+// 32768 261 / 254, 65536 498 / 490; n = 6, K = 40, 65536 tokens 394 / 381; n = 5, K = 30, 32768 tokens 146.9 / 147.7, 65536 315 /
+// 312.  n = 8, K = 66, C = 1024, 4000 tokens 53.4 / 46.9, 8000 (1 million) 76.5 / 73.4, 16384 125 / 137, C = 256, 16384 tokens 50.6 /
+// 58.6; n = 6, K = 128, C = 1024, 16384 tokens 115 / 125; n = 5, full form, C = 2560, 1500 tokens (480 thousand) 67.8 / 61.7, C = 1024, 6000 tokens
+// 68.4 / 67.7, C = 320, 8000 tokens 44.3 / 40.9, 12000 tokens 52.7 / 53.1.
 bool group_coeffs_pre_ok(const mhcl_desc &d) {
-  const bool three = 3 * group_lds_bytes(d.n, res_logits(d), false) <= 150 * 1024;
   if (!coeffs_group_ok(d)) return false;
-  return three ? pre_chunks(d) <= (1 << 21) : pre_chunks(d) <= (1 << 19) && d.T <= 128 * kGTok;
+  return res_logits(d) <= 64 ? pre_chunks(d) <= (1 << 23) : pre_chunks(d) <= (1 << 19) && d.T <= 128 * kGTok;
 }
 hipError_t launch_coeffs_pre_group(const mhcl_desc &d, const RawSums &raw, const float *b, const float *alpha,
                                    const void *x, float *H_res, float *H_pre, float *H_post, void *h,
