@@ -992,17 +992,20 @@ hipError_t launch_token_coeffs(const mhcl_desc &d, const RawSums &raw, const flo
   return launch_token_stage<kOutForward>(d, in, out, s);
 }
 
-// Two launches / one, us for both forward calls, by the 16-byte chunks of h.  Permutation form, n = 4: 16 tokens of
-// C = 4096 19.7 / 17.0, C = 768, 1000 tokens 19.9 / 17.4, 3001 23.9 / 23.7, C = 1024, 5003 tokens (640 thousand
-// chunks) 39.1 / 37.6, C = 768, 8192 tokens 44.7 / 45.1; n = 2, C = 512, 9000 tokens 23.3 / 23.8; fp64 slices, f32, 4096 tokens (786 thousand) 51.6 / 50.3,
-// 20000 tokens 228 / 230; four lanes per token, C = 64, 16384 tokens (131 thousand) 19.2 / 16.5, 65536 tokens
-// 36.8 / 37.6.  Sinkhorn-Knopp, whose stage is the longer, C = 768: 3001 tokens 25.3 / 23.5, 65536 344 / 340.
+// Two launches / one, us for mhcl_fwd_coeffs_pre, by the 16-byte chunks of h.  Permutation form, n = 4: C = 1024, 3000 tokens 18.1 /
+// 16.5, 5120 (655 thousand chunks) 23.5 / 22.6, 7000 28.2 / 27.9, 8000 (a million) 30.6 / 30.7, C = 768, 8192 tokens (786 thousand)
+// 25.8 / 26.4 (C = 4096 still gains there: 1500 tokens 28.5 / 26.8); fp64 slices, bf16, C = 1000, 5300 tokens (662 thousand) 50.7 / 50.3,
+// 6000 51.9 / 52.7; n = 3, f32, C = 1024, 2600 tokens (666 thousand) 21.9 / 21.4, 3000 23.1 / 23.2, 6000 36.7 / 38.7.  f32 at n = 4,
+// whose projection is the longer: C = 768, 4096 tokens (786 thousand) 34.8 / 33.2, 8000 60.1 / 59.6, C = 4096, 3000 tokens (3 million)
+// 109 / 107, C = 2048, 8000 tokens (4 million) 144 / 148.  n = 2, C = 512, 9000 tokens 23.3 / 23.8 (both forward calls); four lanes per token, C = 64,
+// 16384 tokens (131 thousand) 19.2 / 16.5, 65536 tokens 36.8 / 37.6.  Sinkhorn-Knopp, whose stage is the longer, C = 768: 3001
+// tokens 25.3 / 23.5, 65536 344 / 340.
 bool token_coeffs_pre_ok(const mhcl_desc &d, const RawSums &raw) {
   if (coeffs_group_ok(d) || (raw.parts < 8 && !raw.wide && token_per_lane(d, false))) return false;
   const int64_t chunks = pre_chunks(d);
   if (d.res_mode == MHCL_RES_SK) return chunks <= (1 << 23);
   if (token_stage_many(d, false) || d.n <= 2) return chunks <= (1 << 18);
-  return chunks <= (raw.wide ? 3 << 18 : 5 << 17);
+  return chunks <= (raw.wide && d.io_dtype == MHCL_F32 && d.n == 4 ? 3 << 20 : 5 << 17);
 }
 hipError_t launch_token_coeffs_pre(const mhcl_desc &d, const RawSums &raw, const float *b, const float *alpha,
                                    const void *x, float *H_res, float *H_pre, float *H_post, void *h,

@@ -21,6 +21,9 @@ CASES = [_wl(4, 4096, 1), _wl(4, 4096, 17), _wl(3, 200, 7), _wl(4, 768, 683), _w
          _wl(4, 768, 3001, mode="sk"), _wl(5, 136, 333, mode="sk"), _wl(1, 64, 70000, mode="sk"),
          _wl(5, 1024, 16), _wl(5, 64, 65, "f32"), _wl(8, 512, 33, "bf16", "subset", 30), _wl(8, 8, 700, "bf16", "subset", 100),
          _wl(6, 256, 2000, "f32", "subset", 20), _wl(7, 64, 3000, "bf16", "subset", 128),
+         # fp64 slices: both sides of the line, bf16 and f32
+         _wl(4, 1288, 4070), _wl(4, 1288, 4071), _wl(3, 1288, 2035, "f32"), _wl(3, 1288, 2036, "f32"), _wl(4, 3072, 4096, "f32"),
+         _wl(4, 3072, 4097, "f32"),
          # more than 64 permutations: one launch for few tokens only
          _wl(8, 64, 8192, "bf16", "subset", 65), _wl(8, 64, 8193, "bf16", "subset", 65), _wl(6, 512, 8192, "bf16", "subset", 80),
          _wl(6, 520, 8192, "bf16", "subset", 80), _wl(6, 512, 20000, "bf16", "subset", 64)]
