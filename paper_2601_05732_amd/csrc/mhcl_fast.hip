@@ -2059,11 +2059,16 @@ hipError_t launch_pack_w_ab(const mhcl_desc &d, int M, const float *W, const Fas
   return hipGetLastError();
 }
 
-// Few tokens: the launch that packs W is a tenth of the step; with more, every block splits W again.  Steps, us, packed /
-// as it is: n = 4, C = 768, 100 tokens 43.7 / 41.4, 3001 (Sinkhorn-Knopp) 74.4 / 72.6, 8000 124.5 / 125.3, 16384 239 / 242;
-// C = 4096, 200 tokens 66.5 / 65.2, 2000 159.5 / 159.6; n = 2, C = 1024, 3000 tokens 52.9 / 51.3; n = 3, C = 1024, 500 tokens
-// 38.8 / 39.0, 4000 73.2 / 75.1 (rows of 12 or 15 logits: eight of them are no aligned vectors).
-bool narrow_direct(const mhcl_desc &d) { return !fast_bwd_wide(d) && d.T <= (d.n == 3 ? 1024 : 4096); }
+// Few tokens: the launch that packs W is a tenth of the backward; with more, every block splits W again.  mhcl_bwd_fused, us,
+// packed / as it is: n = 4, C = 768, 64 tokens 27.3 / 25.1, 2500 45.6 / 43.8, 4000 52.5 / 50.9, 6000 74.3 / 74.6; Sinkhorn-Knopp 55.5 /
+// 53.5 and 77.6 / 77.2; n = 2, C = 1024, 4000 tokens 39.9 / 37.7; n = 3, Sinkhorn-Knopp, C = 512, 4000 tokens 42.1 / 41.3, C = 4096
+// 145.3 / 144.7.  The permutation form at n = 3 gains less and loses from a million T C on: C = 256, 4000 tokens 28.6 / 27.1, 6000
+// 34.4 / 36.0; C = 512, 1500 tokens 27.6 / 26.2, 2500 33.7 / 35.2; C = 1024, 1000 tokens 30.4 / 28.9, 1500 34.9 / 36.2; C = 2048, 800
+// tokens 37.1 / 38.3; C = 4096, 250 tokens 36.1 / 35.2, 800 47.6 / 48.7.
+bool narrow_direct(const mhcl_desc &d) {
+  if (fast_bwd_wide(d) || d.T > 4096) return false;
+  return d.n != 3 || d.res_mode == MHCL_RES_SK || d.T * d.C <= (1 << 20);
+}
 
 hipError_t launch_bwd_reduce(const mhcl_desc &d, int M, const void *x, const void *y, const float *W,
                              const void *g_xout, const void *g_h, const FastBwdWs &w,

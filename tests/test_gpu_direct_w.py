@@ -1,4 +1,5 @@
-"""The two passes of the bf16 backward for n <= 4 with W as it is (up to 4096 tokens, 1024 at n = 3) and packed, and the sums behind g_b and
+"""The two passes of the bf16 backward for n <= 4 with W as it is (up to 4096 tokens; the permutation form at n = 3
+up to 2^20 tokens times columns) and packed, and the sums behind g_b and
 g_alpha in pass 2's launch (one chunk of tokens) or after it, against the oracle: logits that fill their tiles, end
 inside a group of eight, or need scalar loads; tolerances as in gpu_harness.py."""
 import pytest
@@ -16,7 +17,8 @@ def _wl(n, C, T, mode="lite"):
 
 CASES = [_wl(1, 64, 1), _wl(1, 192, 65, "sk"), _wl(2, 64, 64), _wl(2, 128, 63, "sk"), _wl(3, 64, 66), _wl(3, 320, 129, "sk"),
          _wl(4, 64, 64), _wl(4, 128, 65), _wl(4, 64, 200, "sk"), _wl(4, 1024, 40), _wl(4, 64, 4096), _wl(4, 64, 4097),
-         _wl(2, 64, 4096), _wl(3, 128, 1024), _wl(3, 128, 1025, "sk"), _wl(1, 2048, 300), _wl(3, 1024, 1)]
+         _wl(2, 64, 4096), _wl(3, 128, 1024), _wl(3, 128, 1025, "sk"), _wl(3, 1024, 1024), _wl(3, 1024, 1025), _wl(3, 64, 4096),
+         _wl(3, 64, 4097), _wl(3, 192, 4096, "sk"), _wl(3, 192, 4097, "sk"), _wl(1, 2048, 300), _wl(3, 1024, 1)]
 
 
 @pytest.mark.parametrize("wl", CASES, ids=lambda w: w.name)
