@@ -19,8 +19,9 @@ constexpr int kTokBlock = L == 4 ? 64 : 32;
 template <int L>
 constexpr int kTokThreads = L * kTokBlock<L>;
 
-// kinds of output
-enum { kOutForward, kOutFast, kOutFull };
+// kinds of output (kOutLogits: the forward's with the logits)
+enum { kOutForward, kOutLogits, kOutFast, kOutFull };
+constexpr bool out_bwd(int out) { return out == kOutFast || out == kOutFull; }
 
 template <int CTRL>
 __device__ __forceinline__ float dpp(float v) {
@@ -122,7 +123,7 @@ struct TokenIn {
 };
 struct TokenOut {
   float *H_res, *H_pre, *H_post;                     // forward
-  float *z, *spread;                                 // forward, optional: logits, max - min of the residual ones
+  float *z, *spread;                                 // kOutLogits: logits, max - min of the residual ones
   float *rec;                                        // backward: records of `rec_ld` floats
   int rec_ld;
   uint16_t *vr_hi, *vr_lo, *vrT_hi, *vrT_lo;         // fast
@@ -215,7 +216,7 @@ __device__ __forceinline__ void stage_wide(const float *src, int slices, int64_t
 template <int N, int L>
 constexpr int kLines = L == 16 ? 4 : N;   // lines per token, as they are spaced
 template <int N, int MODE, int OUT, int L>
-constexpr int kSkPerIter = (MODE == MHCL_RES_SK && OUT != kOutForward)
+constexpr int kSkPerIter = (MODE == MHCL_RES_SK && out_bwd(OUT))
                                ? 2 * 2 * kTokBlock<L> * kLines<N, L> : 0;
 
 template <int N, int MODE, int OUT, int L>
@@ -226,7 +227,7 @@ __device__ __forceinline__ void token_stage(const TokenIn &in, const TokenOut &o
   constexpr int KK = MODE == MHCL_RES_LITE ? (R + L - 1) / L : CC;   // residual logits per lane
   constexpr int GG = (2 * N + L - 1) / L;                      // gates per lane
   constexpr int MP32 = (M + 31) / 32 * 32, MP16 = (M + 15) / 16 * 16;
-  constexpr bool BWD = OUT != kOutForward, F16ROWS = OUT == kOutFast && N == 5;
+  constexpr bool BWD = out_bwd(OUT), F16ROWS = OUT == kOutFast && N == 5;
   static_assert(MODE == MHCL_RES_SK || N <= 4, "the table of n = 5 does not fit these lanes");
   static_assert(N <= 4 ? L == 4 || L == 16 : L == 8, "lanes per token");
   constexpr int UL = (M + 2) | 1;                              // odd row lengths keep banks apart
@@ -312,17 +313,15 @@ __device__ __forceinline__ void token_stage(const TokenIn &in, const TokenOut &o
       zmax = fmaxf(zmax, a[kk]);
     }
     zmax = group_reduce<L>(zmax, Max{});
-    if constexpr (!BWD) {
-      if (out.z != nullptr) {   // (all lanes take part in the minimum)
-        float zneg = -INFINITY;
+    if constexpr (OUT == kOutLogits) {
+      float zneg = -INFINITY;
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {
-          zneg = fmaxf(zneg, owns(kk) ? -a[kk] : -INFINITY);
-          if (live && owns(kk)) out.z[t * M + logit(kk)] = a[kk];
-        }
-        zneg = group_reduce<L>(zneg, Max{});
-        if (live && l == 0) out.spread[t] = zmax + zneg;
+      for (int kk = 0; kk < KK; ++kk) {
+        zneg = fmaxf(zneg, owns(kk) ? -a[kk] : -INFINITY);
+        if (live && owns(kk)) out.z[t * M + logit(kk)] = a[kk];
       }
+      zneg = group_reduce<L>(zneg, Max{});
+      if (live && l == 0) out.spread[t] = zmax + zneg;
     }
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) a[kk] = owns(kk) ? expf(a[kk] - zmax) : 0.f;
@@ -376,8 +375,8 @@ __device__ __forceinline__ void token_stage(const TokenIn &in, const TokenOut &o
       ug[gi] = u[R + gt];
       const float zg = logit_of(a_gate[gi], r, ug[gi], bg[gi]), sg = sigmoidf(zg);
       gate[gi] = gt < N ? sg : 2.f * sg;
-      if constexpr (!BWD) {
-        if (out.z != nullptr && live && l + L * gi < 2 * N) out.z[t * M + R + gt] = zg;
+      if constexpr (OUT == kOutLogits) {
+        if (live && l + L * gi < 2 * N) out.z[t * M + R + gt] = zg;
       }
     }
 
@@ -554,7 +553,7 @@ __global__ __launch_bounds__(kTokThreads<L>) void token_pre_kernel(TokenIn in, T
 template <int OUT>
 hipError_t launch_token_stage(const mhcl_desc &d, const TokenIn &in,
                               const TokenOut &out, hipStream_t s) {
-  const bool many = token_stage_many(d, OUT != kOutForward);
+  const bool many = token_stage_many(d, out_bwd(OUT));
   const int64_t blocks64 = (d.T + 63) / 64;
   const unsigned blocks = static_cast<unsigned>(many ? blocks64 : 2 * blocks64);
   auto go = [&](auto nn, auto mm) {
@@ -562,7 +561,7 @@ hipError_t launch_token_stage(const mhcl_desc &d, const TokenIn &in,
     constexpr int LF = N <= 4 ? 16 : 8;   // lanes per token with few tokens
     auto kern = token_stage_kernel<N, MODE, OUT, LF>;
     int threads = kTokThreads<LF>, per_iter = kSkPerIter<N, MODE, OUT, LF>;
-    if constexpr (N <= 4 && (MODE == MHCL_RES_LITE || OUT == kOutForward)) {
+    if constexpr (N <= 4 && (MODE == MHCL_RES_LITE || !out_bwd(OUT))) {
       if (many) {
         kern = token_stage_kernel<N, MODE, OUT, 4>;
         threads = kTokThreads<4>;
@@ -1023,7 +1022,7 @@ hipError_t launch_token_coeffs_logits(const mhcl_desc &d, const RawSums &raw, co
                                       float *z, float *spread, hipStream_t s) {
   TokenOut out{};
   out.H_res = H_res; out.H_pre = H_pre; out.H_post = H_post; out.z = z; out.spread = spread;
-  return launch_token_stage<kOutForward>(d, token_in(d, raw, b, alpha), out, s);
+  return launch_token_stage<kOutLogits>(d, token_in(d, raw, b, alpha), out, s);
 }
 
 hipError_t launch_token_bwd_fast(const mhcl_desc &d, const float *b, const float *alpha,
