@@ -33,8 +33,11 @@ __device__ __forceinline__ void pre_from_slices(const PreArgs &p, unsigned block
   const int64_t t = live ? t0 + tok : T - 1;
   int tokens = static_cast<int>((static_cast<unsigned>(rem) + THREADS - 1) / static_cast<unsigned>(vpr)) + 1;
   if (tokens > T - t0) tokens = static_cast<int>(T - t0);
+  // (the parameters of a thread's first gate ahead of everything else)
+  const float alpha_pre = alpha[1], b_first = b[R + static_cast<int>(threadIdx.x) % N];
   auto gate = [&](int i, float u, float ssq) {
-    gate_s[i] = sigmoidf(logit_of(alpha[1], rms_factor(ssq, nC, eps), u, b[R + i % N]));
+    const float bias = i < THREADS ? b_first : b[R + i % N];
+    gate_s[i] = sigmoidf(logit_of(alpha_pre, rms_factor(ssq, nC, eps), u, bias));
   };
   float v[N][V];
   auto load_x = [&]() {
