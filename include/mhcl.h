@@ -53,8 +53,10 @@
  *    significant bits, 2^-17 of each product) and sum in fp32.  So the same token's
  *    H_*, z and h may differ at that level between a small batch and a large one,
  *    and between the forward and what mhcl_bwd_fused recomputes; bf16 results
- *    then differ by single roundings.  Each is within the other's error of the
- *    exact value, and any one call gives the same bits every time.
+ *    then differ by single roundings.  (In how many parts a row is summed depends on T
+ *    too, at the level of fp32 rounding or, in fp64, below it.)  Each is within the other's
+ *    error of the exact value, any one call gives the same bits every time, and equal
+ *    tokens of one forward call get the same bits wherever they stand in the batch.
  *  - x is [T, n, C] and is flattened stream-major: x_hat[j*C + c] = x[j][c].
  *  - W is one [n*C, M] matrix, b is [M]; columns are [res | pre | post] with
  *    M = n! + 2n (MHCL_RES_LITE; res column k belongs to permutation k) or
@@ -297,8 +299,8 @@ enum {
   MHCL_STAGE_FWD_PRE = 2,    /* h = H_pre x (with the coefficients where one launch takes both) */
   MHCL_STAGE_POST = 3,       /* x_out = H_res x + H_post y                               */
   MHCL_STAGE_BWD_REDUCE = 4, /* backward pass 1: all per-token reductions + coefficients */
-  MHCL_STAGE_BWD_OUT = 5,    /* backward pass 2: g_x and g_y                             */
-  MHCL_STAGE_BWD_GW = 6      /* backward: g_W, the reduction over tokens                 */
+  MHCL_STAGE_BWD_OUT = 5,    /* backward pass 2: g_x and g_y (with g_W where one launch takes both) */
+  MHCL_STAGE_BWD_GW = 6      /* backward: g_W, the reduction over tokens, in a launch of its own (bf16, n >= 5 or a subset) */
 };
 
 /* Arms the NEXT library call made by this host thread: it records the

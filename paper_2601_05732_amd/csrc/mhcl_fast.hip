@@ -1759,12 +1759,13 @@ static void proj_shape(const mhcl_desc &d, int *kc, int *tok) {
   });
 }
 
-// K steps per part.  A part costs its share of the walk times the blocks that a CU gets one after the other,
-// plus a slice that the per-token stage adds; more parts only where that gains a tenth.  mhcl_coeffs in us, with
-// powers of two up to four that divide the steps / with this: n = 4, C = 4096, 3000 tokens (24 blocks: 8 parts) 50 / 31,
-// 9000 tokens (71 blocks: 3) 106 / 73; C = 2048, 20000 tokens (157 blocks: 3) 105 / 75; C = 1024, 5003 tokens
-// (40 blocks: 6) 15.3 / 14.2; n = 5, C = 2560, 3000 tokens (12 blocks: 16) 118 / 67, 10000 tokens (40 blocks: 6)
-// 125 / 112; n = 8, K = 64, C = 1024, 5000 tokens (20 blocks: 12) 70 / 50.
+// How rows are split into parts.  A part costs its share of the walk times the blocks that a CU gets one after the other,
+// plus a slice that the per-token stage adds; more parts only where that gains a tenth, and as the static array has room
+// for.  mhcl_coeffs, us, with powers of two up to four that divide the steps / with this: n = 4, C = 4096, 3000 tokens (24
+// blocks: 10 parts) 39.4 / 24.7, 9000 tokens (71 blocks: 3) 91.6 / 72.7; C = 2048, 20000 tokens (157 blocks: 3) 98.5 / 76.6;
+// C = 1024, 2048 tokens (16 blocks: 16) 14.5 / 11.6, 5003 tokens (40 blocks: 6) 15.8 / 14.8; n = 5, C = 2560, 3000 tokens (12
+// blocks: 5, all that the array holds) 105 / 90, 10000 tokens (40 blocks: 4 either way) 119; C = 1024, 3000 tokens (8) 56.8 / 44.9;
+// n = 8, K = 64, C = 1024, 5000 tokens (20 blocks: 8) 57.5 / 44.5.
 constexpr int kMaxMfmaBlocks = 768;   // of a projection that is split
 namespace {
 struct MfmaSplit {

@@ -575,7 +575,10 @@ __global__ __launch_bounds__(64 * kGxWaves, 1) void gx_fullprec_kernel(GxArgs p)
 // sums (g_b and g_alpha, one block each) and g_x, g_y.  None needs another's result, and all but the columns read x.
 // With launch_proj_dots, steps in us, five launches / two or three: f32, n = 4, C = 64, 256 tokens 41.2 / 29.7; C = 768, 33
 // tokens 44.1 / 34.0, 4096 tokens 166 / 150; bf16, n = 3, C = 200, 2000 tokens 41.4 / 34.5, n = 4, 10000 tokens 136 / 113;
-// separable calls n = 4, C = 1024, 300 tokens 68 / 59, 5003 tokens 168 / 157.
+// separable calls n = 4, C = 1024, 300 tokens 68 / 59, 5003 tokens 168 / 157.  By itself, the fused backward, two launches and the
+// sums / one: n = 5, bf16, C = 1000, 300 tokens 63.6 / 51.2, 8000 342 / 337, 30000 1197 / 1169; n = 5, f32, 30000 tokens 1491 / 1482;
+// n = 4, bf16, C = 1000, 80000 tokens 1800 / 1768, f32, C = 768, 40000 1030 / 1002, 80000 2000 / 2022; separable calls n = 4, C = 1024,
+// 60000 tokens 1714 / 1673.
 struct GwArgs {
   int64_t chunk;
   float *out;
@@ -784,9 +787,11 @@ hipError_t launch_gw_fullprec(const mhcl_desc &d, int M, const void *x, const fl
   });
 }
 
-// Windows of W per block, blocks along C and tokens per block: one round of resident blocks, two per compute unit,
-// or one beside that of launch_gw_fullprec's role (whole step or separable calls, two / one: f32, n = 4, C = 768,
-// 4096 tokens 153 / 150 us; bf16, C = 1024, 5003 tokens 162 / 156, C = 200, 10000 tokens 123 / 113)
+// Windows of W per block, blocks along C and tokens per block: one round of resident blocks, two per compute unit.  In one launch
+// with g_W, whose up to 256 blocks come first, half as many (whole step or separable calls, two per compute unit / one: f32, n = 4, C = 768,
+// 4096 tokens 153 / 150 us; bf16, C = 1024, 5003 tokens 162 / 156, C = 200, 10000 tokens 123 / 113).  Up to n = 3, and at n = 4
+// in f32, the registers let a block of either role stand on a compute unit at once; elsewhere (148 to 224 registers) g_x follows
+// as the blocks of g_W end.
 struct GxShape {
   int win, lds, xblocks, tokens_per_block, chunks;
 };

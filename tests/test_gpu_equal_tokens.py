@@ -1,6 +1,6 @@
 """Equal tokens of one call get equal coefficients, logits and h wherever they stand in the batch, in every bit: a token's
 sums are added in an order that does not depend on its place.  Rows long enough to be walked in many chunks and in
-one or more parts, whole and ragged, batches of several blocks of the bf16 projection."""
+one or more parts, whole and ragged, batches of several blocks of either projection."""
 import pytest
 import torch
 
@@ -11,12 +11,16 @@ from gpu_harness import GpuLayer, desc_for
 pytestmark = pytest.mark.gpu
 
 
-def _wl(n, C, T, mode="lite", K=0):
-    return si.Workload(f"n{n}_c{C}_t{T}_{mode}{K}", n=n, C=C, T=T, io="bf16", res_mode=mode, n_perm=K, backward=False)
+def _wl(n, C, T, mode="lite", K=0, io="bf16"):
+    return si.Workload(f"n{n}_c{C}_t{T}_{mode}{K}" + ("_f32" if io == "f32" else ""), n=n, C=C, T=T, io=io, res_mode=mode,
+                       n_perm=K, backward=False)
 
 
 CASES = [_wl(4, 64, 3000), _wl(4, 256, 5000), _wl(4, 1024, 2048), _wl(4, 1024, 40000), _wl(3, 1472, 2600), _wl(1, 2496, 2700, "sk"),
-         _wl(4, 4096, 1409), _wl(4, 768, 3001, "sk"), _wl(5, 448, 1000), _wl(8, 1024, 5000, "subset", 64)]
+         _wl(4, 4096, 1409), _wl(4, 768, 3001, "sk"), _wl(5, 448, 1000), _wl(8, 1024, 5000, "subset", 64),
+         # the fp64 projection in parts and whole, one token per lane
+         _wl(4, 4096, 100), _wl(6, 512, 300, "subset", 100), _wl(4, 768, 3000, io="f32"), _wl(3, 200, 20000, "sk", io="f32"),
+         _wl(2, 64, 70000, "sk")]
 
 
 @pytest.mark.parametrize("wl", CASES, ids=lambda w: w.name)
