@@ -21,17 +21,17 @@ constexpr int kMaxSkIters = 32;
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) {
   return __uint_as_float(static_cast<uint32_t>(b) << 16);
 }
-// round to nearest, ties to even; NaN stays NaN
+// Round to nearest, ties to even; NaN stays NaN: v_cvt_pk_bf16_f32, the same bits as seven integer instructions a value
+// (us with those / this: mhcl_fwd_coeffs_pre with mhcl_post, n = 4, C = 2048, 32768 tokens 375 / 365; the separable step at C = 1024,
+// 5003 tokens 155 / 149; the packing of W at n = 4, C = 4096 7.8 / 4.5).
 __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return static_cast<uint16_t>((u >> 16) | 0x40u);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return static_cast<uint16_t>(u >> 16);
+  return __builtin_bit_cast(uint16_t, static_cast<__bf16>(f));
 }
 __device__ __forceinline__ float bf16lo(uint32_t p) { return __uint_as_float(p << 16); }
 __device__ __forceinline__ float bf16hi(uint32_t p) { return __uint_as_float(p & 0xffff0000u); }
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
-  return static_cast<uint32_t>(f32_to_bf16(lo)) | (static_cast<uint32_t>(f32_to_bf16(hi)) << 16);
+  typedef __bf16 pair __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, pair{static_cast<__bf16>(lo), static_cast<__bf16>(hi)});
 }
 
 // w = hi + lo up to 2^-17 of its size
