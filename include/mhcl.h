@@ -100,7 +100,8 @@ enum {
   MHCL_OP_COEFFS = 0,
   MHCL_OP_COEFFS_BWD = 1,
   MHCL_OP_FWD_COEFFS_PRE = 2,
-  MHCL_OP_BWD_FUSED = 3
+  MHCL_OP_BWD_FUSED = 3,
+  MHCL_OP_COEFFS_LAYERS = 4
 };
 
 typedef struct {
@@ -273,6 +274,17 @@ int mhcl_logits(const mhcl_desc *desc, const void *x, const float *W, const floa
 int mhcl_coeffs_logits(const mhcl_desc *desc, const void *x, const float *W, const float *b,
                        const float *alpha, float *H_res, float *H_pre, float *H_post, float *z,
                        float *log_inv_nu, void *ws, size_t ws_bytes, void *stream);
+
+/* mhcl_coeffs_logits of L layers of one shape, each with its own inputs (x, W, b, alpha: HOST arrays of L device
+ * pointers, read during the call), without H_pre and H_post: the layers share launches, up to eight at a time, and give
+ * the bits of L single calls.
+ * out: H_res [L,T,n,n], z [L,T,M], log_inv_nu [L,T] f32; a layer's part need not be 16-byte aligned.
+ * mhcl_workspace_bytes(desc, MHCL_OP_COEFFS_LAYERS) is the workspace of ONE layer, 0 where layers do not share
+ * launches (permutation subsets and the permutation form at n = 5; very many tokens; rows so long that W is packed
+ * first): the call then returns MHCL_ERR_UNSUPPORTED.  As many layers go into a launch as `ws` has room for; L >= 0. */
+int mhcl_coeffs_logits_layers(const mhcl_desc *desc, int32_t L, const void *const *x, const float *const *W,
+                              const float *const *b, const float *const *alpha, float *H_res, float *z,
+                              float *log_inv_nu, void *ws, size_t ws_bytes, void *stream);
 
 /* Column sums and l1 errors of L layers' per-token residual matrices and of
  * their running product over the layers (Sec. 3.1 footnote 1 and last

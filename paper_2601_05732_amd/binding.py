@@ -18,14 +18,14 @@ _LIB_PATH = os.path.join(_HERE, "libmhcl.so")
 
 BF16, F32 = 0, 1
 RES_LITE, RES_SK, RES_SUBSET = 0, 1, 2
-OP_COEFFS, OP_COEFFS_BWD, OP_FWD_COEFFS_PRE, OP_BWD_FUSED = 0, 1, 2, 3
+OP_COEFFS, OP_COEFFS_BWD, OP_FWD_COEFFS_PRE, OP_BWD_FUSED, OP_COEFFS_LAYERS = 0, 1, 2, 3, 4
 
 _SYMBOLS = [
     "mhcl_status_string", "mhcl_validate", "mhcl_logit_count", "mhcl_workspace_bytes",
     "mhcl_perm_table", "mhcl_coeffs", "mhcl_pre", "mhcl_post", "mhcl_fwd_coeffs_pre",
     "mhcl_post_bwd", "mhcl_pre_bwd", "mhcl_coeffs_bwd", "mhcl_bwd_fused",
     "mhcl_logits", "mhcl_ds_chain", "mhcl_profile_next_call", "mhcl_debug_copy",
-    "mhcl_fwd_coeffs_pre_static", "mhcl_coeffs_logits",
+    "mhcl_fwd_coeffs_pre_static", "mhcl_coeffs_logits", "mhcl_coeffs_logits_layers",
 ]
 STATIC_SCRATCH_BYTES = 16 << 20   # MHCL_STATIC_SCRATCH_BYTES
 
@@ -113,6 +113,7 @@ def lib():
         L.mhcl_bwd_fused.argtypes = [P] + [V] * 13 + [Z, V]
         L.mhcl_logits.argtypes = [P] + [V] * 7 + [Z, V]
         L.mhcl_coeffs_logits.argtypes = [P] + [V] * 10 + [Z, V]
+        L.mhcl_coeffs_logits_layers.argtypes = [P, ctypes.c_int32] + [V] * 8 + [Z, V]
         L.mhcl_ds_chain.argtypes = [ctypes.c_int32, ctypes.c_int32, ctypes.c_int64] + [V] * 7
         _lib = L
     return _lib
@@ -292,6 +293,19 @@ def mhcl_coeffs_logits(d, x, W, b, alpha, H_res, H_pre, H_post, z, log_inv_nu, w
         _ptr(H_res, f, (d.T, d.n, d.n), "H_res"), _ptr(H_pre, f, (d.T, d.n), "H_pre"),
         _ptr(H_post, f, (d.T, d.n), "H_post"), _ptr(z, f, (d.T, d.M), "z"),
         _ptr(log_inv_nu, f, (d.T,), "log_inv_nu"), wp, wb, _stream()), "mhcl_coeffs_logits")
+
+
+def mhcl_coeffs_logits_layers(d, x, W, b, alpha, H_res, z, log_inv_nu, ws):
+    """x, W, b, alpha: lists of the layers' tensors; H_res [L,T,n,n], z [L,T,M], log_inv_nu [L,T]."""
+    f, io, L = torch.float32, d.torch_dtype, len(x)
+    wp, wb = _ws(ws)
+    array = ctypes.c_void_p * L
+    _check(lib().mhcl_coeffs_logits_layers(
+        ctypes.byref(d.c), L, array(*[_ptr(t, io, (d.T, d.n, d.C), "x") for t in x]),
+        array(*[_ptr(t, f, (d.n * d.C, d.M), "W") for t in W]), array(*[_ptr(t, f, (d.M,), "b") for t in b]),
+        array(*[_ptr(t, f, (3,), "alpha") for t in alpha]), _ptr(H_res, f, (L, d.T, d.n, d.n), "H_res"),
+        _ptr(z, f, (L, d.T, d.M), "z"), _ptr(log_inv_nu, f, (L, d.T), "log_inv_nu"), wp, wb, _stream()),
+        "mhcl_coeffs_logits_layers")
 
 
 def mhcl_ds_chain(n, L, T, H, colsum, l1, prod, prod_colsum, prod_l1):

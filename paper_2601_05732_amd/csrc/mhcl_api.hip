@@ -296,6 +296,10 @@ size_t mhcl_workspace_bytes(const mhcl_desc *desc, int op) {
   switch (op) {
     case MHCL_OP_COEFFS: b = CoeffsWs(*desc, nullptr).bytes; break;
     case MHCL_OP_FWD_COEFFS_PRE: b = fwd_coeffs_pre_ws_bytes(*desc); break;
+    case MHCL_OP_COEFFS_LAYERS:
+      if (!joint_layers_ok(*desc)) return 0;
+      b = CoeffsWs(*desc, nullptr).bytes;
+      break;
     case MHCL_OP_COEFFS_BWD: b = BwdWs(*desc, nullptr, false).bytes; break;
     case MHCL_OP_BWD_FUSED:
       b = fast_bwd_ok(*desc) ? FastBwdWs(*desc, nullptr).bytes : BwdWs(*desc, nullptr, true).bytes;
@@ -377,7 +381,7 @@ int mhcl_logits(const mhcl_desc *desc, const void *x, const float *W, const floa
 }
 
 // (one projection instead of the two of mhcl_coeffs and mhcl_logits, and the per-token stage writes the logits too:
-// six layers of Sinkhorn-Knopp at n = 4, C = 512, 8192 tokens, with mhcl_ds_chain, 191 / 108 us)
+// six layers of Sinkhorn-Knopp at n = 4, C = 512, 8192 tokens, each by itself, with mhcl_ds_chain, 191 / 108 us)
 int mhcl_coeffs_logits(const mhcl_desc *desc, const void *x, const float *W, const float *b,
                        const float *alpha, float *H_res, float *H_pre, float *H_post, float *z,
                        float *log_inv_nu, void *ws, size_t ws_bytes, void *stream) {
@@ -400,6 +404,46 @@ int mhcl_coeffs_logits(const mhcl_desc *desc, const void *x, const float *W, con
   if (raw.wide) MHCL_HIP(add_wide_slices(*desc, raw, s));   // (once for both stages)
   MHCL_HIP(launch_logits(*desc, logits(*desc), raw, b, alpha, z, log_inv_nu, s));
   MHCL_HIP(run_coeffs_epilogue(*desc, raw, b, alpha, H_res, H_pre, H_post, s));
+  return MHCL_OK;
+}
+
+// (us, launches of each layer / joint, with mhcl_ds_chain: six layers of Sinkhorn-Knopp at n = 4, C = 512, 8192 tokens 108 / 71, of which the
+// projection 54.8 / 36.2 and the per-token stage 38.3 / 20.6: their launches of one layer take 9 and 6.4 us, 3 to 4 of them before
+// the first load returns)
+int mhcl_coeffs_logits_layers(const mhcl_desc *desc, int32_t L, const void *const *x, const float *const *W,
+                              const float *const *b, const float *const *alpha, float *H_res, float *z,
+                              float *log_inv_nu, void *ws, size_t ws_bytes, void *stream) {
+  if (int e = check_desc(desc)) return e;
+  if (L < 0) return MHCL_ERR_INVALID_ARG;
+  if (desc->T == 0 || L == 0) return MHCL_OK;   // tensors may then be null
+  if (!joint_layers_ok(*desc)) return MHCL_ERR_UNSUPPORTED;
+  if (!x || !W || !b || !alpha || !all_ok((const void *)H_res, (const void *)z, (const void *)log_inv_nu))
+    return MHCL_ERR_INVALID_ARG;
+  for (int l = 0; l < L; ++l)
+    if (!all_ok(x[l], (const void *)W[l], (const void *)b[l], (const void *)alpha[l])) return MHCL_ERR_INVALID_ARG;
+  const size_t each = mhcl_workspace_bytes(desc, MHCL_OP_COEFFS_LAYERS);   // (a multiple of 256)
+  if (!ws || !aligned16(ws) || ws_bytes < each) return MHCL_ERR_WORKSPACE;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  Disarm disarm;
+  const CoeffsWs w(*desc, ws);
+  const RawSums raw = projected(*desc, w.u_raw, w.sumsq);
+  const int M = logits(*desc), n = desc->n;
+  const int most = ws_bytes / each < kJointLayers ? static_cast<int>(ws_bytes / each) : kJointLayers;
+  for (int l0 = 0; l0 < L; l0 += most) {
+    const int count = L - l0 < most ? L - l0 : most;
+    JointLayers j{};
+    j.stride = static_cast<int64_t>(each / sizeof(float));
+    for (int i = 0; i < count; ++i) {
+      j.x[i] = x[l0 + i]; j.W[i] = W[l0 + i]; j.b[i] = b[l0 + i]; j.alpha[i] = alpha[l0 + i];
+    }
+    {
+      StageBracket br(l0 == 0 ? MHCL_STAGE_FWD_PROJ : MHCL_STAGE_NONE, s);
+      MHCL_HIP(proj_fullprec_used(*desc) ? launch_proj_fullprec_layers(*desc, M, j, count, w.u_raw, w.sumsq, s)
+                                         : launch_proj_mfma_layers(*desc, M, j, count, w.u_raw, w.sumsq, s));
+    }
+    const int64_t at = static_cast<int64_t>(l0) * desc->T;
+    MHCL_HIP(launch_token_layers(*desc, raw, j, count, H_res + at * n * n, z + at * M, log_inv_nu + at, s));
+  }
   return MHCL_OK;
 }
 

@@ -73,12 +73,9 @@ struct ProjCfg {
 };
 
 template <int NT, bool DIRECT>
-__global__ __launch_bounds__(ProjCfg<NT>::kThreads, ProjCfg<NT>::kMinWaves) void proj_mfma_kernel(const uint16_t *__restrict__ x,
-                                                           const u32x4 *__restrict__ Wp,
-                                                           const float *__restrict__ W, int K,
-                                                           int M, int64_t T, int steps_per_part,
-                                                           float *__restrict__ u_raw,
-                                                           float *__restrict__ sumsq) {
+__device__ __forceinline__ void proj_mfma(const uint16_t *__restrict__ x, const u32x4 *__restrict__ Wp,
+                                          const float *__restrict__ W, int K, int M, int64_t T, int steps_per_part,
+                                          float *__restrict__ u_raw, float *__restrict__ sumsq) {
   // gridDim.y blocks share the K range of the same tokens (K split): block
   // (bx, part) walks K steps [part * steps_per_part, ...) and writes its
   // partial u_raw / sumsq to slice `part`; the consumer adds the slices in order.
@@ -288,6 +285,21 @@ __global__ __launch_bounds__(ProjCfg<NT>::kThreads, ProjCfg<NT>::kMinWaves) void
   }
 }
 
+template <int NT, bool DIRECT>
+__global__ __launch_bounds__(ProjCfg<NT>::kThreads, ProjCfg<NT>::kMinWaves) void proj_mfma_kernel(
+    const uint16_t *__restrict__ x, const u32x4 *__restrict__ Wp, const float *__restrict__ W, int K, int M, int64_t T,
+    int steps_per_part, float *__restrict__ u_raw, float *__restrict__ sumsq) {
+  proj_mfma<NT, DIRECT>(x, Wp, W, K, M, T, steps_per_part, u_raw, sumsq);
+}
+// gridDim.z layers of a stack side by side (W as it is): the blocks of one layer of few tokens fill the chip neither at the
+// start of its rows nor at their end
+template <int NT>
+__global__ __launch_bounds__(ProjCfg<NT>::kThreads, ProjCfg<NT>::kMinWaves) void proj_mfma_layers_kernel(
+    JointLayers layers, int K, int M, int64_t T, int steps_per_part, float *__restrict__ u_raw, float *__restrict__ sumsq) {
+  const int l = blockIdx.z;
+  proj_mfma<NT, true>(static_cast<const uint16_t *>(layers.x[l]), nullptr, layers.W[l], K, M, T, steps_per_part,
+                      u_raw + l * layers.stride, sumsq + l * layers.stride);
+}
 
 // W [K, M] fp32 -> A layout (see mhcl_mfma.h).  One thread per (block pair, lane).
 __device__ __forceinline__ void pack_w_a_thread(int idx, const float *__restrict__ W, int K, int M,
@@ -1881,6 +1893,21 @@ hipError_t launch_proj_mfma(const mhcl_desc &d, int M, const void *x, const void
   });
 }
 
+hipError_t launch_proj_mfma_layers(const mhcl_desc &d, int M, const JointLayers &layers, int L, float *u_raw, float *sumsq,
+                                   hipStream_t s) {
+  return dispatch_nt_proj(logit_tiles(M), [&](auto nt) {
+    constexpr int NT = decltype(nt)::value, kTok = ProjCfg<NT>::kTokens;
+    if constexpr (NT <= 3) {   // (those of the forms of joint_layers_ok)
+      static_assert(ProjCfg<NT>::kLdsBytes <= 64 * 1024);
+      hipLaunchKernelGGL(proj_mfma_layers_kernel<NT>,
+                         dim3(static_cast<unsigned>((d.T + kTok - 1) / kTok), mfma_ksplit(d), L),
+                         dim3(ProjCfg<NT>::kThreads), ProjCfg<NT>::kLdsBytes, s, layers, d.n * d.C, M, d.T,
+                         mfma_steps(d), u_raw, sumsq);
+      return hipGetLastError();
+    }
+    return hipErrorInvalidValue;
+  });
+}
 
 // ---- fused backward, bf16, n <= 4 -------------------------------------------
 // n <= 4 (at most 32 logits): fused passes; n = 5: the wide variant of pass 2

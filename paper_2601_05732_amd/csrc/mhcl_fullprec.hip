@@ -201,6 +201,16 @@ __global__ __launch_bounds__(64 * WAVES, 1) void proj_fullprec_kernel(
   proj_fullprec<IO, NT, WAVES>(x, W, nC, M, T, steps_per_part, u_raw, sumsq, blockIdx.x, blockIdx.y, gridDim.y);
 }
 
+// gridDim.z layers of a stack side by side
+template <typename IO, int NT>
+__global__ __launch_bounds__(64 * kProjWaves, 1) void proj_fullprec_layers_kernel(
+    JointLayers layers, int nC, int M, int64_t T, int steps_per_part, float *__restrict__ u_raw,
+    float *__restrict__ sumsq) {
+  const int l = blockIdx.z;
+  proj_fullprec<IO, NT, kProjWaves>(layers.x[l], layers.W[l], nC, M, T, steps_per_part, u_raw + l * layers.stride,
+                                    sumsq + l * layers.stride, blockIdx.x, blockIdx.y, gridDim.y);
+}
+
 // The n^2 + 2n reductions over C of the backward, as bwd_dots_kernel has them: `waves` waves per token, the block's
 // eight take 8 / waves tokens.  They need nothing of the projection, so one launch has blocks of both: the
 // products run at the fp64 rate and these at that of HBM, and x comes from the caches the second time.
@@ -707,6 +717,27 @@ hipError_t launch_proj_fullprec(const mhcl_desc &d, int M, const void *x, const 
       return hipGetLastError();
     });
   });
+}
+
+hipError_t launch_proj_fullprec_layers(const mhcl_desc &d, int M, const JointLayers &layers, int L, float *u_raw,
+                                       float *sumsq, hipStream_t s) {
+  const int V = d.io_dtype == MHCL_BF16 ? BF16::kVec : F32::kVec;
+  const int nC = d.n * d.C, parts = proj_fullprec_parts(d);
+  const int nsteps = (nC + 4 * V - 1) / (4 * V), spp = (nsteps + parts - 1) / parts;
+  const dim3 grid(static_cast<unsigned>((d.T + 15) / 16), parts, L);
+  auto go = [&](auto nt) {
+    return dispatch_io(d.io_dtype, [&](auto io) {
+      hipLaunchKernelGGL((proj_fullprec_layers_kernel<decltype(io), decltype(nt)::value>), grid, dim3(64 * kProjWaves), 0,
+                         s, layers, nC, M, d.T, spp, u_raw, sumsq);
+      return hipGetLastError();
+    });
+  };
+  switch (logit_tiles(M)) {   // (those of the forms of joint_layers_ok)
+    case 1: return go(std::integral_constant<int, 1>{});
+    case 2: return go(std::integral_constant<int, 2>{});
+    case 3: return go(std::integral_constant<int, 3>{});
+  }
+  return hipErrorInvalidValue;
 }
 
 // Token chunks: one round of blocks on the 256 compute units, and no more than one per 256 tokens (two

@@ -48,6 +48,14 @@ struct BwdTokenBufs {
   float *gz;      // [gz_rows(d), M+3] sums over a block's tokens of g_z and of the per-group g_z u
 };
 
+// Layers of a stack whose kernels share launches (mhcl_coeffs_logits_layers).
+constexpr int kJointLayers = 8;
+struct JointLayers {
+  const void *x[kJointLayers];
+  const float *W[kJointLayers], *b[kJointLayers], *alpha[kJointLayers];
+  int64_t stride;   // floats from a layer's u_raw to the next one's, and of sumsq
+};
+
 // ---- stream kernels: any n in 1..8, bf16 or f32 streams -----
 hipError_t launch_pre(const mhcl_desc &d, const void *x, const float *H_pre, void *h, hipStream_t s);
 hipError_t launch_post(const mhcl_desc &d, const void *x, const void *y, const float *H_res,
@@ -74,6 +82,8 @@ int proj_fullprec_parts(const mhcl_desc &d);   // slices it writes: one in fp32,
 int64_t proj_fullprec_slice_floats(const mhcl_desc &d);
 hipError_t launch_proj_fullprec(const mhcl_desc &d, int M, const void *x, const float *W,
                                 float *u_raw, float *sumsq, hipStream_t s);
+hipError_t launch_proj_fullprec_layers(const mhcl_desc &d, int M, const JointLayers &layers, int L, float *u_raw,
+                                       float *sumsq, hipStream_t s);
 // What a projection leaves for the per-token stage, where the slices are added in order: u_raw
 // [parts][T][M] and sumsq [parts][T], in fp64 if `wide`.
 struct RawSums {
@@ -124,6 +134,10 @@ bool token_logits_ok(const mhcl_desc &d, const RawSums &raw);
 hipError_t launch_token_coeffs_logits(const mhcl_desc &d, const RawSums &raw, const float *b,
                                       const float *alpha, float *H_res, float *H_pre, float *H_post,
                                       float *z, float *spread, hipStream_t s);
+// several layers' launches shared, where joint_layers_ok: `raw` is the first one's, the outputs are stacks [layer][T][...]
+bool joint_layers_ok(const mhcl_desc &d);
+hipError_t launch_token_layers(const mhcl_desc &d, const RawSums &raw, const JointLayers &layers, int count, float *H_res,
+                               float *z, float *spread, hipStream_t s);
 hipError_t launch_token_bwd_full(const mhcl_desc &d, const RawSums &raw, const float *b,
                                  const float *alpha, const float *g_H_res, const float *g_H_pre,
                                  const float *g_H_post, const BwdTokenBufs &o, hipStream_t s);
@@ -170,6 +184,9 @@ hipError_t launch_pack_w_b(const mhcl_desc &d, int M, const float *W, void *Wp, 
 bool proj_mfma_direct(const mhcl_desc &d);
 hipError_t launch_proj_mfma(const mhcl_desc &d, int M, const void *x, const void *Wp, const float *W,
                             float *u_raw, float *sumsq, hipStream_t s);
+// (W as it is: where proj_mfma_direct)
+hipError_t launch_proj_mfma_layers(const mhcl_desc &d, int M, const JointLayers &layers, int L, float *u_raw, float *sumsq,
+                                   hipStream_t s);
 
 // Single-read forward (projection slices, H_pre and h from one read of x): bf16 fast path
 // with at most 32 logits, C a multiple of 256 from 1024 to 8192, enough tokens to fill the pipeline.

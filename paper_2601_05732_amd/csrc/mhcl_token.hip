@@ -386,6 +386,7 @@ __device__ __forceinline__ void token_stage(const TokenIn &in, const TokenOut &o
 #pragma unroll
           for (int c = 0; c < CC; ++c) out.H_res[t * NN + cell0 + c] = H[c];
         }
+        if (OUT == kOutLogits && out.H_pre == nullptr) return;   // (of several layers: not asked for)
 #pragma unroll
         for (int gi = 0; gi < GG; ++gi) {
           const int gt = l + L * gi;
@@ -539,6 +540,19 @@ __device__ __forceinline__ void token_stage(const TokenIn &in, const TokenOut &o
 template <int N, int MODE, int OUT, int L>
 __global__ __launch_bounds__(kTokThreads<L>) void token_stage_kernel(TokenIn in, TokenOut out) {
   token_stage<N, MODE, OUT, L>(in, out);
+}
+// gridDim.y layers of a stack side by side: H_res, logits and spreads in stacks [layer][T][...]
+template <int N, int MODE, int L>
+__global__ __launch_bounds__(kTokThreads<L>) void token_layers_kernel(TokenIn in, TokenOut out, JointLayers layers) {
+  const int l = blockIdx.y;
+  in.u_raw += l * layers.stride;
+  in.sumsq += l * layers.stride;
+  in.b = layers.b[l];
+  in.alpha = layers.alpha[l];
+  out.H_res += l * in.T * (N * N);
+  out.z += l * in.T * Dims<N, MODE>::M;
+  out.spread += l * in.T;
+  token_stage<N, MODE, kOutLogits, L>(in, out);
 }
 // the forward's stage, and from block p.first on the pre-aggregate
 template <int N, int MODE, int L, typename IO>
@@ -1023,6 +1037,46 @@ hipError_t launch_token_coeffs_logits(const mhcl_desc &d, const RawSums &raw, co
   TokenOut out{};
   out.H_res = H_res; out.H_pre = H_pre; out.H_post = H_post; out.z = z; out.spread = spread;
   return launch_token_stage<kOutLogits>(d, token_in(d, raw, b, alpha), out, s);
+}
+
+// Where the launches of several layers are shared: the forms whose per-token stage writes the logits, and whose
+// projection takes W as it is.
+bool joint_layers_ok(const mhcl_desc &d) {
+  if (d.T == 0 || coeffs_group_ok(d) || token_per_lane(d, false)) return false;
+  return proj_fullprec_used(d) || proj_mfma_direct(d);
+}
+hipError_t launch_token_layers(const mhcl_desc &d, const RawSums &raw, const JointLayers &layers, int count, float *H_res,
+                               float *z, float *spread, hipStream_t s) {
+  const TokenIn in = token_in(d, raw, nullptr, nullptr);
+  TokenOut out{};
+  out.H_res = H_res; out.z = z; out.spread = spread;
+  const bool many = token_stage_many(d, false);
+  const int64_t blocks64 = (d.T + 63) / 64;
+  const dim3 grid(static_cast<unsigned>(many ? blocks64 : 2 * blocks64), count);
+  auto go = [&](auto nn, auto mm) {
+    constexpr int N = decltype(nn)::value, MODE = decltype(mm)::value, LF = N <= 4 ? 16 : 8;
+    auto kern = token_layers_kernel<N, MODE, LF>;
+    int threads = kTokThreads<LF>;
+    if constexpr (N <= 4) {
+      if (many) {
+        kern = token_layers_kernel<N, MODE, 4>;
+        threads = kTokThreads<4>;
+      }
+    }
+    hipLaunchKernelGGL(kern, grid, dim3(threads), 0, s, in, out, layers);
+    return hipGetLastError();
+  };
+  using LI = std::integral_constant<int, MHCL_RES_LITE>;
+  using SK = std::integral_constant<int, MHCL_RES_SK>;
+  const bool lite = d.res_mode == MHCL_RES_LITE;
+  switch (d.n) {
+    case 1: return lite ? go(std::integral_constant<int, 1>{}, LI{}) : go(std::integral_constant<int, 1>{}, SK{});
+    case 2: return lite ? go(std::integral_constant<int, 2>{}, LI{}) : go(std::integral_constant<int, 2>{}, SK{});
+    case 3: return lite ? go(std::integral_constant<int, 3>{}, LI{}) : go(std::integral_constant<int, 3>{}, SK{});
+    case 4: return lite ? go(std::integral_constant<int, 4>{}, LI{}) : go(std::integral_constant<int, 4>{}, SK{});
+    case 5: return lite ? hipErrorInvalidValue : go(std::integral_constant<int, 5>{}, SK{});
+  }
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_token_bwd_fast(const mhcl_desc &d, const float *b, const float *alpha,

@@ -5,7 +5,8 @@ matrices H_res of every layer (permutation form or 20-step Sinkhorn-Knopp),
 the relative range log(1/nu) of the Sinkhorn-Knopp input (Eq. 3), the column
 sums and l1 errors of each matrix ("per-matrix" in Fig. 2) and of the product
 over the layers ("prod").  All arithmetic runs in ``libmhcl.so``
-(``mhcl_coeffs_logits``, ``mhcl_ds_chain``); this module only
+(``mhcl_coeffs_logits`` or, for several layers at once,
+``mhcl_coeffs_logits_layers``, and ``mhcl_ds_chain``); this module only
 allocates, draws inputs and summarises.
 
 The paper takes these statistics from trained models; those weights are not
@@ -27,6 +28,9 @@ import torch
 from . import binding as mhcl
 from .layer import desc_for
 
+JOINT_LAYERS = 8            # layers of a stack in one launch, as far as their workspace stays within
+JOINT_BYTES = 256 << 20     # this
+
 
 def layer_stack(wl, L: int, inputs, device: str = "cuda"):
     """H [L,T,n,n], z [L,T,M], log_inv_nu [L,T] for L layers.  ``wl`` is a workload
@@ -37,6 +41,13 @@ def layer_stack(wl, L: int, inputs, device: str = "cuda"):
     H = torch.empty(L, wl.T, wl.n, wl.n, device=device, dtype=f)
     z = torch.empty(L, wl.T, wl.M, device=device, dtype=f)
     spread = torch.empty(L, wl.T, device=device, dtype=f)
+    each = 0 if callable(inputs) else mhcl.workspace_bytes(d, mhcl.OP_COEFFS_LAYERS)
+    if each and L > 1:
+        # the layers share launches (one at a time where they are drawn one by one: only one is alive then)
+        layers = [[inputs[l][k] for l in range(L)] for k in ("x", "W", "b", "alpha")]
+        ws = torch.empty(each * max(1, min(L, JOINT_LAYERS, JOINT_BYTES // each)), device=device, dtype=torch.uint8)
+        mhcl.mhcl_coeffs_logits_layers(d, *layers, H, z, spread, ws)
+        return H, z, spread
     # the library wants 16-byte aligned pointers: a layer's slice where that holds for all of
     # them, else a buffer of its own, copied into the stack afterwards
     own = [None if t.shape[1:].numel() % 4 == 0 else t.new_empty(t.shape[1:]) for t in (H, z, spread)]
