@@ -164,6 +164,12 @@ int mhcl_pre(const mhcl_desc *desc, const void *x, const float *H_pre, void *h, 
 int mhcl_post(const mhcl_desc *desc, const void *x, const void *y, const float *H_res,
               const float *H_post, void *x_out, void *stream);
 
+/* The ends of a stack of layers whose input [T,C] is copied into the n streams and whose output is their sum (a
+ * choice of the autograd front end, not the paper's); each is the other's backward.
+ * in : x[t][i][c] = x0[t][c];  out: out[t][c] = sum_i x[t][i][c], in fp32 in the order of the streams, rounded once. */
+int mhcl_streams_in(const mhcl_desc *desc, const void *x0, void *x, void *stream);
+int mhcl_streams_out(const mhcl_desc *desc, const void *x, void *out, void *stream);
+
 /* mhcl_coeffs and mhcl_pre in one call (one validation, one workspace).
  * bf16 streams with at most 32 logits, C a multiple of 256 from 1024 to 8192
  * and at least 512 * floor(65536 / C) tokens: ONE kernel reads x from HBM once and produces the

@@ -14,6 +14,10 @@ and its backward, once the gradient on x_out has arrived, is
     g_h                    = backward of f               (autograd)
     g_x, g_W, g_b, g_alpha = mhcl_bwd_fused(x, y, g_xout, g_h)
 
+The graph nodes of plain calls are C++ (``torch_ext/autograd.cpp``: the same calls and gradients at a third of the
+host time); calls under function transforms, tracing or dispatch modes, with tensor subclasses, or that an argument
+check will refuse, take the nodes below.
+
 The two graph nodes of a layer share a small link object: the node of the post
 update hands g_xout and y over to the node of the coefficients, whose backward
 runs the fused kernel and returns the whole g_x.  Autograd runs the post node
@@ -37,6 +41,35 @@ from . import binding as mhcl
 from .layer import PHASE_G_X, PHASE_G_XOUT, PHASE_X, empty_stream
 
 
+_ext = None
+
+
+def _native():
+    """The C++ graph nodes; raises if they have not been built."""
+    global _ext
+    if _ext is None:
+        mhcl.lib()
+        from . import _autograd_native
+        _ext = _autograd_native
+    return _ext
+
+
+def _plain(*tensors) -> bool:
+    """Whether nothing but plain autograd looks at a call on these GPU tensors: no subclass, function transform,
+    forward-mode level, dispatch or function mode, trace or compilation (the C++ nodes know none of them)."""
+    try:
+        C = torch._C
+        return (all(type(t) in (torch.Tensor, torch.nn.Parameter) and t.is_cuda for t in tensors)
+                and not C._are_functorch_transforms_active() and C._len_torch_dispatch_stack() == 0
+                and C._len_torch_function_stack() == 0 and C._get_tracing_state() is None
+                and torch.autograd.forward_ad._current_level < 0 and not torch.compiler.is_compiling())
+    except AttributeError:      # a torch without one of these
+        return False
+
+
+_IO = {torch.bfloat16: mhcl.BF16, torch.float32: mhcl.F32}
+
+
 class _Link:
     """What the post node leaves for the coefficient node of the same layer."""
     __slots__ = ("y", "g_xout", "H_pre", "g_x_phase", "perm")
@@ -49,7 +82,7 @@ class _Link:
 
 def _desc(x, res_mode, sk_iters, eps, perm=None):
     T, n, C = x.shape
-    io = {torch.bfloat16: mhcl.BF16, torch.float32: mhcl.F32}[x.dtype]
+    io = _IO[x.dtype]
     return mhcl.Desc(n, C, T, io, res_mode, sk_iters, eps, perm)
 
 
@@ -160,15 +193,45 @@ class HyperConnection(torch.nn.Module):
                                   n_perm=0 if perm is None else int(perm.shape[0]))
         self.W, self.b, self.alpha = (torch.nn.Parameter(t) for t in (W, b, alpha))
 
+    def _takes_native(self, x) -> bool:
+        W, b, alpha, perm, f = self.W, self.b, self.alpha, self.perm, torch.float32
+        if x.dtype not in _IO or not _plain(x, W, b, alpha, *(() if perm is None else (perm,))):
+            return False
+        if perm is not None and not (perm.dtype is torch.int8 and perm.dim() == 2 and perm.is_contiguous()):
+            return False
+        R = {mhcl.RES_LITE: math.factorial(self.n), mhcl.RES_SK: self.n * self.n,
+             mhcl.RES_SUBSET: 0 if perm is None else perm.shape[0]}[self.res_mode]
+        M = R + 2 * self.n
+        return (W.dtype is f and b.dtype is f and alpha.dtype is f and W.shape == (self.n * self.C, M) and b.shape == (M,)
+                and alpha.shape == (3,) and W.is_contiguous() and b.is_contiguous() and alpha.is_contiguous())
+
+    def _native_link(self, x, g_x_phase):
+        return _native().link(self.n, self.C, x.shape[0], _IO[x.dtype], self.res_mode, self.sk_iters, self.eps, self.perm,
+                              g_x_phase)
+
     def forward(self, x: torch.Tensor, f):
         if x.dim() != 3 or x.shape[1] != self.n or x.shape[2] != self.C:
             raise ValueError(f"x must be [T, {self.n}, {self.C}], got {tuple(x.shape)}")
         x = x.contiguous()
+        if self._takes_native(x):
+            nodes, T = _native(), x.shape[0]
+            link = self._native_link(x, self.g_x_phase)
+            h, H_res, H_post = nodes.coeffs_pre(x, self.W, self.b, self.alpha, link)
+            y = f(h)
+            if not (isinstance(y, torch.Tensor) and y.is_cuda and y.dtype is x.dtype and y.shape == (T, self.C)):
+                mhcl._ptr(y.contiguous(), x.dtype, (T, self.C), "y")      # raises
+            return nodes.post(x, y, H_res, H_post, link)
         link = _Link(self.g_x_phase, self.perm)
         cfg = (self.res_mode, self.sk_iters, self.eps)
         h, H_res, H_post, _ = _CoeffsPre.apply(x, self.W, self.b, self.alpha, link, *cfg)
         y = f(h)
         return _Post.apply(x, y, H_res, H_post, link, *cfg)
+
+
+def _dense(t: torch.Tensor) -> torch.Tensor:
+    """`t` contiguous and 16-byte aligned, as the kernels read it."""
+    t = t.contiguous()
+    return t if t.data_ptr() % 16 == 0 else t.clone()
 
 
 class HyperConnectionStack(torch.nn.Module):
@@ -186,7 +249,14 @@ class HyperConnectionStack(torch.nn.Module):
              for l in range(len(self.fs))])
 
     def forward(self, x0: torch.Tensor):
-        x = x0.unsqueeze(1).expand(-1, self.n, -1).contiguous()
+        ends = None
+        if len(self.layers) and x0.dim() == 2 and x0.shape[1] == self.layers[0].C and x0.dtype in _IO and _plain(x0):
+            # (the gradient on the last layer's x_out lies as a further layer's g_x would)
+            ends = self.layers[0]._native_link(x0, PHASE_G_X if len(self.layers) % 2 == 0 else PHASE_G_XOUT)
+            x = _dense(x0)
+            x = _native().streams_in(x, ends)
+        else:
+            x = x0.unsqueeze(1).expand(-1, self.n, -1).contiguous()
         for layer, f in zip(self.layers, self.fs):
             x = layer(x, f)
-        return x.sum(dim=1)
+        return x.sum(dim=1) if ends is None else _native().streams_out(x, ends)

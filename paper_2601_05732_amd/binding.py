@@ -25,7 +25,7 @@ _SYMBOLS = [
     "mhcl_perm_table", "mhcl_coeffs", "mhcl_pre", "mhcl_post", "mhcl_fwd_coeffs_pre",
     "mhcl_post_bwd", "mhcl_pre_bwd", "mhcl_coeffs_bwd", "mhcl_bwd_fused",
     "mhcl_logits", "mhcl_ds_chain", "mhcl_profile_next_call", "mhcl_debug_copy",
-    "mhcl_fwd_coeffs_pre_static", "mhcl_coeffs_logits", "mhcl_coeffs_logits_layers",
+    "mhcl_fwd_coeffs_pre_static", "mhcl_coeffs_logits", "mhcl_coeffs_logits_layers", "mhcl_streams_in", "mhcl_streams_out",
 ]
 STATIC_SCRATCH_BYTES = 16 << 20   # MHCL_STATIC_SCRATCH_BYTES
 
@@ -113,6 +113,7 @@ def lib():
         L.mhcl_bwd_fused.argtypes = [P] + [V] * 13 + [Z, V]
         L.mhcl_logits.argtypes = [P] + [V] * 7 + [Z, V]
         L.mhcl_coeffs_logits.argtypes = [P] + [V] * 10 + [Z, V]
+        L.mhcl_streams_in.argtypes = L.mhcl_streams_out.argtypes = [P] + [V] * 3
         L.mhcl_coeffs_logits_layers.argtypes = [P, ctypes.c_int32] + [V] * 8 + [Z, V]
         L.mhcl_ds_chain.argtypes = [ctypes.c_int32, ctypes.c_int32, ctypes.c_int64] + [V] * 7
         _lib = L
@@ -208,6 +209,18 @@ def mhcl_post(d, x, y, H_res, H_post, x_out):
         ctypes.byref(d.c), _ptr(x, io, (d.T, d.n, d.C), "x"), _ptr(y, io, (d.T, d.C), "y"),
         _ptr(H_res, f, (d.T, d.n, d.n), "H_res"), _ptr(H_post, f, (d.T, d.n), "H_post"),
         _ptr(x_out, io, (d.T, d.n, d.C), "x_out"), _stream()), "mhcl_post")
+
+
+def mhcl_streams_in(d, x0, x):
+    io = d.torch_dtype
+    _check(lib().mhcl_streams_in(ctypes.byref(d.c), _ptr(x0, io, (d.T, d.C), "x0"), _ptr(x, io, (d.T, d.n, d.C), "x"),
+                                 _stream()), "mhcl_streams_in")
+
+
+def mhcl_streams_out(d, x, out):
+    io = d.torch_dtype
+    _check(lib().mhcl_streams_out(ctypes.byref(d.c), _ptr(x, io, (d.T, d.n, d.C), "x"), _ptr(out, io, (d.T, d.C), "out"),
+                                  _stream()), "mhcl_streams_out")
 
 
 def mhcl_fwd_coeffs_pre(d, x, W, b, alpha, H_res, H_pre, H_post, h, ws):

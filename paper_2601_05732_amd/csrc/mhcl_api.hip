@@ -485,6 +485,24 @@ int mhcl_post(const mhcl_desc *desc, const void *x, const void *y, const float *
   return MHCL_OK;
 }
 
+int mhcl_streams_in(const mhcl_desc *desc, const void *x0, void *x, void *stream) {
+  if (int e = check_desc(desc)) return e;
+  if (desc->T == 0) return MHCL_OK;   // per-token tensors may then be null
+  if (!all_ok(x0, (const void *)x) || x == x0) return MHCL_ERR_INVALID_ARG;
+  Disarm disarm;
+  MHCL_HIP(launch_streams_in(*desc, x0, x, static_cast<hipStream_t>(stream)));
+  return MHCL_OK;
+}
+
+int mhcl_streams_out(const mhcl_desc *desc, const void *x, void *out, void *stream) {
+  if (int e = check_desc(desc)) return e;
+  if (desc->T == 0) return MHCL_OK;
+  if (!all_ok(x, (const void *)out) || x == out) return MHCL_ERR_INVALID_ARG;
+  Disarm disarm;
+  MHCL_HIP(launch_streams_out(*desc, x, out, static_cast<hipStream_t>(stream)));
+  return MHCL_OK;
+}
+
 int mhcl_fwd_coeffs_pre(const mhcl_desc *desc, const void *x, const float *W, const float *b,
                         const float *alpha, float *H_res, float *H_pre, float *H_post, void *h,
                         void *ws, size_t ws_bytes, void *stream) {

@@ -3,6 +3,7 @@
 // reproducible.
 #include "mhcl_common.h"
 #include "mhcl_internal.h"
+#include "mhcl_mfma.h"
 
 namespace mhcl {
 
@@ -83,6 +84,40 @@ __global__ __launch_bounds__(kBlock) void pre_kernel(const void *__restrict__ x,
     for (int e = 0; e < V; ++e) acc[e] = fmaf(w, v[e], acc[e]);
   }
   IO::store(h, t * C + c, acc);
+}
+
+// The ends of a stack, one thread per 16-byte chunk of a row of C.  Bound by HBM or the memory-side cache: n = 4, C = 1024,
+// 2048 tokens, bf16, us a call, torch's copy and sum / these: in 16.0 / 6.1 (21 MB), out 7.5 / 4.3.
+template <typename IO, int N>
+__global__ __launch_bounds__(kBlock) void streams_in_kernel(const u32x4 *__restrict__ x0, u32x4 *__restrict__ x, int C,
+                                                            int64_t T) {
+  const int vpr = C / IO::kVec;
+  const int64_t idx = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
+  if (idx >= T * vpr) return;
+  const int64_t t = idx / vpr, c = idx - t * vpr;
+  const u32x4 v = x0[idx];
+#pragma unroll
+  for (int j = 0; j < N; ++j) x[(t * N + j) * vpr + c] = v;
+}
+template <typename IO, int N>
+__global__ __launch_bounds__(kBlock) void streams_out_kernel(const void *__restrict__ x, void *__restrict__ out, int C,
+                                                             int64_t T) {
+  constexpr int V = IO::kVec;
+  const int vpr = C / V;
+  const int64_t idx = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
+  if (idx >= T * vpr) return;
+  const int64_t t = idx / vpr;
+  const int c = static_cast<int>(idx % vpr) * V;
+  float acc[V], v[N][V];
+#pragma unroll
+  for (int j = 0; j < N; ++j) IO::load(x, (t * N + j) * C + c, v[j]);
+#pragma unroll
+  for (int e = 0; e < V; ++e) {
+    acc[e] = v[0][e];
+#pragma unroll
+    for (int j = 1; j < N; ++j) acc[e] += v[j][e];
+  }
+  IO::store(out, t * C + c, acc);
 }
 
 // x_out = H_res x + H_post^T y   (Eq. 1)
@@ -320,6 +355,27 @@ hipError_t launch_pre(const mhcl_desc &d, const void *x, const float *H_pre, voi
       constexpr int N = decltype(nn)::value;
       hipLaunchKernelGGL((pre_kernel<IO, N>), dim3(blocks_for(d.T * (d.C / IO::kVec), kBlock)),
                          dim3(kBlock), 0, s, x, H_pre, h, d.C, d.T);
+      return hipGetLastError();
+    });
+  });
+}
+
+hipError_t launch_streams_in(const mhcl_desc &d, const void *x0, void *x, hipStream_t s) {
+  return dispatch_io(d.io_dtype, [&](auto io) {
+    return dispatch_n(d.n, [&](auto nn) {
+      using IO = decltype(io);
+      hipLaunchKernelGGL((streams_in_kernel<IO, decltype(nn)::value>), dim3(blocks_for(d.T * (d.C / IO::kVec), kBlock)),
+                         dim3(kBlock), 0, s, static_cast<const u32x4 *>(x0), static_cast<u32x4 *>(x), d.C, d.T);
+      return hipGetLastError();
+    });
+  });
+}
+hipError_t launch_streams_out(const mhcl_desc &d, const void *x, void *out, hipStream_t s) {
+  return dispatch_io(d.io_dtype, [&](auto io) {
+    return dispatch_n(d.n, [&](auto nn) {
+      using IO = decltype(io);
+      hipLaunchKernelGGL((streams_out_kernel<IO, decltype(nn)::value>), dim3(blocks_for(d.T * (d.C / IO::kVec), kBlock)),
+                         dim3(kBlock), 0, s, x, out, d.C, d.T);
       return hipGetLastError();
     });
   });

@@ -65,6 +65,9 @@ hipError_t launch_post_bwd(const mhcl_desc &d, const void *x, const void *y, con
                            float *g_H_res, float *g_H_post, hipStream_t s);
 hipError_t launch_pre_bwd(const mhcl_desc &d, const void *x, const float *H_pre, const void *g_h,
                           void *g_x, float *g_H_pre, hipStream_t s);
+// x = n copies of x0, out = the sum of x's streams
+hipError_t launch_streams_in(const mhcl_desc &d, const void *x0, void *x, hipStream_t s);
+hipError_t launch_streams_out(const mhcl_desc &d, const void *x, void *out, hipStream_t s);
 // dots only: g_H_res = <g_xout[i], x[j]>, g_H_post = <g_xout[i], y>, g_H_pre = <g_h, x[j]>
 hipError_t launch_bwd_dots(const mhcl_desc &d, const void *x, const void *y, const void *g_xout,
                            const void *g_h, float *g_H_res, float *g_H_post, float *g_H_pre,
