@@ -71,9 +71,11 @@ __device__ __forceinline__ void column_sums(const float (&v)[CC], float (&s)[CC]
 }
 template <int L, int CC>
 __device__ __forceinline__ float row_sum(const float (&v)[CC]) {
+  // (the same sums whether a lane has a row, up to four entries, or an entry)
+  if constexpr (CC == 4) return lane_add(lane_add(v[0], v[1]), lane_add(v[2], v[3]));
   float s = v[0];
 #pragma unroll
-  for (int c = 1; c < CC; ++c) s += v[c];
+  for (int c = 1; c < CC; ++c) s = lane_add(s, v[c]);
   if constexpr (L == 16) {
     s = lane_add(s, dpp<kXor1>(s));
     s = lane_add(s, dpp<kXor2>(s));
@@ -1061,7 +1063,11 @@ hipError_t launch_token_layers(const mhcl_desc &d, const RawSums &raw, const Joi
   const TokenIn in = token_in(d, raw, nullptr, nullptr);
   TokenOut out{};
   out.H_res = H_res; out.z = z; out.spread = spread;
-  const bool many = token_stage_many(d, false);
+  // Four lanes per token from the tokens of all layers on where sums over rows and columns are all that lanes share
+  // (six layers of 8192 tokens, sixteen / four, us: n = 4 16.5 / 12.4, n = 3, four layers 11.1 / 7.4; n = 2, six of 4000 8.9 / 6.8).
+  // Not over fp64 slices, and not in the permutation form, whose weights would be summed in another order.
+  const bool many = token_stage_many(d, false) ||
+                    (d.res_mode == MHCL_RES_SK && d.n <= 4 && !raw.wide && d.T * count >= 16384);
   const int64_t blocks64 = (d.T + 63) / 64;
   const dim3 grid(static_cast<unsigned>(many ? blocks64 : 2 * blocks64), count);
   auto go = [&](auto nn, auto mm) {

@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 
 CASES = [(4, 512, 1251, "bf16", "sk", 6), (4, 64, 33, "bf16", "lite", 9), (2, 24, 65, "f32", "sk", 2),
          (5, 128, 1700, "bf16", "sk", 3), (3, 64, 16385, "bf16", "lite", 2), (1, 8, 1, "f32", "lite", 17),
-         (4, 1024, 40, "bf16", "sk", 2)]
+         (4, 1024, 40, "bf16", "sk", 2), (4, 64, 5003, "bf16", "sk", 4), (3, 64, 8192, "bf16", "sk", 2),
+         (2, 128, 2700, "bf16", "sk", 7), (1, 64, 4097, "bf16", "sk", 4)]
 
 
 @pytest.mark.parametrize("room", [1, 2, 8])
