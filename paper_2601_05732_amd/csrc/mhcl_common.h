@@ -40,7 +40,9 @@ __device__ __forceinline__ void split_bf16(float w, uint16_t &hi, uint16_t &lo) 
   lo = f32_to_bf16(w - bf16_to_f32(hi));
 }
 
-// A 16-byte chunk of a stream tensor held as fp32 lanes.
+// A 16-byte chunk of a stream tensor held as fp32 lanes. load_once and store_once are for data that is not soon read again:
+// the chunk does not displace what is (nt bit of the load or store).
+typedef uint32_t chunk16 __attribute__((ext_vector_type(4)));
 struct BF16 {
   static constexpr int kVec = 8;      // elements per 16 bytes
   __device__ static __forceinline__ void load(const void *p, size_t elem, float (&v)[8]) {
@@ -54,6 +56,15 @@ struct BF16 {
     q.z = pack_bf16x2(v[4], v[5]); q.w = pack_bf16x2(v[6], v[7]);
     *reinterpret_cast<uint4 *>(static_cast<uint16_t *>(p) + elem) = q;
   }
+  __device__ static __forceinline__ void load_once(const void *p, size_t elem, float (&v)[8]) {
+    const chunk16 q = __builtin_nontemporal_load(reinterpret_cast<const chunk16 *>(static_cast<const uint16_t *>(p) + elem));
+    v[0] = bf16lo(q.x); v[1] = bf16hi(q.x); v[2] = bf16lo(q.y); v[3] = bf16hi(q.y);
+    v[4] = bf16lo(q.z); v[5] = bf16hi(q.z); v[6] = bf16lo(q.w); v[7] = bf16hi(q.w);
+  }
+  __device__ static __forceinline__ void store_once(void *p, size_t elem, const float (&v)[8]) {
+    const chunk16 q = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
+    __builtin_nontemporal_store(q, reinterpret_cast<chunk16 *>(static_cast<uint16_t *>(p) + elem));
+  }
 };
 struct F32 {
   static constexpr int kVec = 4;
@@ -63,6 +74,14 @@ struct F32 {
   }
   __device__ static __forceinline__ void store(void *p, size_t elem, const float (&v)[4]) {
     *reinterpret_cast<float4 *>(static_cast<float *>(p) + elem) = make_float4(v[0], v[1], v[2], v[3]);
+  }
+  __device__ static __forceinline__ void load_once(const void *p, size_t elem, float (&v)[4]) {
+    const chunk16 q = __builtin_nontemporal_load(reinterpret_cast<const chunk16 *>(static_cast<const float *>(p) + elem));
+    v[0] = __uint_as_float(q.x); v[1] = __uint_as_float(q.y); v[2] = __uint_as_float(q.z); v[3] = __uint_as_float(q.w);
+  }
+  __device__ static __forceinline__ void store_once(void *p, size_t elem, const float (&v)[4]) {
+    const chunk16 q = {__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])};
+    __builtin_nontemporal_store(q, reinterpret_cast<chunk16 *>(static_cast<float *>(p) + elem));
   }
 };
 

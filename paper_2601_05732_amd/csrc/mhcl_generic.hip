@@ -120,8 +120,14 @@ __global__ __launch_bounds__(kBlock) void streams_out_kernel(const void *__restr
   IO::store(out, t * C + c, acc);
 }
 
-// x_out = H_res x + H_post^T y   (Eq. 1)
-template <typename IO, int N>
+// x_out = H_res x + H_post^T y   (Eq. 1). Bound by memory: one pass over x, y and x_out. bf16 x_out is written past the caches: no
+// kernel of this layer reads it, while x, which lies in the last-level cache after the first pass over it, is read again here
+// and by the backward. us of a step with plain / with such stores: n = 3, C = 1024, 65536 tokens 837 / 824; n = 8, C = 1024, 16384
+// tokens 826 / 795; n = 4, C = 1024, 16384 tokens 314 / 301; Sinkhorn-Knopp, n = 4, C = 768, 3001 tokens 72.0 / 69.2. The layer
+// that reads x_out next does not miss it: four layers in a row, forward only, a layer at C = 1024, 8192 tokens 67.1 / 64.4, at
+// 2048 tokens 23.7 / 22.6. f32 streams gain 0 to 2 % and lose 2 to 3 % where a step's tensors just fill that cache
+// (n = 4, C = 768, 3500 tokens 142.3 / 146.6): plain until x exceeds it. ReadOnce: see launch_post.
+template <typename IO, int N, bool ReadOnce>
 __global__ __launch_bounds__(kBlock) void post_kernel(const void *__restrict__ x,
                                                       const void *__restrict__ y,
                                                       const float *__restrict__ H_res,
@@ -135,8 +141,16 @@ __global__ __launch_bounds__(kBlock) void post_kernel(const void *__restrict__ x
   const int c = static_cast<int>(idx % vpr) * V;
   float xv[N][V], yv[V];
 #pragma unroll
-  for (int j = 0; j < N; ++j) IO::load(x, (t * N + j) * C + c, xv[j]);
-  IO::load(y, t * C + c, yv);
+  for (int j = 0; j < N; ++j) {
+    if constexpr (ReadOnce)
+      IO::load_once(x, (t * N + j) * C + c, xv[j]);
+    else
+      IO::load(x, (t * N + j) * C + c, xv[j]);
+  }
+  if constexpr (ReadOnce)
+    IO::load_once(y, t * C + c, yv);
+  else
+    IO::load(y, t * C + c, yv);
 #pragma unroll
   for (int i = 0; i < N; ++i) {
     float acc[V];
@@ -151,7 +165,10 @@ __global__ __launch_bounds__(kBlock) void post_kernel(const void *__restrict__ x
     const float wp = H_post[t * N + i];
 #pragma unroll
     for (int e = 0; e < V; ++e) acc[e] += wp * yv[e];
-    IO::store(x_out, (t * N + i) * C + c, acc);
+    if constexpr (ReadOnce || IO::kVec == 8)
+      IO::store_once(x_out, (t * N + i) * C + c, acc);
+    else
+      IO::store(x_out, (t * N + i) * C + c, acc);
   }
 }
 
@@ -387,9 +404,18 @@ hipError_t launch_post(const mhcl_desc &d, const void *x, const void *y, const f
     return dispatch_n(d.n, [&](auto nn) {
       using IO = decltype(io);
       constexpr int N = decltype(nn)::value;
-      hipLaunchKernelGGL((post_kernel<IO, N>), dim3(blocks_for(d.T * (d.C / IO::kVec), kBlock)),
-                         dim3(kBlock), 0, s, x, y, H_res, H_post, x_out, d.C, d.T);
-      return hipGetLastError();
+      auto go = [&](auto once) {
+        hipLaunchKernelGGL((post_kernel<IO, N, decltype(once)::value>), dim3(blocks_for(d.T * (d.C / IO::kVec), kBlock)),
+                           dim3(kBlock), 0, s, x, y, H_res, H_post, x_out, d.C, d.T);
+        return hipGetLastError();
+      };
+      // x that exceeds the cache has left it before any later reader comes, and is then read past it as well, with y (us
+      // without / with: mhcl_fwd_coeffs_pre with mhcl_post at n = 4, C = 2048, 32768 tokens 374 / 352; a step at C = 4096 1970 / 1950,
+      // at n = 3, C = 1024, 65536 tokens 824 / 816). Up to that size the backward of the same layer may still find x
+      // there: a step at n = 8, C = 1024, 16384 tokens (256 MiB) 795 / 826, at n = 4, C = 1024, 16384 tokens 289 / 307. f32, with
+      // the stores: a step at n = 4, C = 4096, 8192 tokens (512 MiB) 1504 / 1472.
+      const int64_t x_bytes = d.T * N * d.C * (16 / IO::kVec);
+      return x_bytes > kLastLevelCache ? go(std::true_type{}) : go(std::false_type{});
     });
   });
 }

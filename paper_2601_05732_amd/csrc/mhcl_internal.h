@@ -21,6 +21,9 @@ inline int64_t slice_tokens(int64_t T, int parts1, int64_t most) {
   const int64_t split = parts1 * T < most ? parts1 * T : most;
   return split > T ? split : T;
 }
+// the cache between the L2s and HBM
+constexpr int64_t kLastLevelCache = int64_t{256} << 20;
+
 inline size_t align_up(size_t v, size_t a = 256) { return (v + a - 1) / a * a; }
 
 // Carves a caller-provided workspace into 256-byte aligned pieces.
