@@ -197,7 +197,8 @@ class HyperConnection(torch.nn.Module):
         W, b, alpha, perm, f = self.W, self.b, self.alpha, self.perm, torch.float32
         if x.dtype not in _IO or not _plain(x, W, b, alpha, *(() if perm is None else (perm,))):
             return False
-        if perm is not None and not (perm.dtype is torch.int8 and perm.dim() == 2 and perm.is_contiguous()):
+        if perm is not None and not (perm.dtype is torch.int8 and perm.dim() == 2 and perm.shape[1] == self.n
+                                     and perm.is_contiguous()):
             return False
         R = {mhcl.RES_LITE: math.factorial(self.n), mhcl.RES_SK: self.n * self.n,
              mhcl.RES_SUBSET: 0 if perm is None else perm.shape[0]}[self.res_mode]

@@ -187,6 +187,10 @@ LinkPtr make_link(int64_t n, int64_t C, int64_t T, int io_dtype, int res_mode, i
   l->d.sk_iters = sk_iters;
   l->d.eps = static_cast<float>(eps);
   if (perm) {
+    // (as binding.Desc: the kernels index the table as [K][n])
+    TORCH_CHECK_VALUE(perm->scalar_type() == at::kChar && perm->dim() == 2 && perm->size(1) == n && perm->is_contiguous(),
+                      "perm must be a contiguous int8 tensor [K, n]");
+    TORCH_CHECK_VALUE(T == 0 || perm->is_cuda(), "perm must be a GPU tensor");
     l->perm = *perm;
     l->d.n_perm = static_cast<int32_t>(perm->size(0));
     l->d.perm = static_cast<const int8_t *>(perm->data_ptr());
