@@ -249,15 +249,23 @@ class HyperConnectionStack(torch.nn.Module):
             [HyperConnection(n, C, res_mode, one_index=l % n, device=device, layer_index=l, **kw)
              for l in range(len(self.fs))])
 
+    def _native_ends(self, x0):
+        """What the kernels of the ends share, or None where they cannot read x0 (then torch copies and sums)."""
+        first = self.layers[0] if len(self.layers) else None
+        if not (isinstance(first, HyperConnection) and first.n == self.n and _plain(x0) and x0.dtype in _IO and x0.dim() == 2
+                and x0.shape[1] == first.C and not x0.is_neg()):
+            return None
+        # (the gradient on the last layer's x_out lies as a further layer's g_x would)
+        return first._native_link(x0, PHASE_G_X if len(self.layers) % 2 == 0 else PHASE_G_XOUT)
+
     def forward(self, x0: torch.Tensor):
-        ends = None
-        if len(self.layers) and x0.dim() == 2 and x0.shape[1] == self.layers[0].C and x0.dtype in _IO and _plain(x0):
-            # (the gradient on the last layer's x_out lies as a further layer's g_x would)
-            ends = self.layers[0]._native_link(x0, PHASE_G_X if len(self.layers) % 2 == 0 else PHASE_G_XOUT)
-            x = _dense(x0)
-            x = _native().streams_in(x, ends)
-        else:
-            x = x0.unsqueeze(1).expand(-1, self.n, -1).contiguous()
+        ends = self._native_ends(x0)
+        x = x0.unsqueeze(1).expand(-1, self.n, -1).contiguous() if ends is None else _native().streams_in(_dense(x0), ends)
         for layer, f in zip(self.layers, self.fs):
             x = layer(x, f)
-        return x.sum(dim=1) if ends is None else _native().streams_out(x, ends)
+        # (a layer is a module: hooks, or what it was replaced with, may return another tensor than the layer's own)
+        if (ends is None or not _plain(x) or x.dtype is not x0.dtype or x.shape != (*x0.shape[:1], self.n, *x0.shape[1:])
+                or x.device != x0.device or x.layout is not torch.strided or not x.is_contiguous() or x.is_neg()
+                or x.data_ptr() % 16):
+            return x.sum(dim=1)
+        return _native().streams_out(x, ends)

@@ -3,7 +3,7 @@ import pytest
 import torch
 
 from paper_2601_05732_amd import autograd, binding
-from paper_2601_05732_amd.autograd import HyperConnection
+from paper_2601_05732_amd.autograd import HyperConnection, HyperConnectionStack
 
 
 @pytest.mark.parametrize("table", [torch.arange(5, dtype=torch.int8).repeat(3, 1), torch.arange(7, dtype=torch.int8).repeat(3, 1),
@@ -21,3 +21,76 @@ def test_permutation_tables_that_are_not_k_by_n_int8_are_refused(monkeypatch, ta
     assert layer._takes_native(x)
     layer.perm = table                  # (the Python node refuses it)
     assert not layer._takes_native(x)
+
+
+class _Ends:
+    """Stands for the C++ module on the CPU: its ends take only what the kernels can read."""
+
+    def __init__(self, n):
+        self.n, self.outs = n, 0
+
+    def streams_in(self, x0, link):
+        assert x0.is_contiguous() and x0.data_ptr() % 16 == 0
+        self.shape = (x0.shape[0], self.n, x0.shape[1])
+        self.dtype = x0.dtype
+        return x0.unsqueeze(1).expand(-1, self.n, -1).contiguous()
+
+    def streams_out(self, x, link):
+        assert x.shape == self.shape and x.dtype is self.dtype and x.is_contiguous() and x.data_ptr() % 16 == 0 \
+            and not x.is_neg()
+        self.outs += 1
+        return x.sum(dim=1)
+
+
+class _Copy(HyperConnection):      # a layer that needs no library
+    def forward(self, x, f):
+        return f(x)
+
+
+_CHANGES = {"none": lambda x: x, "other type": lambda x: x.double(), "fewer tokens": lambda x: x[:5],
+            "other width": lambda x: x[..., :8].contiguous(), "other streams": lambda x: x[:, :2].contiguous(),
+            "not contiguous": lambda x: x.transpose(0, 2).contiguous().transpose(0, 2),
+            "odd address": lambda x: torch.cat([x.flatten()[:1], x.flatten()])[1:].view_as(x),
+            "negated view": torch._neg_view, "subclass": lambda x: x.as_subclass(torch.nn.Buffer)}
+
+
+@pytest.mark.parametrize("change", _CHANGES)
+def test_the_end_of_a_stack_takes_what_the_last_layer_returns(monkeypatch, change):
+    n, C, T = 4, 64, 9
+    stack = HyperConnectionStack(n, C, [lambda x: x * 2] * 2, device="cpu")
+    stack.layers = torch.nn.ModuleList([_Copy(n, C, device="cpu") for _ in range(2)])
+    stack.layers[1].register_forward_hook(lambda m, a, x: _CHANGES[change](x))
+    ends = _Ends(n)
+    monkeypatch.setattr(autograd, "_plain", lambda *ts: all(type(t) is torch.Tensor for t in ts))
+    monkeypatch.setattr(autograd, "_native", lambda: ends)
+    monkeypatch.setattr(HyperConnection, "_native_link", lambda *a: object())
+    x0 = torch.randn(T, C)
+    want = _CHANGES[change](x0.unsqueeze(1).expand(-1, n, -1).contiguous() * 4).sum(dim=1)
+    assert torch.equal(stack(x0), want)
+    assert ends.outs == (change == "none")
+
+
+@pytest.mark.parametrize("x0", [torch.randn(9, 64).double(), torch._neg_view(torch.randn(9, 64))], ids=["double", "negated view"])
+def test_the_start_of_a_stack_copies_in_torch_what_the_kernels_cannot_read(monkeypatch, x0):
+    stack = HyperConnectionStack(4, 64, [lambda x: x * 2], device="cpu")
+    stack.layers = torch.nn.ModuleList([_Copy(4, 64, device="cpu")])
+    monkeypatch.setattr(autograd, "_plain", lambda *t: True)
+    monkeypatch.setattr(autograd, "_native", lambda: pytest.fail("read by the kernels"))
+    monkeypatch.setattr(HyperConnection, "_native_link", lambda *a: object())
+    assert torch.equal(stack(x0), (x0 * 2).unsqueeze(1).expand(-1, 4, -1).sum(dim=1))
+
+
+def test_a_stack_whose_first_layer_was_wrapped(monkeypatch):
+    class Wrapped(torch.nn.Module):
+        def __init__(self, inner):
+            super().__init__()
+            self.inner = inner
+
+        def forward(self, x, f):
+            return self.inner(x, f)
+
+    stack = HyperConnectionStack(4, 64, [lambda x: x * 2], device="cpu")
+    stack.layers = torch.nn.ModuleList([Wrapped(_Copy(4, 64, device="cpu"))])
+    monkeypatch.setattr(autograd, "_plain", lambda *t: True)
+    x0 = torch.randn(9, 64)
+    assert torch.equal(stack(x0), (x0 * 2).unsqueeze(1).expand(-1, 4, -1).sum(dim=1))
