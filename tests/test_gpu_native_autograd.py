@@ -115,6 +115,26 @@ def test_refusals_are_those_of_the_python_nodes(monkeypatch):
             layer(dual, _f)
 
 
+@pytest.mark.parametrize("cast", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("io", [torch.bfloat16, torch.float32])
+def test_autocast_gives_the_types_and_values_of_the_python_nodes(monkeypatch, io, cast):
+    torch.manual_seed(6)
+    stack = HyperConnectionStack(4, 64, [_f] * 2)
+    _params(stack, 7)
+    x0 = torch.randn(33, 64, device="cuda").to(io).requires_grad_()
+
+    def run():
+        with torch.autocast("cuda", dtype=cast):
+            out = stack(x0)
+        return [out, *torch.autograd.grad(out.square().sum(), [x0, *stack.parameters()])]
+
+    native, python = _both(monkeypatch, run)
+    assert native[0].dtype is python[0].dtype is torch.float32
+    assert torch.equal(native[0], python[0])
+    for a, b in zip(native[1:], python[1:]):
+        torch.testing.assert_close(a, b, rtol=1e-2 if io is torch.bfloat16 else 1e-5, atol=1e-2 if io is torch.bfloat16 else 1e-5)
+
+
 def test_saved_tensor_hooks_see_what_the_nodes_keep():
     layer = HyperConnection(4, 64)
     x = torch.randn(9, 4, 64, device="cuda", requires_grad=True)

@@ -94,3 +94,17 @@ def test_a_stack_whose_first_layer_was_wrapped(monkeypatch):
     monkeypatch.setattr(autograd, "_plain", lambda *t: True)
     x0 = torch.randn(9, 64)
     assert torch.equal(stack(x0), (x0 * 2).unsqueeze(1).expand(-1, 4, -1).sum(dim=1))
+
+
+@pytest.mark.parametrize("io", [torch.bfloat16, torch.float32])
+def test_the_end_of_a_stack_sums_as_autocast_does(monkeypatch, io):
+    stack = HyperConnectionStack(4, 64, [lambda x: x * 2], device="cpu")
+    stack.layers = torch.nn.ModuleList([_Copy(4, 64, device="cpu")])
+    ends = _Ends(4)
+    monkeypatch.setattr(autograd, "_plain", lambda *t: True)
+    monkeypatch.setattr(autograd, "_native", lambda: ends)
+    monkeypatch.setattr(HyperConnection, "_native_link", lambda *a: object())
+    x0 = torch.randn(9, 64).to(io)
+    monkeypatch.setattr(torch, "is_autocast_enabled", lambda device=None: device == "cuda")
+    stack(x0)
+    assert ends.outs == 0                           # left to torch, whose sum autocast turns into one in fp32
