@@ -9,7 +9,6 @@
 
 #include <c10/hip/HIPStream.h>
 
-#include <string>
 #include <tuple>
 
 #include "../../include/mhcl.h"
@@ -21,15 +20,18 @@ using torch::autograd::AutogradContext;
 using torch::autograd::Function;
 using torch::autograd::variable_list;
 
-struct StatusError : std::runtime_error {
-  StatusError(int status, const std::string &where)
-      : std::runtime_error(where + ": status " + std::to_string(status) + " (" + mhcl_status_string(status) + ")"),
-        status(status), where(where) {}
-  int status;
-  std::string where;
-};
+// Raises what binding.py raises for the same status. As a Python exception from here on: a backward runs in autograd's
+// threads, which carry those over to the caller as they are and make a RuntimeError of all others.
+[[noreturn]] void raise(int status, const char *where) {
+  py::gil_scoped_acquire gil;
+  const py::object type = py::module_::import("paper_2601_05732_amd.binding").attr("MhclError"), error = type(status, where);
+  PyErr_SetObject(type.ptr(), error.ptr());
+  python_error e;
+  e.persist();
+  throw e;
+}
 void check(int status, const char *where) {
-  if (status != MHCL_OK) throw StatusError(status, where);
+  if (status != MHCL_OK) raise(status, where);
 }
 
 void *stream() { return c10::hip::getCurrentHIPStream().stream(); }
@@ -208,21 +210,13 @@ std::tuple<Tensor, Tensor, Tensor> coeffs_pre(const Tensor &x, const Tensor &W, 
 }  // namespace
 
 PYBIND11_MODULE(TORCH_EXTENSION_NAME, m) {
+  const auto wrap = [](auto f) { return torch::wrap_pybind_function(f); };   // (Python exceptions go on to the caller)
   py::class_<Link, LinkPtr>(m, "Link");
-  m.def("link", &make_link);
-  m.def("coeffs_pre", &coeffs_pre);
-  m.def("post", [](const Tensor &x, const Tensor &y, const Tensor &H_res, const Tensor &H_post, const LinkPtr &link) {
-    return Post::apply(x, y, H_res, H_post, link);
-  });
-  m.def("streams_in", [](const Tensor &x0, const LinkPtr &link) { return StreamsIn::apply(x0, link); });
-  m.def("streams_out", [](const Tensor &x, const LinkPtr &link) { return StreamsOut::apply(x, link); });
-  // as the same failure of a call through binding.py
-  py::register_local_exception_translator([](std::exception_ptr p) {
-    try {
-      if (p) std::rethrow_exception(p);
-    } catch (const StatusError &e) {
-      const py::object error = py::module_::import("paper_2601_05732_amd.binding").attr("MhclError");
-      py::set_error(error, error(e.status, e.where));
-    }
-  });
+  m.def("link", wrap(&make_link));
+  m.def("coeffs_pre", wrap(&coeffs_pre));
+  m.def("post", wrap([](const Tensor &x, const Tensor &y, const Tensor &H_res, const Tensor &H_post, const LinkPtr &link) {
+          return Post::apply(x, y, H_res, H_post, link);
+        }));
+  m.def("streams_in", wrap([](const Tensor &x0, const LinkPtr &link) { return StreamsIn::apply(x0, link); }));
+  m.def("streams_out", wrap([](const Tensor &x, const LinkPtr &link) { return StreamsOut::apply(x, link); }));
 }

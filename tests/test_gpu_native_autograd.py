@@ -18,6 +18,11 @@ def _f(h):
     return torch.nn.functional.silu(h)
 
 
+def _odd(t):
+    """`t` as a contiguous tensor whose address is no multiple of 16."""
+    return torch.cat([t.flatten()[:1], t.flatten()])[1:].view_as(t)
+
+
 def _params(module, seed):
     g = torch.Generator(device="cuda").manual_seed(seed)
     with torch.no_grad():
@@ -93,12 +98,23 @@ def test_refusals_are_those_of_the_python_nodes(monkeypatch):
         torch.autograd.grad(out.sum(), [x])
 
     narrow = torch.arange(5, dtype=torch.int8, device="cuda").repeat(3, 1)      # five columns where there are six streams
+    class Odd(torch.autograd.Function):                     # its gradient lies at an odd address
+        @staticmethod
+        def forward(ctx, h):
+            return h * 1
+
+        @staticmethod
+        def backward(ctx, g):
+            return _odd(g)
+
     cases = [(again, RuntimeError), (lambda: layer(x, lambda h: h.half()), ValueError),
              (lambda: layer(x, lambda h: h[:, :8]), ValueError), (lambda: layer(x.half(), _f), KeyError),
              (lambda: HyperConnection(4, 12)(x[..., :12].contiguous(), _f), mhcl.MhclError),
              (lambda: HyperConnectionStack(4, 12, [_f])(x[:, 0, :12]), mhcl.MhclError),
              (lambda: HyperConnection(6, 64, "subset", perm=narrow)(torch.zeros(9, 6, 64, device="cuda"), _f), ValueError),
              (lambda: HyperConnectionStack(6, 64, [_f], "subset", perm=narrow)(x[:, 0]), ValueError),
+             (lambda: torch.autograd.grad(layer(x, _f), [x], _odd(torch.randn_like(x))), mhcl.MhclError),
+             (lambda: torch.autograd.grad(layer(x, Odd.apply).sum(), [x]), mhcl.MhclError),
              (lambda: torch.func.grad(lambda v: layer(v, _f).sum())(x.detach()), RuntimeError),
              (lambda: torch.func.vmap(lambda v: layer(v, _f))(torch.stack([x.detach()] * 2)), RuntimeError)]
     for call, error in cases:
