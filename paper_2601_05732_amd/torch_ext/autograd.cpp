@@ -210,7 +210,9 @@ std::tuple<Tensor, Tensor, Tensor> coeffs_pre(const Tensor &x, const Tensor &W, 
 }  // namespace
 
 PYBIND11_MODULE(TORCH_EXTENSION_NAME, m) {
-  const auto wrap = [](auto f) { return torch::wrap_pybind_function(f); };   // (Python exceptions go on to the caller)
+  // (Python exceptions go on to the caller; other threads run during the calls, as during torch's own: an allocation or a
+  // launch may wait for the GPU, and the GPU for what another thread is to do)
+  const auto wrap = [](auto f) { return torch::wrap_pybind_function_no_gil(f); };
   py::class_<Link, LinkPtr>(m, "Link");
   m.def("link", wrap(&make_link));
   m.def("coeffs_pre", wrap(&coeffs_pre));

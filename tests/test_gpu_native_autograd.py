@@ -1,6 +1,9 @@
 """The C++ graph nodes against the Python ones: the same bits in outputs and gradients, the same refusals, and the calls
 that stay with the Python nodes."""
 import gc
+import sys
+import threading
+import time
 
 import numpy as np
 import pytest
@@ -177,6 +180,35 @@ def test_a_graph_that_is_dropped_frees_what_it_held():
         assert torch.cuda.memory_allocated() == before
     finally:
         gc.enable()
+
+
+def test_other_threads_run_during_the_calls():
+    layer = HyperConnection(4, 64)
+    x = torch.randn(64, 4, 64, device="cuda")
+    nodes, link = autograd._native(), layer._native_link(x, 0)
+    count, stop, ran, interval = [0], [], 0, sys.getswitchinterval()
+
+    def spin():                         # runs whenever it is let
+        while not stop:
+            count[0] += 1
+            time.sleep(0)
+
+    thread = threading.Thread(target=spin, daemon=True)
+    with torch.no_grad():
+        nodes.coeffs_pre(x, layer.W, layer.b, layer.alpha, link)
+        thread.start()
+        time.sleep(0.05)
+        sys.setswitchinterval(1000.0)   # the interpreter itself switches no more: only what the calls release counts
+        try:
+            for _ in range(1000):
+                before = count[0]
+                nodes.coeffs_pre(x, layer.W, layer.b, layer.alpha, link)
+                ran += count[0] > before
+        finally:
+            sys.setswitchinterval(interval)
+            stop.append(1)
+            thread.join()
+    assert ran > 500                    # (at most one in thirty where the calls held the interpreter, nearly all of them now)
 
 
 @pytest.mark.parametrize("io", ["bf16", "f32"])
