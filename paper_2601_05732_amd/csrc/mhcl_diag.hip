@@ -83,8 +83,10 @@ __device__ __forceinline__ float l1_error(const float (&Q)[N * N], float (&cs)[N
 
 // Q_l = H_l Q_{l-1}, Q_0 = I: later layers multiply on the left, the order in
 // which Eq. 1 applies them.
-// (Bound by the chain of loads: a layer's matrix is requested while the one before is multiplied, n = 4, six layers, 8192
-// tokens 6.5 / 4.9 us.)
+// (Bound by the chain of loads of few waves: blocks of one wave spread over all compute units. us with 128 / 64 threads, six layers: n = 4,
+// 8192 tokens 5.5 / 5.2, n = 8 16.6 / 15.6; 65536 tokens, n = 4 8.9 / 9.0, n = 8 26.1 / 26.1. A layer's matrix requested while the one
+// before is multiplied gains only at n = 7 and 8 with many layers, 24 of 8192 tokens 57.1 / 49.0, and loses with many tokens,
+// n = 8, 65536 tokens, one layer 11.6 / 12.8, n = 6, 24 layers 56.8 / 58.1: not done.)
 constexpr int kChainThreads = 64;
 template <int N>
 __global__ __launch_bounds__(kChainThreads) void ds_chain_kernel(
@@ -93,19 +95,13 @@ __global__ __launch_bounds__(kChainThreads) void ds_chain_kernel(
     float *__restrict__ prod_l1) {
   const int64_t t = static_cast<int64_t>(blockIdx.x) * kChainThreads + threadIdx.x;
   if (t >= T) return;
-  float Q[N * N], Hl[N * N], next[N * N], Qn[N * N], cs[N];
-  auto fetch = [&](int l) {
-#pragma unroll
-    for (int e = 0; e < N * N; ++e) next[e] = H[(static_cast<int64_t>(l) * T + t) * (N * N) + e];
-  };
-  fetch(0);
+  float Q[N * N], Hl[N * N], Qn[N * N], cs[N];
 #pragma unroll
   for (int e = 0; e < N * N; ++e) Q[e] = (e / N == e % N) ? 1.f : 0.f;
   for (int l = 0; l < L; ++l) {
     const int64_t lt = static_cast<int64_t>(l) * T + t;
 #pragma unroll
-    for (int e = 0; e < N * N; ++e) Hl[e] = next[e];
-    fetch(l + 1 < L ? l + 1 : l);
+    for (int e = 0; e < N * N; ++e) Hl[e] = H[lt * N * N + e];
     const float e1 = l1_error<N>(Hl, cs);
     if (l1) l1[lt] = e1;
     if (colsum) {
