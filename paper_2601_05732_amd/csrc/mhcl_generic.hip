@@ -120,14 +120,10 @@ __global__ __launch_bounds__(kBlock) void streams_out_kernel(const void *__restr
   IO::store(out, t * C + c, acc);
 }
 
-// x_out = H_res x + H_post^T y   (Eq. 1). Bound by memory: one pass over x, y and x_out. bf16 x_out is written past the caches: no
-// kernel of this layer reads it, while x, which lies in the last-level cache after the first pass over it, is read again here
-// and by the backward. us of a step with plain / with such stores: n = 3, C = 1024, 65536 tokens 837 / 824; n = 8, C = 1024, 16384
-// tokens 826 / 795; n = 4, C = 1024, 16384 tokens 314 / 301; Sinkhorn-Knopp, n = 4, C = 768, 3001 tokens 72.0 / 69.2. The layer
-// that reads x_out next does not miss it: four layers in a row, forward only, a layer at C = 1024, 8192 tokens 67.1 / 64.4, at
-// 2048 tokens 23.7 / 22.6. f32 streams gain 0 to 2 % and lose 2 to 3 % where a step's tensors just fill that cache
-// (n = 4, C = 768, 3500 tokens 142.3 / 146.6): plain until x exceeds it. ReadOnce: see launch_post.
-template <typename IO, int N, bool ReadOnce>
+// x_out = H_res x + H_post^T y   (Eq. 1). Bound by memory: one pass over x, y and x_out. Stores past the caches leave x, which
+// the backward reads again, in the last-level cache; the rule and its figures stand at launch_post.
+enum class Past { kNone, kStores, kAll };   // which accesses go past the caches
+template <typename IO, int N, Past PAST>
 __global__ __launch_bounds__(kBlock) void post_kernel(const void *__restrict__ x,
                                                       const void *__restrict__ y,
                                                       const float *__restrict__ H_res,
@@ -142,12 +138,12 @@ __global__ __launch_bounds__(kBlock) void post_kernel(const void *__restrict__ x
   float xv[N][V], yv[V];
 #pragma unroll
   for (int j = 0; j < N; ++j) {
-    if constexpr (ReadOnce)
+    if constexpr (PAST == Past::kAll)
       IO::load_once(x, (t * N + j) * C + c, xv[j]);
     else
       IO::load(x, (t * N + j) * C + c, xv[j]);
   }
-  if constexpr (ReadOnce)
+  if constexpr (PAST == Past::kAll)
     IO::load_once(y, t * C + c, yv);
   else
     IO::load(y, t * C + c, yv);
@@ -165,7 +161,7 @@ __global__ __launch_bounds__(kBlock) void post_kernel(const void *__restrict__ x
     const float wp = H_post[t * N + i];
 #pragma unroll
     for (int e = 0; e < V; ++e) acc[e] += wp * yv[e];
-    if constexpr (ReadOnce || IO::kVec == 8)
+    if constexpr (PAST != Past::kNone)
       IO::store_once(x_out, (t * N + i) * C + c, acc);
     else
       IO::store(x_out, (t * N + i) * C + c, acc);
@@ -404,18 +400,31 @@ hipError_t launch_post(const mhcl_desc &d, const void *x, const void *y, const f
     return dispatch_n(d.n, [&](auto nn) {
       using IO = decltype(io);
       constexpr int N = decltype(nn)::value;
-      auto go = [&](auto once) {
-        hipLaunchKernelGGL((post_kernel<IO, N, decltype(once)::value>), dim3(blocks_for(d.T * (d.C / IO::kVec), kBlock)),
+      const int64_t x_bytes = d.T * N * d.C * (16 / IO::kVec);
+      auto go = [&](auto past) {
+        hipLaunchKernelGGL((post_kernel<IO, N, decltype(past)::value>), dim3(blocks_for(d.T * (d.C / IO::kVec), kBlock)),
                            dim3(kBlock), 0, s, x, y, H_res, H_post, x_out, d.C, d.T);
         return hipGetLastError();
       };
-      // x that exceeds the cache has left it before any later reader comes, and is then read past it as well, with y (us
-      // without / with: mhcl_fwd_coeffs_pre with mhcl_post at n = 4, C = 2048, 32768 tokens 374 / 352; a step at C = 4096 1970 / 1950,
-      // at n = 3, C = 1024, 65536 tokens 824 / 816). Up to that size the backward of the same layer may still find x
-      // there: a step at n = 8, C = 1024, 16384 tokens (256 MiB) 795 / 826, at n = 4, C = 1024, 16384 tokens 289 / 307. f32, with
-      // the stores: a step at n = 4, C = 4096, 8192 tokens (512 MiB) 1504 / 1472.
-      const int64_t x_bytes = d.T * N * d.C * (16 / IO::kVec);
-      return x_bytes > kLastLevelCache ? go(std::true_type{}) : go(std::false_type{});
+      // Figures: us a layer of four (three above 256 MiB) in a row, x_out being the next one's x; f forward, t forward and backward.
+      // x that exceeds the last-level cache has left it before any later reader comes, and is then read past it as well, with y
+      // (stores alone / both: n = 3, C = 1024, 45000 tokens f 236 / 219, t 697 / 680; n = 4, C = 4096, 8400 tokens f 223 / 210, t 687 / 674;
+      // n = 8, C = 1024, 64 permutations, 17000 tokens f 266 / 263, t 932 / 932; f32, none / both, n = 4, C = 1024, 17000 tokens f 304 / 293,
+      // t 871 / 855). The same layer step after step on the same inputs loses up to 1.7 % with both between 256 and 330 MiB (n = 8, 17000
+      // tokens 889 / 904) and gains above; up to 256 MiB its backward may still find x there (n = 8, 16384 tokens 795 / 826).
+      if (x_bytes > kLastLevelCache) return go(std::integral_constant<Past, Past::kAll>{});
+      // bf16, none / stores: n = 4, C = 1024, 2048 tokens f 24.5 / 23.6, t 74.1 / 73.6, 8192 tokens f 68.3 / 66.0, t 184.5 / 183.7; Sinkhorn-Knopp,
+      // C = 768, 3001 tokens f 25.4 / 25.1, t 79.3 / 77.9; n = 2, C = 1024, 32768 tokens f 142 / 132, t 389 / 376. What loses: x of 24 to 32 MiB,
+      // forward only (n = 4, C = 1024, 3000 tokens f 28.8 / 29.5, t 89.3 / 89.5). Below 4 MiB x_out stays in the L2s for the next layer
+      // (n = 4, C = 4096, 64 tokens f 19.6 / 19.8, C = 512, 700 tokens f 16.6 / 16.8; at 4 MiB, C = 2048, 256 tokens f 18.33 / 18.26). More than
+      // 64 logits, whose projection walks x in another form: n = 5, C = 1024, 4096 tokens, M = 64 f 51.8 / 51.6, M = 66 f 52.9 / 54.9,
+      // t 178 / 181, M = 130 f 72.2 / 74.2; 7000 tokens f 104.7 / 104.4, C = 2560, 3000 tokens (73 MiB) f 140.7 / 142.9, 4096 tokens f 178 / 176, t 523 / 517.
+      // f32 gains 0 to 2 % and loses 2 to 3 % where a step's tensors just fill that cache (C = 768, 3500 tokens 142.3 / 146.6).
+      if constexpr (IO::kVec == BF16::kVec) {
+        if (x_bytes >= (res_logits(d) + 2 * N > 64 ? int64_t{80} << 20 : int64_t{4} << 20))
+          return go(std::integral_constant<Past, Past::kStores>{});
+      }
+      return go(std::integral_constant<Past, Past::kNone>{});
     });
   });
 }

@@ -1,5 +1,6 @@
-"""mhcl_post on streams that exceed the 256 MiB last-level cache, where x and y are read past it: the bits of
-the same tokens given in two calls below that size, which read them through it; and the exact value of a few tokens."""
+"""mhcl_post on streams that exceed the 256 MiB last-level cache, where x and y are read past it, and from the sizes on
+from which x_out is written past the caches: the bits of the same tokens given in two calls below that size; and the exact
+value of a few tokens."""
 import pytest
 import torch
 
@@ -10,8 +11,8 @@ from gpu_harness import desc_for, TOL_BF16_OUT, TOL_F32
 pytestmark = pytest.mark.gpu
 
 
-# one token above and exactly at 256 MiB, rows that divide the cache's size and one that does not
-@pytest.mark.parametrize("n,C,T,io", [(4, 4096, 8193, "bf16"), (4, 4096, 8192, "bf16"), (3, 1000, 44740, "bf16"),
+# exactly at the lines of the stores (4 MiB, and 80 MiB with more than 64 logits); one token above and exactly at 256 MiB, rows that divide the cache's size and one that does not
+@pytest.mark.parametrize("n,C,T,io", [(4, 1024, 512, "bf16"), (5, 1024, 8192, "bf16"), (4, 4096, 8193, "bf16"), (4, 4096, 8192, "bf16"), (3, 1000, 44740, "bf16"),
                                       (1, 8192, 8193, "f32"), (2, 2056, 16400, "f32")])
 def test_large_streams_equal_their_halves(n, C, T, io):
     dt = torch.bfloat16 if io == "bf16" else torch.float32
