@@ -83,12 +83,11 @@ __device__ __forceinline__ float l1_error(const float (&Q)[N * N], float (&cs)[N
 
 // Q_l = H_l Q_{l-1}, Q_0 = I: later layers multiply on the left, the order in
 // which Eq. 1 applies them.
-// (Bound by the chain of loads of few waves: blocks of one wave spread over all compute units. us with 128 / 64 threads, six layers: n = 4,
-// 8192 tokens 5.5 / 5.2, n = 8 16.6 / 15.6; 65536 tokens, n = 4 8.9 / 9.0, n = 8 26.1 / 26.1. A layer's matrix requested while the one
-// before is multiplied gains only at n = 7 and 8 with many layers, 24 of 8192 tokens 57.1 / 49.0, and loses with many tokens,
-// n = 8, 65536 tokens, one layer 11.6 / 12.8, n = 6, 24 layers 56.8 / 58.1: not done.)
+// (Bound by the chain of loads of few waves: blocks of one wave spread over all compute units, six layers of 8192 tokens, H from the caches, us
+// with 128 / 64 threads: n = 4 5.5 / 5.2, n = 8 16.6 / 15.6. AHEAD: a layer's matrix is requested while the one before is multiplied;
+// see launch_ds_chain.)
 constexpr int kChainThreads = 64;
-template <int N>
+template <int N, bool AHEAD>
 __global__ __launch_bounds__(kChainThreads) void ds_chain_kernel(
     const float *__restrict__ H, int L, int64_t T, float *__restrict__ colsum,
     float *__restrict__ l1, float *__restrict__ prod, float *__restrict__ prod_colsum,
@@ -96,12 +95,23 @@ __global__ __launch_bounds__(kChainThreads) void ds_chain_kernel(
   const int64_t t = static_cast<int64_t>(blockIdx.x) * kChainThreads + threadIdx.x;
   if (t >= T) return;
   float Q[N * N], Hl[N * N], Qn[N * N], cs[N];
+  [[maybe_unused]] float next[AHEAD ? N * N : 1];
+  auto fetch = [&](int l, float *to) {
+#pragma unroll
+    for (int e = 0; e < N * N; ++e) to[e] = H[(static_cast<int64_t>(l) * T + t) * (N * N) + e];
+  };
+  if constexpr (AHEAD) fetch(0, next);
 #pragma unroll
   for (int e = 0; e < N * N; ++e) Q[e] = (e / N == e % N) ? 1.f : 0.f;
   for (int l = 0; l < L; ++l) {
     const int64_t lt = static_cast<int64_t>(l) * T + t;
+    if constexpr (AHEAD) {
 #pragma unroll
-    for (int e = 0; e < N * N; ++e) Hl[e] = H[lt * N * N + e];
+      for (int e = 0; e < N * N; ++e) Hl[e] = next[e];
+      if (l + 1 < L) fetch(l + 1, next);
+    } else {
+      fetch(l, Hl);
+    }
     const float e1 = l1_error<N>(Hl, cs);
     if (l1) l1[lt] = e1;
     if (colsum) {
@@ -159,9 +169,12 @@ hipError_t launch_ds_chain(int n, int L, int64_t T, const float *H, float *colsu
                            float *prod, float *prod_colsum, float *prod_l1, hipStream_t s) {
   auto go = [&](auto nn) {
     constexpr int N = decltype(nn)::value;
-    hipLaunchKernelGGL(ds_chain_kernel<N>, dim3(static_cast<unsigned>((T + kChainThreads - 1) / kChainThreads)),
-                       dim3(kChainThreads), 0, s, H, L, T, colsum,
-                       l1, prod, prod_colsum, prod_l1);
+    // Up to two waves a compute unit (us without / with, H not from the caches: six layers of 8192 tokens n = 2 6.9 / 6.3, n = 4 9.3 / 8.6, n = 8
+    // 24.5 / 23.1, 32768 tokens n = 4 15.2 / 14.8, n = 8 35.6 / 34.2). More waves hide the loads by themselves, and then the second
+    // matrix's registers cost: 65536 tokens n = 4 18.7 / 19.0, n = 8 54.9 / 57.4, one layer 20.4 / 22.8.
+    const auto kern = T <= 2 * 256 * kChainThreads ? ds_chain_kernel<N, true> : ds_chain_kernel<N, false>;
+    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>((T + kChainThreads - 1) / kChainThreads)), dim3(kChainThreads), 0, s, H, L, T,
+                       colsum, l1, prod, prod_colsum, prod_l1);
     return hipGetLastError();
   };
   switch (n) {

@@ -180,3 +180,13 @@ def test_depth_statistics_at_the_paper_shape():
     print(f"SK(20): max |colsum-1| per matrix {dev1:.3g}, product over {L} layers {devp:.3g}; "
           f"frac log(1/nu)>30: {float((res['sk'][1] > 30).float().mean()):.3f}", flush=True)
     assert dev1 > 1e-3 and devp > dev1
+
+
+@pytest.mark.parametrize("L", [1, 3])
+@pytest.mark.parametrize("n", range(1, 9))
+def test_chain_with_layers_requested_ahead_has_the_bits_of_the_one_without(n, L):
+    T = 32769                                             # one token above the line
+    H = torch.rand(L, T, n, n, device="cuda")
+    whole, first = diag.chain(H), diag.chain(H[:, :-1].contiguous())
+    for k, v in whole.items():
+        assert torch.equal(v[:-1] if k == "prod" else v[:, :-1], first[k]), k
