@@ -16,7 +16,7 @@ and its backward, once the gradient on x_out has arrived, is
 
 The graph nodes of plain calls are C++ (``torch_ext/autograd.cpp``: the same calls and gradients at a third of the
 host time); calls under function transforms, tracing or dispatch modes, with tensor subclasses, or that an argument
-check will refuse, take the nodes below.
+check will refuse, or where the extension is missing, take the nodes below.
 
 The two graph nodes of a layer share a small link object: the node of the post
 update hands g_xout and y over to the node of the coefficients, whose backward
@@ -34,6 +34,7 @@ into every stream and sums the streams at the end (a choice, not the paper's).
 from __future__ import annotations
 
 import math
+import warnings
 
 import torch
 
@@ -45,13 +46,19 @@ _ext = None
 
 
 def _native():
-    """The C++ graph nodes; raises if they have not been built."""
+    """The C++ graph nodes, or None, after a warning, where the extension is missing or was built for another torch or
+    Python: the nodes below make the same calls into the library (which itself has no replacement: without it this raises)."""
     global _ext
     if _ext is None:
         mhcl.lib()
-        from . import _autograd_native
-        _ext = _autograd_native
-    return _ext
+        try:
+            from . import _autograd_native
+            _ext = _autograd_native
+        except ImportError as e:
+            warnings.warn(f"the graph nodes in C++ cannot be loaded ({e}): those in Python take two to three times the host "
+                          "time; `python -m paper_2601_05732_amd.build` builds them", RuntimeWarning, stacklevel=2)
+            _ext = False
+    return _ext or None
 
 
 def _plain(*tensors) -> bool:
@@ -195,7 +202,7 @@ class HyperConnection(torch.nn.Module):
 
     def _takes_native(self, x) -> bool:
         W, b, alpha, perm, f = self.W, self.b, self.alpha, self.perm, torch.float32
-        if x.dtype not in _IO or not _plain(x, W, b, alpha, *(() if perm is None else (perm,))):
+        if x.dtype not in _IO or not _plain(x, W, b, alpha, *(() if perm is None else (perm,))) or _native() is None:
             return False
         if perm is not None and not (perm.dtype is torch.int8 and perm.dim() == 2 and perm.shape[1] == self.n
                                      and perm.is_contiguous()):
@@ -253,7 +260,7 @@ class HyperConnectionStack(torch.nn.Module):
         """What the kernels of the ends share, or None where they cannot read x0 (then torch copies and sums)."""
         first = self.layers[0] if len(self.layers) else None
         if not (isinstance(first, HyperConnection) and first.n == self.n and _plain(x0) and x0.dtype in _IO and x0.dim() == 2
-                and x0.shape[1] == first.C and not x0.is_neg()):
+                and x0.shape[1] == first.C and not x0.is_neg() and _native() is not None):
             return None
         # (the gradient on the last layer's x_out lies as a further layer's g_x would)
         return first._native_link(x0, PHASE_G_X if len(self.layers) % 2 == 0 else PHASE_G_XOUT)

@@ -1,4 +1,6 @@
 """Host side of the C++ graph nodes (no GPU needed): what they are given and what they refuse."""
+import sys
+
 import pytest
 import torch
 
@@ -75,7 +77,8 @@ def test_the_start_of_a_stack_copies_in_torch_what_the_kernels_cannot_read(monke
     stack = HyperConnectionStack(4, 64, [lambda x: x * 2], device="cpu")
     stack.layers = torch.nn.ModuleList([_Copy(4, 64, device="cpu")])
     monkeypatch.setattr(autograd, "_plain", lambda *t: True)
-    monkeypatch.setattr(autograd, "_native", lambda: pytest.fail("read by the kernels"))
+    monkeypatch.setattr(_Ends, "streams_in", lambda *a: pytest.fail("read by the kernels"))
+    monkeypatch.setattr(autograd, "_native", lambda: _Ends(4))
     monkeypatch.setattr(HyperConnection, "_native_link", lambda *a: object())
     assert torch.equal(stack(x0), (x0 * 2).unsqueeze(1).expand(-1, 4, -1).sum(dim=1))
 
@@ -108,3 +111,14 @@ def test_the_end_of_a_stack_sums_as_autocast_does(monkeypatch, io):
     monkeypatch.setattr(torch, "is_autocast_enabled", lambda device=None: device == "cuda")
     stack(x0)
     assert ends.outs == 0                           # left to torch, whose sum autocast turns into one in fp32
+
+
+def test_without_the_extension_the_python_nodes_are_taken(monkeypatch):
+    monkeypatch.setattr(autograd, "_ext", None)
+    monkeypatch.delattr("paper_2601_05732_amd._autograd_native", raising=False)
+    monkeypatch.setitem(sys.modules, "paper_2601_05732_amd._autograd_native", None)      # its import raises ImportError
+    monkeypatch.setattr(autograd, "_plain", lambda *t: True)
+    stack = HyperConnectionStack(4, 64, [lambda h: h], device="cpu")
+    with pytest.warns(RuntimeWarning, match="graph nodes in C\\+\\+"):
+        assert not stack.layers[0]._takes_native(torch.zeros(3, 4, 64))
+    assert stack._native_ends(torch.zeros(3, 64)) is None        # (and no second warning)
