@@ -4,10 +4,12 @@ import gc
 import sys
 import threading
 import time
+from types import SimpleNamespace
 
 import numpy as np
 import pytest
 import torch
+from torch.utils.checkpoint import checkpoint, set_checkpoint_early_stop
 
 import paper_2601_05732_amd as mhcl
 import synth_inputs as si
@@ -33,18 +35,35 @@ def _params(module, seed):
             p.add_(torch.randn(p.shape, device="cuda", generator=g) * 0.1)
 
 
+def _counted(call, names):
+    def counted(*args):
+        names.append(call.__name__)
+        return call(*args)
+    return counted
+
+
 def _both(monkeypatch, run):
-    native = run()
+    """`run()` with the C++ nodes and with those in Python; where it returns tensors, that it took the former and the latter."""
+    taken = []
+    with monkeypatch.context() as m:
+        nodes = autograd._native()
+        m.setattr(autograd, "_ext", SimpleNamespace(**{k: _counted(getattr(nodes, k), taken) for k in
+                                                       ("link", "coeffs_pre", "post", "streams_in", "streams_out")}))
+        native = run()
+        if isinstance(native, list):
+            assert "coeffs_pre" in taken and "post" in taken
     with monkeypatch.context() as m:
         m.setattr(autograd, "_plain", lambda *t: False)
+        taken.clear()
         python = run()
+        assert not taken
     return native, python
 
 
 @pytest.mark.parametrize("mode,io,n,C,T", [("lite", torch.bfloat16, 4, 256, 130), ("sk", torch.float32, 3, 40, 21),
                                            ("subset", torch.bfloat16, 6, 128, 90), ("lite", torch.float32, 1, 8, 1),
                                            ("lite", torch.bfloat16, 5, 64, 3)])
-@pytest.mark.parametrize("L", [1, 3])
+@pytest.mark.parametrize("L", [1, 2, 3])
 def test_stack_gives_the_bits_of_the_python_nodes(monkeypatch, mode, io, n, C, T, L):
     g = torch.Generator(device="cuda").manual_seed(L)
     x0 = torch.randn(T, C, device="cuda", generator=g).to(io).requires_grad_()
@@ -70,25 +89,97 @@ def test_layer_outputs_and_gradients_have_the_same_bits_with_odd_layouts(monkeyp
     layer = HyperConnection(n, C)
     _params(layer, 5)
     x = torch.randn(T, C, n, device="cuda").transpose(1, 2).requires_grad_()        # not contiguous
-    G = torch.randn(T * n * C + 1, device="cuda")[1:].reshape(T, n, C)[::1].transpose(0, 0)
+    G = torch.randn(n, T, C, device="cuda").transpose(0, 1)
 
     def run():
         out = layer(x, lambda h: _f(h).t().contiguous().t())                        # nor what f returns
-        return [out, *torch.autograd.grad(out, [x, *layer.parameters()], G.clone())]
+        return [out, *torch.autograd.grad(out, [x, *layer.parameters()], G)]
 
     for a, b in zip(*_both(monkeypatch, run)):
         assert torch.equal(a, b)
 
 
-def test_ends_take_any_address_and_layout():
+@pytest.mark.parametrize("io", [torch.float32, torch.bfloat16])
+def test_ends_take_any_address_and_layout(io):
     stack = HyperConnectionStack(4, 64, [_f], "lite")
     T, C = 21, 64
-    for x0 in (torch.randn(T * C + 1, device="cuda")[1:].reshape(T, C), torch.randn(C, T, device="cuda").t()):
+    dense, G = torch.randn(T, C, device="cuda").to(io), torch.randn(T, C, device="cuda").to(io)
+
+    def run(x0, G):
         leaf = x0.detach().requires_grad_()
         out = stack(leaf)
-        g, = torch.autograd.grad(out, [leaf], torch.randn(T * C + 1, device="cuda")[1:].reshape(T, C))
-        want = stack(x0.clone().contiguous())
-        assert torch.equal(out, want) and g.shape == x0.shape
+        return out, *torch.autograd.grad(out, [leaf, *stack.parameters()], G)
+
+    want = run(dense, G)
+    for x0, g in ((_odd(dense), _odd(G)), (dense.t().contiguous().t(), G.t().contiguous().t()), (dense, G[:1].expand(T, C))):
+        ref = want if torch.equal(g, G) else run(dense, g.contiguous())
+        for a, b in zip(run(x0, g), ref):
+            assert a.shape == b.shape and torch.equal(a, b)
+
+
+_LAST = {"float64": lambda x: x.double(), "fewer tokens": lambda x: x[:5], "transposed": lambda x: x.transpose(0, 2).contiguous().transpose(0, 2),
+         "odd address": lambda x: _odd(x), "on the host": lambda x: x.cpu()}
+
+
+@pytest.mark.parametrize("change", _LAST)
+def test_a_hook_on_the_last_layer_may_change_its_output(monkeypatch, change):
+    stack = HyperConnectionStack(4, 64, [_f] * 2)
+    _params(stack, 8)
+    stack.layers[1].register_forward_hook(lambda m, a, x: _LAST[change](x))
+    x0 = torch.randn(9, 64, device="cuda", requires_grad=True)
+
+    def run():
+        out = stack(x0)
+        return [out, *torch.autograd.grad(out.square().sum(), [x0, *stack.parameters()])]
+
+    native, python = _both(monkeypatch, run)
+    assert native[0].dtype is python[0].dtype and torch.equal(native[0], python[0])
+    for a, b in zip(native[1:], python[1:]):
+        torch.testing.assert_close(a, b, rtol=1e-5, atol=1e-5)      # (the start's sum over streams: another order)
+
+
+def _aside(run):
+    """`run` on a stream of its own, behind work on it."""
+    def aside():
+        stream = torch.cuda.Stream()
+        stream.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(stream):
+            torch.randn(2048, 2048, device="cuda") @ torch.randn(2048, 2048, device="cuda")
+            out = run()
+        torch.cuda.current_stream().wait_stream(stream)
+        return out
+    return aside
+
+
+def test_side_streams_inference_and_checkpoints_as_with_the_python_nodes(monkeypatch):
+    layer = HyperConnection(4, 64)
+    _params(layer, 9)
+    x = torch.randn(130, 4, 64, device="cuda", requires_grad=True)
+
+    def grads(call):
+        out = call(x)
+        return [out, *torch.autograd.grad(out.square().sum(), [x, *layer.parameters()])]
+
+    def checkpointed(early):
+        def call(v):
+            with set_checkpoint_early_stop(early):
+                return checkpoint(lambda u: layer(u, _f).square(), v, use_reentrant=False)
+        return call
+
+    def inference():
+        with torch.inference_mode():
+            return [layer(x, _f)]
+
+    runs = [_aside(lambda: grads(lambda v: layer(v, _f))), inference,
+            lambda: grads(checkpointed(True)), lambda: grads(checkpointed(False))]
+    plain = [t.detach() for t in grads(lambda v: layer(v, _f))]
+    for i, run in enumerate(runs):
+        native, python = _both(monkeypatch, run)
+        assert len(native) == len(python)
+        for a, b in zip(native, python):
+            assert torch.equal(a, b), i
+        if i == 0:
+            assert all(torch.equal(a, b) for a, b in zip(native, plain))
 
 
 def test_refusals_are_those_of_the_python_nodes(monkeypatch):
