@@ -41,9 +41,10 @@ def layer_stack(wl, L: int, inputs, device: str = "cuda"):
     H = torch.empty(L, wl.T, wl.n, wl.n, device=device, dtype=f)
     z = torch.empty(L, wl.T, wl.M, device=device, dtype=f)
     spread = torch.empty(L, wl.T, device=device, dtype=f)
-    each = 0 if callable(inputs) else mhcl.workspace_bytes(d, mhcl.OP_COEFFS_LAYERS)
+    # (one at a time where they are drawn one by one, by a callable or a sequence that makes its items: only one is alive then)
+    each = mhcl.workspace_bytes(d, mhcl.OP_COEFFS_LAYERS) if isinstance(inputs, (list, tuple)) else 0
     if each and L > 1:
-        # the layers share launches (one at a time where they are drawn one by one: only one is alive then)
+        # the layers share launches
         layers = [[inputs[l][k] for l in range(L)] for k in ("x", "W", "b", "alpha")]
         ws = torch.empty(each * max(1, min(L, JOINT_LAYERS, JOINT_BYTES // each)), device=device, dtype=torch.uint8)
         mhcl.mhcl_coeffs_logits_layers(d, *layers, H, z, spread, ws)
