@@ -272,8 +272,7 @@ class HyperConnectionStack(torch.nn.Module):
             x = layer(x, f)
         # (a layer is a module: hooks, or what it was replaced with, may return another tensor than the layer's own; under
         # autocast torch's sum is in fp32 and returns fp32)
-        if (ends is None or not _plain(x) or x.dtype is not x0.dtype or x.shape != (*x0.shape[:1], self.n, *x0.shape[1:])
-                or x.device != x0.device or x.layout is not torch.strided or not x.is_contiguous() or x.is_neg()
-                or x.data_ptr() % 16 or torch.is_autocast_enabled("cuda")):
+        if (ends is None or type(x) is not torch.Tensor or not _native().readable(x, x0, ends)
+                or torch.is_autocast_enabled("cuda")):
             return x.sum(dim=1)
         return _native().streams_out(x, ends)

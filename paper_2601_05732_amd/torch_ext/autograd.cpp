@@ -201,6 +201,14 @@ LinkPtr make_link(int64_t n, int64_t C, int64_t T, int io_dtype, int res_mode, i
   return l;
 }
 
+// whether x lies in memory as the kernels of a stack with input x0 read it
+bool readable(const Tensor &x, const Tensor &x0, const LinkPtr &link) {
+  const mhcl_desc &d = link->d;
+  return x.layout() == at::kStrided && x.scalar_type() == x0.scalar_type() && x.device() == x0.device() && x.dim() == 3 &&
+         x.size(0) == d.T && x.size(1) == d.n && x.size(2) == d.C && x.is_contiguous() && !x.is_neg() &&
+         (reinterpret_cast<uintptr_t>(x.data_ptr()) & 15u) == 0;
+}
+
 std::tuple<Tensor, Tensor, Tensor> coeffs_pre(const Tensor &x, const Tensor &W, const Tensor &b, const Tensor &alpha,
                                               const LinkPtr &link) {
   const variable_list out = CoeffsPre::apply(x, W, b, alpha, link);
@@ -220,5 +228,6 @@ PYBIND11_MODULE(TORCH_EXTENSION_NAME, m) {
           return Post::apply(x, y, H_res, H_post, link);
         }));
   m.def("streams_in", wrap([](const Tensor &x0, const LinkPtr &link) { return StreamsIn::apply(x0, link); }));
+  m.def("readable", torch::wrap_pybind_function(&readable));
   m.def("streams_out", wrap([](const Tensor &x, const LinkPtr &link) { return StreamsOut::apply(x, link); }));
 }

@@ -48,7 +48,7 @@ def _both(monkeypatch, run):
     with monkeypatch.context() as m:
         nodes = autograd._native()
         m.setattr(autograd, "_ext", SimpleNamespace(**{k: _counted(getattr(nodes, k), taken) for k in
-                                                       ("link", "coeffs_pre", "post", "streams_in", "streams_out")}))
+                                                       ("link", "coeffs_pre", "post", "readable", "streams_in", "streams_out")}))
         native = run()
         if isinstance(native, list):
             assert "coeffs_pre" in taken and "post" in taken

@@ -29,13 +29,17 @@ class _Ends:
     """Stands for the C++ module on the CPU: its ends take only what the kernels can read."""
 
     def __init__(self, n):
-        self.n, self.outs = n, 0
+        self.n, self.outs, self.module = n, 0, autograd._native()
 
     def streams_in(self, x0, link):
         assert x0.is_contiguous() and x0.data_ptr() % 16 == 0
         self.shape = (x0.shape[0], self.n, x0.shape[1])
         self.dtype = x0.dtype
         return x0.unsqueeze(1).expand(-1, self.n, -1).contiguous()
+
+    def readable(self, x, x0, link):
+        link = self.module.link(self.n, x0.shape[1], x0.shape[0], binding.F32, binding.RES_SK, 20, 1e-6, None, 0)
+        return self.module.readable(x, x0, link)
 
     def streams_out(self, x, link):
         assert x.shape == self.shape and x.dtype is self.dtype and x.is_contiguous() and x.data_ptr() % 16 == 0 \
@@ -78,7 +82,8 @@ def test_the_start_of_a_stack_copies_in_torch_what_the_kernels_cannot_read(monke
     stack.layers = torch.nn.ModuleList([_Copy(4, 64, device="cpu")])
     monkeypatch.setattr(autograd, "_plain", lambda *t: True)
     monkeypatch.setattr(_Ends, "streams_in", lambda *a: pytest.fail("read by the kernels"))
-    monkeypatch.setattr(autograd, "_native", lambda: _Ends(4))
+    ends = _Ends(4)
+    monkeypatch.setattr(autograd, "_native", lambda: ends)
     monkeypatch.setattr(HyperConnection, "_native_link", lambda *a: object())
     assert torch.equal(stack(x0), (x0 * 2).unsqueeze(1).expand(-1, 4, -1).sum(dim=1))
 
