@@ -63,7 +63,8 @@ def _native():
 
 def _plain(*tensors) -> bool:
     """Whether nothing but plain autograd looks at a call on these GPU tensors: no subclass, function transform,
-    forward-mode level, dispatch or function mode, trace or compilation (the C++ nodes know none of them)."""
+    forward-mode level, dispatch or function mode, trace or compilation (the C++ nodes know none of them).
+    A default device (torch.set_default_device, `with torch.device(...)`) is a function mode as well."""
     try:
         C = torch._C
         return (all(type(t) in (torch.Tensor, torch.nn.Parameter) and t.is_cuda for t in tensors)
